@@ -441,7 +441,10 @@ int sparq_workspace_bytes(const sparq_shape* caller_shape, size_t* out_bytes) {
   if (!out_bytes) return SPARQ_EINVAL;
   const sparq_shape sized = bounded(caller_shape);
   const sparq_shape* shape = &sized;
-  *out_bytes = workspace_need(shape);
+  // a bulk append is served by any workspace that the other calls accept, on fewer workgroups if that is short
+  const size_t need = workspace_need(shape);
+  const size_t append = tiled_k(shape) ? 0 : kWorkspaceHeader + append_scratch_bytes((int64_t)shape->B * shape->H_kv, shape->S_max, shape->d_h);
+  *out_bytes = append > need ? append : need;
   return SPARQ_OK;
 }
 
@@ -467,6 +470,7 @@ int sparq_kv_append(const sparq_shape* caller_shape, const sparq_cache* cache, c
   a.k_new = k_new; a.v_new = v_new; a.n_new_per_seq = n_new_per_seq; a.err = static_cast<int32_t*>(workspace);
   a.B = shape->B; a.H_kv = shape->H_kv; a.S_max = a.S_stride = caller_shape->S_max;   // S_bound does not limit an append
   a.d_h = shape->d_h; a.n_new = n_new; a.tiled = tiled_k(shape) ? 1 : 0;
+  a.scratch = static_cast<char*>(workspace) + kWorkspaceHeader; a.scratch_bytes = workspace_bytes - kWorkspaceHeader;
   return launch_append(a, shape->dtype, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 

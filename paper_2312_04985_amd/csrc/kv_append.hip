@@ -68,76 +68,169 @@ __global__ __launch_bounds__(512) void append_one_row(const AppendArgs a) {
 }
 
 // ---- many rows per sequence (prefill / cache construction) ----
-// One workgroup per (sequence, KV head); tiles of 64 positions go through LDS to be written
-// transposed; value columns are summed in fp64 and folded into the mean once.
+// The rows of a (sequence, KV head) are cut into tiles of ATP positions, aligned to 64 positions of the cache so that a
+// tile's columns of Kt are whole 128-byte lines, and dealt to n_split workgroups: a prompt for one sequence with 8 KV
+// heads is 8 x 249 tiles.  A thread owns 8 channels of 8 consecutive positions: it copies its 8 pieces of K and of V,
+// transposes the keys in registers and hands them over through LDS as 16-byte pieces of a channel row, which leave as
+// runs of 2 ATP bytes.  Bound by HBM (2 rows in, 3 out); value columns are summed in fp64, one partial sum per
+// workgroup, and append_finish folds them into the mean.
+// Measured (whole call; before: one workgroup per KV head, columns in 2-byte stores): a prompt of 31 777 rows for 8 KV
+// heads, d_h 128 (325 MB read and written) 2301 -> 77 us, of which this kernel takes 62-67 (5 TB/s; a large copy
+// reaches 4.7) and append_finish 6; chunks of 1-512 rows for 512 KV heads (169 MB) 64 -> 50 us.
 constexpr int BT = 256;       // threads
-constexpr int TILE = 64;      // positions per tile
+// (rows of K and V leave as non-temporal stores: 84 -> 78 us for that prompt; the columns of Kt do not: 78 -> 82)
+__device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 v; v.x = c.x; v.y = c.y; v.z = c.z; v.w = c.w;
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+}
+template <int DH>
+constexpr int ATP = 8 * BT / (DH / 8);     // positions per tile: 256, 128, 64 for d_h = 64, 128, 256 (32 KB of keys)
+
+// transpose 8 rows x 8 channels of 16-bit codes: w[c] = the 8 rows' codes of channel c
+__device__ __forceinline__ void transpose_piece(const uint4 (&rows)[8], uint4 (&w)[8]) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const uint32_t a = c < 2 ? rows[e].x : (c < 4 ? rows[e].y : (c < 6 ? rows[e].z : rows[e].w));
+      const uint32_t b = c < 2 ? rows[e + 1].x : (c < 4 ? rows[e + 1].y : (c < 6 ? rows[e + 1].z : rows[e + 1].w));
+      o[e >> 1] = (c & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+    }
+    w[c] = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+}
 
 template <class T, int DH>
 __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
-  constexpr int CPR = DH / 8;            // 16-byte chunks per row
-  constexpr int RPP = BT / CPR;          // rows per pass
-  constexpr int LD = DH + 2;             // padded LDS row (elements): conflict-free column reads
-  __shared__ uint16_t tile[TILE * LD];
+  constexpr int CPR = DH / 8;            // 16-byte pieces per row
+  constexpr int RPP = BT / CPR;          // groups of 8 positions per tile
+  constexpr int TP = ATP<DH>;
+  __shared__ __align__(16) uint4 tile[DH * RPP];   // [channel][group ^ (channel / 8)]: no bank conflicts either way
   __shared__ double colsum[RPP][DH];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t head = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int split = blockIdx.x % a.n_split;
+  const size_t head = blockIdx.x / a.n_split;
   const int b = (int)(head / a.H_kv);
   const int S = a.seq_lens[b];
   int n = a.n_new_per_seq ? a.n_new_per_seq[b] : a.n_new;
   n = n < 0 ? 0 : (n > a.n_new ? a.n_new : n);
+  const bool full = S < 0 || S + n > a.S_max;
+  if (a.n_split > 1 && split == 0 && tid == 0) a.span_ws[head] = make_int2(S, full ? 0 : n);
   if (n == 0) return;
-  if (S < 0 || S + n > a.S_max) {
-    if (tid == 0) atomicOr(a.err, 1);
+  if (full) {
+    if (split == 0 && tid == 0) atomicOr(a.err, 1);
     return;
   }
-  const int sub = tid % CPR, prow = tid / CPR;
-  const uint16_t* ksrc = reinterpret_cast<const uint16_t*>(a.k_new) + head * a.n_new * DH;
-  const uint16_t* vsrc = reinterpret_cast<const uint16_t*>(a.v_new) + head * a.n_new * DH;
-  uint16_t* Kdst = reinterpret_cast<uint16_t*>(a.K) + (head * a.S_stride + S) * DH;
-  uint16_t* Vdst = reinterpret_cast<uint16_t*>(a.V) + (head * a.S_stride + S) * DH;
-  uint16_t* Ktdst = reinterpret_cast<uint16_t*>(a.Kt) + head * DH * (size_t)a.S_stride + S;
+  const int sub = tid % CPR, grp = tid / CPR;
+  const uint16_t* ksrc = reinterpret_cast<const uint16_t*>(a.k_new) + head * a.n_new * DH + sub * 8;   // row i is position S + i
+  const uint16_t* vsrc = reinterpret_cast<const uint16_t*>(a.v_new) + head * a.n_new * DH + sub * 8;
+  uint16_t* Khead = reinterpret_cast<uint16_t*>(a.K) + head * a.S_stride * (size_t)DH + sub * 8;
+  uint16_t* Vhead = reinterpret_cast<uint16_t*>(a.V) + head * a.S_stride * (size_t)DH + sub * 8;
+  uint16_t* Kthead = reinterpret_cast<uint16_t*>(a.Kt) + head * DH * (size_t)a.S_stride;
+  const int E = S + n, S_fl = S & ~7;
+  const int p_begin = (S & ~63) + split * a.tiles_per_split * TP;
+  const int p_end = p_begin + a.tiles_per_split * TP < E ? p_begin + a.tiles_per_split * TP : E;
   double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int n0 = 0; n0 < n; n0 += TILE) {
-    const int rows = (n - n0) < TILE ? (n - n0) : TILE;
-    for (int rr = prow; rr < rows; rr += RPP) {
-      const size_t off = (size_t)(n0 + rr) * DH + sub * 8;
-      const uint4 kc = load16(ksrc + off), vc = load16(vsrc + off);
-      *reinterpret_cast<uint4*>(Kdst + off) = kc;
-      *reinterpret_cast<uint4*>(Vdst + off) = vc;
-      uint32_t* t32 = reinterpret_cast<uint32_t*>(tile + rr * LD + sub * 8);   // LD even: 4-byte aligned
-      t32[0] = kc.x; t32[1] = kc.y; t32[2] = kc.z; t32[3] = kc.w;
-      float f[8];
-      unpack8<T>(vc, f);
+  for (int p0 = p_begin; p0 < p_end; p0 += TP) {
+    const int p = p0 + grp * 8;          // this thread's 8 positions
+    uint4 kr[8], vr[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) sum[e] += (double)f[e];
+    for (int e = 0; e < 8; ++e) {
+      const int q = p + e;
+      const bool is_new = q >= S && q < E;
+      kr[e] = vr[e] = make_uint4(0u, 0u, 0u, 0u);
+      if (is_new) {
+        kr[e] = load16(ksrc + (size_t)(q - S) * DH);
+        vr[e] = load16(vsrc + (size_t)(q - S) * DH);
+      } else if (q >= S_fl && q < S) {   // cached before this call and not yet in the S-contiguous copy
+        kr[e] = load16(Khead + (size_t)q * DH);
+      }
     }
-    __syncthreads();
-    if (a.Kt)
-      for (int j = wave; j < DH; j += BT / 64)
-        if (lane < rows) Ktdst[(size_t)j * a.S_stride + n0 + lane] = tile[lane * LD + j];
-    __syncthreads();
-  }
-  // the up to 7 rows that were cached before this call and not yet in the S-contiguous copy
-  if (a.Kt) {
-    const int S_fl = S & ~7;
-    const uint16_t* Khead = reinterpret_cast<const uint16_t*>(a.K) + head * a.S_stride * (size_t)DH;
-    uint16_t* Kthead = reinterpret_cast<uint16_t*>(a.Kt) + head * DH * (size_t)a.S_stride;
-    for (int i = tid; i < (S - S_fl) * DH; i += BT) {
-      const int e = i / DH, j = i - e * DH;
-      Kthead[(size_t)j * a.S_stride + S_fl + e] = Khead[(size_t)(S_fl + e) * DH + j];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int q = p + e;
+      if (q >= S && q < E) {
+        store16_nt(Khead + (size_t)q * DH, kr[e]);
+        store16_nt(Vhead + (size_t)q * DH, vr[e]);
+        float f[8];
+        unpack8<T>(vr[e], f);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sum[c] += (double)f[c];
+      }
+    }
+    if (a.Kt) {                          // null: the cache keeps K once
+      uint4 w[8];
+      transpose_piece(kr, w);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) tile[(sub * 8 + c) * RPP + (grp ^ (sub & (RPP - 1)))] = w[c];
+      __syncthreads();
+      for (int i = tid; i < DH * RPP; i += BT) {
+        const int j = i / RPP, u = i % RPP, q = p0 + u * 8;
+        const uint4 v = tile[j * RPP + (u ^ ((j >> 3) & (RPP - 1)))];
+        uint16_t* dst = Kthead + (size_t)j * a.S_stride + q;
+        if (q >= S_fl && q + 8 <= E) {
+          *reinterpret_cast<uint4*>(dst) = v;
+        } else if (q >= S_fl && q < E) { // the last, unfinished group: its positions only
+          const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 0; e < 7; ++e)
+            if (q + e < E) dst[e] = (uint16_t)(x[e >> 1] >> (16 * (e & 1)));
+        }
+      }
+      __syncthreads();
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) colsum[prow][sub * 8 + e] = sum[e];
+  for (int c = 0; c < 8; ++c) colsum[grp][sub * 8 + c] = sum[c];
   __syncthreads();
   if (tid < DH) {
     double tot = 0.0;
-    for (int p = 0; p < RPP; ++p) tot += colsum[p][tid];
-    float* vm = a.v_mean + head * DH + tid;
-    const double before = S > 0 ? (double)S * (double)*vm : 0.0;   // S = 0: whatever the buffer held is ignored
+    for (int g = 0; g < RPP; ++g) tot += colsum[g][tid];
+    if (a.n_split > 1) {
+      a.part_ws[(head * a.n_split + split) * DH + tid] = tot;
+    } else {
+      float* vm = a.v_mean + head * DH + tid;
+      const double before = S > 0 ? (double)S * (double)*vm : 0.0;   // S = 0: whatever the buffer held is ignored
+      *vm = (float)((before + tot) / (double)(S + n));
+    }
+  }
+}
+
+// The means and lengths after append_rows over several workgroups per KV head: one workgroup per (sequence, KV head).
+// The old length and the row count come from the workspace: seq_lens is written here.
+template <int DH>
+__global__ __launch_bounds__(BT) void append_finish(const AppendArgs a) {
+  constexpr int NG = BT / DH;
+  __shared__ double sm[NG][DH];
+  const int c = threadIdx.x % DH, grp = threadIdx.x / DH;
+  const size_t head = blockIdx.x;
+  const int b = (int)(head / a.H_kv);
+  const int2 sn = a.span_ws[head];
+  const int S = sn.x, n = sn.y;
+  if (n == 0) return;
+  float* vm = a.v_mean + head * DH + c;
+  const double before = S > 0 ? (double)S * (double)*vm : 0.0;     // S = 0: whatever the buffer held is ignored
+  const int per = a.tiles_per_split * ATP<DH>;
+  const int used = (S + n - (S & ~63) + per - 1) / per;            // workgroups that had rows
+  const double* part = a.part_ws + head * a.n_split * DH + c;
+  double tot = 0.0;
+  for (int s0 = grp; s0 < used; s0 += NG * 8) {                    // eight partials in flight
+    double v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = s0 + t * NG < used ? part[(size_t)(s0 + t * NG) * DH] : 0.0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) tot += v[t];
+  }
+  sm[grp][c] = tot;
+  __syncthreads();
+  if (grp == 0) {
+#pragma unroll
+    for (int g = 1; g < NG; ++g) tot += sm[g][c];
     *vm = (float)((before + tot) / (double)(S + n));
   }
+  if (head % a.H_kv == 0 && threadIdx.x == 0) a.seq_lens[b] = S + n;
 }
 
 // ---- the tiled single-copy key layout: tiles of 8 positions, channel-major inside a tile ----
@@ -145,23 +238,12 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
 // positions 8 floor(S / 8) .. S - 1, which do not fill a tile yet, wait in a buffer of 8 rows per KV head
 // (AppendArgs::Kt) and move into their tile, as one contiguous block, when the eighth arrives.
 
-// transpose 8 rows x 8 channels of 16-bit codes (rows[e] = the 16 bytes of row e) and store the 8 channels'
-// position runs: 128 contiguous bytes at `dst`
+// the transposed piece of 8 rows x 8 channels as 128 contiguous bytes at `dst`
 __device__ __forceinline__ void store_tile_piece(uint16_t* dst, const uint4 (&rows)[8]) {
-  uint32_t w[8][4];
+  uint4 w[8];
+  transpose_piece(rows, w);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { w[e][0] = rows[e].x; w[e][1] = rows[e].y; w[e][2] = rows[e].z; w[e][3] = rows[e].w; }
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {            // channel c of the piece: positions 0..7
-    uint32_t o[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      const uint32_t lo = (c & 1) ? (w[e][c >> 1] >> 16) : (w[e][c >> 1] & 0xffffu);
-      const uint32_t hi = (c & 1) ? (w[e + 1][c >> 1] >> 16) : (w[e + 1][c >> 1] & 0xffffu);
-      o[e >> 1] = lo | (hi << 16);
-    }
-    reinterpret_cast<uint4*>(dst)[c] = make_uint4(o[0], o[1], o[2], o[3]);
-  }
+  for (int c = 0; c < 8; ++c) reinterpret_cast<uint4*>(dst)[c] = w[c];
 }
 
 // one row per sequence: one workgroup per sequence, a thread moves one 16-byte chunk (8 channels) of one KV head
@@ -367,25 +449,61 @@ __global__ void clear_words(int32_t* w, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) w[i] = 0;
 }
 
-template <class T>
-hipError_t launch_rows(const AppendArgs& a, hipStream_t s) {
-  const dim3 grid(a.B * a.H_kv);
-  switch (a.d_h) {
-    case 64:  if (a.tiled) hipLaunchKernelGGL((append_rows_tiled<T, 64>), grid, dim3(BT), 0, s, a);
-              else hipLaunchKernelGGL((append_rows<T, 64>), grid, dim3(BT), 0, s, a); break;
-    case 128: if (a.tiled) hipLaunchKernelGGL((append_rows_tiled<T, 128>), grid, dim3(BT), 0, s, a);
-              else hipLaunchKernelGGL((append_rows<T, 128>), grid, dim3(BT), 0, s, a); break;
-    case 256: if (a.tiled) hipLaunchKernelGGL((append_rows_tiled<T, 256>), grid, dim3(BT), 0, s, a);
-              else hipLaunchKernelGGL((append_rows<T, 256>), grid, dim3(BT), 0, s, a); break;
-    default: return hipErrorInvalidValue;
+// Workgroups per KV head of a bulk append of `tiles` tiles per head: about kAppendGroups in all (8 per CU; five of them
+// fit by LDS), at most 128 per head, so that append_finish reads few partial sums.
+constexpr int64_t kAppendGroups = 2048;
+int64_t append_groups(int64_t heads, int64_t tiles) {
+  const int64_t per = (tiles * heads + kAppendGroups - 1) / kAppendGroups, n = (tiles + per - 1) / per;
+  return n < 128 ? n : 128;
+}
+
+template <class T, int DH>
+hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
+  AppendArgs a = args;
+  const int64_t heads = (int64_t)a.B * a.H_kv;
+  if (a.tiled) {
+    hipLaunchKernelGGL((append_rows_tiled<T, DH>), dim3(heads), dim3(BT), 0, s, a);
+  } else {
+    // Workgroups per KV head: one per tile until there are kAppendGroups in all, then longer runs of tiles, and no
+    // more than the scratch holds partial sums of (512 KV heads, up to 512 rows each: 4 per head 51 us, 2 per head
+    // 67 us).  A call on a cache that is not aligned to 64 positions may touch one tile more.
+    const int64_t tiles = ((int64_t)a.n_new + 63 + ATP<DH> - 1) / ATP<DH>;
+    int64_t n = append_groups(heads, tiles);
+    const int64_t held = (int64_t)(a.scratch_bytes / (heads * (DH * sizeof(double) + sizeof(int2))));
+    if (n > held) n = held > 1 ? held : 1;
+    const int64_t per = (tiles + n - 1) / n;
+    n = (tiles + per - 1) / per;
+    a.n_split = (int)n; a.tiles_per_split = (int)per;
+    a.part_ws = reinterpret_cast<double*>(a.scratch);
+    a.span_ws = reinterpret_cast<int2*>(a.part_ws + (n > 1 ? heads * n * DH : 0));
+    hipLaunchKernelGGL((append_rows<T, DH>), dim3(heads * n), dim3(BT), 0, s, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bump_seq_lens, dim3((a.B + 255) / 256), dim3(256), 0, s, a);
+  if (!a.tiled && a.n_split > 1) hipLaunchKernelGGL(append_finish<DH>, dim3(heads), dim3(BT), 0, s, a);
+  else hipLaunchKernelGGL(bump_seq_lens, dim3((a.B + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
+template <class T>
+hipError_t launch_rows(const AppendArgs& a, hipStream_t s) {
+  switch (a.d_h) {
+    case 64:  return launch_rows_dh<T, 64>(a, s);
+    case 128: return launch_rows_dh<T, 128>(a, s);
+    case 256: return launch_rows_dh<T, 256>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
+
+size_t append_scratch_bytes(int64_t heads, int S_max, int d_h) {
+  const int64_t positions = 8 * BT / (d_h / 8), tiles = (S_max + 63 + positions - 1) / positions;
+  int64_t n = kAppendGroups / heads + 1;           // append_groups of any number of tiles up to these
+  n = n < tiles ? n : tiles;
+  n = n < 128 ? n : 128;
+  return n > 1 ? (size_t)heads * n * (d_h * sizeof(double) + sizeof(int2)) : 0;
+}
 
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t s) {
   if (a.n_new == 1) {

@@ -40,6 +40,11 @@ struct AppendArgs {
   int32_t B, H_kv, S_max, d_h, n_new;   // S_max: no length may pass it
   int32_t S_stride;   // positions per head in K and V and per channel row in Kt
   int32_t tiled;   // the tiled single-copy key layout: K holds tiles of 8 positions, Kt the rows of the newest < 8
+  void* scratch = nullptr; size_t scratch_bytes = 0;   // room for the partial sums of a bulk append (16-byte aligned)
+  // set by the launcher of a bulk append: workgroups per KV head and tiles of each, their partial sums of the value
+  // columns [B * H_kv][n_split][d_h], old length and row count of each KV head
+  int32_t n_split = 1, tiles_per_split = 1;
+  double* part_ws = nullptr; int2* span_ws = nullptr;
 };
 
 struct DenseArgs {
@@ -153,6 +158,8 @@ size_t gs_merge_lds_bytes(int n2, int cand_cap);
 hipError_t launch_decode_shared_split(const GsArgs& a, int dtype, hipStream_t s);
 // z_ws: [B * H][S_max] fp32 scratch for the logit numerators
 hipError_t launch_decode_shared(const DecodeArgs& a, float* z_ws, int dtype, hipStream_t s);
+// what a bulk append on a cache of S_max positions can use of AppendArgs::scratch (with less it runs on fewer workgroups)
+size_t append_scratch_bytes(int64_t heads, int S_max, int d_h);
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t s);
 hipError_t launch_dense(const DenseArgs& a, int dtype, hipStream_t s);
 hipError_t launch_copy_probe(void* dst, const void* src, size_t n_bytes, hipStream_t s);
