@@ -39,18 +39,35 @@ int check_cache(const sparq_cache* c, const sparq_shape* s) {
   return SPARQ_OK;
 }
 
-// split-sequence plan of dense_decode: enough workgroups to fill 256 CUs several times over,
-// runs of at least 256 rows
-void dense_plan(const sparq_shape* s, int* n_split, int* rows_per_split) {
-  const int64_t heads = (int64_t)s->B * s->H_kv;
-  int64_t want = (2048 + heads - 1) / heads;
+// runs of at least 256 rows, about `target` workgroups over `units`, at most `most` runs (0: any number)
+void dense_split(const sparq_shape* s, int64_t units, int64_t target, int64_t most, int* n_split, int* rows_per_split) {
+  int64_t want = (target + units - 1) / units;
   const int64_t cap = s->S_max / 256 > 0 ? s->S_max / 256 : 1;
   if (want > cap) want = cap;
+  if (most && want > most) want = most;
   if (want < 1) want = 1;
   int rows = (int)((s->S_max + want - 1) / want);
   rows = (rows + 63) / 64 * 64;
   *rows_per_split = rows;
   *n_split = (s->S_max + rows - 1) / rows;
+}
+
+// Split-sequence plan of dense_decode.  Two workgroups fit on a CU, so 1024 are two rounds of the chip: lengths that
+// differ are evened out and the merges stay short.  Measured us at 256 / 512 / 1024 / 2048 workgroups: 512 units of 4096
+// rows 155 / 155 / 159 / 161; 60 units, 8 heads each, 8192 rows 64 / 54 / 54 / 60; 128 and 264 units with lengths over
+// 16x 252 / 256 / 199 / 190 and 143 / 140 / 110 / 100, hence 2048 where the caller says that lengths differ.  Few units
+// would be merged from very many partial results: 8 units of 32 768 rows 28.5 us from 31 each, 31.6 from 57; fewer
+// units need that many to fill the chip (one unit of 40 000 rows, 8 heads: 43 us from 64 each, 36 from 126).
+void dense_plan(const sparq_shape* s, int* n_split, int* rows_per_split) {
+  const int64_t units = (int64_t)s->B * s->H_kv * dense_bundles(s->H / s->H_kv, s->d_h);
+  dense_split(s, units, (s->flags & SPARQ_FLAG_RAGGED_BATCH) ? 2048 : 1024, units >= 8 ? 32 : (units >= 3 ? 64 : kDenseSplits), n_split, rows_per_split);
+}
+
+// Partial results that the workspace has room for, per (sequence, KV head): what 2048 workgroups would leave.
+int dense_room(const sparq_shape* s) {
+  int n_split, rows;
+  dense_split(s, (int64_t)s->B * s->H_kv, 2048, 0, &n_split, &rows);
+  return n_split;
 }
 
 // The shape that plans, LDS and workspace are sized for: the caller's bound on the lengths (S_bound), where one is
@@ -289,9 +306,7 @@ LongLayout long_layout(const sparq_shape* s, const PlanInfo& p) {
 }
 
 size_t workspace_need(const sparq_shape* s) {
-  int n_split, rows;
-  dense_plan(s, &n_split, &rows);
-  size_t need = (size_t)kControlBytes + (size_t)s->B * s->H * n_split * (s->d_h + 2) * sizeof(float);
+  size_t need = (size_t)kControlBytes + (size_t)s->B * s->H * dense_room(s) * (s->d_h + 2) * sizeof(float);
   const PlanInfo p = choose_plan(s);
   size_t e = 0;
   if (p.plan == kPlanLong) e = long_layout(s, p).end;
@@ -443,7 +458,7 @@ int sparq_workspace_bytes(const sparq_shape* caller_shape, size_t* out_bytes) {
   const sparq_shape* shape = &sized;
   // a bulk append is served by any workspace that the other calls accept, on fewer workgroups if that is short
   const size_t need = workspace_need(shape);
-  const size_t append = tiled_k(shape) ? 0 : kWorkspaceHeader + append_scratch_bytes((int64_t)shape->B * shape->H_kv, shape->S_max, shape->d_h);
+  const size_t append = tiled_k(shape) ? 0 : kAppendScratchOffset + append_scratch_bytes((int64_t)shape->B * shape->H_kv, shape->S_max, shape->d_h);
   *out_bytes = append > need ? append : need;
   return SPARQ_OK;
 }
@@ -470,7 +485,7 @@ int sparq_kv_append(const sparq_shape* caller_shape, const sparq_cache* cache, c
   a.k_new = k_new; a.v_new = v_new; a.n_new_per_seq = n_new_per_seq; a.err = static_cast<int32_t*>(workspace);
   a.B = shape->B; a.H_kv = shape->H_kv; a.S_max = a.S_stride = caller_shape->S_max;   // S_bound does not limit an append
   a.d_h = shape->d_h; a.n_new = n_new; a.tiled = tiled_k(shape) ? 1 : 0;
-  a.scratch = static_cast<char*>(workspace) + kWorkspaceHeader; a.scratch_bytes = workspace_bytes - kWorkspaceHeader;
+  a.scratch = static_cast<char*>(workspace) + kAppendScratchOffset; a.scratch_bytes = workspace_bytes - kAppendScratchOffset;
   return launch_append(a, shape->dtype, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
@@ -568,6 +583,7 @@ int dense_decode(const sparq_shape* caller_shape, const sparq_cache* cache, cons
   DenseArgs a;
   a.K = cache->K; a.V = cache->V; a.seq_lens = cache->seq_lens; a.q = q; a.out = out;
   a.partials = reinterpret_cast<float*>(static_cast<char*>(workspace) + kControlBytes);
+  a.tickets = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + kTicketOffset);
   a.err = static_cast<int32_t*>(workspace);
   a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
   dense_plan(shape, &a.n_split, &a.rows_per_split);

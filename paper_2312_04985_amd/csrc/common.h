@@ -8,6 +8,8 @@ namespace sparq {
 constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // ---- 16-bit storage formats: exact widening to fp32, round-to-nearest-even narrowing ----
 struct F16 {
   static __device__ __forceinline__ float lo(uint32_t w) {
@@ -18,6 +20,12 @@ struct F16 {
   }
   static __device__ __forceinline__ float widen(uint16_t c) { return (float)__builtin_bit_cast(_Float16, c); }
   static __device__ __forceinline__ uint16_t narrow(float x) { return __builtin_bit_cast(uint16_t, (_Float16)x); }
+  // c[m][n] += sum_k a[m][k] b[n][k] over 32 k: lane l holds a[l % 16], b[l % 16] at k = 8 (l / 16) .. + 7 and
+  // c[4 (l / 16) + i][l % 16]
+  static __device__ __forceinline__ f32x4 mfma_16x16x32(const uint4& a, const uint4& b, f32x4 c) {
+    typedef _Float16 v8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+  }
 };
 
 struct BF16 {
@@ -28,6 +36,10 @@ struct BF16 {
     uint32_t u = __float_as_uint(x);
     u += 0x7fffu + ((u >> 16) & 1u);   // finite inputs only
     return (uint16_t)(u >> 16);
+  }
+  static __device__ __forceinline__ f32x4 mfma_16x16x32(const uint4& a, const uint4& b, f32x4 c) {   // as F16's
+    typedef __bf16 v8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
   }
 };
 
@@ -120,6 +132,48 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
   v += dpp_or_zero<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
   v += dpp_or_zero<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
   return v;
+}
+
+// LDS words that other lanes of the same wave wrote (a wave's LDS accesses are served in order: this only keeps the
+// compiler from moving them past each other)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// ---- results handed to the workgroup of a group that finishes last, inside one launch ----
+// The workgroups of a launch run on 8 XCDs whose L2 caches do not see each other's lines.  What one of them leaves for
+// another is therefore stored and loaded with agent scope (past the L2), word by word: a release fence would write
+// the whole L2 back, which was measured as four times the time of a launch.
+__device__ __forceinline__ void store_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// 16 bytes at byte offset `off` of `base` (wave-uniform), the same way (bit 4 of the cache policy is the agent scope's sc1)
+__device__ __forceinline__ void store_agent4(const float* base, uint32_t off, const float4& v) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+  __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffffffu, 0x00027000), off, 0, 16);
+}
+__device__ __forceinline__ float4 load_agent4(const float* base, uint32_t off) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffffffu, 0x00027000), off, 0, 16);
+  return make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
+}
+
+// Called by all threads of each of the `n` workgroups of a group after their store_agent calls; true in all threads of
+// the one that arrives last, whose load_agent calls then see every store of the others: each wave waits until its own
+// stores have been acknowledged, the workgroup's waves meet, and only then one thread counts the workgroup in.
+// The counter is 0 before the launch and is left 0.  No workgroup waits for another.  `flag`: one word of LDS.
+__device__ __forceinline__ bool last_to_arrive(int* counter, int n, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before == n - 1) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = before == n - 1;
+  }
+  __syncthreads();
+  asm volatile("" ::: "memory");
+  return *flag != 0;
 }
 
 // exp2 that maps (-inf) - (-inf) situations to weight 0 instead of NaN

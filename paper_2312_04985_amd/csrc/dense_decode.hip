@@ -1,7 +1,7 @@
 // Dense single-query attention (Section 3, Eq. 2): the in-library comparison for SparQ.
 // Split along the sequence: each workgroup streams a run of K and V rows of one KV head once
-// for G query heads of its group (online softmax, fp32), writes (acc, m, l) partials; a second
-// kernel merges the partials of each query head.
+// for G query heads of its group (online softmax, fp32).  The last of a KV head's workgroups to finish merges their
+// partial results.
 #include "common.h"
 #include "params.h"
 
@@ -9,17 +9,52 @@ namespace sparq {
 
 namespace {
 
-constexpr int DT = 256;            // threads per workgroup
+constexpr int DT = 256;            // threads per workgroup; two workgroups per CU (256 registers)
 constexpr int DW = DT / kWave;
 
+// A wave takes groups of TPG tiles of 16 rows, two groups in flight.  The scores of a tile are one chain of matrix
+// instructions (16 rows x 16 query heads, of which G are distinct: the heads repeat), which leaves every lane the
+// scores of one row; the softmax then costs one exponential per (row, head) instead of one in each of the d_h / 8
+// lanes that share a row, and the running maximum is looked at once per group: the accumulators are rescaled only
+// when it rises.  The weights go through LDS to the lanes that hold the row's slice of V, as fp32, and V is
+// accumulated by plain fp32 FMAs.  Products of 16-bit inputs are exact in the matrix unit and summed in fp32.
+// Bound by HBM.  Measured (before: scores by FMAs and lane sums, two exponentials and a rescaling per row, head and lane,
+// and a second launch for the merge): 8 KV heads of 32 768 rows, 4 query heads each, bf16 47.4 -> 28.6 us (134 MB);
+// 60 KV heads of 8192 rows, 8 heads each 122 -> 54; 512 KV heads of 4096 rows, one head each 176 -> 159 (6.8 TB/s);
+// one row group of one head 10.6 -> 8.3.
 template <class T, int DH, int G>
-__global__ __launch_bounds__(DT) void dense_partial(const DenseArgs a) {
-  constexpr int LPR = DH / 8, RPW = kWave / LPR, RPI = DW * RPW, UNR = 4;
+struct DenseGeometry {
+  static constexpr int LPR = DH / 8, RPW = kWave / LPR;      // lanes per row of V, rows per load of a wave
+  static constexpr int KK = DH / 32;                         // matrix instructions (16-byte pieces per lane) per tile
+  static constexpr int TPG = DH == 256 ? 1 : (DH == 128 ? 2 : 4) / (G == 8 ? 2 : 1);   // two groups fit the registers
+  static constexpr int R = 16 * TPG;                         // rows per group
+  static constexpr int NV = R / RPW;                         // loads of V per group
+  static constexpr int NH = G < 4 ? G : 4;                   // scores of a row that one lane holds
+};
+
+template <class T>
+__device__ __forceinline__ void store_out4(uint16_t* dst, const float4& y, float scale) {
+  const uint32_t lo = T::narrow(y.x * scale) | ((uint32_t)T::narrow(y.y * scale) << 16);
+  const uint32_t hi = T::narrow(y.z * scale) | ((uint32_t)T::narrow(y.w * scale) << 16);
+  *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
+}
+
+template <class T, int DH, int G>
+__global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
+  using Geo = DenseGeometry<T, DH, G>;
+  constexpr int LPR = Geo::LPR, RPW = Geo::RPW, KK = Geo::KK, TPG = Geo::TPG, R = Geo::R, NV = Geo::NV, NH = Geo::NH;
+  __shared__ __align__(16) float ps[DW][R][G];   // weights of a wave's group of rows
   __shared__ float part[DW][G][DH + 2];
+  __shared__ float stat[kDenseSplits * G * 2];      // the last workgroup's merge: (max, denominator) of every partial
+  __shared__ float4 red[DT];
+  __shared__ int ticket;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = a.H / a.H_kv, gpk = g / G;       // query-head bundles per KV head
-  int x = blockIdx.x;
-  const int split = x % a.n_split; x /= a.n_split;
+  // Workgroups are dealt round-robin to the 8 XCDs: the unit varies fastest, so that every XCD gets its share of the
+  // splits at the ends of the sequences, which a ragged batch leaves empty.
+  const int units = a.B * a.H_kv * gpk, split = blockIdx.x / units;
+  int x = blockIdx.x - split * units;
+  const int unit = x;                            // (sequence, KV head, bundle)
   const int bundle = x % gpk; x /= gpk;
   const int hk = x % a.H_kv, b = x / a.H_kv;
   const int h0 = hk * g + bundle * G;            // first query head served here
@@ -27,162 +62,236 @@ __global__ __launch_bounds__(DT) void dense_partial(const DenseArgs a) {
   S = S < 0 ? 0 : (S > a.S_max ? a.S_max : S);
   const int s0 = split * a.rows_per_split;
   const int s1 = (s0 + a.rows_per_split) < S ? (s0 + a.rows_per_split) : S;
-
-  const int sub = lane % LPR, slot = wave * RPW + lane / LPR;
-  const size_t kv_head = (size_t)b * a.H_kv + hk;
-  const char* K_head = reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2) + sub * 16;
-  const char* V_head = reinterpret_cast<const char*>(a.V) + kv_head * a.S_stride * (size_t)(DH * 2) + sub * 16;
-  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)b * a.H + h0) * DH + sub * 8;
-  const float qscale = kLog2e / sqrtf((float)DH);
-  float q8[G][8], acc[G][8], m_run[G], l_run[G];
-#pragma unroll
-  for (int t = 0; t < G; ++t) {
-    float f[8];
-    unpack8<T>(load16(qp + (size_t)t * DH), f);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { q8[t][e] = f[e] * qscale; acc[t][e] = 0.0f; }
-    m_run[t] = -INFINITY; l_run[t] = 0.0f;
+  uint16_t* out = reinterpret_cast<uint16_t*>(a.out) + ((size_t)b * a.H + h0) * DH;
+  if (s0 >= S) {                                 // nothing of this sequence here; an empty sequence: zeros
+    if (S == 0 && split == 0)
+      for (int i = tid; i < G * DH; i += DT) out[i] = 0;
+    return;
   }
+  const int n_live = (S + a.rows_per_split - 1) / a.rows_per_split;   // workgroups of this unit that have rows
 
-  for (int n0 = s0; n0 < s1; n0 += RPI * UNR) {
-    uint4 kr[UNR], vr[UNR];
-    bool ok[UNR];
+  const size_t kv_head = (size_t)b * a.H_kv + hk;
+  const int row16 = lane & 15, quarter = lane >> 4;
+  const int sub = lane % LPR, vrow = lane / LPR;
+  const char* K_head = reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2);
+  const char* V_head = reinterpret_cast<const char*>(a.V) + kv_head * a.S_stride * (size_t)(DH * 2);
+  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)b * a.H + h0 + row16 % G) * DH + quarter * 8;
+  uint4 qf[KK];                                  // row (lane % 16) % G of the query, channels 32 kk + 8 quarter ..
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int n = n0 + u * RPI + slot;
-      ok[u] = n < s1;
-      const size_t off = (size_t)(ok[u] ? n : s0) * (size_t)(DH * 2);
-      kr[u] = load16(K_head + off);
-      vr[u] = load16(V_head + off);
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const uint4*>(qp + kk * 32);
+  const float qscale = kLog2e / sqrtf((float)DH);
+  float acc[G][8], m_ref[NH], l_run[NH];
+#pragma unroll
+  for (int t = 0; t < G; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[t][e] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NH; ++i) { m_ref[i] = -INFINITY; l_run[i] = 0.0f; }
+
+  auto issue = [&](uint4 (&kr)[TPG][KK], uint4 (&vr)[NV], int r0) {
+#pragma unroll
+    for (int t = 0; t < TPG; ++t) {
+      const int n = r0 + t * 16 + row16;
+      const uint32_t off = (uint32_t)(n < s1 ? n : s0) * (uint32_t)(DH * 2) + quarter * 16;    // < S_max * 512 bytes
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) kr[t][kk] = load16(K_head + off + kk * 64);
     }
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      float kf[8], vf[8];
-      unpack8<T>(kr[u], kf);
-      unpack8<T>(vr[u], vf);
+    for (int u = 0; u < NV; ++u) {
+      const int n = r0 + u * RPW + vrow;
+      vr[u] = load16(V_head + ((uint32_t)(n < s1 ? n : s0) * (uint32_t)(DH * 2) + sub * 16));
+    }
+  };
+  auto consume = [&](const uint4 (&kr)[TPG][KK], const uint4 (&vr)[NV], int r0) {
+    float sc[TPG][NH];                           // scores of row r0 + 16 t + lane % 16, heads (4 quarter + i) % G
+    bool above = false;
 #pragma unroll
-      for (int t = 0; t < G; ++t) {
-        float dot = 0.0f;
+    for (int t = 0; t < TPG; ++t) {
+      f32x4 c = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dot = fmaf(kf[e], q8[t][e], dot);
-        dot = lanes_sum<LPR>(dot);
-        if (ok[u]) {
-          const float m_new = fmaxf(m_run[t], dot);
-          const float sc = exp2f(m_run[t] - m_new), pr = exp2f(dot - m_new);
-          l_run[t] = l_run[t] * sc + pr;
+      for (int kk = 0; kk < KK; ++kk) c = T::mfma_16x16x32(qf[kk], kr[t][kk], c);
+      const bool ok = r0 + t * 16 + row16 < s1;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[t][e] = acc[t][e] * sc + pr * vf[e];
-          m_run[t] = m_new;
-        }
+      for (int i = 0; i < NH; ++i) {
+        sc[t][i] = ok ? c[i] * qscale : -INFINITY;
+        above = above || sc[t][i] > m_ref[i];
       }
     }
+    if (__ballot(above)) {                       // the maximum of some head rises: uniform, rare after the first groups
+      float w[NH];
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        float mx = sc[0][i];
+#pragma unroll
+        for (int t = 1; t < TPG; ++t) mx = fmaxf(mx, sc[t][i]);
+        mx = fmaxf(group_max<16>(mx), m_ref[i]);
+        w[i] = weight_exp2(m_ref[i], mx);
+        m_ref[i] = mx;
+        l_run[i] *= w[i];
+      }
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        const float wt = lane_f(w[t % NH], t / NH * 16);      // head t lives in quarter t / 4
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] *= wt;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TPG; ++t) {
+      float p[NH];
+#pragma unroll
+      for (int i = 0; i < NH; ++i) { p[i] = exp2_weight(sc[t][i] - m_ref[i]); l_run[i] += p[i]; }
+      if (quarter < (G + 3) / 4) {               // the other quarters hold copies
+#pragma unroll
+        for (int i = 0; i < NH; ++i) ps[wave][t * 16 + row16][quarter * 4 + i] = p[i];
+      }
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      float f[8], w[G];
+#pragma unroll
+      for (int t = 0; t < G; ++t) w[t] = ps[wave][u * RPW + vrow][t];
+      unpack8<T>(vr[u], f);
+#pragma unroll
+      for (int t = 0; t < G; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(w[t], f[e], acc[t][e]);
+    }
+    wave_lds_fence();                            // the next group overwrites the weights
+  };
+
+  int r0 = s0 + wave * R;
+  if (r0 < s1) {
+    uint4 ka[TPG][KK], va[NV], kb[TPG][KK], vb[NV];
+    issue(ka, va, r0);
+    for (;;) {
+      const int r1 = r0 + DW * R, r2 = r1 + DW * R;
+      if (r1 >= s1) { consume(ka, va, r0); break; }
+      issue(kb, vb, r1);
+      consume(ka, va, r0);
+      if (r2 >= s1) { consume(kb, vb, r1); break; }
+      issue(ka, va, r2);
+      consume(kb, vb, r1);
+      r0 = r2;
+    }
   }
-  // merge the row groups of a wave, then the waves, per query head
+  // merge the row groups of a wave (they share the reference maximum), then the waves, per query head
 #pragma unroll
   for (int t = 0; t < G; ++t) {
 #pragma unroll
-    for (int o = LPR; o < kWave; o <<= 1) {
-      const float m_o = __shfl_xor(m_run[t], o), l_o = __shfl_xor(l_run[t], o);
-      const float m_new = fmaxf(m_run[t], m_o);
-      const float s1w = weight_exp2(m_run[t], m_new), s2w = weight_exp2(m_o, m_new);
-      l_run[t] = l_run[t] * s1w + l_o * s2w;
+    for (int o = LPR; o < kWave; o <<= 1)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[t][e] = acc[t][e] * s1w + __shfl_xor(acc[t][e], o) * s2w;
-      m_run[t] = m_new;
-    }
+      for (int e = 0; e < 8; ++e) acc[t][e] += __shfl_xor(acc[t][e], o);
     if (lane < LPR) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) part[wave][t][sub * 8 + e] = acc[t][e];
-      if (lane == 0) { part[wave][t][DH] = m_run[t]; part[wave][t][DH + 1] = l_run[t]; }
     }
   }
-  __syncthreads();
-  for (int i = tid; i < G * DH; i += DT) {
-    const int t = i / DH, c = i - t * DH;
-    float m_all = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < DW; ++w) m_all = fmaxf(m_all, part[w][t][DH]);
-    float l_all = 0.0f, y = 0.0f;
+  for (int i = 0; i < NH; ++i) {
+    const float l = group_sum<16>(l_run[i]);
+    if (row16 == 0 && quarter < (G + 3) / 4) { part[wave][quarter * 4 + i][DH] = m_ref[i]; part[wave][quarter * 4 + i][DH + 1] = l; }
+  }
+  __syncthreads();
+  // partial (y, m, l) of this workgroup: 4 channels of a head per thread
+  constexpr int SLOTS = G * DH / 4, GRPS = DT / SLOTS;
+  static_assert(GRPS >= 1, "a slot of 4 channels per thread");
+  const int slot = tid % SLOTS, grp = tid / SLOTS, t_s = slot / (DH / 4), c_s = slot % (DH / 4) * 4;
+  float4 y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float m_all = -INFINITY, l_all = 0.0f;
+  const float* y_parts = a.partials + (size_t)unit * a.n_split * (G * DH);                  // [n_split][G][DH]
+  float* s_parts = a.partials + (size_t)units * a.n_split * (G * DH) + (size_t)unit * a.n_split * (G * 2);   // [n_split][G][2]
+  if (grp == 0) {
+#pragma unroll
+    for (int w = 0; w < DW; ++w) m_all = fmaxf(m_all, part[w][t_s][DH]);
 #pragma unroll
     for (int w = 0; w < DW; ++w) {
-      const float s = weight_exp2(part[w][t][DH], m_all);
-      l_all += part[w][t][DH + 1] * s;
-      y += part[w][t][c] * s;
+      const float s = weight_exp2(part[w][t_s][DH], m_all);
+      const float* y = &part[w][t_s][c_s];
+      l_all += part[w][t_s][DH + 1] * s;
+      y4.x += y[0] * s; y4.y += y[1] * s; y4.z += y[2] * s; y4.w += y[3] * s;
     }
-    float* dst = a.partials + (((size_t)b * a.H + h0 + t) * a.n_split + split) * (DH + 2);
-    dst[c] = y;
-    if (c == 0) { dst[DH] = m_all; dst[DH + 1] = l_all; }
-  }
-}
-
-// Merge of the n_split partials of one (sequence, query head).  512 threads = 512 / d_h groups of d_h
-// channels; group g folds partials g, g + NG, ... online (four loads in flight per thread), the groups
-// are merged through LDS.
-constexpr int CT = 512;
-
-template <class T, int DH>
-__global__ __launch_bounds__(CT) void dense_combine(const DenseArgs a) {
-  constexpr int NG = CT / DH;
-  __shared__ float sm[NG * (DH + 2)];
-  const int u = blockIdx.x, c = threadIdx.x % DH, grp = threadIdx.x / DH;
-  const float* src = a.partials + (size_t)u * a.n_split * (DH + 2);
-  float m = -INFINITY, l = 0.0f, y = 0.0f;
-  for (int s0 = grp; s0 < a.n_split; s0 += NG * 4) {
-    float pm[4], pl[4], py[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int s = s0 + t * NG;
-      const bool on = s < a.n_split;
-      pm[t] = on ? src[s * (DH + 2) + DH] : -INFINITY;
-      pl[t] = on ? src[s * (DH + 2) + DH + 1] : 0.0f;
-      py[t] = on ? src[s * (DH + 2) + c] : 0.0f;
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float m_new = fmaxf(m, pm[t]);
-      const float w_old = weight_exp2(m, m_new), w = weight_exp2(pm[t], m_new);
-      l = l * w_old + pl[t] * w;
-      y = y * w_old + py[t] * w;
-      m = m_new;
+    if (n_live == 1) {
+      store_out4<T>(out + slot * 4, y4, 1.0f / l_all);
+    } else {
+      store_agent4(y_parts, (uint32_t)(split * SLOTS + slot) * 16, y4);
+      if (c_s == 0) { store_agent(s_parts + (split * G + t_s) * 2, m_all); store_agent(s_parts + (split * G + t_s) * 2 + 1, l_all); }
     }
   }
-  sm[grp * (DH + 2) + c] = y;
-  if (c == 0) { sm[grp * (DH + 2) + DH] = m; sm[grp * (DH + 2) + DH + 1] = l; }
+  if (n_live == 1) return;
+  if (!last_to_arrive(a.tickets + unit, n_live, &ticket)) return;
+  // the merge: the partials of a channel are shared by GRPS threads, eight in flight each; n_live <= kDenseSplits
+  constexpr int FLY = 8;
+  float4 v[FLY];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int j = 0; j < FLY; ++j) {
+      const int s = s0 + j * GRPS;
+      v[j] = load_agent4(y_parts, (uint32_t)((s < n_live ? s : 0) * SLOTS + slot) * 16);
+    }
+  };
+  fetch(grp);
+  for (int i = tid; i < n_live * G; i += DT) { stat[i * 2] = load_agent(s_parts + i * 2); stat[i * 2 + 1] = load_agent(s_parts + i * 2 + 1); }
   __syncthreads();
-  if (grp == 0) {
-    float m_all = -INFINITY;
+  for (int t = wave; t < G; t += DW) {           // two partials per lane: their weights, with the denominator in them
+    float m[2], l[2];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) m_all = fmaxf(m_all, sm[g * (DH + 2) + DH]);
-    float l_all = 0.0f, y_all = 0.0f;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const float w = weight_exp2(sm[g * (DH + 2) + DH], m_all);
-      l_all += sm[g * (DH + 2) + DH + 1] * w;
-      y_all += sm[g * (DH + 2) + c] * w;
+    for (int j = 0; j < 2; ++j) {
+      const int p = (lane + j * kWave) * G + t;
+      const bool on = lane + j * kWave < n_live;
+      m[j] = on ? stat[p * 2] : -INFINITY; l[j] = on ? stat[p * 2 + 1] : 0.0f;
     }
-    uint16_t* out = reinterpret_cast<uint16_t*>(a.out) + (size_t)u * DH;
-    out[c] = l_all > 0.0f ? T::narrow(y_all / l_all) : (uint16_t)0;   // empty sequence: zeros
+    const float m_max = wave_max(fmaxf(m[0], m[1]));
+    const float w0 = weight_exp2(m[0], m_max), w1 = weight_exp2(m[1], m_max);
+    const float l_sum = wave_sum(l[0] * w0 + l[1] * w1);
+    if (lane < n_live) stat[(lane * G + t) * 2] = w0 / l_sum;
+    if (lane + kWave < n_live) stat[((lane + kWave) * G + t) * 2] = w1 / l_sum;
   }
+  __syncthreads();
+  y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int s0 = grp;;) {
+#pragma unroll
+    for (int j = 0; j < FLY; ++j) {
+      const int s = s0 + j * GRPS;
+      const float w = s < n_live ? stat[(s * G + t_s) * 2] : 0.0f;
+      if (s < n_live) { y4.x += v[j].x * w; y4.y += v[j].y * w; y4.z += v[j].z * w; y4.w += v[j].w * w; }
+    }
+    s0 += FLY * GRPS;
+    if (s0 - grp >= n_live) break;
+    fetch(s0);
+  }
+  if (GRPS > 1) {
+    red[tid] = y4;
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int k = 1; k < GRPS; ++k) {
+        const float4 o = red[k * SLOTS + slot];
+        y4.x += o.x; y4.y += o.y; y4.z += o.z; y4.w += o.w;
+      }
+    }
+  }
+  if (grp == 0) store_out4<T>(out + slot * 4, y4, 1.0f);
 }
 
 template <class T, int DH, int G>
 hipError_t launch_g(const DenseArgs& a, hipStream_t s) {
-  const int g = a.H / a.H_kv;
-  const int blocks = a.B * a.H_kv * (g / G) * a.n_split;
+  const int blocks = a.B * a.H_kv * (a.H / a.H_kv / G) * a.n_split;
   hipLaunchKernelGGL((dense_partial<T, DH, G>), dim3(blocks), dim3(DT), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dense_combine<T, DH>), dim3(a.B * a.H), dim3(CT), 0, s, a);
   return hipGetLastError();
 }
 
 template <class T, int DH>
 hipError_t launch_dh(const DenseArgs& a, hipStream_t s) {
-  const int g = a.H / a.H_kv;
-  if (g % 8 == 0 && DH <= 128) return launch_g<T, DH, 8>(a, s);
-  if (g % 4 == 0) return launch_g<T, DH, 4>(a, s);
-  if (g % 2 == 0) return launch_g<T, DH, 2>(a, s);
-  return launch_g<T, DH, 1>(a, s);
+  switch (dense_bundle(a.H / a.H_kv, DH)) {
+    case 8:
+      if constexpr (DH <= 128) return launch_g<T, DH, 8>(a, s);
+      return hipErrorInvalidValue;
+    case 4: return launch_g<T, DH, 4>(a, s);
+    case 2: return launch_g<T, DH, 2>(a, s);
+    default: return launch_g<T, DH, 1>(a, s);
+  }
 }
 
 }  // namespace

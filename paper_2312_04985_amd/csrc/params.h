@@ -10,6 +10,11 @@ constexpr int kDecodeThreads = 512;     // threads per workgroup of the fused de
 constexpr int kRadixBins = 2048;        // 11-bit digits: passes of 11, 11 and 10 bits
 constexpr int kWorkspaceHeader = 256;   // bytes; word 0 is the error word
 constexpr int kControlBytes = 65536;    // control block at the start of the workspace, zeroed by sparq_workspace_init
+// Counters of workgroups that have finished (last_to_arrive), inside the control block behind the header: all 0 between
+// launches.  The rest of the control block is scratch of the bulk append.
+constexpr int kTicketOffset = kWorkspaceHeader;
+constexpr int kTickets = (16384 - kWorkspaceHeader) / 4;
+constexpr int kAppendScratchOffset = 16384;
 constexpr int kMaxSplit = 16;           // most workgroups one (sequence, head) is split over
 constexpr int kSplitMaxUnits = 128;     // the digit-bucket plan (few units, long caches) serves at most this many (sequence, head) units
 constexpr int kProbeBlocks = 256 * 8;   // workgroups (of 256 threads) of the bandwidth probes
@@ -49,7 +54,9 @@ struct AppendArgs {
 
 struct DenseArgs {
   const void* K; const void* V; const int32_t* seq_lens; const void* q; void* out;
-  float* partials;   // [B*H, n_split, d_h + 2]
+  float* partials;   // [unit][n_split][heads of the bundle][d_h] numerators, then [unit][n_split][heads][2] (max,
+                     // denominator); a unit is a (sequence, KV head, bundle of query heads)
+  int32_t* tickets;  // one counter per (sequence, KV head, bundle), 0 between launches; used where n_split > 1
   int32_t* err;
   int32_t B, H, H_kv, S_max, d_h, n_split, rows_per_split;
   int32_t S_stride;   // positions per head in K and V
@@ -161,6 +168,10 @@ hipError_t launch_decode_shared(const DecodeArgs& a, float* z_ws, int dtype, hip
 // what a bulk append on a cache of S_max positions can use of AppendArgs::scratch (with less it runs on fewer workgroups)
 size_t append_scratch_bytes(int64_t heads, int S_max, int d_h);
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t s);
+constexpr int kDenseSplits = 128;   // most workgroups one unit of dense_decode is split over (two per lane in the merge)
+// bundles of query heads that share a pass over their KV head's rows, for g query heads per KV head
+constexpr int dense_bundle(int g, int d_h) { return g % 8 == 0 && d_h <= 128 ? 8 : (g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1)); }
+constexpr int dense_bundles(int g, int d_h) { return g / dense_bundle(g, d_h); }
 hipError_t launch_dense(const DenseArgs& a, int dtype, hipStream_t s);
 hipError_t launch_copy_probe(void* dst, const void* src, size_t n_bytes, hipStream_t s);
 hipError_t launch_read_probe(const void* src, size_t n_bytes, void* sink, hipStream_t s);

@@ -1,0 +1,33 @@
+"""dense_decode over several workgroups per KV head: edges of its row groups and splits, every bundle of query heads."""
+import pytest
+import torch
+
+from oracle import sparq_oracle as O
+from paper_2312_04985_amd import workloads as W
+
+import harness as Hn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_h,g,dtype", [(64, 8, "f16"), (64, 1, "bf16"), (128, 8, "bf16"), (128, 4, "f16"), (128, 3, "bf16"),
+                                         (256, 8, "bf16"), (256, 4, "f16"), (256, 2, "bf16")])
+@pytest.mark.parametrize("b,h_kv,lens", [
+    (4, 1, (1, 15, 16, 17)),                # below and above one tile of 16 rows
+    (4, 2, (0, 255, 256, 321)),             # an empty sequence; one split, one row into the next
+    (1, 1, (8192 + 5,)),                    # one unit over many splits
+    (9, 1, (2500, 1, 2049, 0, 640, 576, 577, 1024, 2560)),   # more units than 8: other splits, some of them empty
+])
+def test_dense_decode_edges(d_h, g, dtype, b, h_kv, lens):
+    w = W.Workload("dense", b, g * h_kv, h_kv, d_h, max(lens), 8, 8, dtype, seed=700 + d_h + g + b)
+    print("[case]", d_h, g, dtype, b, h_kv, lens, flush=True)
+    seq = torch.tensor(lens, dtype=torch.int32)
+    c = Hn.build_cache(w, seq_lens=seq, v_offset=True)
+    for scale in (1.0, 0.03):               # one row takes all the weight; many share it (the maximum keeps rising)
+        q = W.draw_queries(w, c.K_src, seq, q_scale=scale)[0].contiguous()
+        for _ in range(2):                  # the second call finds the counters as the first one left them
+            out = c.cache.dense(q)
+        K, V = Hn.host_cache_codes(c, c.cache.S_max)
+        ref = O.dense_decode(K, V, W.to_codes(q), seq.numpy(), dtype=w.dtype_code)
+        Hn.check_output(out.float().cpu().numpy(), ref, w.dtype_code)
+    assert c.cache.error_flags() == 0
