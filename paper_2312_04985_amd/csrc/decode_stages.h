@@ -310,67 +310,13 @@ __device__ __forceinline__ void flush_key_columns(uint16_t* Kt_head, const uint1
 
 struct SelectLds {
   uint32_t* hist;   // [2][kRadixBins] double-buffered digit histograms (swizzled slots)
-  uint32_t* wcnt;   // [2][NW] wave totals of the compaction scan, double-buffered
+  uint32_t* wcnt;   // [NW] wave totals of the compaction scan
   int* ctl;         // [8]
   float* red;       // [2 * NW]
 };
 
-// Radix select with digits of 11, 11 and 10 bits from the top.  On entry hist[0] holds the counts of
-// the first digit of keys[0..S) and hist[1] is zero.  Pass p counts into hist[p & 1] while the other
-// buffer is cleared; one wave finds the threshold digit, everyone picks it up after a barrier; the loop
-// ends as soon as the remaining bin is taken whole.  On return the selected keys are those with
-// (key & pmask) > pval plus the first `need` keys (by position) with (key & pmask) == pval.
-// kq = 0 (everything comes from the local window) selects nothing: returns a predicate no key meets.
-__device__ __forceinline__ void radix_select(const uint32_t* keys, int S, int kq, const SelectLds& sl,
-                                             int tid, int lane, int wave, uint32_t& pmask, uint32_t& pval, int& need) {
-  const int n_chunks = (S + 7) >> 3;
-  if (kq == 0) { pmask = 0xffffffffu; pval = 0xffffffffu; need = 0; return; }
-  pmask = 0u; pval = 0u; need = kq;
-  int in_bin = 0;          // keys in the bin decided by the previous pass
-  for (int pass = 0; pass < 3; ++pass) {
-    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-    const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
-    uint32_t* hist = sl.hist + (pass & 1) * kRadixBins;
-    if (pass > 0) {
-      uint32_t* other = sl.hist + ((pass + 1) & 1) * kRadixBins;   // free since the last barrier
-      for (int i = tid; i < kRadixBins; i += NT) other[i] = 0u;
-      if (in_bin <= kTieHeavy) {
-        for (int c = tid; c < n_chunks; c += NT) {
-          const uint4* src = reinterpret_cast<const uint4*>(keys + c * 8);
-          const uint4 lo = src[0], hi = src[1];
-          const uint32_t kx[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (c * 8 + e < S && (kx[e] & pmask) == pval) atomicAdd(&hist[hist_slot((kx[e] >> shift) & dmask)], 1u);
-        }
-      } else {
-        // thousands of keys share the decided bits (duplicated keys, underflowed scores): they may share the next
-        // digit too, and plain atomics on one address would take microseconds; count per wave first
-        for (int c0 = 0; c0 < n_chunks; c0 += NT) {
-          const int c = c0 + tid;
-          const bool on = c < n_chunks;
-          const uint4* src = reinterpret_cast<const uint4*>(keys + (on ? c : 0) * 8);
-          const uint4 lo = src[0], hi = src[1];
-          const uint32_t kx[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            hist_add_ties(hist, (kx[e] >> shift) & dmask, on && c * 8 + e < S && (kx[e] & pmask) == pval, lane);
-        }
-      }
-      __syncthreads();
-    }
-    if (wave == 0) find_threshold_bin(hist, need, lane, sl.ctl);
-    __syncthreads();
-    pval |= (uint32_t)sl.ctl[0] << shift;
-    pmask |= dmask << shift;
-    need = sl.ctl[1];
-    in_bin = sl.ctl[2];
-    if (need == in_bin) break;   // every key matching the decided bits is taken: no ties to split
-  }
-}
-
 // Exclusive prefix sum of v over the workgroup in thread order; *total gets the sum.
-// One barrier; callers alternate `wsum` between two NW-word buffers on consecutive calls.
+// One barrier; `wsum`: NW words.
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum, int lane, int wave,
                                                     uint32_t* total) {
   const uint32_t incl = wave_scan_incl(v);
@@ -387,109 +333,189 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum, 
   return before + incl - v;
 }
 
-// Ordered compaction of the selected positions into list[0..kq) (ascending) and
-// alpha = (sum over the selected of exp((d - dmax)/tau)) / (sum over all): Step 3's weight.
-// A lane owns up to 4 consecutive chunks per sweep (the chunks of a sweep are dealt out evenly), so lane order is
-// position order and one workgroup scan of the packed (above-threshold, equal-to-threshold) counts orders a whole
-// sweep of up to 32 NT positions: one barrier for lengths up to 16 384, whatever the length is a multiple of.  (Sweeps of NT chunks,
-// one per lane, needed ceil(S / 4096) scans, and a last sweep of a few chunks still cost 0.5 us of one wave's
-// dependent arithmetic: 3-4 us per launch at a length just above a multiple of 4096 with 2048 heads.)
-// Before the scan a lane reads its keys and sums the softmax weights: of all keys, of the keys above the
-// threshold (taken for sure), and of the keys equal to it on the decided bits; after it only the positions are
-// written, from two bit masks.  Which of the equal keys are taken (the first `need` by position) does not matter
-// for the sums: either all of them are (the select stopped early because the whole bin is taken), or all 32 bits
-// are decided and they share one weight.
-// `list` may be the key array itself: the list overwrites it from the front; a write never lands beyond the
-// position it records and all reads of a sweep precede its writes (the scan's barrier).  With key_out the keys
-// are read again after the scan: list must then be another array.
-// Ends with a barrier that also publishes the list.  esc = log2(e) / tau.  With WITH_ALPHA = false only
-// the list is produced (the grouped-query kernel gets alpha per query head elsewhere) and 0 is returned.
-// Positions >= forced_from (the local window) are taken whatever their keys; the predicate applies to
-// the positions before them.  Optional: key_out[n] receives the key of the n-th selected entry, the
-// entries written to list / idx_out are offset by pos_base, sums_out[0..1] receive the denominator and the
-// numerator of alpha.
-template <bool WITH_ALPHA = true>
-__device__ __forceinline__ float compact_selected(const uint32_t* keys, uint32_t* list, int S, int forced_from,
-                                                  uint32_t pmask, uint32_t pval, int need, float dmax, float esc,
-                                                  int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid,
-                                                  int lane, int wave, uint32_t* key_out = nullptr, int pos_base = 0,
-                                                  float* sums_out = nullptr) {
-  const int n_chunks = (S + 7) >> 3;
-  float zsum = 0.0f, asum = 0.0f, esum = 0.0f;
-  uint32_t run_gt = 0, run_eq = 0;
-  int sweep = 0;
-  for (int c0 = 0; c0 < n_chunks; c0 += 4 * NT, ++sweep) {
-    // the chunks of this sweep dealt out evenly, in order: the first `rem` lanes take one more than the others
-    const int n_here = n_chunks - c0 < 4 * NT ? n_chunks - c0 : 4 * NT;
-    const int per = n_here / NT, rem = n_here - per * NT;
-    const int cb = c0 + tid * per + (tid < rem ? tid : rem);   // the lane's first chunk of this sweep
-    const int mine = per + (tid < rem ? 1 : 0);
-    uint32_t gt_bits = 0, eq_bits = 0;           // bit 8 i + e: key e of the lane's i-th chunk
+// What select_compact adds up beside the list.
+enum class Sums {
+  kNone,        // nothing
+  kNumerator,   // alpha's numerator, sum over the selected of exp((d - dmax) / tau); the caller's threads bring the denominator
+  kBoth         // the numerator and the denominator, sum over all keys
+};
+
+// Step 2a as a whole: the k_old positions of largest key among keys[0..S_old) (ties to the lower position) and all
+// positions S_old .. S-1 (the local window), ascending, into list[0 .. k_old + S - S_old).
+// On entry hist[0] holds the counts of the first digit of keys[0..S_old), hist[1] is zero, and a barrier lies behind
+// them.  Digits of 11, 11 and 10 bits from the top.  The threshold's first digit comes from hist[0]; then every lane
+// reads its keys once and keeps two bit masks of them, "larger digit" and "equal digit".  What follows works on the
+// set bits only: the few keys that share the threshold's digit are counted by their next digit, one wave finds the
+// threshold among them, and their bits are sorted out, until the remaining bin is taken whole (with distinct keys:
+// after the second digit as a rule).  A lane owns consecutive positions, so lane order is position order and one
+// workgroup scan of the packed (larger, equal) counts orders the list, whatever the length.
+// Bound by vector instructions and by the serial steps of one workgroup.  Measured against a select that swept all keys
+// again for every digit and a compaction that took a softmax weight of every key (the denominator now comes with the
+// stream, where the memory is waited for anyway): step of 2048 heads at S = 8192 143.4 -> 139.8 us, 256 heads at 16 000
+// 71.6 -> 67.2, 32 heads at 3981 20.7 -> 19.9, one head at 1023 11.4 -> 11.0.
+// Which of the equal keys are taken (the first `need` by position) does not matter for the sums: either all of them
+// are, or all 32 bits are decided and they share one weight.
+// `list` may be the key array itself: it overwrites it from the front, a write never lands beyond the position it
+// records, and all reads of keys precede the scan's barrier.  With key_out (receives the key of the n-th entry) the keys
+// are read again after it: list must then be another array.  Entries of list / idx_out are offset by pos_base.
+// esc = log2(e) / tau; z = the calling thread's share of the denominator relative to dmax (kNumerator).
+// Ends with a barrier that also publishes the list.  Returns alpha; sums_out[0..1] receive the denominator and the
+// numerator.
+// kOwnWords: bit masks of each kind per lane, for up to 32 NT kOwnWords positions.
+template <Sums SUMS, int kOwnWords>
+__device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
+                                                float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
+                                                int wave, uint32_t* key_out, int pos_base, float* sums_out) {
+  // first digit of the threshold
+  uint32_t first = 0xffffffffu, last = 0xffffffffu;       // keys that share the decided bits lie in first .. last
+  int need = k_old, in_bin = k_old;
+  if (k_old > 0) {                                        // (0: everything comes from the window)
+    if (wave == 0) find_threshold_bin(sl.hist, k_old, lane, sl.ctl);
+    __syncthreads();
+    first = (uint32_t)sl.ctl[0] << 21; last = first | 0x1fffffu;
+    need = sl.ctl[1]; in_bin = sl.ctl[2];
+  }
+  // this lane's positions: granules of 4 (few keys: more lanes take part) or 8, dealt out evenly, in order
+  const int gran = S <= 4 * NT ? 4 : 8;
+  const int n_gran = (S + gran - 1) / gran, per = n_gran / NT, rem = n_gran - per * NT;
+  const int own = (tid * per + (tid < rem ? tid : rem)) * gran, n_own = (per + (tid < rem ? 1 : 0)) * gran;
+  uint32_t gt[kOwnWords], eq[kOwnWords];                  // bit i of word w: position own + 32 w + i
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = cb + i;
-      if (i < mine) {
-        const uint4* src = reinterpret_cast<const uint4*>(keys + c * 8);
-        const uint4 lo = src[0], hi = src[1];
-        const uint32_t kx[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  for (int w = 0; w < kOwnWords; ++w) {
+    gt[w] = eq[w] = 0;
+    const int at = own + 32 * w;
+    if (32 * w < n_own) {
+      const int old_here = S_old - at, all_here = S - at < n_own - 32 * w ? S - at : n_own - 32 * w;   // of this lane's own
+      const uint32_t old_mask = old_here >= 32 ? ~0u : (old_here <= 0 ? 0u : (1u << old_here) - 1u);
+      const uint32_t all_mask = all_here >= 32 ? ~0u : (all_here <= 0 ? 0u : (1u << all_here) - 1u);
+      uint32_t g = 0, ge = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const bool valid = (c * 8 + e) < S;
-          const bool old = (c * 8 + e) < forced_from;
-          const uint32_t hi_bits = kx[e] & pmask;
-          const bool g = valid && (hi_bits > pval || !old), q = valid && old && hi_bits == pval;
-          gt_bits |= (uint32_t)g << (8 * i + e); eq_bits |= (uint32_t)q << (8 * i + e);
-          if (WITH_ALPHA) {
-            const float w = exp2_weight((key_to_float(kx[e]) - dmax) * esc);
-            zsum += valid ? w : 0.0f;
-            asum += g ? w : 0.0f;
-            esum += q ? w : 0.0f;
+      for (int i = 7; i >= 0; --i) {
+        if (32 * w + 4 * i < n_own) {
+          const uint4 v = *reinterpret_cast<const uint4*>(keys + at + 4 * i);
+          const uint32_t kx[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 3; e >= 0; --e) {
+            g = g + g + (kx[e] > last ? 1u : 0u);
+            ge = ge + ge + (kx[e] >= first ? 1u : 0u);
+            if (SUMS == Sums::kBoth) z += 4 * i + e < all_here ? exp2_weight((key_to_float(kx[e]) - dmax) * esc) : 0.0f;
           }
         }
       }
+      eq[w] = ge & ~g & old_mask;
+      gt[w] = (g & old_mask) | (all_mask & ~old_mask);
     }
-    uint32_t total;
-    const uint32_t ex = block_scan_excl((uint32_t)__popc(gt_bits) | ((uint32_t)__popc(eq_bits) << 16),
-                                        sl.wcnt + (sweep & 1) * NW, lane, wave, &total);
-    const uint32_t gt_before = run_gt + (ex & 0xffffu);
-    const uint32_t eq_before = run_eq + (ex >> 16);
-    uint32_t o = gt_before + (eq_before < (uint32_t)need ? eq_before : (uint32_t)need);
-    // the taken keys of this lane: everything above the threshold and the first equal keys while they are needed
-    uint32_t take_bits = gt_bits;
-    if (eq_bits) {
-      uint32_t eb = eq_bits;
-      for (int room = need - (int)eq_before; eb && room > 0; --room) {
-        const uint32_t low = eb & (0u - eb);
-        take_bits |= low; eb ^= low;
-      }
+  }
+  auto each = [&](uint32_t (&bits)[kOwnWords], auto&& f) {      // f(word, bit, position) for every set bit
+#pragma unroll
+    for (int w = 0; w < kOwnWords; ++w)
+      for (uint32_t b = bits[w]; b; b &= b - 1) f(w, b & (0u - b), own + 32 * w + __ffs(b) - 1);
+  };
+  for (int pass = 1; pass < 3 && need != in_bin; ++pass) {
+    const int shift = pass == 1 ? 10 : 0;
+    const uint32_t dmask = pass == 1 ? 0x7ffu : 0x3ffu;
+    uint32_t* hist = sl.hist + (pass & 1) * kRadixBins;
+    if (pass == 2) {                                      // hist[0] has served the first digit
+      for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
+      __syncthreads();
     }
-    for (uint32_t tb = take_bits; tb; tb &= tb - 1) {
-      const int at = cb * 8 + (__ffs(tb) - 1);
+    if (in_bin <= kTieHeavy) {
+      each(eq, [&](int, uint32_t, int at) { atomicAdd(&hist[hist_slot((keys[at] >> shift) & dmask)], 1u); });
+    } else {
+      // thousands of keys share the decided bits (duplicated keys, underflowed scores): they may share the next
+      // digit too, and plain atomics on one address would take microseconds; count per wave first
+#pragma unroll
+      for (int w = 0; w < kOwnWords; ++w)
+        for (int i = 0; i < 32; ++i) {
+          const bool on = (eq[w] >> i) & 1u;
+          if (__ballot(on) == 0) continue;
+          hist_add_ties(hist, (keys[on ? own + 32 * w + i : 0] >> shift) & dmask, on, lane);
+        }
+    }
+    __syncthreads();
+    if (wave == 0) find_threshold_bin(hist, need, lane, sl.ctl);
+    __syncthreads();
+    const uint32_t digit = (uint32_t)sl.ctl[0];
+    need = sl.ctl[1]; in_bin = sl.ctl[2];
+    first |= digit << shift;
+    each(eq, [&](int w, uint32_t bit, int at) {
+      const uint32_t d = (keys[at] >> shift) & dmask;
+      if (d != digit) eq[w] &= ~bit;
+      if (d > digit) gt[w] |= bit;
+    });
+  }
+  float asum = 0.0f, esum = 0.0f;
+  if (SUMS != Sums::kNone) {
+    each(gt, [&](int, uint32_t, int at) { asum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
+    each(eq, [&](int, uint32_t, int at) { esum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
+  }
+  uint32_t n_gt = 0, n_eq = 0;
+#pragma unroll
+  for (int w = 0; w < kOwnWords; ++w) { n_gt += __popc(gt[w]); n_eq += __popc(eq[w]); }
+  uint32_t total;
+  const uint32_t ex = block_scan_excl(n_gt | (n_eq << 16), sl.wcnt, lane, wave, &total);
+  const uint32_t eq_before = ex >> 16;
+  uint32_t o = (ex & 0xffffu) + (eq_before < (uint32_t)need ? eq_before : (uint32_t)need);
+  int room = need - (int)eq_before;                       // equal keys still to be taken from this lane on
+#pragma unroll
+  for (int w = 0; w < kOwnWords; ++w) {
+    uint32_t take = gt[w];
+    for (uint32_t b = eq[w]; b && room > 0; --room, b &= b - 1) take |= b & (0u - b);
+    for (; take; take &= take - 1) {
+      const int at = own + 32 * w + __ffs(take) - 1;
       list[o] = (uint32_t)(pos_base + at);
       if (key_out) key_out[o] = keys[at];
       if (idx_out && (int)o < idx_stride) idx_out[o] = pos_base + at;
       ++o;
     }
-    run_gt += total & 0xffffu;
-    run_eq += total >> 16;
   }
-  if (!WITH_ALPHA) {
+  if (SUMS == Sums::kNone) {
     __syncthreads();
     return 0.0f;
   }
-  // run_eq is now the number of equal keys in the whole array, the same in every thread
-  const bool all_equal_taken = (uint32_t)need >= run_eq;
+  const bool all_equal_taken = (uint32_t)need >= (total >> 16);
   if (all_equal_taken) asum += esum;
-  zsum = wave_sum(zsum); asum = wave_sum(asum);
-  if (lane == 0) { sl.red[wave] = zsum; sl.red[NW + wave] = asum; }
+  z = wave_sum(z); asum = wave_sum(asum);
+  if (lane == 0) { sl.red[wave] = z; sl.red[NW + wave] = asum; }
   __syncthreads();
   float zt = 0.0f, at = 0.0f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) { zt += sl.red[w]; at += sl.red[NW + w]; }
-  if (!all_equal_taken) at += (float)need * exp2_weight((key_to_float(pval) - dmax) * esc);
+  if (!all_equal_taken) at += (float)need * exp2_weight((key_to_float(first) - dmax) * esc);
+  // numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
   if (sums_out) { sums_out[0] = zt; sums_out[1] = at; }
-  return at / zt;
+  const float alpha = at / zt;
+  return k_old == S_old || alpha > 1.0f ? 1.0f : alpha;
 }
+
+template <Sums SUMS>
+__device__ __forceinline__ float select_compact(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
+                                                float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
+                                                int wave, uint32_t* key_out = nullptr, int pos_base = 0, float* sums_out = nullptr) {
+  // (one mask per lane as a case of its own: straight code without the loops over masks, 0.4 us of a call of 11 us)
+  if (S <= 32 * NT)
+    return select_compact_words<SUMS, 1>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
+                                         pos_base, sums_out);
+  return select_compact_words<SUMS, 3>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
+                                       pos_base, sums_out);      // LDS ends at about 40 000 keys
+}
+
+// A thread's share of the softmax denominator, summed while the logit numerators are produced: relative to the
+// largest value the thread has seen, brought to the sequence's maximum at the end.
+struct RunningSum {
+  float ref = -3.0e38f, z = 0.0f;
+  template <int M>
+  __device__ __forceinline__ void add(const float (&d)[M], float esc) {
+    float m = ref;
+#pragma unroll
+    for (int e = 0; e < M; ++e) m = fmaxf(m, d[e]);
+    z *= exp2_weight((ref - m) * esc);
+#pragma unroll
+    for (int e = 0; e < M; ++e) z += exp2_weight((d[e] - m) * esc);
+    ref = m;
+  }
+  __device__ __forceinline__ float relative_to(float dmax, float esc) const { return z * exp2_weight((ref - dmax) * esc); }
+};
 
 // ------------------------------------------------------------------------------------------------
 // Step 2b: exact softmax attention over gathered rows (Eq. 8), online softmax in the exp2 domain

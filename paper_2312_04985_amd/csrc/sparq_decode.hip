@@ -168,14 +168,13 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   const size_t row_bytes = TILED ? 16 : (size_t)a.S_stride * 2;
   const char* Kt_head = TILED ? reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2)
                               : reinterpret_cast<const char*>(a.Kt) + kv_head * DH * row_bytes;
-  float tmax = -INFINITY;
+  const float esc = kLog2e / tau;
+  RunningSum zs;
   auto finish = [&](int c, const float (&acc)[8]) {
     uint32_t kx[8];
+    zs.add(acc, esc);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      tmax = fmaxf(tmax, acc[e]);
-      kx[e] = float_to_key(acc[e]);
-    }
+    for (int e = 0; e < 8; ++e) kx[e] = float_to_key(acc[e]);
     hist_add_chunk(L.sel.hist, kx, win.S_old - c * 8);
     uint4* dst = reinterpret_cast<uint4*>(L.keys + c * 8);
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
@@ -184,15 +183,15 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   stream_channel_rows<T>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, TILED ? DH * 16u : 16u);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, L.qry.qs, r8, lane);
-    tmax = fmaxf(tmax, dot);
     if (lane == 0) {
+      zs.add({dot}, esc);
       const uint32_t key = float_to_key(dot);
       L.keys[S_fl + wave] = key;
       if (S_fl + wave < win.S_old) atomicAdd(&L.sel.hist[hist_slot(key >> 21)], 1u);
     }
   }
   SPARQ_STAMP(2);
-  tmax = wave_max(tmax);
+  const float tmax = wave_max(zs.ref);
   if (lane == 0) L.sel.red[wave] = tmax;
   __syncthreads();
   SPARQ_STAMP(3);
@@ -201,12 +200,9 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, L.sel.red[w]);
 
   // ---------------- stage 2 ----------------
-  uint32_t pmask, pval;
-  int need;
-  radix_select(L.keys, win.S_old, win.k_old, L.sel, tid, lane, wave, pmask, pval, need);
   SPARQ_STAMP(4);
-  const float alpha = compact_selected(L.keys, L.keys, S, win.S_old, pmask, pval, need, dmax, kLog2e / tau, idx_out, a.idx_stride,
-                                       L.sel, tid, lane, wave);
+  const float alpha = select_compact<Sums::kNumerator>(L.keys, L.keys, S, win.S_old, win.k_old, dmax, esc, zs.relative_to(dmax, esc),
+                                                       idx_out, a.idx_stride, L.sel, tid, lane, wave);
   SPARQ_STAMP(5);
   if (tid == 0) {
     if (a.alpha_out) a.alpha_out[u] = alpha;

@@ -103,15 +103,14 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   const int end = p0 + len < S_fl ? p0 + len : S_fl;     // whole chunks of this span that are in Kt
   const size_t row_bytes = (size_t)d.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
-  float tmax = -INFINITY;
+  const float esc = kLog2e / tau;
+  RunningSum zs;
   stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, p0 >> 3, end > p0 ? end >> 3 : p0 >> 3, tid,
                          [&](int c, const float (&acc)[8]) {
     uint32_t kx[8];
+    zs.add(acc, esc);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      tmax = fmaxf(tmax, acc[e]);
-      kx[e] = float_to_key(acc[e]);
-    }
+    for (int e = 0; e < 8; ++e) kx[e] = float_to_key(acc[e]);
     hist_add_chunk(hist, kx, win.S_old - c * 8);
     uint4* dst = reinterpret_cast<uint4*>(keys + (c * 8 - p0));
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
@@ -119,14 +118,14 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   });
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, qs, r8, lane);
-    tmax = fmaxf(tmax, dot);
     if (lane == 0) {
+      zs.add({dot}, esc);
       const uint32_t key = float_to_key(dot);
       keys[S_fl + wave - p0] = key;
       if (S_fl + wave < win.S_old) atomicAdd(&hist[hist_slot(key >> 21)], 1u);
     }
   }
-  tmax = wave_max(tmax);
+  const float tmax = wave_max(zs.ref);
   if (lane == 0) red[wave] = tmax;
   __syncthreads();
   float dmax = red[0];
@@ -140,14 +139,11 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   n_old = n_old < 0 ? 0 : (n_old > len ? len : n_old);
   const int k_old = win.k_old < n_old ? win.k_old : n_old;
   const SelectLds sel{hist, wcnt, ctl, red};
-  uint32_t pmask, pval;
-  int need;
-  radix_select(keys, n_old, k_old, sel, tid, lane, wave, pmask, pval, need);
   uint32_t* cand_key = a.cand_key_ws + slot * a.cand_cap;
   uint32_t* cand_pos = reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap;
   float sums[2];
-  compact_selected(keys, cand_pos, len, n_old, pmask, pval, need, dmax, kLog2e / tau, nullptr, 0, sel, tid, lane, wave,
-                   cand_key, p0, sums);
+  select_compact<Sums::kNumerator>(keys, cand_pos, len, n_old, k_old, dmax, esc, zs.relative_to(dmax, esc), nullptr, 0, sel, tid, lane,
+                                   wave, cand_key, p0, sums);
   if (tid == 0) {
     a.cnt_ws[slot] = k_old + (len - n_old);
     a.tmax_ws[slot] = dmax;
@@ -220,11 +216,8 @@ __global__ __launch_bounds__(NT) void long_merge(const LongArgs a) {
   }
   __syncthreads();
   const SelectLds sel{hist, wcnt, ctl, red};
-  uint32_t pmask, pval;
-  int need;
-  radix_select(keys, n_free, win.k_old, sel, tid, lane, wave, pmask, pval, need);
   float sums[2];
-  compact_selected(keys, keys, n_cand, n_free, pmask, pval, need, dmax, esc, nullptr, 0, sel, tid, lane, wave, nullptr, 0, sums);
+  select_compact<Sums::kNumerator>(keys, keys, n_cand, n_free, win.k_old, dmax, esc, 0.0f, nullptr, 0, sel, tid, lane, wave, nullptr, 0, sums);
   const float alpha = sums[1] / zsum;
   // candidate numbers -> positions
   int32_t* list = a.list_ws + (size_t)u * d.S_max;

@@ -202,11 +202,8 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   __syncthreads();
 
   // ---------------- stage 2: the kq positions of largest group score ----------------
-  uint32_t pmask, pval;
-  int need;
-  radix_select(L.keys, win.S_old, win.k_old, L.sel, tid, lane, wave, pmask, pval, need);
   int32_t* idx_out = a.idx_out ? a.idx_out + u0 * a.idx_stride : nullptr;
-  compact_selected<false>(L.keys, L.keys, S, win.S_old, pmask, pval, need, 0.0f, 0.0f, idx_out, a.idx_stride, L.sel, tid, lane, wave);
+  select_compact<Sums::kNone>(L.keys, L.keys, S, win.S_old, win.k_old, 0.0f, 0.0f, 0.0f, idx_out, a.idx_stride, L.sel, tid, lane, wave);
   if (idx_out) {
     if (tid == 0 && kq > a.idx_stride) atomicOr(a.err, 4);
     for (int n = kq + tid; n < a.idx_stride; n += NT) idx_out[n] = -1;

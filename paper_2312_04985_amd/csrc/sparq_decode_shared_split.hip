@@ -274,11 +274,8 @@ __global__ __launch_bounds__(NT, 2) void gs_select(const GsArgs a) {
   n_old = n_old < 0 ? 0 : (n_old > len ? len : n_old);
   const int k_old = win.k_old < n_old ? win.k_old : n_old;
   const SelectLds sel{hist, wcnt, ctl, red};
-  uint32_t pmask, pval;
-  int need;
-  radix_select(keys, n_old, k_old, sel, tid, lane, wave, pmask, pval, need);
-  compact_selected<false>(keys, reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap, len, n_old, pmask, pval, need,
-                          0.0f, 0.0f, nullptr, 0, sel, tid, lane, wave, a.cand_key_ws + slot * a.cand_cap, p0);
+  select_compact<Sums::kNone>(keys, reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap, len, n_old, k_old, 0.0f, 0.0f, 0.0f,
+                              nullptr, 0, sel, tid, lane, wave, a.cand_key_ws + slot * a.cand_cap, p0);
   if (tid == 0) a.cnt_ws[slot] = k_old + (len - n_old);
 }
 
@@ -339,10 +336,7 @@ __global__ __launch_bounds__(NT) void gs_merge(const GsArgs a) {
   }
   __syncthreads();
   const SelectLds sel{hist, wcnt, ctl, red};
-  uint32_t pmask, pval;
-  int need;
-  radix_select(keys, n_free, win.k_old, sel, tid, lane, wave, pmask, pval, need);
-  compact_selected<false>(keys, keys, n_cand, n_free, pmask, pval, need, 0.0f, 0.0f, nullptr, 0, sel, tid, lane, wave);
+  select_compact<Sums::kNone>(keys, keys, n_cand, n_free, win.k_old, 0.0f, 0.0f, 0.0f, nullptr, 0, sel, tid, lane, wave);
 
   // candidate numbers -> positions; alpha_h = sum over the selected positions of s-hat_h from the stored logits
   float mh[G], inv_z[G], esc[G], asum[G];

@@ -160,11 +160,8 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, L.sel.red[w]);
 
   // ---------------- stage 2 ----------------
-  uint32_t pmask, pval;
-  int need;
-  radix_select(L.keys, win.S_old, win.k_old, L.sel, tid, lane, wave, pmask, pval, need);
-  const float alpha = compact_selected(L.keys, L.keys, S, win.S_old, pmask, pval, need, dmax, kLog2e / tau, idx_out,
-                                       a.idx_stride, L.sel, tid, lane, wave);
+  const float alpha = select_compact<Sums::kBoth>(L.keys, L.keys, S, win.S_old, win.k_old, dmax, kLog2e / tau, 0.0f, idx_out,
+                                                  a.idx_stride, L.sel, tid, lane, wave);
   if (tid == 0) {
     if (a.alpha_out) a.alpha_out[u] = alpha;
     if (idx_out && kq > a.idx_stride) atomicOr(a.err, 4);

@@ -1,0 +1,34 @@
+"""Step 2's selection at the lengths where its lanes own another number of keys: four, eight, a whole bit mask, three."""
+import pytest
+import torch
+
+from paper_2312_04985_amd import binding as B
+from paper_2312_04985_amd import workloads as W
+
+import harness as Hn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("S", [3, 2047, 2049, 4100, 16384, 16385, 33000])
+@pytest.mark.parametrize("window,dup", [(0, 0), (13, 0), (37, 2500)])
+def test_selection_edges(S, window, dup):
+    w = W.Workload("edges", 2, 3, 3, 64, S, 8, max(1, S // 9), "f16" if S % 2 else "bf16", planted=(1, 2), seed=800 + S + window)
+    print("[case]", S, window, dup, flush=True)
+    b = Hn.build_cache(w, v_offset=True, dup_rows=min(dup, S))
+    for scale in (1.0, 0.03):
+        q = W.draw_queries(w, b.K_src, b.seq_lens, q_scale=scale)[0].contiguous()
+        print(Hn.compare_decode(b, q, local_window=window), flush=True)
+
+
+@pytest.mark.parametrize("same", [3000, 16500])
+def test_thousands_of_equal_keys_around_the_threshold(same):
+    """Keys that share every digit, and keys that share the first: the lowest positions are taken, alpha is their share."""
+    w = W.Workload("equal", 1, 2, 2, 64, same + 300, 8, 700, "f16", seed=830, recipe="gaussian")
+    b = Hn.build_cache(w)
+    b.K_src[:, :, 150:150 + same] = b.K_src[:, :, 150:151]
+    b = Hn.Built(w, type(b.cache)(w.B, w.H, w.H_kv, W.round_up(w.S, 64), w.d_h, w.r, w.k, w.torch_dtype), b.K_src, b.V_src, b.seq_lens, None)
+    b.cache.append(b.K_src, b.V_src)
+    for stream in range(3):
+        q = W.draw_queries(w, b.K_src, b.seq_lens, stream=stream)[0].contiguous()
+        print(Hn.compare_decode(b, q, local_window=11), flush=True)
