@@ -215,7 +215,7 @@ int sparq_decode_noalloc(const sparq_shape* shape, const sparq_cache* cache, con
  * The whole decode step in one call: exactly sparq_kv_append with n_new = 1 followed by
  * sparq_decode (Section 4: the step writes k and v, updates the mean value vector and attends
  * over the cache including the new token).  One launch where one workgroup serves a head; the
- * three launches of the few-heads-long-cache plan with the append in the last one; for the other
+ * launches of the few-heads-long-cache plan and of the two-level plan with the append in the last one; for the other
  * plans the append kernel followed by the decode launches.  The small state is not updated in place:
  * the new lengths and means are written to seq_lens_next [B] and v_mean_next [B, H_kv, d_h]
  * (device, must not alias cache->seq_lens / cache->v_mean, which are only read) and the caller

@@ -116,12 +116,7 @@ bool two_level_plan(const sparq_shape* s, int span, size_t lds_max, PlanInfo* p)
   if (n_span > kMaxSpans) return false;
   const int cap = s->k < span ? s->k : span;
   if (long_scores_lds_bytes(span, s->d_h) > lds_max || long_merge_lds_bytes((int)n_span, cap) > lds_max) return false;
-  const int64_t units = (int64_t)s->B * s->H;
-  int64_t n = 512 / units;                      // gather workgroups per unit: fill the chip, >= 64 rows each
-  if (n > kMaxSplit) n = kMaxSplit;
-  if (n > s->k / 64) n = s->k / 64;
-  if (n < 1) n = 1;
-  p->n_span = (int)n_span; p->span_len = span; p->cand_cap = cap; p->n_split = (int)n;
+  p->n_span = (int)n_span; p->span_len = span; p->cand_cap = cap;
   return true;
 }
 
@@ -286,7 +281,7 @@ BucketLayout bucket_layout(const sparq_shape* s, const PlanInfo& p) {
   return l;
 }
 
-struct LongLayout { size_t tmax, zsum, cnt, tau, alpha, ckey, cpos, list, part, end; };
+struct LongLayout { size_t tmax, zsum, cnt, tau, ckey, cpos, end; };
 
 LongLayout long_layout(const sparq_shape* s, const PlanInfo& p) {
   const size_t units = (size_t)s->B * s->H;
@@ -296,12 +291,10 @@ LongLayout long_layout(const sparq_shape* s, const PlanInfo& p) {
   l.zsum = off; off = align256(off + units * p.n_span * sizeof(float));
   l.cnt = off; off = align256(off + units * p.n_span * sizeof(int32_t));
   l.tau = off; off = align256(off + units * sizeof(float));
-  l.alpha = off; off = align256(off + units * sizeof(float));
   l.ckey = off; off = align256(off + units * p.n_span * p.cand_cap * sizeof(uint32_t));
   l.cpos = off; off = align256(off + units * p.n_span * p.cand_cap * sizeof(int32_t));
-  l.list = off; off = align256(off + units * s->S_max * sizeof(int32_t));
-  l.part = off; off = align256(off + units * p.n_split * (s->d_h + 2) * sizeof(float));
-  l.end = off;
+  // (a position list per unit, as this plan once kept: it decides which shapes sparq_decode_noalloc refuses)
+  l.end = align256(off + units * s->S_max * sizeof(int32_t));
   return l;
 }
 
@@ -338,9 +331,9 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
   if (p.plan == kPlanFused) return launch_decode(a, shape->dtype, s);
   const bool one_k = p.plan == kPlanSingleK;
   DecodeArgs d = a;
-  if (a.k_new && p.plan != kPlanBucket && p.plan != kPlanSharedBucket) {
-    // the one-workgroup-per-head kernel and the digit-bucket plans have the append built in; the other plans
-    // append into the *_next state with the append kernel, then decode from that state
+  if (a.k_new && p.plan != kPlanBucket && p.plan != kPlanSharedBucket && p.plan != kPlanLong) {
+    // the one-workgroup-per-head kernel, the digit-bucket plans and the two-level plan have the append built in; the
+    // other plans append into the *_next state with the append kernel, then decode from that state
     AppendArgs ap;
     ap.K = a.K; ap.Kt = one_k ? nullptr : a.Kt; ap.V = a.V; ap.v_mean = const_cast<float*>(a.v_mean); ap.seq_lens = const_cast<int32_t*>(a.seq_lens);
     ap.v_mean_out = a.v_mean_next; ap.seq_lens_out = a.seq_lens_next;
@@ -406,16 +399,13 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     const LongLayout l = long_layout(shape, p);
     LongArgs la;
     la.d = d;
-    la.n_span = p.n_span; la.span_len = p.span_len; la.cand_cap = p.cand_cap; la.n_split = p.n_split;
+    la.n_span = p.n_span; la.span_len = p.span_len; la.cand_cap = p.cand_cap;
     la.tmax_ws = reinterpret_cast<float*>(w + l.tmax);
     la.zsum_ws = reinterpret_cast<float*>(w + l.zsum);
     la.cnt_ws = reinterpret_cast<int32_t*>(w + l.cnt);
     la.tau_ws = reinterpret_cast<float*>(w + l.tau);
-    la.alpha_ws = reinterpret_cast<float*>(w + l.alpha);
     la.cand_key_ws = reinterpret_cast<uint32_t*>(w + l.ckey);
     la.cand_pos_ws = reinterpret_cast<int32_t*>(w + l.cpos);
-    la.list_ws = reinterpret_cast<int32_t*>(w + l.list);
-    la.part_ws = reinterpret_cast<float*>(w + l.part);
     return launch_decode_long(la, shape->dtype, s);
   }
   return hipErrorInvalidValue;
@@ -615,7 +605,7 @@ const char* sparq_decode_plan(const sparq_shape* caller_shape) {
   const sparq_shape* shape = &sized;
   switch (choose_plan(shape).plan) {
     case kPlanFused: return "sparq_decode_fused (one workgroup per head, one launch)";
-    case kPlanLong: return "long_scores + long_merge + split_gather + split_combine (two-level selection plan)";
+    case kPlanLong: return "long_scores + long_finish (two-level selection plan)";
     case kPlanBucket: return "bk_scores + bk_select_gather + bk_combine (digit-bucket plan)";
     case kPlanShared: return "sparq_decode_shared (grouped-query rule, one workgroup per KV head)";
     case kPlanSharedBucket: return "gs_logits + bk_group_scores + bk_select_gather + bk_combine (grouped-query rule on the digit-bucket plan)";

@@ -71,16 +71,12 @@ struct LongArgs {
   int32_t n_span;          // workgroups per (sequence, head) in the scoring launch
   int32_t span_len;        // positions per span
   int32_t cand_cap;        // candidates one span may hand on = min(k, span_len)
-  int32_t n_split;         // workgroups per (sequence, head) in the gather launch
   float* tmax_ws;          // [B * H][n_span] largest logit numerator of each span
   float* zsum_ws;          // [B * H][n_span] sum over the span of exp((d - span max) / tau)
   int32_t* cnt_ws;         // [B * H][n_span] candidates of each span
   float* tau_ws;           // [B * H]
-  float* alpha_ws;         // [B * H]
   uint32_t* cand_key_ws;   // [B * H][n_span][cand_cap] keys of the candidates, position-ascending
   int32_t* cand_pos_ws;    // [B * H][n_span][cand_cap] their positions
-  int32_t* list_ws;        // [B * H][S_max] selected positions, ascending
-  float* part_ws;          // [B * H][n_split][d_h + 2] attention partials
 };
 
 // grouped-query rule over several workgroups per (sequence, KV head)
@@ -102,12 +98,11 @@ struct GsArgs {
   float* part_ws;          // [B * H][n_split][d_h + 2] attention partials
 };
 
-// the gather and merge launches shared by the multi-launch plans
+// the last launch of the grouped-query plan over several workgroups
 struct SplitArgs {
   DecodeArgs d;
   int32_t n_split;       // gather workgroups per (sequence, head)
   float* alpha_ws;       // [B * H]
-  int32_t* list_ws;      // [B * H][S_max] selected positions, ascending
   float* part_ws;        // [B * H][n_split][d_h + 2] attention partials
 };
 
@@ -155,10 +150,6 @@ hipError_t launch_decode_bucket_group(const BucketArgs& a, int dtype, hipStream_
 // the first launch of the grouped-query plans alone: logit numerators and per-head span statistics (uses d, n1, span1,
 // z_ws, stat_ws, esc_ws of `a`)
 hipError_t launch_group_logits(const GsArgs& a, int dtype, hipStream_t s);
-// the gather launch and the merge (gather over slices of list_ws, merge): uses d, n_split,
-// alpha_ws, list_ws, part_ws of `a`
-hipError_t launch_split_gather(const SplitArgs& a, int dtype, hipStream_t s);
-// the last launch alone: uses d, n_split, alpha_ws, part_ws
 hipError_t launch_split_combine(const SplitArgs& a, int dtype, hipStream_t s);
 size_t gs_select_lds_bytes(int span2);
 size_t gs_merge_lds_bytes(int n2, int cand_cap);

@@ -6,9 +6,13 @@
 //   long_scores    (units x n_span workgroups) Step 1 on a span of span_len positions, keys in LDS; the
 //                  span's own top-min(k, span) positions go to the workspace as (key, position) candidates,
 //                  position-ascending, with the span's largest logit and its softmax denominator
-//   long_merge     (one workgroup per unit) the candidates of all spans into LDS (at most n_span x k),
-//                  the same radix select and ordered compaction over them, alpha, the position list
-//   split_gather / split_combine   exact attention over slices of the list, merge and blend
+//   long_finish    (one workgroup per unit) the candidates of all spans into LDS (at most n_span x k),
+//                  the same radix select and ordered compaction over them, alpha, the position list, exact attention over
+//                  the selected rows, the blend, and inside sparq_decode_step the append
+// (Measured for 512 units of 40 960 positions, k = 1024, per step: with the append, the merge, the gather and the last
+// merge as launches of their own 313 us, so 300; everything in one launch, the workgroup of a unit's last span going
+// on with the unit, 350-358: with the memory saturated each of its round trips to other workgroups' results takes
+// microseconds.)
 // The local window is part of both levels: its positions are the last ones of the sequence, every span
 // hands on those it holds, and they are the last candidates of the merge.
 #include "decode_stages.h"
@@ -58,11 +62,9 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
 
   uint16_t qcode = 0;
   if (tid < DH) qcode = reinterpret_cast<const uint16_t*>(d.q)[(size_t)u * DH + tid];
-  int S = d.seq_lens[b];
-  if (S < 0 || S > d.S_max) {
-    if (tid == 0 && s == 0) atomicOr(d.err, 8);
-    S = S < 0 ? 0 : d.S_max;
-  }
+  bool appended, bad, full;      // inside a step the row being appended counts as position S_b; long_finish writes it
+  const int S = visible_length(d, b, appended, bad, full);
+  if (tid == 0 && s == 0 && (bad || full)) atomicOr(d.err, (bad ? 8 : 0) | (full ? 1 : 0));
   int32_t* idx_out = d.idx_out ? d.idx_out + (size_t)u * d.idx_stride : nullptr;
   if (S == 0) {   // nothing cached: span 0 writes the defined outputs, the later launches skip the unit
     if (s == 0) {
@@ -93,12 +95,17 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
     if (tid == 0) a.tau_ws[u] = tau;
   }
 
-  // the newest S mod 8 positions are not in Kt: the span that holds them takes them from the rows of K
-  const int S_fl = S & ~7, r8 = (d.r + 7) & ~7;
+  // the newest S mod 8 positions are not in Kt (inside a step: up to 8, Kt being up to date for the length before the
+  // call): the span that holds them takes them from the rows of K, the row being appended from the inputs
+  const int S_fl = (appended ? S - 1 : S) & ~7, r8 = (d.r + 7) & ~7;
   const int n_tail = (S_fl >= p0 && S_fl < p0 + len) ? S - S_fl : 0;
   TailRow tail;
-  if (wave < n_tail)
-    tail = tail_row_issue(reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH, chan, r8, lane);
+  if (wave < n_tail) {
+    const uint16_t* krow = appended && wave == n_tail - 1
+                               ? reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH
+                               : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
+    tail = tail_row_issue(krow, chan, r8, lane);
+  }
 
   const int end = p0 + len < S_fl ? p0 + len : S_fl;     // whole chunks of this span that are in Kt
   const size_t row_bytes = (size_t)d.S_stride * 2;
@@ -151,23 +158,46 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   }
 }
 
-// One workgroup per unit: merge the candidates of the spans.
-__global__ __launch_bounds__(NT) void long_merge(const LongArgs a) {
+// One workgroup per unit: merge the candidates of the spans and do the rest of the unit.
+template <class T, int DH>
+__global__ __launch_bounds__(NT, 4) void long_finish(const LongArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   const DecodeArgs& d = a.d;
   const int cap_all = a.n_span * a.cand_cap;
-  uint32_t* keys = smem;                                          // [round_up(cap_all, 8)]
-  uint32_t* hist = keys + ((cap_all + 7) & ~7);                   // [2][kRadixBins]
+  uint32_t* keys = smem;                                          // [round_up(cap_all, 8)]; later the list
+  uint32_t* hist = keys + ((cap_all + 7) & ~7);                   // [2][kRadixBins]; later the waves' partial results
   float* red = reinterpret_cast<float*>(hist + 2 * kRadixBins);   // [32]
   uint32_t* wcnt = reinterpret_cast<uint32_t*>(red + 32);         // [16]
   int* ctl = reinterpret_cast<int*>(wcnt + 16);                   // [8]
   int* off = ctl + 8;                                             // [kMaxSpans + 1] candidates before each span
   float* stat = reinterpret_cast<float*>(off + kMaxSpans + 8);    // [2]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int u = blockIdx.x, b = u / d.H;
-  int S = d.seq_lens[b];
-  S = S < 0 ? 0 : (S > d.S_max ? d.S_max : S);
-  if (S == 0) return;                      // outputs written by long_scores
+  const int U = d.B * d.H;
+  int u = blockIdx.x;
+  if ((U & 7) == 0) u = (u & 7) * (U >> 3) + (u >> 3);            // the heads of a KV group share an XCD
+  const int b = u / d.H, h = u - b * d.H, hk = h / (d.H / d.H_kv);
+  const size_t kv_head = (size_t)b * d.H_kv + hk;
+  bool appended, bad, full;
+  const int S = visible_length(d, b, appended, bad, full);
+  const bool owner = d.k_new && h == hk * (d.H / d.H_kv);         // writes the row and the new mean
+  if (d.k_new && h == 0 && tid == 0) {   // a length beyond the bound of this call that the buffers can hold is carried over as it is
+    const int S_in = d.seq_lens[b];
+    d.seq_lens_next[b] = (S_in > d.S_max && S_in <= d.S_stride) ? S_in : S;
+  }
+  // what the end of the unit needs is requested early
+  float vm = 0.0f;
+  uint16_t kc = 0, vc = 0;
+  if (tid < DH) {
+    vm = d.v_mean[kv_head * DH + tid];
+    if (appended) {
+      kc = reinterpret_cast<const uint16_t*>(d.k_new)[kv_head * DH + tid];
+      vc = reinterpret_cast<const uint16_t*>(d.v_new)[kv_head * DH + tid];
+    }
+  }
+  if (S == 0) {                            // outputs written by long_scores
+    if (owner && tid < DH) d.v_mean_next[kv_head * DH + tid] = vm;
+    return;
+  }
   int kb = d.k_per_seq ? d.k_per_seq[b] : d.k;
   kb = kb < 1 ? 1 : (kb > d.k ? d.k : kb);
   const int kq = kb < S ? kb : S;
@@ -175,6 +205,9 @@ __global__ __launch_bounds__(NT) void long_merge(const LongArgs a) {
   const Window win = make_window(d.local_window, S, kq);
   const float tau = a.tau_ws[u];
   const float esc = kLog2e / tau;
+  using G = RowGeometry<DH>;
+  const int sub = lane % G::LPR;
+  const uint4 qraw = load16(reinterpret_cast<const uint16_t*>(d.q) + (size_t)u * DH + sub * 8);
 
   for (int i = tid; i < 2 * kRadixBins; i += NT) hist[i] = 0u;
   if (wave == 0) {   // kMaxSpans = 64: one lane per span
@@ -194,23 +227,27 @@ __global__ __launch_bounds__(NT) void long_merge(const LongArgs a) {
   const int n_cand = off[a.n_span];
   const int n_free = n_cand - win.n_local;        // candidates that compete; the window's come last
   const float dmax = stat[0], zsum = stat[1];
-  for (int s = 0; s < a.n_span; ++s) {
-    const int o = off[s], cnt = off[s + 1] - o;
-    const uint32_t* src = a.cand_key_ws + ((size_t)u * a.n_span + s) * a.cand_cap;
-    for (int n0 = 0; n0 < cnt; n0 += 4 * NT) {      // four loads in flight per thread
-      uint32_t key[4];
+  const uint32_t* unit_key = a.cand_key_ws + (size_t)u * a.n_span * a.cand_cap;
+  const int32_t* unit_pos = a.cand_pos_ws + (size_t)u * a.n_span * a.cand_cap;
+  auto entry = [&](int ci) {                      // candidate number -> entry of the unit's candidate arrays
+    int lo = 0, hi = a.n_span - 1;                // the last span that starts at or before it
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (off[mid] <= ci) lo = mid; else hi = mid - 1;
+    }
+    return lo * a.cand_cap + (ci - off[lo]);
+  };
+  constexpr int FLY = 8;                          // eight loads in flight per thread, across the spans
+  for (int n0 = tid; n0 < n_cand; n0 += FLY * NT) {
+    uint32_t key[FLY];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int n = n0 + t * NT + tid;
-        key[t] = n < cnt ? src[n] : 0u;
-      }
+    for (int j = 0; j < FLY; ++j) key[j] = n0 + j * NT < n_cand ? unit_key[entry(n0 + j * NT)] : 0u;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int n = n0 + t * NT + tid;
-        if (n < cnt) {
-          keys[o + n] = key[t];
-          if (o + n < n_free) atomicAdd(&hist[hist_slot(key[t] >> 21)], 1u);
-        }
+    for (int j = 0; j < FLY; ++j) {
+      const int n = n0 + j * NT;
+      if (n < n_cand) {
+        keys[n] = key[j];
+        if (n < n_free) atomicAdd(&hist[hist_slot(key[j] >> 21)], 1u);
       }
     }
   }
@@ -219,41 +256,82 @@ __global__ __launch_bounds__(NT) void long_merge(const LongArgs a) {
   float sums[2];
   select_compact<Sums::kNumerator>(keys, keys, n_cand, n_free, win.k_old, dmax, esc, 0.0f, nullptr, 0, sel, tid, lane, wave, nullptr, 0, sums);
   const float alpha = sums[1] / zsum;
-  // candidate numbers -> positions
-  int32_t* list = a.list_ws + (size_t)u * d.S_max;
-  for (int n = tid; n < kq; n += NT) {
-    const int ci = (int)keys[n];
-    int s = 0;
-    while (s + 1 < a.n_span && off[s + 1] <= ci) ++s;
-    const int pos = a.cand_pos_ws[((size_t)u * a.n_span + s) * a.cand_cap + (ci - off[s])];
-    list[n] = pos;
-    if (idx_out && n < d.idx_stride) idx_out[n] = pos;
+  for (int n0 = tid; n0 < kq; n0 += FLY * NT) {   // candidate numbers -> positions, in place
+    int pos[FLY];
+#pragma unroll
+    for (int j = 0; j < FLY; ++j) pos[j] = n0 + j * NT < kq ? unit_pos[entry((int)keys[n0 + j * NT])] : 0;
+#pragma unroll
+    for (int j = 0; j < FLY; ++j) {
+      const int n = n0 + j * NT;
+      if (n < kq) {
+        keys[n] = (uint32_t)pos[j];
+        if (idx_out && n < d.idx_stride) idx_out[n] = pos[j];
+      }
+    }
   }
   if (tid == 0) {
-    a.alpha_ws[u] = alpha;
     if (d.alpha_out) d.alpha_out[u] = alpha;
     if (idx_out && kq > d.idx_stride) atomicOr(d.err, 4);
   }
   if (idx_out) for (int n = kq + tid; n < d.idx_stride; n += NT) idx_out[n] = -1;
+  __syncthreads();
+
+  // ---- exact attention over the selected rows, blend, append: as in sparq_decode_fused ----
+  const int* list = reinterpret_cast<const int*>(keys);
+  uint16_t* K_rows = reinterpret_cast<uint16_t*>(d.K) + kv_head * d.S_stride * (size_t)DH;
+  const char* K_head = reinterpret_cast<const char*>(K_rows) + sub * 16;
+  const char* V_head = reinterpret_cast<const char*>(d.V) + kv_head * d.S_stride * (size_t)(DH * 2) + sub * 16;
+  const float qscale = kLog2e / sqrtf((float)DH);
+  float q8[8];
+  unpack8<T>(qraw, q8);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) q8[e] *= qscale;
+  // positions are ascending: the appended row can only be the last entry, and is taken from the inputs
+  const bool new_selected = appended && list[kq - 1] == S - 1;
+  float m_run = -INFINITY, l_run = 0.0f;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  attend_rows<T, DH>(K_head, V_head, list, 0, kq - (new_selected ? 1 : 0), q8, lane, wave, m_run, l_run, acc);
+  if (new_selected)
+    attend_row_from_codes<T, DH>(reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH,
+                                 reinterpret_cast<const uint16_t*>(d.v_new) + kv_head * DH, q8, lane, wave, m_run, l_run, acc);
+  float* part = reinterpret_cast<float*>(hist);
+  store_wave_partial<DH>(m_run, l_run, acc, part, lane, wave);
+  __syncthreads();
+  if (tid < DH) {
+    float m_all, l_all, y3;
+    combine_partials<DH>(part, NW, tid, m_all, l_all, y3);
+    y3 /= l_all;
+    if (appended) {                                // the mean with the new row; the mean of no rows is ignored
+      if (S == 1) vm = 0.0f;
+      vm += (T::widen(vc) - vm) * (1.0f / (float)S);
+    }
+    float y = y3;
+    if (!(d.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * vm;
+    reinterpret_cast<uint16_t*>(d.out)[(size_t)u * DH + tid] = T::narrow(y);
+    // nobody reads row S - 1 of K or V, or columns of Kt, in this launch; the mean goes to the *_next buffer
+    if (owner) {
+      d.v_mean_next[kv_head * DH + tid] = vm;
+      if (appended) {
+        reinterpret_cast<uint16_t*>(d.V)[(kv_head * d.S_stride + (S - 1)) * DH + tid] = vc;
+        K_rows[(size_t)(S - 1) * DH + tid] = kc;
+        if ((S & 7) == 0)
+          flush_key_columns(reinterpret_cast<uint16_t*>(d.Kt) + kv_head * DH * (size_t)d.S_stride, K_rows, d.S_stride, DH, S, tid, kc);
+      }
+    }
+  }
 }
 
 template <class T, int DH>
-hipError_t launch_long(const LongArgs& a, int dtype, hipStream_t s) {
+hipError_t launch_long(const LongArgs& a, hipStream_t s) {
   const int units = a.d.B * a.d.H;
   const size_t lds1 = 4 * ((size_t)a.span_len + scores_fixed_words<DH>()), lds2 = long_merge_lds_bytes(a.n_span, a.cand_cap);
-  auto k1 = long_scores<T, DH>;
   hipError_t e;
   if ((e = allow_lds<long_scores<T, DH>>(lds1)) != hipSuccess) return e;
-  if ((e = allow_lds<long_merge>(lds2)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k1, dim3(units * a.n_span), dim3(NT), lds1, s, a);
+  if ((e = allow_lds<long_finish<T, DH>>(lds2)) != hipSuccess) return e;
+  hipLaunchKernelGGL((long_scores<T, DH>), dim3(units * a.n_span), dim3(NT), lds1, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(long_merge, dim3(units), dim3(NT), lds2, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  SplitArgs g;
-  g.d = a.d; g.n_split = a.n_split;
-  g.alpha_ws = a.alpha_ws;
-  g.list_ws = a.list_ws; g.part_ws = a.part_ws;
-  return launch_split_gather(g, dtype, s);
+  hipLaunchKernelGGL((long_finish<T, DH>), dim3(units), dim3(NT), lds2, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -274,9 +352,9 @@ size_t long_merge_lds_bytes(int n_span, int cand_cap) {
 hipError_t launch_decode_long(const LongArgs& a, int dtype, hipStream_t s) {
   const bool bf = dtype == 1;
   switch (a.d.d_h) {
-    case 64:  return bf ? launch_long<BF16, 64>(a, dtype, s) : launch_long<F16, 64>(a, dtype, s);
-    case 128: return bf ? launch_long<BF16, 128>(a, dtype, s) : launch_long<F16, 128>(a, dtype, s);
-    case 256: return bf ? launch_long<BF16, 256>(a, dtype, s) : launch_long<F16, 256>(a, dtype, s);
+    case 64:  return bf ? launch_long<BF16, 64>(a, s) : launch_long<F16, 64>(a, s);
+    case 128: return bf ? launch_long<BF16, 128>(a, s) : launch_long<F16, 128>(a, s);
+    case 256: return bf ? launch_long<BF16, 256>(a, s) : launch_long<F16, 256>(a, s);
     default:  return hipErrorInvalidValue;
   }
 }

@@ -535,7 +535,7 @@ hipError_t launch_gs(const GsArgs& a, int dtype, hipStream_t s) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   SplitArgs c;
   c.d = a.d; c.n_split = a.n_split;
-  c.alpha_ws = a.alpha_ws; c.list_ws = nullptr;
+  c.alpha_ws = a.alpha_ws;
   c.part_ws = a.part_ws;
   return launch_split_combine(c, dtype, s);
 }
