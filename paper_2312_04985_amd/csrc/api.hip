@@ -254,7 +254,7 @@ GsLayout gs_layout(const sparq_shape* s, const PlanInfo& p) {
   return l;
 }
 
-struct BucketLayout { size_t tmax, zsum, anum, tau, zden, coarse, fine, skey, spos, part, z, stat, esc, end; };
+struct BucketLayout { size_t tmax, zsum, anum, tau, coarse, fine, skey, spos, part, z, stat, esc, end; };
 
 BucketLayout bucket_layout(const sparq_shape* s, const PlanInfo& p) {
   const size_t units = (size_t)s->B * s->H, slots = units * p.n_span;
@@ -264,7 +264,6 @@ BucketLayout bucket_layout(const sparq_shape* s, const PlanInfo& p) {
   l.zsum = off; off = align256(off + slots * sizeof(float));
   l.anum = off; off = align256(off + slots * sizeof(float));
   l.tau = off; off = align256(off + units * sizeof(float));
-  l.zden = off; off = align256(off + units * sizeof(float));
   l.coarse = off; off = align256(off + slots * 64 * sizeof(uint16_t));
   l.fine = off; off = align256(off + slots * bk_fine_len() * sizeof(uint16_t));
   l.skey = off; off = align256(off + slots * p.span_len * sizeof(uint32_t));
@@ -374,7 +373,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     ba.zsum_ws = reinterpret_cast<float*>(w + l.zsum);
     ba.anum_ws = reinterpret_cast<float*>(w + l.anum);
     ba.tau_ws = reinterpret_cast<float*>(w + l.tau);
-    ba.zden_ws = reinterpret_cast<float*>(w + l.zden);
+    ba.tickets = reinterpret_cast<int32_t*>(w + kTicketOffset);
     ba.coarse_ws = reinterpret_cast<uint16_t*>(w + l.coarse);
     ba.fine_ws = reinterpret_cast<uint16_t*>(w + l.fine);
     ba.skey_ws = reinterpret_cast<uint32_t*>(w + l.skey);
@@ -606,9 +605,9 @@ const char* sparq_decode_plan(const sparq_shape* caller_shape) {
   switch (choose_plan(shape).plan) {
     case kPlanFused: return "sparq_decode_fused (one workgroup per head, one launch)";
     case kPlanLong: return "long_scores + long_finish (two-level selection plan)";
-    case kPlanBucket: return "bk_scores + bk_select_gather + bk_combine (digit-bucket plan)";
+    case kPlanBucket: return "bk_scores + bk_select_gather (digit-bucket plan)";
     case kPlanShared: return "sparq_decode_shared (grouped-query rule, one workgroup per KV head)";
-    case kPlanSharedBucket: return "gs_logits + bk_group_scores + bk_select_gather + bk_combine (grouped-query rule on the digit-bucket plan)";
+    case kPlanSharedBucket: return "gs_logits + bk_group_scores + bk_select_gather (grouped-query rule on the digit-bucket plan)";
     case kPlanSharedSplit: return "gs_logits + gs_select + gs_merge + gs_gather + split_combine (grouped-query rule, several workgroups per KV head)";
     case kPlanSingleK: return "sparq_decode_single_k (key cache stored once)";
     default: return "unsupported";

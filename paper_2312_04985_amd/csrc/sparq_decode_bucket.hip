@@ -15,16 +15,18 @@
 //               only among identical keys, over the position.  Each workgroup then writes its own span's
 //               selected positions, ascending (into idx_out at its place in the unit's list), its share of
 //               alpha's numerator, gathers its own span's selected rows of K and V (Step 2b) and leaves one
-//               attention partial per span
-//   bk_combine  (one workgroup per unit) merges the spans' partials, alpha, blend, store
+//               attention partial per span; the workgroup that finishes last of a unit's spans merges the partials, and
+//               blends and stores (a launch of its own for that took 4.8 us and its start: 32 heads on 8 KV heads at 32 768
+//               positions 34.8 -> 33.5 us per step, one head 27.2 -> 24.1)
 // Every workgroup attends over the selected rows of its own span: the gather is balanced when the selected
 // positions are spread over the sequence, and takes as long as the busiest span when they are not.
 // The local window is part of it: its positions count as bucket 2047, above every key's.
 // The grouped-query rule runs on the same plan: gs_logits leaves every head's logit numerators and statistics in
 // the workspace, bk_group_scores turns the group score into keys and publishes the spans per KV unit, and
-// bk_select_gather<GROUP> / bk_combine run per query head on the KV unit's tables (alpha from the head's own logits).
-// Inside sparq_decode_step the three launches count the row being appended as position S_b (taken from the
-// inputs wherever it is needed) and bk_combine writes it to the cache, after every read of the earlier launches.
+// bk_select_gather<GROUP> runs per query head on the KV unit's tables (alpha from the head's own logits).
+// Inside sparq_decode_step the launches count the row being appended as position S_b (taken from the inputs wherever it
+// is needed); the last workgroup of the first query head of a KV group writes it to the cache: no launch reads that row
+// from the cache, and the columns of Kt that it may complete are only read by the first launch.
 #include "group_stages.h"
 
 namespace sparq {
@@ -402,7 +404,9 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   int u, s;
   map_span(U, a.n_span, u, s);
   const int b = u / d.H, h = u - b * d.H;
-  const size_t kv_head = (size_t)b * d.H_kv + h / (d.H / d.H_kv);
+  const int hk = h / (d.H / d.H_kv);
+  const size_t kv_head = (size_t)b * d.H_kv + hk;
+  const bool owner = d.k_new && h == hk * (d.H / d.H_kv);             // its last workgroup writes the appended row and the mean
   const size_t slot = (size_t)u * a.n_span + s;                       // this workgroup's partial and numerator
   const size_t slot0 = (GROUP ? kv_head : (size_t)u) * a.n_span;      // the spans whose tables and sorted arrays it reads
   using G = RowGeometry<DH>;
@@ -429,7 +433,14 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
     tm = a.tmax_ws[slot0 + lane]; zs = a.zsum_ws[slot0 + lane];
   }
 
-  if (S == 0) return;                      // outputs written by bk_scores
+  if (d.k_new && h == 0 && s == 0 && tid == 0) {   // a length beyond the bound of this call that the buffers can hold is carried over as it is
+    const int S_in = d.seq_lens[b];
+    d.seq_lens_next[b] = (S_in > d.S_max && S_in <= d.S_stride) ? S_in : S;
+  }
+  if (S == 0) {                            // outputs written by the first launch
+    if (owner && s == 0 && tid < DH) d.v_mean_next[kv_head * DH + tid] = d.v_mean[kv_head * DH + tid];
+    return;
+  }
   kb = kb < 1 ? 1 : (kb > d.k ? d.k : kb);
   const int kq = kb < S ? kb : S;
   const int p0 = s * P;
@@ -439,11 +450,8 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
     if (idx_out) for (int n = kq + tid; n < d.idx_stride; n += NT) idx_out[n] = -1;
     if (tid == 0 && idx_out && kq > d.idx_stride) atomicOr(d.err, 4);
   }
-  if (p0 >= S) {                           // nothing of this sequence lies in this span: an empty partial
-    if (tid < DH) my_part[tid] = 0.0f;
-    if (tid == 0) { my_part[DH] = -INFINITY; my_part[DH + 1] = 0.0f; a.anum_ws[slot] = 0.0f; }
-    return;
-  }
+  if (p0 >= S) return;                     // nothing of this sequence lies in this span
+  const int n_live = (S + P - 1) / P;      // spans that have positions
   const int len = S - p0 < P ? S - p0 : P;
 
   // ---- the threshold digit d0: the largest d with N(d) = sum over spans of A_s[d] >= kq ----
@@ -472,8 +480,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   }
   __syncthreads();
   const int lc = ctl[0];
-  const float gmax = red[30];
-  if (s == 0 && tid == 0) a.zden_ws[u] = red[31];
+  const float gmax = red[30], zden = red[31];
   for (int i = tid; i < a.n_span * 33; i += NT) {
     const int t = i / 33, j = i - t * 33;
     tabF[i] = a.fine_ws[(slot0 + t) * kFineLen + lc * 32 + j];
@@ -669,7 +676,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
     float t = 0.0f;
 #pragma unroll
     for (int i = 0; i < NW; ++i) t += red[i];
-    a.anum_ws[slot] = t;
+    store_agent(a.anum_ws + slot, t);
   }
 
   // ---- Step 2b over this span's selected rows -> one partial (numerator, max, denominator) per span ----
@@ -697,66 +704,35 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   if (tid < DH) {
     float m_all, l_all, y;
     combine_partials<DH>(part, NW, tid, m_all, l_all, y);
-    my_part[tid] = y;
-    if (tid == 0) { my_part[DH] = m_all; my_part[DH + 1] = l_all; }
+    store_agent(my_part + tid, y);
+    if (tid == 0) { store_agent(my_part + DH, m_all); store_agent(my_part + DH + 1, l_all); }
   }
-}
 
-// One workgroup per unit: merge the spans' partials, alpha from the spans' numerators, blend with the mean
-// value vector (Eq. 10), round and store.
-template <class T, int DH>
-__global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
-  const DecodeArgs& d = a.d;
-  const int u = blockIdx.x, c = threadIdx.x;
-  const int b = u / d.H, h = u - b * d.H;
-  const size_t kv_head = (size_t)b * d.H_kv + h / (d.H / d.H_kv);
-  bool appended, bad, full;
-  const int S = visible_length(d, b, appended, bad, full);
-  float vm = d.v_mean[kv_head * DH + c];
-  // the step's append, after every read of the cache by the earlier launches: the workgroup of the first query
-  // head of a KV group writes the rows, the 8 columns of Kt that the row may complete, and the new mean
-  // (the same update as sparq_kv_append's; the mean of no rows is ignored); lengths and means go to the *_next
-  // buffers.  The inputs are requested here; the stores are issued after the merge (stores ahead of the partials'
-  // loads would sit on their critical path: the memory counter retires both in order).
+  // ---- the unit's last workgroup: merge the spans' partials, alpha from the spans' numerators, blend with the mean
+  // value vector (Eq. 10), round and store, append ----
+  float vm = 0.0f;
   uint16_t vcode = 0, kc = 0;
-  const bool owner = h == (h / (d.H / d.H_kv)) * (d.H / d.H_kv);
-  if (d.k_new) {
-    vcode = reinterpret_cast<const uint16_t*>(d.v_new)[kv_head * DH + c];
-    if (owner && appended) kc = reinterpret_cast<const uint16_t*>(d.k_new)[kv_head * DH + c];
-  }
-  auto append_stores = [&]() {
-    if (owner) {
-      d.v_mean_next[kv_head * DH + c] = vm;
-      if (appended) {
-        uint16_t* K_rows = reinterpret_cast<uint16_t*>(d.K) + kv_head * d.S_stride * (size_t)DH;
-        reinterpret_cast<uint16_t*>(d.V)[(kv_head * d.S_stride + (S - 1)) * DH + c] = vcode;
-        K_rows[(size_t)(S - 1) * DH + c] = kc;
-        if ((S & 7) == 0)
-          flush_key_columns(reinterpret_cast<uint16_t*>(d.Kt) + kv_head * DH * (size_t)d.S_stride, K_rows, d.S_stride, DH, S, c, kc);
-      }
+  if (tid < DH) {                          // requested while the partial is on its way
+    vm = d.v_mean[kv_head * DH + tid];
+    if (appended) {
+      vcode = reinterpret_cast<const uint16_t*>(d.v_new)[kv_head * DH + tid];
+      kc = reinterpret_cast<const uint16_t*>(d.k_new)[kv_head * DH + tid];
     }
-    if (h == 0 && c == 0) {   // a length beyond the bound of this call that the buffers can hold is carried over as it is
-      const int S_in = d.seq_lens[b];
-      d.seq_lens_next[b] = (S_in > d.S_max && S_in <= d.S_stride) ? S_in : S;
-    }
-  };
-  if (S <= 0) {                            // outputs written by bk_scores
-    if (d.k_new) append_stores();
-    return;
   }
+  if (!last_to_arrive(a.tickets + u, n_live, ctl + 15)) return;
+  if (tid >= DH) return;
+  const int c = tid;
   const float* parts = a.part_ws + (size_t)u * a.n_span * (DH + 2);
-  const int ln = c & (kWave - 1);
-  const float num = wave_sum(ln < a.n_span ? a.anum_ws[(size_t)u * a.n_span + ln] : 0.0f);   // fixed order
-  const float zden = a.zden_ws[u];
+  const float num_part = lane < n_live ? load_agent(a.anum_ws + (size_t)u * a.n_span + lane) : 0.0f;
   float m_all = -INFINITY, l_all = 0.0f, y3 = 0.0f;
-  for (int w0 = 0; w0 < a.n_span; w0 += 16) {          // sixteen partials of this channel in flight at a time
+  for (int w0 = 0; w0 < n_live; w0 += 16) {            // sixteen partials of this channel in flight at a time
     float pm[16], pl[16], py[16];
 #pragma unroll
     for (int w = 0; w < 16; ++w) {
-      const bool on = w0 + w < a.n_span;
-      pm[w] = on ? parts[(w0 + w) * (DH + 2) + DH] : -INFINITY;
-      pl[w] = on ? parts[(w0 + w) * (DH + 2) + DH + 1] : 0.0f;
-      py[w] = on ? parts[(w0 + w) * (DH + 2) + c] : 0.0f;
+      const bool on = w0 + w < n_live;
+      const float* p = parts + (on ? w0 + w : 0) * (DH + 2);
+      pm[w] = load_agent(p + DH); pl[w] = load_agent(p + DH + 1); py[w] = load_agent(p + c);
+      if (!on) { pm[w] = -INFINITY; pl[w] = 0.0f; py[w] = 0.0f; }
     }
     float m_new = m_all;
 #pragma unroll
@@ -772,16 +748,25 @@ __global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
     m_all = m_new;
   }
   y3 /= l_all;
-  const float alpha = num / zden;
+  const float alpha = wave_sum(num_part) / zden;       // fixed order
   if (c == 0 && d.alpha_out) d.alpha_out[u] = alpha;
-  if (d.k_new && appended) {               // the mean with the new row: what the blend uses and the owner stores
+  if (appended) {                          // the mean with the new row: what the blend uses and the owner stores
     if (S == 1) vm = 0.0f;
     vm += (T::widen(vcode) - vm) * (1.0f / (float)S);
   }
   float y = y3;
   if (!(d.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * vm;
   reinterpret_cast<uint16_t*>(d.out)[(size_t)u * DH + c] = T::narrow(y);
-  if (d.k_new) append_stores();
+  if (owner) {
+    d.v_mean_next[kv_head * DH + c] = vm;
+    if (appended) {
+      uint16_t* K_rows = reinterpret_cast<uint16_t*>(d.K) + kv_head * d.S_stride * (size_t)DH;
+      reinterpret_cast<uint16_t*>(d.V)[(kv_head * d.S_stride + (S - 1)) * DH + c] = vcode;
+      K_rows[(size_t)(S - 1) * DH + c] = kc;
+      if ((S & 7) == 0)
+        flush_key_columns(reinterpret_cast<uint16_t*>(d.Kt) + kv_head * DH * (size_t)d.S_stride, K_rows, d.S_stride, DH, S, c, kc);
+    }
+  }
 }
 
 template <class T, int DH>
@@ -794,12 +779,10 @@ hipError_t launch_bucket(const BucketArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((bk_scores<T, DH>), dim3(units * a.n_span), dim3(NT), lds1, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((bk_select_gather<T, DH, false>), dim3(units * a.n_span), dim3(NT), lds2, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((bk_combine<T, DH>), dim3(units), dim3(DH), 0, s, a);
   return hipGetLastError();
 }
 
-// the grouped-query rule: the keys come from the group's stored logits, the rest is the same two launches
+// the grouped-query rule: the keys come from the group's stored logits, the rest is the same launch
 template <class T, int DH>
 hipError_t launch_bucket_group(const BucketArgs& a, hipStream_t s) {
   const int units = a.d.B * a.d.H, ukv = a.d.B * a.d.H_kv;
@@ -819,8 +802,6 @@ hipError_t launch_bucket_group(const BucketArgs& a, hipStream_t s) {
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((bk_select_gather<T, DH, true>), dim3(units * a.n_span), dim3(NT), lds2, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((bk_combine<T, DH>), dim3(units), dim3(DH), 0, s, a);
   return hipGetLastError();
 }
 
