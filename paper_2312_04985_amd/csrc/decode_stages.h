@@ -21,12 +21,13 @@ constexpr int kTieHeavy = 2048;  // a radix bin with more keys than this is coun
 // find_threshold_bin sit in 32 different rows of 64 words: lane-consecutive, conflict-free reads.
 __device__ __forceinline__ uint32_t hist_slot(uint32_t digit) { return ((digit & 31u) << 6) | (digit >> 5); }
 
-// First-digit counts of the 8 keys of one chunk: runs of equal digits among neighbours (duplicated keys) are
-// added with one atomic.  n_valid = how many of the 8 keys count (the leading ones).
-__device__ __forceinline__ void hist_add_chunk(uint32_t* hist, const uint32_t (&kx)[8], int n_valid) {
+// First-digit counts of M neighbouring keys: runs of equal digits (duplicated keys) are
+// added with one atomic.  n_valid = how many of the M keys count (the leading ones).
+template <int M>
+__device__ __forceinline__ void hist_add_chunk(uint32_t* hist, const uint32_t (&kx)[M], int n_valid) {
   uint32_t run_d = kx[0] >> 21, run_n = n_valid > 0 ? 1u : 0u;
 #pragma unroll
-  for (int e = 1; e < 8; ++e) {
+  for (int e = 1; e < M; ++e) {
     const uint32_t d = kx[e] >> 21;
     const uint32_t v = e < n_valid ? 1u : 0u;
     if (d != run_d) {

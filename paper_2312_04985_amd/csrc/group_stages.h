@@ -12,13 +12,13 @@ namespace sparq {
 // underflows to 0 for every position far below all heads' maxima: thousands of exactly equal keys, which the
 // fp64 definition does not have, and which serialise the histogram atomics of the select (6 us per pass over
 // 8192 keys instead of 1).  The logarithm keeps them apart at the same relative accuracy (the rounding of x_h
-// dominates either way).  inv_z = 1 / Z_h as the callers hold it.
+// dominates either way).  log_z = log2(1 / Z_h).
 template <int G>
 __device__ __forceinline__ float group_score(const float (&d)[G], const float (&mh)[G], const float (&esc)[G],
-                                             const float (&inv_z)[G]) {
+                                             const float (&log_z)[G]) {
   float x[G], mx = -INFINITY;
 #pragma unroll
-  for (int h = 0; h < G; ++h) { x[h] = (d[h] - mh[h]) * esc[h] + log2f(inv_z[h]); mx = fmaxf(mx, x[h]); }
+  for (int h = 0; h < G; ++h) { x[h] = (d[h] - mh[h]) * esc[h] + log_z[h]; mx = fmaxf(mx, x[h]); }
   float s = 0.0f;
 #pragma unroll
   for (int h = 0; h < G; ++h) s += exp2f(x[h] - mx);
@@ -43,6 +43,12 @@ __device__ __forceinline__ void combine_span_stats(const float* stat_unit, int n
     const float z_all = wave_sum(m[h] == -INFINITY ? 0.0f : z[h] * exp2f((m[h] - m_all) * esc[h]));
     if (lane == 0) { out[h * 2] = m_all; out[h * 2 + 1] = 1.0f / z_all; }
   }
+}
+
+// One head's (running maximum, sum) over the 64 lanes of a wave: the sum relative to the common maximum.
+__device__ __forceinline__ void wave_merge(const RunningSum& rs, float esc, float& m, float& z) {
+  m = wave_max(rs.ref);
+  z = wave_sum(rs.relative_to(m, esc));
 }
 
 struct GroupQueryLds {

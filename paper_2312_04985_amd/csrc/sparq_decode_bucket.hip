@@ -29,6 +29,8 @@
 // from the cache, and the columns of Kt that it may complete are only read by the first launch.
 #include "group_stages.h"
 
+#include <type_traits>
+
 namespace sparq {
 
 namespace {
@@ -207,48 +209,53 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
   float tmax = -INFINITY;
   const int c_begin = p0 >> 3, c_end = end > p0 ? end >> 3 : p0 >> 3;
-  auto finish = [&](int c, const float (&acc)[8]) {
-    uint32_t kx[8];
+  auto finish4 = [&](int rel, const float4& d4) {          // positions p0 + rel .. + 3
+    const float acc[4] = {d4.x, d4.y, d4.z, d4.w};
+    uint32_t kx[4], dg[4];                                 // hist_add_chunk counts by the first 11 bits of what it is given
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 4; ++e) {
       tmax = fmaxf(tmax, acc[e]);
       kx[e] = float_to_key(acc[e]);
+      dg[e] = bucket_digit<false>(kx[e]) << 21;
     }
-    uint32_t dg[8];                                        // hist_add_chunk counts by the first 11 bits of what it is given
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dg[e] = bucket_digit<false>(kx[e]) << 21;
-    hist_add_chunk(hist, dg, win.S_old - c * 8);          // the window's positions are counted below
-    uint4* dst = reinterpret_cast<uint4*>(keys + (c * 8 - p0));
-    dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
-    dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
+    hist_add_chunk(hist, dg, win.S_old - (p0 + rel));      // the window's positions are counted below
+    *reinterpret_cast<uint4*>(keys + rel) = make_uint4(kx[0], kx[1], kx[2], kx[3]);
   };
   const int nb = r8 >> 3;                                 // batches of 8 channel rows
-  if (c_end - c_begin <= NT / 2 && nb >= 2) {
-    // At most half as many chunks as threads: the two halves of the workgroup share every chunk, each taking
-    // half of the channel rows, so that a thread's loads are all in flight at once (r <= 32) instead of going
-    // through the pipeline in two dependent rounds.  The halves' partial sums meet in LDS (the arrays of the
-    // sort, which are idle until then), and the first half of the threads finishes the chunks.
-    const int half = tid >> 8, t = tid & (NT / 2 - 1);
-    const int b0 = half ? (nb + 1) >> 1 : 0, b1 = half ? nb : (nb + 1) >> 1;
-    float* pacc = reinterpret_cast<float*>(half ? spos : skey);
-    stream_channel_rows<T, NT / 2>(Kt_head, row_bytes, chan + 8 * b0, qs + 8 * b0, 8 * (b1 - b0), c_begin, c_end, t,
-                                   [&](int c, const float (&acc)[8]) {
-      float4* dst = reinterpret_cast<float4*>(pacc + (c * 8 - p0));
+  // When a span has few chunks, F groups of NT / F threads share every chunk, each taking 1 / F of the channel rows, so that
+  // a thread's loads are all in flight at once instead of going through the pipeline in dependent rounds.  The groups'
+  // partial sums meet in LDS (in arrays that are idle until the sort, and in `keys`, each place of which is read by the
+  // thread that then writes it), and every thread finishes 4 positions at a time.  (Not with more chunks than a group has
+  // threads: 264 chunks over 256 threads twice 34.0 us per step, over 512 threads once 33.5.)
+  auto shared_chunks = [&](auto groups) {
+    constexpr int F = decltype(groups)::value, TG = NT / F;
+    const int f = tid / TG, b0 = f * nb / F, b1 = (f + 1) * nb / F;
+    float* parts[4] = {reinterpret_cast<float*>(skey), reinterpret_cast<float*>(spos), reinterpret_cast<float*>(keys), reinterpret_cast<float*>(cur)};
+    float* mine = f == 0 ? parts[0] : (f == 1 ? parts[1] : (f == 2 ? parts[2] : parts[3]));
+    stream_channel_rows<T, TG>(Kt_head, row_bytes, chan + 8 * b0, qs + 8 * b0, 8 * (b1 - b0), c_begin, c_end, tid - f * TG,
+                               [&](int c, const float (&acc)[8]) {
+      float4* dst = reinterpret_cast<float4*>(mine + (c * 8 - p0));
       dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
       dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
     });
     __syncthreads();
-    if (half == 0 && c_begin + t < c_end) {
-      const int c = c_begin + t;
-      const float4* x = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(skey) + (c * 8 - p0));
-      const float4* y = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(spos) + (c * 8 - p0));
-      const float4 x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
-      const float acc[8] = {x0.x + y0.x, x0.y + y0.y, x0.z + y0.z, x0.w + y0.w, x1.x + y1.x, x1.y + y1.y, x1.z + y1.z, x1.w + y1.w};
-      finish(c, acc);
+    for (int rel = tid * 4; rel < (c_end - c_begin) * 8; rel += NT * 4) {
+      float4 d4 = *reinterpret_cast<const float4*>(parts[0] + rel);
+#pragma unroll
+      for (int g = 1; g < F; ++g) {                        // in the order of the channel list
+        const float4 o = *reinterpret_cast<const float4*>(parts[g] + rel);
+        d4.x += o.x; d4.y += o.y; d4.z += o.z; d4.w += o.w;
+      }
+      finish4(rel, d4);
     }
-  } else {
-    stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, c_begin, c_end, tid, finish);
-  }
+  };
+  const int n_chunks = c_end - c_begin;
+  if (n_chunks <= NT / 4 && nb >= 4) shared_chunks(std::integral_constant<int, 4>{});
+  else if (n_chunks <= NT / 2 && nb >= 2) shared_chunks(std::integral_constant<int, 2>{});
+  else stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, c_begin, c_end, tid, [&](int c, const float (&acc)[8]) {
+    finish4(c * 8 - p0, make_float4(acc[0], acc[1], acc[2], acc[3]));
+    finish4(c * 8 - p0 + 4, make_float4(acc[4], acc[5], acc[6], acc[7]));
+  });
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, qs, r8, lane);
     tmax = fmaxf(tmax, dot);
@@ -330,31 +337,25 @@ __global__ __launch_bounds__(NT, 2) void bk_group_scores(const BucketArgs a) {
   for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
   if (wave == 0) combine_span_stats<G>(a.stat_ws + (size_t)ukv * a.n1 * G * 2, a.n1, a.esc_ws + u0, lane, hs);
   __syncthreads();
-  float mh[G], inv_z[G], esc[G];
+  float mh[G], log_z[G], esc[G];
 #pragma unroll
-  for (int h = 0; h < G; ++h) { mh[h] = hs[h * 2]; inv_z[h] = hs[h * 2 + 1]; esc[h] = a.esc_ws[u0 + h]; }
+  for (int h = 0; h < G; ++h) { mh[h] = hs[h * 2]; log_z[h] = log2f(hs[h * 2 + 1]); esc[h] = a.esc_ws[u0 + h]; }
   const float* z_unit = a.z_ws + u0 * (size_t)d.S_max + p0;
-  const int n_chunks = (len + 7) >> 3;
-  for (int c = tid; c < n_chunks; c += NT) {
-    float4 lo[G], hi[G];
+  for (int rel = tid * 4; rel < len; rel += NT * 4) {
+    float4 z4[G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float4* src = reinterpret_cast<const float4*>(z_unit + (size_t)h * d.S_max + c * 8);
-      lo[h] = src[0]; hi[h] = src[1];
-    }
-    uint32_t kx[8], dg[8];
+    for (int h = 0; h < G; ++h) z4[h] = *reinterpret_cast<const float4*>(z_unit + (size_t)h * d.S_max + rel);
+    uint32_t kx[4], dg[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 4; ++e) {
       float dv[G];
 #pragma unroll
-      for (int h = 0; h < G; ++h) dv[h] = e < 4 ? (&lo[h].x)[e] : (&hi[h].x)[e - 4];
-      kx[e] = c * 8 + e < len ? float_to_key(group_score<G>(dv, mh, esc, inv_z)) : 0u;
+      for (int h = 0; h < G; ++h) dv[h] = (&z4[h].x)[e];
+      kx[e] = rel + e < len ? float_to_key(group_score<G>(dv, mh, esc, log_z)) : 0u;
       dg[e] = bucket_digit<true>(kx[e]) << 21;      // hist_add_chunk counts by the first 11 bits of what it is given
     }
-    hist_add_chunk(hist, dg, (win.S_old < p0 + len ? win.S_old : p0 + len) - (p0 + c * 8));
-    uint4* dst = reinterpret_cast<uint4*>(keys + c * 8);
-    dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
-    dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
+    hist_add_chunk(hist, dg, (win.S_old < p0 + len ? win.S_old : p0 + len) - (p0 + rel));
+    *reinterpret_cast<uint4*>(keys + rel) = make_uint4(kx[0], kx[1], kx[2], kx[3]);
   }
   // the part of the local window that lies in this span counts as the top digit
   const int w0 = win.S_old > p0 ? win.S_old - p0 : 0;

@@ -116,9 +116,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
 #pragma unroll
     for (int h = 0; h < G; ++h) tdot[h] = tail_row_dot<T>(tail, L.qs + h * DH, r8, lane);
   }
-  float mt[G], zt[G];   // running max of the logit numerator, sum of exp2((d - max) * esc)
-#pragma unroll
-  for (int h = 0; h < G; ++h) { mt[h] = -INFINITY; zt[h] = 0.0f; }
+  RunningSum rs[G];     // running max of the logit numerator, sum of exp2((d - max) * esc)
   float* z_unit = z_ws + u0 * (size_t)a.S_max;        // [G][S_max] logit numerators of this group
   stream_channel_rows_group<T, G>(Kt_head, row_bytes, L.chan, L.qs, DH, a.r, 0, n_chunks, tid,
                                   [&](int c, const float (&acc)[G][8]) {
@@ -127,12 +125,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
       float4* dst = reinterpret_cast<float4*>(z_unit + (size_t)h * a.S_max + c * 8);
       dst[0] = make_float4(acc[h][0], acc[h][1], acc[h][2], acc[h][3]);
       dst[1] = make_float4(acc[h][4], acc[h][5], acc[h][6], acc[h][7]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = acc[h][e];
-        if (v > mt[h]) { zt[h] = zt[h] * exp2f((mt[h] - v) * esc[h]) + 1.0f; mt[h] = v; }
-        else zt[h] += exp2f((v - mt[h]) * esc[h]);
-      }
+      rs[h].add(acc[h], esc[h]);
     }
   });
   if (wave < n_tail && lane == 0) {
@@ -140,21 +133,14 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     for (int h = 0; h < G; ++h) {
       const float v = tdot[h];
       z_unit[(size_t)h * a.S_max + S_fl + wave] = v;
-      if (v > mt[h]) { zt[h] = zt[h] * exp2f((mt[h] - v) * esc[h]) + 1.0f; mt[h] = v; }
-      else zt[h] += exp2f((v - mt[h]) * esc[h]);
+      rs[h].add({v}, esc[h]);
     }
   }
-  float mh[G], inv_z[G];
+  float mh[G], inv_z[G], log_z[G];
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    float m = mt[h], z = zt[h];
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const float m_o = __shfl_xor(m, o), z_o = __shfl_xor(z, o);
-      const float m_new = fmaxf(m, m_o);
-      z = (m == -INFINITY ? 0.0f : z * exp2f((m - m_new) * esc[h])) + (m_o == -INFINITY ? 0.0f : z_o * exp2f((m_o - m_new) * esc[h]));
-      m = m_new;
-    }
+    float m, z;
+    wave_merge(rs[h], esc[h], m, z);
     if (lane == 0) { L.stat[(wave * G + h) * 2] = m; L.stat[(wave * G + h) * 2 + 1] = z; }
   }
   __syncthreads();
@@ -167,9 +153,9 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = L.stat[(w * G + h) * 2];
-      if (mw != -INFINITY) z += L.stat[(w * G + h) * 2 + 1] * exp2f((mw - m) * esc[h]);
+      z += L.stat[(w * G + h) * 2 + 1] * exp2f((mw - m) * esc[h]);    // 0 of a wave without positions
     }
-    mh[h] = m; inv_z[h] = 1.0f / z;
+    mh[h] = m; inv_z[h] = 1.0f / z; log_z[h] = log2f(inv_z[h]);
   }
 
   // ---------------- pass B: group score = sum over heads of s-hat, as keys ----------------
@@ -187,7 +173,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
       float dv[G];
 #pragma unroll
       for (int h = 0; h < G; ++h) dv[h] = e < 4 ? (&lo[h].x)[e] : (&hi[h].x)[e - 4];
-      kx[e] = float_to_key(group_score<G>(dv, mh, esc, inv_z));
+      kx[e] = float_to_key(group_score<G>(dv, mh, esc, log_z));
       if (c * 8 + e < win.S_old) atomicAdd(&L.sel.hist[hist_slot(kx[e] >> 21)], 1u);
     }
     uint4* dst = reinterpret_cast<uint4*>(L.keys + c * 8);
@@ -195,7 +181,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   }
   if (wave < n_tail && lane == 0) {
-    const uint32_t key = float_to_key(group_score<G>(tdot, mh, esc, inv_z));
+    const uint32_t key = float_to_key(group_score<G>(tdot, mh, esc, log_z));
     L.keys[S_fl + wave] = key;
     if (S_fl + wave < win.S_old) atomicAdd(&L.sel.hist[hist_slot(key >> 21)], 1u);
   }

@@ -28,10 +28,12 @@ __device__ __forceinline__ void map_kv(int Ukv, int n, int& ukv, int& s) {
   }
 }
 
-// Thread groups that share the chunks of a gs_logits span (see there): 4 or 2 when the span has at most NT / 4 or
-// NT / 2 chunks and there are that many batches of 8 channel rows, else 1.  Host and device agree through this.
+// Thread groups that share the chunks of a gs_logits span (see there): 4 or 2 when the span has at most half as many
+// chunks more than a group has threads and there are that many batches of 8 channel rows, else 1.  (A few threads' second
+// chunk costs less than idle groups: with the four-position finish below 16.1 -> 12.5 us for 136 chunks of 32 rows.)  Host
+// and device agree through this.
 __host__ __device__ constexpr int logit_row_groups(int span1, int n_batches) {
-  return (span1 <= NT / 4 * 8 && n_batches >= 4) ? 4 : ((span1 <= NT / 2 * 8 && n_batches >= 2) ? 2 : 1);
+  return (span1 <= NT / 4 * 8 * 3 / 2 && n_batches >= 4) ? 4 : ((span1 <= NT / 2 * 8 * 3 / 2 && n_batches >= 2) ? 2 : 1);
 }
 
 template <class T, int DH, int G>
@@ -96,21 +98,14 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
   const size_t row_bytes = (size_t)d.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
   float* z_unit = a.z_ws + u0 * (size_t)d.S_max;
-  float mt[G], zt[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) { mt[h] = -INFINITY; zt[h] = 0.0f; }
+  RunningSum rs[G];
   auto finish = [&](int c, const float (&acc)[G][8]) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       float4* dst = reinterpret_cast<float4*>(z_unit + (size_t)h * d.S_max + c * 8);
       dst[0] = make_float4(acc[h][0], acc[h][1], acc[h][2], acc[h][3]);
       dst[1] = make_float4(acc[h][4], acc[h][5], acc[h][6], acc[h][7]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = acc[h][e];
-        if (v > mt[h]) { zt[h] = zt[h] * exp2f((mt[h] - v) * esc[h]) + 1.0f; mt[h] = v; }
-        else zt[h] += exp2f((v - mt[h]) * esc[h]);
-      }
+      rs[h].add(acc[h], esc[h]);
     }
   };
   const int c_begin = p0 >> 3, c_end = end > p0 ? end >> 3 : p0 >> 3;
@@ -148,20 +143,17 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
       });
     }
     __syncthreads();
-    for (int c = c_begin + tid; c < c_end; c += NT) {
-      float acc[G][8];
+    for (int rel = tid * 4; rel < (c_end - c_begin) * 8; rel += NT * 4) {     // 4 positions at a time: more threads take part
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[h][e] = 0.0f;
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int part = 0; part < F; ++part) {                 // in the order of the channel list
-          const float4* src = reinterpret_cast<const float4*>(pacc + (size_t)(part * G + h) * P + (c * 8 - p0));
-          const float4 x0 = src[0], x1 = src[1];
-          acc[h][0] += x0.x; acc[h][1] += x0.y; acc[h][2] += x0.z; acc[h][3] += x0.w;
-          acc[h][4] += x1.x; acc[h][5] += x1.y; acc[h][6] += x1.z; acc[h][7] += x1.w;
+          const float4 x = *reinterpret_cast<const float4*>(pacc + (size_t)(part * G + h) * P + rel);
+          acc[0] += x.x; acc[1] += x.y; acc[2] += x.z; acc[3] += x.w;
         }
+        *reinterpret_cast<float4*>(z_unit + (size_t)h * d.S_max + p0 + rel) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        rs[h].add(acc, esc[h]);
       }
-      finish(c, acc);
     }
   } else {
     stream_channel_rows_group<T, G>(Kt_head, row_bytes, chan, qs, DH, d.r, c_begin, c_end, tid, finish);
@@ -174,20 +166,13 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
     for (int h = 0; h < G; ++h) {
       const float v = tdot[h];
       z_unit[(size_t)h * d.S_max + S_fl + wave] = v;
-      if (v > mt[h]) { zt[h] = zt[h] * exp2f((mt[h] - v) * esc[h]) + 1.0f; mt[h] = v; }
-      else zt[h] += exp2f((v - mt[h]) * esc[h]);
+      rs[h].add({v}, esc[h]);
     }
   }
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    float m = mt[h], z = zt[h];
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const float m_o = __shfl_xor(m, o), z_o = __shfl_xor(z, o);
-      const float m_new = fmaxf(m, m_o);
-      z = (m == -INFINITY ? 0.0f : z * exp2f((m - m_new) * esc[h])) + (m_o == -INFINITY ? 0.0f : z_o * exp2f((m_o - m_new) * esc[h]));
-      m = m_new;
-    }
+    float m, z;
+    wave_merge(rs[h], esc[h], m, z);
     if (lane == 0) { stat[(wave * G + h) * 2] = m; stat[(wave * G + h) * 2 + 1] = z; }
   }
   __syncthreads();
@@ -201,7 +186,7 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
     float z = 0.0f;
     for (int w = 0; w < NW; ++w) {
       const float mw = stat[(w * G + h) * 2];
-      if (mw != -INFINITY) z += stat[(w * G + h) * 2 + 1] * exp2f((mw - m) * e_h);
+      z += stat[(w * G + h) * 2 + 1] * exp2f((mw - m) * e_h);       // 0 of a wave without positions
     }
     stat_out[h * 2] = m; stat_out[h * 2 + 1] = z;
   }
@@ -240,9 +225,9 @@ __global__ __launch_bounds__(NT, 2) void gs_select(const GsArgs a) {
   for (int i = tid; i < 2 * kRadixBins; i += NT) hist[i] = 0u;
   if (wave == 0) combine_span_stats<G>(a.stat_ws + (size_t)ukv * a.n1 * G * 2, a.n1, a.esc_ws + u0, lane, hs);
   __syncthreads();
-  float mh[G], inv_z[G], esc[G];
+  float mh[G], log_z[G], esc[G];
 #pragma unroll
-  for (int h = 0; h < G; ++h) { mh[h] = hs[h * 2]; inv_z[h] = hs[h * 2 + 1]; esc[h] = a.esc_ws[u0 + h]; }
+  for (int h = 0; h < G; ++h) { mh[h] = hs[h * 2]; log_z[h] = log2f(hs[h * 2 + 1]); esc[h] = a.esc_ws[u0 + h]; }
   const float* z_unit = a.z_ws + u0 * (size_t)d.S_max + p0;
   const int n_chunks = (len + 7) >> 3;
   for (int c = tid; c < n_chunks; c += NT) {
@@ -259,7 +244,7 @@ __global__ __launch_bounds__(NT, 2) void gs_select(const GsArgs a) {
         float dv[G];
 #pragma unroll
         for (int h = 0; h < G; ++h) dv[h] = e < 4 ? (&lo[h].x)[e] : (&hi[h].x)[e - 4];
-        kx[e] = float_to_key(group_score<G>(dv, mh, esc, inv_z));
+        kx[e] = float_to_key(group_score<G>(dv, mh, esc, log_z));
         if (p0 + c * 8 + e < win.S_old) atomicAdd(&hist[hist_slot(kx[e] >> 21)], 1u);
       } else {
         kx[e] = 0u;
@@ -513,7 +498,7 @@ template <class T, int DH, int G>
 hipError_t launch_logits(const GsArgs& a, hipStream_t s) {
   const int F = logit_row_groups(a.span1, (a.d.r + 7) >> 3);
   const size_t lds = F > 1 ? (size_t)F * G * a.span1 * sizeof(float) : 0;
-  hipError_t e = allow_lds<gs_logits<T, DH, G>>(lds + 16 * 1024, 128 * 1024);   // at most 64 KiB dynamic on top of the static arrays
+  hipError_t e = allow_lds<gs_logits<T, DH, G>>(lds + 16 * 1024, 128 * 1024);   // at most 96 KiB dynamic on top of the static arrays
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gs_logits<T, DH, G>), dim3(a.d.B * a.d.H_kv * a.n1), dim3(NT), lds, s, a);
   return hipGetLastError();
