@@ -475,6 +475,7 @@ int sparq_kv_append(const sparq_shape* caller_shape, const sparq_cache* cache, c
   a.B = shape->B; a.H_kv = shape->H_kv; a.S_max = a.S_stride = caller_shape->S_max;   // S_bound does not limit an append
   a.d_h = shape->d_h; a.n_new = n_new; a.tiled = tiled_k(shape) ? 1 : 0;
   a.scratch = static_cast<char*>(workspace) + kAppendScratchOffset; a.scratch_bytes = workspace_bytes - kAppendScratchOffset;
+  a.tickets = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + kTicketOffset);
   return launch_append(a, shape->dtype, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 

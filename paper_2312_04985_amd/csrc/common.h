@@ -147,6 +147,8 @@ __device__ __forceinline__ void wave_lds_fence() {
 // the whole L2 back, which was measured as four times the time of a launch.
 __device__ __forceinline__ void store_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_agent(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double load_agent(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // 16 bytes at byte offset `off` of `base` (wave-uniform), the same way (bit 4 of the cache policy is the agent scope's sc1)
 __device__ __forceinline__ void store_agent4(const float* base, uint32_t off, const float4& v) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -73,7 +73,9 @@ __global__ __launch_bounds__(512) void append_one_row(const AppendArgs a) {
 // heads is 8 x 249 tiles.  A thread owns 8 channels of 8 consecutive positions: it copies its 8 pieces of K and of V,
 // transposes the keys in registers and hands them over through LDS as 16-byte pieces of a channel row, which leave as
 // runs of 2 ATP bytes.  Bound by HBM (2 rows in, 3 out); value columns are summed in fp64, one partial sum per
-// workgroup, and append_finish folds them into the mean.
+// workgroup.  With few workgroups the last one of a KV head folds them into the mean, and the last KV head of a sequence
+// advances its length (counters in the control block); with many, whose stores saturate the memory that every such
+// hand-over waits for, a second launch does it, append_finish or bump_seq_lens (see launch_rows_dh).
 // Measured (whole call; before: one workgroup per KV head, columns in 2-byte stores): a prompt of 31 777 rows for 8 KV
 // heads, d_h 128 (325 MB read and written) 2301 -> 77 us, of which this kernel takes 62-67 (5 TB/s; a large copy
 // reaches 4.7) and append_finish 6; chunks of 1-512 rows for 512 KV heads (169 MB) 64 -> 50 us.
@@ -109,6 +111,7 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   constexpr int TP = ATP<DH>;
   __shared__ __align__(16) uint4 tile[DH * RPP];   // [channel][group ^ (channel / 8)]: no bank conflicts either way
   __shared__ double colsum[RPP][DH];
+  __shared__ int last;
   const int tid = threadIdx.x;
   const int split = blockIdx.x % a.n_split;
   const size_t head = blockIdx.x / a.n_split;
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   int n = a.n_new_per_seq ? a.n_new_per_seq[b] : a.n_new;
   n = n < 0 ? 0 : (n > a.n_new ? a.n_new : n);
   const bool full = S < 0 || S + n > a.S_max;
-  if (a.n_split > 1 && split == 0 && tid == 0) a.span_ws[head] = make_int2(S, full ? 0 : n);
+  if (!a.tickets && a.n_split > 1 && split == 0 && tid == 0) a.span_ws[head] = make_int2(S, full ? 0 : n);
   if (n == 0) return;
   if (full) {
     if (split == 0 && tid == 0) atomicOr(a.err, 1);
@@ -132,6 +135,7 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   const int E = S + n, S_fl = S & ~7;
   const int p_begin = (S & ~63) + split * a.tiles_per_split * TP;
   const int p_end = p_begin + a.tiles_per_split * TP < E ? p_begin + a.tiles_per_split * TP : E;
+  if (p_begin >= E && a.tickets) return;   // (a second launch reads the partial sums of workgroups with rows only)
   double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int p0 = p_begin; p0 < p_end; p0 += TP) {
     const int p = p0 + grp * 8;          // this thread's 8 positions
@@ -189,13 +193,35 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
     double tot = 0.0;
     for (int g = 0; g < RPP; ++g) tot += colsum[g][tid];
     if (a.n_split > 1) {
-      a.part_ws[(head * a.n_split + split) * DH + tid] = tot;
+      double* mine = a.part_ws + (head * a.n_split + split) * DH + tid;
+      if (a.tickets) store_agent(mine, tot); else *mine = tot;
     } else {
       float* vm = a.v_mean + head * DH + tid;
       const double before = S > 0 ? (double)S * (double)*vm : 0.0;   // S = 0: whatever the buffer held is ignored
       *vm = (float)((before + tot) / (double)(S + n));
     }
   }
+  if (!a.tickets) return;
+  if (a.n_split > 1) {
+    const int per = a.tiles_per_split * TP, used = (E - (S & ~63) + per - 1) / per;     // workgroups of this head with rows
+    if (!last_to_arrive(a.tickets + a.B + head, used, &last)) return;
+    if (tid < DH) {
+      float* vm = a.v_mean + head * DH + tid;
+      const double before = S > 0 ? (double)S * (double)*vm : 0.0;
+      const double* part = a.part_ws + head * a.n_split * DH + tid;
+      double tot = 0.0;
+      for (int s0 = 0; s0 < used; s0 += 8) {                           // eight partials in flight
+        double v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = s0 + t < used ? load_agent(part + (size_t)(s0 + t) * DH) : 0.0;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) tot += v[t];
+      }
+      *vm = (float)((before + tot) / (double)(S + n));
+    }
+  }
+  // every workgroup of the sequence has read its length by the time its KV head is counted
+  if (last_to_arrive(a.tickets + b, a.H_kv, &last) && tid == 0) a.seq_lens[b] = E;
 }
 
 // The means and lengths after append_rows over several workgroups per KV head: one workgroup per (sequence, KV head).
@@ -457,6 +483,11 @@ int64_t append_groups(int64_t heads, int64_t tiles) {
   return n < 128 ? n : 128;
 }
 
+// Up to so many workgroups one launch does a bulk append (whole call, two launches / one: 64 workgroups of 100-row chunks
+// 18.6 / 15.9 us, 200 of a prompt 19.6 / 18.3, 576 30.4 / 29.9); beyond it the hand-overs cost as much as a launch and then
+// more (1992 workgroups 77.5 / 80.1).
+constexpr int64_t kAppendOneLaunch = 512;
+
 template <class T, int DH>
 hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
   AppendArgs a = args;
@@ -476,7 +507,9 @@ hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
     a.n_split = (int)n; a.tiles_per_split = (int)per;
     a.part_ws = reinterpret_cast<double*>(a.scratch);
     a.span_ws = reinterpret_cast<int2*>(a.part_ws + (n > 1 ? heads * n * DH : 0));
+    if (heads * n > kAppendOneLaunch || heads + a.B > kTickets) a.tickets = nullptr;
     hipLaunchKernelGGL((append_rows<T, DH>), dim3(heads * n), dim3(BT), 0, s, a);
+    if (a.tickets) return hipGetLastError();
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -46,6 +46,7 @@ struct AppendArgs {
   int32_t S_stride;   // positions per head in K and V and per channel row in Kt
   int32_t tiled;   // the tiled single-copy key layout: K holds tiles of 8 positions, Kt the rows of the newest < 8
   void* scratch = nullptr; size_t scratch_bytes = 0;   // room for the partial sums of a bulk append (16-byte aligned)
+  int32_t* tickets = nullptr;   // [B], then [B * H_kv]: counters of a bulk append in one launch, 0 between launches
   // set by the launcher of a bulk append: workgroups per KV head and tiles of each, their partial sums of the value
   // columns [B * H_kv][n_split][d_h], old length and row count of each KV head
   int32_t n_split = 1, tiles_per_split = 1;

@@ -24,8 +24,9 @@ MEAN_TOL = 6e-7
     ((120, 1, 300), (300, 480, 513), None),       # one sequence would pass the end: left as it is
     ((61, 3, 0), (510, 499, 257), 65536),         # the smallest workspace: fewer partial sums fit
 ])
-def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch):
-    n_b, h_kv, s_max = 3, 2, 576
+@pytest.mark.parametrize("h_kv", [2, 120])         # one launch; more than 512 workgroups: a second launch for means and lengths
+def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch, h_kv):
+    n_b, s_max = 3, 576
     w = W.Workload("bulk", n_b, h_kv, h_kv, d_h, s_max, 16, 32, dtype, seed=900 + d_h + rows[0])
     print("[case]", d_h, dtype, start, rows, scratch, flush=True)
     old_k, old_v = W.draw_kv(w, "cuda", n_rows=max(max(start), 1), v_offset=True)
@@ -61,3 +62,4 @@ def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch):
             assert (c.v_mean[b].double().cpu() - mean).abs().max().item() <= MEAN_TOL
         else:
             assert torch.equal(c.v_mean[b].double().cpu(), mean0[b])
+    assert c.workspace[256:16384].count_nonzero() == 0               # the counters are left as they were
