@@ -330,9 +330,9 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
   if (p.plan == kPlanFused) return launch_decode(a, shape->dtype, s);
   const bool one_k = p.plan == kPlanSingleK;
   DecodeArgs d = a;
-  if (a.k_new && p.plan != kPlanBucket && p.plan != kPlanSharedBucket && p.plan != kPlanLong) {
-    // the one-workgroup-per-head kernel, the digit-bucket plans and the two-level plan have the append built in; the
-    // other plans append into the *_next state with the append kernel, then decode from that state
+  if (a.k_new && (p.plan == kPlanSharedSplit || p.plan == kPlanSingleK)) {
+    // the grouped-query rule over several workgroups and the single-copy kernel have no append built in: the append
+    // kernel writes the *_next state, and they decode from that
     AppendArgs ap;
     ap.K = a.K; ap.Kt = one_k ? nullptr : a.Kt; ap.V = a.V; ap.v_mean = const_cast<float*>(a.v_mean); ap.seq_lens = const_cast<int32_t*>(a.seq_lens);
     ap.v_mean_out = a.v_mean_next; ap.seq_lens_out = a.seq_lens_next;

@@ -74,10 +74,17 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   const int b = (int)(kv_head / a.H_kv), hk = (int)(kv_head - (size_t)b * a.H_kv);
   const size_t u0 = (size_t)b * a.H + (size_t)hk * G;   // first query head of the group
 
-  int S = a.seq_lens[b];
-  if (S < 0 || S > a.S_max) {
-    if (tid == 0) atomicOr(a.err, 8);
-    S = S < 0 ? 0 : a.S_max;
+  // Inside sparq_decode_step the row being appended counts as position S_b: it is taken from the inputs, and this workgroup,
+  // the only one of its KV head, writes it at the end (an append launch in front took 5-14 us: 128 KV heads
+  // at 4000 positions 51 -> 44 us per step, two at 500 19.7 -> 15.0).
+  bool appended, bad, full;
+  const int S = visible_length(a, b, appended, bad, full);
+  if (tid == 0) {
+    if (hk == 0 && (bad || full)) atomicOr(a.err, (bad ? 8 : 0) | (full ? 1 : 0));
+    if (a.k_new && hk == 0) {   // a length beyond the bound of this call that the buffers can hold is carried over as it is
+      const int S_in = a.seq_lens[b];
+      a.seq_lens_next[b] = (S_in > a.S_max && S_in <= a.S_stride) ? S_in : S;
+    }
   }
   int kb = a.k_per_seq ? a.k_per_seq[b] : a.k;
   kb = kb < 1 ? 1 : (kb > a.k ? a.k : kb);
@@ -89,6 +96,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     if (tid == 0) atomicOr(a.err, 2);
     if (a.chan_out) for (int i = tid; i < G * a.r; i += NT) a.chan_out[u0 * a.r + i] = -1;
     if (a.idx_out) for (int i = tid; i < G * a.idx_stride; i += NT) a.idx_out[u0 * a.idx_stride + i] = -1;
+    if (a.k_new && tid < DH) a.v_mean_next[kv_head * DH + tid] = a.v_mean[kv_head * DH + tid];
     return;
   }
 
@@ -105,14 +113,17 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   // ---------------- pass A: per-head max and sum-exp of the approximate logits ----------------
   const size_t row_bytes = (size_t)a.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(a.Kt) + kv_head * DH * row_bytes;
-  const int n_chunks = S >> 3;   // whole chunks; the newest S mod 8 positions are not in Kt yet
-  const int S_fl = S & ~7, n_tail = S - S_fl, r8 = (a.r + 7) & ~7;
+  // whole chunks that are in Kt: the newest S mod 8 positions are not in it yet (inside a step: up to 8, Kt being up to
+  // date for the length before the call)
+  const int S_fl = (appended ? S - 1 : S) & ~7, n_chunks = S_fl >> 3, n_tail = S - S_fl, r8 = (a.r + 7) & ~7;
+  uint16_t* K_rows = reinterpret_cast<uint16_t*>(a.K) + kv_head * a.S_stride * (size_t)DH;
+  const uint16_t* k_row = reinterpret_cast<const uint16_t*>(a.k_new) + kv_head * DH;     // used where `appended`
+  const uint16_t* v_row = reinterpret_cast<const uint16_t*>(a.v_new) + kv_head * DH;
   float tdot[G];          // wave w: the logit numerators of position S_fl + w for the G heads, from its K row
 #pragma unroll
   for (int h = 0; h < G; ++h) tdot[h] = 0.0f;
   if (wave < n_tail) {
-    const TailRow tail = tail_row_issue(reinterpret_cast<const uint16_t*>(a.K) + (kv_head * a.S_stride + S_fl + wave) * (size_t)DH,
-                                        L.chan, r8, lane);
+    const TailRow tail = tail_row_issue(appended && wave == n_tail - 1 ? k_row : K_rows + (size_t)(S_fl + wave) * DH, L.chan, r8, lane);
 #pragma unroll
     for (int h = 0; h < G; ++h) tdot[h] = tail_row_dot<T>(tail, L.qs + h * DH, r8, lane);
   }
@@ -231,12 +242,14 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     }
     m_run[h] = -INFINITY; l_run[h] = 0.0f;
   }
-  const int n_groups = (kq + GROUP - 1) / GROUP;
+  // positions are ascending: the appended row can only be the last entry
+  const bool new_selected = appended && list[kq - 1] == S - 1;
+  const int n_rows = kq - (new_selected ? 1 : 0), n_groups = (n_rows + GROUP - 1) / GROUP;
   auto issue = [&](uint4 (&kr)[UNR], uint4 (&vr)[UNR], int g) {
 #pragma unroll
     for (int t = 0; t < UNR; ++t) {
       const int n = g * GROUP + t * Geo::RPI + slot;
-      const uint32_t off = (uint32_t)list[n < kq ? n : kq - 1] * (uint32_t)(DH * 2);
+      const uint32_t off = (uint32_t)list[n < n_rows ? n : n_rows - 1] * (uint32_t)(DH * 2);
       kr[t] = load16(K_head + off);
       vr[t] = load16(V_head + off);
     }
@@ -244,7 +257,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   auto consume = [&](const uint4 (&kr)[UNR], const uint4 (&vr)[UNR], int g) {
 #pragma unroll
     for (int t = 0; t < UNR; ++t) {
-      const bool ok = g * GROUP + t * Geo::RPI + slot < kq;
+      const bool ok = g * GROUP + t * Geo::RPI + slot < n_rows;
       float kf[8], vf[8];
       unpack8<T>(kr[t], kf);
       unpack8<T>(vr[t], vf);
@@ -283,6 +296,10 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
       consume(ka, va, g);
     }
   }
+  if (new_selected) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) attend_row_from_codes<T, DH>(k_row, v_row, q8[h], lane, wave, m_run[h], l_run[h], acc[h]);
+  }
   __syncthreads();   // hist and rankp are dead: `part` may overwrite them
 #pragma unroll
   for (int h = 0; h < G; ++h) {
@@ -309,10 +326,24 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     float alpha = 0.0f;
 #pragma unroll
     for (int hh = 0; hh < G; ++hh) if (hh == h) alpha = a_all * inv_z[hh];
+    float vm = a.v_mean[kv_head * DH + c];
+    if (appended) {                        // the mean with the new row; the mean of no rows is ignored
+      if (S == 1) vm = 0.0f;
+      vm += (T::widen(v_row[c]) - vm) * (1.0f / (float)S);
+    }
     float y = y3;
-    if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * a.v_mean[kv_head * DH + c];
+    if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * vm;
     out[(size_t)h * DH + c] = T::narrow(y);
     if (c == 0 && a.alpha_out) a.alpha_out[u0 + h] = alpha;
+    if (a.k_new && h == 0) {               // everything this workgroup reads of the cache has been read
+      a.v_mean_next[kv_head * DH + c] = vm;
+      if (appended) {
+        reinterpret_cast<uint16_t*>(a.V)[(kv_head * a.S_stride + (S - 1)) * DH + c] = v_row[c];
+        K_rows[(size_t)(S - 1) * DH + c] = k_row[c];
+        if ((S & 7) == 0)
+          flush_key_columns(reinterpret_cast<uint16_t*>(a.Kt) + kv_head * DH * (size_t)a.S_stride, K_rows, a.S_stride, DH, S, c, k_row[c]);
+      }
+    }
   }
 }
 

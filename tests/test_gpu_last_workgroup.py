@@ -36,3 +36,38 @@ def test_last_workgroup_of_a_unit(h, h_kv, group, s_max, lens, r):
     after = Hn.Built(w, b.cache, K_all, V_all, seq + 1, None)
     print(Hn.compare_decode(after, q, flags=flags, step_rows=(k1, v1)), flush=True)
     assert b.cache.workspace[256:16384].count_nonzero() == 0
+
+
+@pytest.mark.parametrize("name,kw,flags,lens", [
+    # one workgroup per KV head under the grouped-query rule: the appended row alone, inside, completing a group of 8, at the bound
+    ("group_one_workgroup", dict(H=8, H_kv=2, d_h=64, r=12, k=40), B.SPARQ_FLAG_GQA_SHARED, (0, 6, 7, 703, 704)),
+    ("group_of_two_wide", dict(H=4, H_kv=2, d_h=256, r=40, k=900), B.SPARQ_FLAG_GQA_SHARED, (1, 15, 511, 703, 704)),
+    # two spans of 8192 and more, many heads: an appended row that is a span of its own
+    ("two_level", dict(H=26, H_kv=26, d_h=64, r=8, k=60), 0, (8191, 8192, 40959, 7, 36000)),
+])
+def test_steps_with_the_append_built_in(name, kw, flags, lens):
+    """Nine steps equal nine appends and decodes; a sequence at its bound is left alone and reported."""
+    s_max = 704 if max(lens) <= 704 else 40960
+    w = W.Workload(name, len(lens), S=s_max, dtype="f16", seed=880 + max(lens), **kw)
+    seq = torch.tensor(lens, dtype=torch.int32)
+    a, f = (Hn.build_cache(w, seq_lens=seq, S_max=s_max, v_offset=True) for _ in range(2))
+    for c in (a, f):
+        c.cache.with_params(w.r, w.k, flags)
+    kn, vn = W.draw_kv(W.scaled(w, seed=w.seed + 1), "cuda", n_rows=9, v_offset=True)
+    for t in range(9):
+        k_t, v_t = kn[:, :, t].contiguous(), vn[:, :, t].contiguous()
+        q = W.draw_queries(w, a.K_src, a.cache.seq_lens.cpu().clamp(max=a.K_src.shape[2]), q_scale=0.03, stream=t)[0].contiguous()
+        if t % 3 == 1:                      # the new row is the best match of the first KV head
+            q[:, :w.g] = (k_t[:, :1].float() * 0.05).to(q.dtype)
+        a.cache.append(k_t, v_t)
+        one, two = a.cache.decode(q, aux=True), f.cache.step(k_t, v_t, q, aux=True)
+        fa, ff = a.cache.error_flags(), f.cache.error_flags()
+        assert fa == ff and fa in (0, B.SPARQ_ERR_APPEND_FULL), (fa, ff)
+        assert torch.equal(a.cache.seq_lens, f.cache.seq_lens) and torch.equal(a.cache.v_mean, f.cache.v_mean)
+        assert torch.equal(one[2], two[2]) and torch.equal(one[3], two[3])
+        assert (one[1] - two[1]).abs().max().item() <= 1e-6
+        # the same rows summed in another order, rounded to 16 bits: one unit in the last place
+        assert ((one[0].float() - two[0].float()).abs() <= 2.0 ** -10 * one[0].float().abs() + 1e-6).all()
+        for b, n in enumerate(a.cache.seq_lens.cpu().tolist()):
+            assert torch.equal(a.cache.K[b, :, :n], f.cache.K[b, :, :n]) and torch.equal(a.cache.V[b, :, :n], f.cache.V[b, :, :n])
+            assert torch.equal(a.cache.Kt[b, :, :, :n & ~7], f.cache.Kt[b, :, :, :n & ~7])
