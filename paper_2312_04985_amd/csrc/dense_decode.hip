@@ -212,7 +212,8 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
       l_all += part[w][t_s][DH + 1] * s;
       y4.x += y[0] * s; y4.y += y[1] * s; y4.z += y[2] * s; y4.w += y[3] * s;
     }
-    if (n_live == 1) {
+    if (n_live == 1) {                           // (a denominator that is no positive number: zeros)
+      if (!(l_all > 0.0f)) { y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f); l_all = 1.0f; }
       store_out4<T>(out + slot * 4, y4, 1.0f / l_all);
     } else {
       store_agent4(y_parts, (uint32_t)(split * SLOTS + slot) * 16, y4);
@@ -246,6 +247,7 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
     const float w0 = weight_exp2(m[0], m_max), w1 = weight_exp2(m[1], m_max);
     const float l_sum = wave_sum(l[0] * w0 + l[1] * w1);
     if (lane < n_live) stat[(lane * G + t) * 2] = w0 / l_sum;
+    if (lane == 0) stat[t * 2 + 1] = l_sum;
     if (lane + kWave < n_live) stat[((lane + kWave) * G + t) * 2] = w1 / l_sum;
   }
   __syncthreads();
@@ -272,6 +274,7 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
       }
     }
   }
+  if (!(stat[t_s * 2 + 1] > 0.0f)) y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (grp == 0) store_out4<T>(out + slot * 4, y4, 1.0f);
 }
 

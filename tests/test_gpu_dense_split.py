@@ -31,3 +31,16 @@ def test_dense_decode_edges(d_h, g, dtype, b, h_kv, lens):
         ref = O.dense_decode(K, V, W.to_codes(q), seq.numpy(), dtype=w.dtype_code)
         Hn.check_output(out.float().cpu().numpy(), ref, w.dtype_code)
     assert c.cache.error_flags() == 0
+
+
+@pytest.mark.parametrize("rows", [200, 3000])      # one workgroup, several
+def test_dense_decode_without_a_denominator(rows):
+    """A key that is not a number gives the heads that share it zeros, and no one else."""
+    w = W.Workload("nan", 2, 4, 2, 128, rows, 8, 8, "f16", seed=790)
+    c = Hn.build_cache(w, v_offset=True)
+    q = W.draw_queries(w, c.K_src, c.seq_lens, q_scale=0.03)[0].contiguous()
+    good = c.cache.dense(q)
+    c.cache.K[1, 0, rows // 2, 5] = float("nan")
+    out = c.cache.dense(q)
+    assert (out[1, :2] == 0).all()
+    assert torch.equal(out[0], good[0]) and torch.equal(out[1, 2:], good[1, 2:])
