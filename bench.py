@@ -312,7 +312,7 @@ def measure(name, K, Wm, args, full):
         "two_launch_step_ms": round(two_call_ms, 5), "decode_launch_ms": round(dec_avg_ms, 5),
         "decode_launch_at_step_lengths_ms": round(dec_same_ms, 5),
         "decode_launch_GBps": round(dec_bytes0 / dec_avg_ms / 1e6, 1), "append_launch_ms": round(append_ms, 5),
-        "roofline": {"kernel": plan + (" with the append built in (sparq_decode_step)" if plan.startswith("sparq_decode_fused") or "digit-bucket" in plan else
+        "roofline": {"kernel": plan + (" with the append built in (sparq_decode_step)" if any(x in plan for x in ("sparq_decode_fused", "digit-bucket", "two-level selection plan", "one workgroup per KV head")) else
                                        "; sparq_decode_step runs append_one_row first"),
                      "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None if group_kv else traffic_from_profile(name),
