@@ -133,13 +133,14 @@ typedef struct {
 
 /* Bytes of device workspace the calls below need for this shape (>= 64 KiB; depends on every field of
  * the shape, flags included).  The first 64 KiB are a control block (word 0 is the error word) that
- * sparq_workspace_init zeroes; the rest is scratch: the split-sequence partials of dense_decode, the partial sums of a
+ * sparq_workspace_init zeroes and the calls use for counters of finished workgroups, which they leave at zero (a
+ * workspace that two calls ran on at the same time has to be initialised again); the rest is scratch: the split-sequence partials of dense_decode, the partial sums of a
  * bulk sparq_kv_append (which runs in a smaller workspace too, on fewer workgroups), and for sparq_decode the
  * keys / candidates / position lists of the multi-launch plans (few heads with long caches, S_max beyond one
  * workgroup's LDS) or the logits of the grouped-query rule.  One workspace serves one stream. */
 int sparq_workspace_bytes(const sparq_shape* shape, size_t* out_bytes);
 
-/* Enqueue a clear of the control block.  Call once after allocating the workspace. */
+/* Enqueue a clear of the control block.  Call once after allocating the workspace, before any other call uses it. */
 int sparq_workspace_init(void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
