@@ -1,5 +1,6 @@
 // Cache maintenance: append key/value rows, keep the S-contiguous key copy and the running
 // mean value vector in step (Section 3 "Mean value reallocation"; Appendix F "Storing K twice").
+#include "append_plan.h"
 #include "decode_stages.h"
 
 namespace sparq {
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(512) void append_one_row(const AppendArgs a) {
 // Measured (whole call; before: one workgroup per KV head, columns in 2-byte stores): a prompt of 31 777 rows for 8 KV
 // heads, d_h 128 (325 MB read and written) 2301 -> 77 us, of which this kernel takes 62-67 (5 TB/s; a large copy
 // reaches 4.7) and append_finish 6; chunks of 1-512 rows for 512 KV heads (169 MB) 64 -> 50 us.
-constexpr int BT = 256;       // threads
+constexpr int BT = kAppendThreads;
 // (rows of K and V leave as non-temporal stores: 84 -> 78 us for that prompt; the columns of Kt do not: 78 -> 82)
 __device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -87,7 +88,7 @@ __device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
 template <int DH>
-constexpr int ATP = 8 * BT / (DH / 8);     // positions per tile: 256, 128, 64 for d_h = 64, 128, 256 (32 KB of keys)
+constexpr int ATP = append_tile(DH);       // positions per tile
 
 // transpose 8 rows x 8 channels of 16-bit codes: w[c] = the 8 rows' codes of channel c
 __device__ __forceinline__ void transpose_piece(const uint4 (&rows)[8], uint4 (&w)[8]) {
@@ -133,9 +134,9 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   uint16_t* Vhead = reinterpret_cast<uint16_t*>(a.V) + head * a.S_stride * (size_t)DH + sub * 8;
   uint16_t* Kthead = reinterpret_cast<uint16_t*>(a.Kt) + head * DH * (size_t)a.S_stride;
   const int E = S + n, S_fl = S & ~7;
-  const int p_begin = (S & ~63) + split * a.tiles_per_split * TP;
-  const int p_end = p_begin + a.tiles_per_split * TP < E ? p_begin + a.tiles_per_split * TP : E;
-  if (p_begin >= E && a.tickets) return;   // (a second launch reads the partial sums of workgroups with rows only)
+  const AppendSplit plan{a.n_split, a.tiles_per_split};
+  const AppendRun run = append_run(S, n, split, plan, DH);
+  const int p_begin = run.begin, p_end = run.end;
   double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int p0 = p_begin; p0 < p_end; p0 += TP) {
     const int p = p0 + grp * 8;          // this thread's 8 positions
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   if (tid < DH) {
     double tot = 0.0;
     for (int g = 0; g < RPP; ++g) tot += colsum[g][tid];
-    if (a.n_split > 1) {
+    if (a.n_split > 1) {                   // (only the partial sums of workgroups with rows are read)
       double* mine = a.part_ws + (head * a.n_split + split) * DH + tid;
       if (a.tickets) store_agent(mine, tot); else *mine = tot;
     } else {
@@ -203,8 +204,8 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   }
   if (!a.tickets) return;
   if (a.n_split > 1) {
-    const int per = a.tiles_per_split * TP, used = (E - (S & ~63) + per - 1) / per;     // workgroups of this head with rows
-    if (!last_to_arrive(a.tickets + a.B + head, used, &last)) return;
+    if (!last_to_arrive(a.tickets + a.B + head, append_arrivals(plan), &last)) return;
+    const int used = run.used;
     if (tid < DH) {
       float* vm = a.v_mean + head * DH + tid;
       const double before = S > 0 ? (double)S * (double)*vm : 0.0;
@@ -220,7 +221,8 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
       *vm = (float)((before + tot) / (double)(S + n));
     }
   }
-  // every workgroup of the sequence has read its length by the time its KV head is counted
+  // Every workgroup of the sequence, those without rows among them, has read its length by the time its KV head is
+  // counted: one that started after the length was written would take the new length for the old one.
   if (last_to_arrive(a.tickets + b, a.H_kv, &last) && tid == 0) a.seq_lens[b] = E;
 }
 
@@ -238,8 +240,7 @@ __global__ __launch_bounds__(BT) void append_finish(const AppendArgs a) {
   if (n == 0) return;
   float* vm = a.v_mean + head * DH + c;
   const double before = S > 0 ? (double)S * (double)*vm : 0.0;     // S = 0: whatever the buffer held is ignored
-  const int per = a.tiles_per_split * ATP<DH>;
-  const int used = (S + n - (S & ~63) + per - 1) / per;            // workgroups that had rows
+  const int used = append_run(S, n, 0, AppendSplit{a.n_split, a.tiles_per_split}, DH).used;   // workgroups that had rows
   const double* part = a.part_ws + head * a.n_split * DH + c;
   double tot = 0.0;
   for (int s0 = grp; s0 < used; s0 += NG * 8) {                    // eight partials in flight
@@ -475,19 +476,6 @@ __global__ void clear_words(int32_t* w, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) w[i] = 0;
 }
 
-// Workgroups per KV head of a bulk append of `tiles` tiles per head: about kAppendGroups in all (8 per CU; five of them
-// fit by LDS), at most 128 per head, so that append_finish reads few partial sums.
-constexpr int64_t kAppendGroups = 2048;
-int64_t append_groups(int64_t heads, int64_t tiles) {
-  const int64_t per = (tiles * heads + kAppendGroups - 1) / kAppendGroups, n = (tiles + per - 1) / per;
-  return n < 128 ? n : 128;
-}
-
-// Up to so many workgroups one launch does a bulk append (whole call, two launches / one: 64 workgroups of 100-row chunks
-// 18.6 / 15.9 us, 200 of a prompt 19.6 / 18.3, 576 30.4 / 29.9); beyond it the hand-overs cost as much as a launch and then
-// more (1992 workgroups 77.5 / 80.1).
-constexpr int64_t kAppendOneLaunch = 512;
-
 template <class T, int DH>
 hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
   AppendArgs a = args;
@@ -495,16 +483,9 @@ hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
   if (a.tiled) {
     hipLaunchKernelGGL((append_rows_tiled<T, DH>), dim3(heads), dim3(BT), 0, s, a);
   } else {
-    // Workgroups per KV head: one per tile until there are kAppendGroups in all, then longer runs of tiles, and no
-    // more than the scratch holds partial sums of (512 KV heads, up to 512 rows each: 4 per head 51 us, 2 per head
-    // 67 us).  A call on a cache that is not aligned to 64 positions may touch one tile more.
-    const int64_t tiles = ((int64_t)a.n_new + 63 + ATP<DH> - 1) / ATP<DH>;
-    int64_t n = append_groups(heads, tiles);
-    const int64_t held = (int64_t)(a.scratch_bytes / (heads * (DH * sizeof(double) + sizeof(int2))));
-    if (n > held) n = held > 1 ? held : 1;
-    const int64_t per = (tiles + n - 1) / n;
-    n = (tiles + per - 1) / per;
-    a.n_split = (int)n; a.tiles_per_split = (int)per;
+    const AppendSplit plan = append_split(heads, a.n_new, DH, (int64_t)(a.scratch_bytes / (heads * (DH * sizeof(double) + sizeof(int2)))));
+    const int64_t n = plan.n_split;
+    a.n_split = plan.n_split; a.tiles_per_split = plan.tiles_per_split;
     a.part_ws = reinterpret_cast<double*>(a.scratch);
     a.span_ws = reinterpret_cast<int2*>(a.part_ws + (n > 1 ? heads * n * DH : 0));
     if (heads * n > kAppendOneLaunch || heads + a.B > kTickets) a.tickets = nullptr;
@@ -531,7 +512,7 @@ hipError_t launch_rows(const AppendArgs& a, hipStream_t s) {
 }  // namespace
 
 size_t append_scratch_bytes(int64_t heads, int S_max, int d_h) {
-  const int64_t positions = 8 * BT / (d_h / 8), tiles = (S_max + 63 + positions - 1) / positions;
+  const int64_t positions = append_tile(d_h), tiles = (S_max + 63 + positions - 1) / positions;
   int64_t n = kAppendGroups / heads + 1;           // append_groups of any number of tiles up to these
   n = n < tiles ? n : tiles;
   n = n < 128 ? n : 128;
