@@ -116,7 +116,7 @@ struct BucketArgs {
   float* zsum_ws;          // [B * H][n_span] sum over the span of exp((d - span max) / tau)
   float* anum_ws;          // [B * H][n_span] the span's share of alpha's numerator (relative to the sequence maximum)
   float* tau_ws;           // [B * H]
-  int32_t* tickets;        // [B * H] counters of finished spans, 0 between launches
+  int32_t* tickets;        // [B * H] counters of finished spans, cleared by the plan's own first launches
   uint16_t* coarse_ws;     // [B * H][n_span][64] A[32 l]
   uint16_t* fine_ws;       // [B * H][n_span][2080] A[d] = keys of the span with first digit >= d
   uint32_t* skey_ws;       // [B * H][n_span][span_len] the span's keys sorted by first digit, descending

@@ -130,6 +130,10 @@ __host__ __device__ constexpr size_t bk_scores_fixed_words() {
   return 2 * (size_t)kRadixBins + NT + 4 * (size_t)DH + 32 + 8;
 }
 
+// A unit's counter of finished spans starts at 0 for the launch that counts, whatever an earlier call left: calls that
+// were wrongly allowed to overlap spoil their own results and no later ones.
+__device__ __forceinline__ void clear_ticket(int32_t* p) { __hip_atomic_store(p, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 template <class T, int DH>
 __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
@@ -160,7 +164,10 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   if (tid < DH) qcode = reinterpret_cast<const uint16_t*>(d.q)[(size_t)u * DH + tid];
   bool appended, bad, full;
   const int S = visible_length(d, b, appended, bad, full);
-  if (tid == 0 && s == 0 && (bad || full)) atomicOr(d.err, (bad ? 8 : 0) | (full ? 1 : 0));
+  if (tid == 0 && s == 0) {
+    if (bad || full) atomicOr(d.err, (bad ? 8 : 0) | (full ? 1 : 0));
+    clear_ticket(a.tickets + u);
+  }
   int32_t* idx_out = d.idx_out ? d.idx_out + (size_t)u * d.idx_stride : nullptr;
   if (S == 0) {   // nothing cached: span 0 writes the defined outputs, the later launches skip the unit
     if (s == 0) {
@@ -322,6 +329,7 @@ __global__ __launch_bounds__(NT, 2) void bk_group_scores(const BucketArgs a) {
   uint16_t* coarse = a.coarse_ws + slot * 64;
   bool appended, bad, full;
   const int S = visible_length(d, b, appended, bad, full);
+  if (s == 0 && tid < G) clear_ticket(a.tickets + u0 + tid);
   if (S == 0) return;                      // reported, and the outputs written, by gs_logits
   int kb = d.k_per_seq ? d.k_per_seq[b] : d.k;
   kb = kb < 1 ? 1 : (kb > d.k ? d.k : kb);

@@ -38,6 +38,24 @@ def test_last_workgroup_of_a_unit(h, h_kv, group, s_max, lens, r):
     assert b.cache.workspace[256:16384].count_nonzero() == 0
 
 
+@pytest.mark.parametrize("h,h_kv,flags", [(4, 2, 0), (4, 1, B.SPARQ_FLAG_GQA_SHARED), (4, 2, B.SPARQ_FLAG_GQA_SHARED)])
+def test_a_unit_is_counted_from_zero(h, h_kv, flags):
+    """What an earlier call left in the counters (sparq_decode_noalloc's buffer cannot be initialised again) changes nothing."""
+    w = W.Workload("count", 3, h, h_kv, 64, 16384, 24, 200, "f16", seed=870 + h_kv)
+    b = Hn.build_cache(w, seq_lens=torch.tensor([16384, 900, 5000], dtype=torch.int32), S_max=16384, v_offset=True)
+    b.cache.with_params(w.r, w.k, flags)
+    assert "digit-bucket" in B.sparq_decode_plan(b.cache.shape)
+    q = W.draw_queries(w, b.K_src, b.seq_lens, q_scale=0.03)[0].contiguous()
+    want = [x.clone() for x in b.cache.decode(q, aux=True)]
+    counters = b.cache.workspace[256:256 + 4 * w.B * h].view(torch.int32)
+    for left in (1, 15, -2, 1 << 20):
+        counters.fill_(left)
+        got = b.cache.decode(q, aux=True)
+        assert all(torch.equal(x, y) for x, y in zip(want, got)), left
+        assert counters.count_nonzero() == 0
+    assert b.cache.error_flags() == 0
+
+
 @pytest.mark.parametrize("name,kw,flags,lens", [
     # one workgroup per KV head under the grouped-query rule: the appended row alone, inside, completing a group of 8, at the bound
     ("group_one_workgroup", dict(H=8, H_kv=2, d_h=64, r=12, k=40), B.SPARQ_FLAG_GQA_SHARED, (0, 6, 7, 703, 704)),
