@@ -73,8 +73,10 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   const size_t kv_head = (size_t)b * a.H_kv + hk;
   const int row16 = lane & 15, quarter = lane >> 4;
   const int sub = lane % LPR, vrow = lane / LPR;
-  const char* K_head = reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2);
-  const char* V_head = reinterpret_cast<const char*>(a.V) + kv_head * a.S_stride * (size_t)(DH * 2);
+  // This run of rows.  Offsets inside it fit 32 bits, those inside a whole head need not: a run is the (units x n_split)-th
+  // part of K, and dense_plan's smallest such product is 128.
+  const char* K_run = reinterpret_cast<const char*>(a.K) + (kv_head * a.S_stride + s0) * (size_t)(DH * 2);
+  const char* V_run = reinterpret_cast<const char*>(a.V) + (kv_head * a.S_stride + s0) * (size_t)(DH * 2);
   const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)b * a.H + h0 + row16 % G) * DH + quarter * 8;
   uint4 qf[KK];                                  // row (lane % 16) % G of the query, channels 32 kk + 8 quarter ..
 #pragma unroll
@@ -92,14 +94,14 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
 #pragma unroll
     for (int t = 0; t < TPG; ++t) {
       const int n = r0 + t * 16 + row16;
-      const uint32_t off = (uint32_t)(n < s1 ? n : s0) * (uint32_t)(DH * 2) + quarter * 16;    // < S_max * 512 bytes
+      const uint32_t off = (uint32_t)(n < s1 ? n - s0 : 0) * (uint32_t)(DH * 2) + quarter * 16;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kr[t][kk] = load16(K_head + off + kk * 64);
+      for (int kk = 0; kk < KK; ++kk) kr[t][kk] = load16(K_run + off + kk * 64);
     }
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
       const int n = r0 + u * RPW + vrow;
-      vr[u] = load16(V_head + ((uint32_t)(n < s1 ? n : s0) * (uint32_t)(DH * 2) + sub * 16));
+      vr[u] = load16(V_run + ((uint32_t)(n < s1 ? n - s0 : 0) * (uint32_t)(DH * 2) + sub * 16));
     }
   };
   auto consume = [&](const uint4 (&kr)[TPG][KK], const uint4 (&vr)[NV], int r0) {

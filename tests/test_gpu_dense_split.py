@@ -3,7 +3,9 @@ import pytest
 import torch
 
 from oracle import sparq_oracle as O
+from paper_2312_04985_amd import binding as B
 from paper_2312_04985_amd import workloads as W
+from paper_2312_04985_amd.cache import DecodeCache
 
 import harness as Hn
 
@@ -44,3 +46,22 @@ def test_dense_decode_without_a_denominator(rows):
     out = c.cache.dense(q)
     assert (out[1, :2] == 0).all()
     assert torch.equal(out[0], good[0]) and torch.equal(out[1, 2:], good[1, 2:])
+
+
+@pytest.mark.parametrize("d_h,g,dtype", [(256, 1, "f16"), (128, 4, "bf16")])
+def test_dense_decode_rows_beyond_4_gib_of_a_head(d_h, g, dtype):
+    """The rows that count lie more than 2^32 bytes behind the head's first one; all others are zeros."""
+    first, n = (1 << 32) // (2 * d_h), 300
+    S = first + n
+    w = W.Workload("far", 1, g, 1, d_h, S, 8, 8, dtype, seed=795)
+    c = DecodeCache(1, g, 1, W.round_up(S, 64), d_h, 8, 8, w.torch_dtype, flags=B.SPARQ_FLAG_SINGLE_K)   # (no second copy of K)
+    gen = torch.Generator().manual_seed(795)
+    K, V, q = (torch.randn(x, generator=gen).to(w.torch_dtype) for x in ((n, d_h), (n, d_h), (g, d_h)))
+    q[:, 0] = 16.0                          # a common part of every score, so that the 2^24 zeros do not take the weight
+    K[:, 0] = 2.0 * d_h ** 0.5
+    c.K[0, 0, first:S], c.V[0, 0, first:S], c.seq_lens[0] = K.cuda(), V.cuda(), S
+    out = c.dense(q.cuda()[None].contiguous())
+    score = q.double() @ K.double().T / d_h ** 0.5
+    e = torch.exp(score - score.max(1, keepdim=True).values)
+    y = (e @ V.double()) / (e.sum(1, keepdim=True) + first * torch.exp(-score.max(1, keepdim=True).values))
+    Hn.check_output(out[0].float().cpu().numpy(), y.numpy(), w.dtype_code)
