@@ -501,9 +501,10 @@ __device__ __forceinline__ float select_compact(const uint32_t* keys, uint32_t* 
 }
 
 // A thread's share of the softmax denominator, summed while the logit numerators are produced: relative to the
-// largest value the thread has seen, brought to the sequence's maximum at the end.
+// largest value the thread has seen, brought to the sequence's maximum at the end.  (It starts at the lowest finite value, so
+// that no maximum lies below it: a thread without positions brings 0.)
 struct RunningSum {
-  float ref = -3.0e38f, z = 0.0f;
+  float ref = -3.402823466e38f, z = 0.0f;
   template <int M>
   __device__ __forceinline__ void add(const float (&d)[M], float esc) {
     float m = ref;
