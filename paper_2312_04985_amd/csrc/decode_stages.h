@@ -482,10 +482,11 @@ __device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint
 #pragma unroll
   for (int w = 0; w < NW; ++w) { zt += sl.red[w]; at += sl.red[NW + w]; }
   if (!all_equal_taken) at += (float)need * exp2_weight((key_to_float(first) - dmax) * esc);
-  // numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
   if (sums_out) { sums_out[0] = zt; sums_out[1] = at; }
+  // numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
+  // (but not a number where they are none)
   const float alpha = at / zt;
-  return k_old == S_old || alpha > 1.0f ? 1.0f : alpha;
+  return alpha > 1.0f || (k_old == S_old && alpha == alpha) ? 1.0f : alpha;
 }
 
 template <Sums SUMS>

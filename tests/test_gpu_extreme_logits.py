@@ -1,4 +1,4 @@
-"""Approximate logits at the ends of what fp32 holds."""
+"""Approximate logits at the ends of what fp32 holds, and logits that are no numbers."""
 import pytest
 import torch
 
@@ -49,3 +49,18 @@ def test_all_logits_near_the_lowest_finite_value(b, h, h_kv, S, k, flags, plan):
     top, mean = c.V[:, :, :k].double().mean(2), c.V[:, :, :S].double().mean(2)
     y = (k / S * top + (1 - k / S) * mean).repeat_interleave(h // h_kv, dim=1)
     Hn.check_output(out.float().cpu().numpy(), y.cpu().numpy(), O.BF16)
+
+
+@pytest.mark.parametrize("S,k", [(300, 300), (701, 40), (17000, 17000)])
+def test_a_key_that_is_no_number_leaves_no_alpha(S, k):
+    """alpha of the heads that read it is not a number, also where everything is selected; the others' is as without it."""
+    c = filled(2, 2, 2, S, k, 0, torch.float16)
+    c.Kt.copy_(c.K.transpose(2, 3))
+    q = torch.randn((2, 2, 64), device="cuda", generator=torch.Generator(device="cuda").manual_seed(841)).half() * 0.1
+    q[:, :, 0] = 1.0                        # channel 0 is among the chosen ones
+    good = c.decode(q, aux=True)[1].clone()
+    c.K[1, 0, S // 2, 0] = c.Kt[1, 0, 0, S // 2] = float("nan")
+    alpha = c.decode(q, aux=True)[1]
+    assert torch.isnan(alpha[1, 0])
+    keep = torch.tensor([[True, True], [False, True]], device="cuda")
+    assert torch.equal(alpha[keep], good[keep]) and (k < S or (alpha[keep] == 1).all())
