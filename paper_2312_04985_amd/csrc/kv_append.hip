@@ -78,8 +78,8 @@ __global__ __launch_bounds__(512) void append_one_row(const AppendArgs a) {
 // advances its length (counters in the control block); with many, whose stores saturate the memory that every such
 // hand-over waits for, a second launch does it, append_finish or bump_seq_lens (see launch_rows_dh).
 // Measured (whole call; before: one workgroup per KV head, columns in 2-byte stores): a prompt of 31 777 rows for 8 KV
-// heads, d_h 128 (325 MB read and written) 2301 -> 77 us, of which this kernel takes 62-67 (5 TB/s; a large copy
-// reaches 4.7) and append_finish 6; chunks of 1-512 rows for 512 KV heads (169 MB) 64 -> 50 us.
+// heads, d_h 128 (325 MB read and written) 2301 -> 70 us; chunks of 1-512 rows for 512 KV heads (169 MB) 63 -> 42 us.  (With a
+// branch around each row's loads the compiler put each one's wait behind it: 79 and 48 us.)
 constexpr int BT = kAppendThreads;
 // (rows of K and V leave as non-temporal stores: 84 -> 78 us for that prompt; the columns of Kt do not: 78 -> 82)
 __device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
@@ -105,17 +105,32 @@ __device__ __forceinline__ void transpose_piece(const uint4 (&rows)[8], uint4 (&
   }
 }
 
+// the codes of positions 0 .. left - 1 of a group of 8, 16 bytes where it is whole
+__device__ __forceinline__ void store_columns(uint16_t* dst, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, int left) {
+  if (left >= 8) {
+    *reinterpret_cast<uint4*>(dst) = make_uint4(x0, x1, x2, x3);
+  } else {                               // the last, unfinished group: its positions only, as 4 + 2 + 1
+    const uint64_t lo = x0 | ((uint64_t)x1 << 32), hi = x2 | ((uint64_t)x3 << 32);
+    if (left & 4) *reinterpret_cast<uint64_t*>(dst) = lo;
+    const uint64_t rest = left & 4 ? hi : lo;
+    if (left & 2) *reinterpret_cast<uint32_t*>(dst + (left & 4)) = (uint32_t)rest;
+    if (left & 1) dst[left & 6] = (uint16_t)(rest >> (left & 2 ? 32 : 0));
+  }
+}
+
 template <class T, int DH>
 __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   constexpr int CPR = DH / 8;            // 16-byte pieces per row
   constexpr int RPP = BT / CPR;          // groups of 8 positions per tile
   constexpr int TP = ATP<DH>;
   __shared__ __align__(16) uint4 tile[DH * RPP];   // [channel][group ^ (channel / 8)]: no bank conflicts either way
-  __shared__ double colsum[RPP][DH];
+  double (*colsum)[DH] = reinterpret_cast<double (*)[DH]>(tile);   // [RPP][DH], after the last tile
   __shared__ int last;
   const int tid = threadIdx.x;
-  const int split = blockIdx.x % a.n_split;
-  const size_t head = blockIdx.x / a.n_split;
+  // Workgroups are dealt round-robin to the 8 XCDs: the head varies fastest, so that the workgroups that find no rows do not
+  // all fall to the same ones (1024 KV heads x 200 rows, every second workgroup without rows: 77 -> 61 us).
+  const int heads = a.B * a.H_kv, split = blockIdx.x / heads;
+  const size_t head = blockIdx.x - split * heads;
   const int b = (int)(head / a.H_kv);
   const int S = a.seq_lens[b];
   int n = a.n_new_per_seq ? a.n_new_per_seq[b] : a.n_new;
@@ -140,49 +155,45 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int p0 = p_begin; p0 < p_end; p0 += TP) {
     const int p = p0 + grp * 8;          // this thread's 8 positions
-    uint4 kr[8], vr[8];
+    if (p + 8 > S_fl && p < p_end) {     // some of them belong to this call, or wait for their place in Kt
+      // all 16 pieces are requested before the first is used: no branch around a load, the rows next to those of the call stand in
+      uint4 kr[8], vr[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int q = p + e;
-      const bool is_new = q >= S && q < E;
-      kr[e] = vr[e] = make_uint4(0u, 0u, 0u, 0u);
-      if (is_new) {
-        kr[e] = load16(ksrc + (size_t)(q - S) * DH);
-        vr[e] = load16(vsrc + (size_t)(q - S) * DH);
-      } else if (q >= S_fl && q < S) {   // cached before this call and not yet in the S-contiguous copy
-        kr[e] = load16(Khead + (size_t)q * DH);
+      for (int e = 0; e < 8; ++e) {
+        const int q = p + e, i = q < S ? 0 : (q < E ? q - S : n - 1);
+        // (S_fl <= q < S: cached before this call and not yet in the S-contiguous copy)
+        kr[e] = load16(q < S ? Khead + (size_t)q * DH : ksrc + (size_t)i * DH);
+        vr[e] = load16(vsrc + (size_t)i * DH);
+      }
+      if (a.Kt) {                        // null: the cache keeps K once
+        uint4 w[8];
+        transpose_piece(kr, w);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) tile[(sub * 8 + c) * RPP + (grp ^ (sub & (RPP - 1)))] = w[c];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int q = p + e;
+        if (q >= S && q < E) {
+          store16_nt(Khead + (size_t)q * DH, kr[e]);
+          store16_nt(Vhead + (size_t)q * DH, vr[e]);
+          float f[8];
+          unpack8<T>(vr[e], f);
+#pragma unroll
+          for (int c = 0; c < 8; ++c) sum[c] += (double)f[c];
+        }
       }
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int q = p + e;
-      if (q >= S && q < E) {
-        store16_nt(Khead + (size_t)q * DH, kr[e]);
-        store16_nt(Vhead + (size_t)q * DH, vr[e]);
-        float f[8];
-        unpack8<T>(vr[e], f);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) sum[c] += (double)f[c];
-      }
-    }
-    if (a.Kt) {                          // null: the cache keeps K once
-      uint4 w[8];
-      transpose_piece(kr, w);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) tile[(sub * 8 + c) * RPP + (grp ^ (sub & (RPP - 1)))] = w[c];
+    if (a.Kt) {
       __syncthreads();
-      for (int i = tid; i < DH * RPP; i += BT) {
-        const int j = i / RPP, u = i % RPP, q = p0 + u * 8;
+      // the groups that hold positions of this call, dealt evenly to the threads (a short append fills a few of RPP)
+      const int u0 = p0 < S_fl ? (S_fl - p0) >> 3 : 0, u1 = (p_end - p0 + 7) >> 3, live = (u1 < RPP ? u1 : RPP) - u0;
+      const float per_live = 1.0f / (float)live;
+      for (int i = tid; i < DH * live; i += BT) {
+        const int j = (int)(((float)i + 0.5f) * per_live), u = u0 + i - j * live, q = p0 + u * 8;   // i / live: i < 2^12
         const uint4 v = tile[j * RPP + (u ^ ((j >> 3) & (RPP - 1)))];
         uint16_t* dst = Kthead + (size_t)j * a.S_stride + q;
-        if (q >= S_fl && q + 8 <= E) {
-          *reinterpret_cast<uint4*>(dst) = v;
-        } else if (q >= S_fl && q < E) { // the last, unfinished group: its positions only
-          const uint32_t x[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int e = 0; e < 7; ++e)
-            if (q + e < E) dst[e] = (uint16_t)(x[e >> 1] >> (16 * (e & 1)));
-        }
+        store_columns(dst, v.x, v.y, v.z, v.w, E - q);
       }
       __syncthreads();
     }
