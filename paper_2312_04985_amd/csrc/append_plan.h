@@ -17,10 +17,20 @@ constexpr int64_t append_groups(int64_t heads, int64_t tiles) {
   return n < 128 ? n : 128;
 }
 
-// Up to so many workgroups one launch does a bulk append (whole call, two launches / one: 64 workgroups of 100-row chunks
-// 18.6 / 15.9 us, 200 of a prompt 19.6 / 18.3, 576 30.4 / 29.9); beyond it the hand-overs cost as much as a launch and then
-// more (1992 workgroups 77.5 / 80.1).
-constexpr int64_t kAppendOneLaunch = 512;
+// Up to so many workgroups one launch does a bulk append.  Device us per call, two launches / one: 8 KV heads x 8 rows 8.6 /
+// 7.5, 64 x 64 9.5 / 9.2, 128 x 8 8.4 / 8.3, 192 x 8 9.0 / 9.6, 512 x 8 9.7 / 14.0; a program that does not capture its calls
+// pays 2.5 us of host time for the second launch, so the line lies a little higher than where the device times cross.
+constexpr int64_t kAppendOneLaunch = 192;
+
+// Short appends for many KV heads, by append_rows_short: up to a quarter of a tile, and up to kAppendShort rows where there
+// are rows enough to fill the memory's pipes with a workgroup per head (append_rows asks for 16 pieces per thread at once,
+// but 8 rows keep 16 to 64 of its 256 threads busy).  Device us per call, short / tiles: 512 heads of 128 x 8 rows 8.1 / 9.5,
+// x 33 10.8 / 11.3, x 64 15.6 / 13.9; 768 x 64 20.3 / 17.9; 1024 x 64 24.3 / 27.3; 2048 x 8 17.6 / 22.1, x 64 45.3 / 43.9; heads of
+// 64, 512 x 64 11.0 / 11.2, 1536 x 33 15.2 / 19.1; heads of 256, 256 x 48 16.2 / 13.0, 512 x 33 18.4 / 19.9, 768 x 64 31.2 / 35.8.
+constexpr int kAppendShort = 64;
+constexpr bool append_short(int64_t heads, int64_t n_new, int d_h) {
+  return n_new <= kAppendShort && (n_new <= append_tile(d_h) / 4 || heads * d_h >= 131072);
+}
 
 // Workgroups per KV head: one per tile until there are kAppendGroups in all, then longer runs of tiles, and no
 // more than the scratch holds partial sums of (512 KV heads, up to 512 rows each: 4 per head 51 us, 2 per head

@@ -23,10 +23,12 @@ MEAN_TOL = 6e-7
     ((7, 0, 450), (513, 0, 64), None),            # nothing for one sequence, the buffer's last row for another
     ((120, 1, 300), (300, 480, 513), None),       # one sequence would pass the end: left as it is
     ((61, 3, 0), (510, 499, 257), 65536),         # the smallest workspace: fewer partial sums fit
+    ((7, 64, 0), (16, 9, 1), None),               # a short append where there are many KV heads (120): rows of a full group and beside it
+    ((63, 560, 13), (64, 17, 3), None),           # ... for d_h 64 up to 64 rows; one sequence would pass the end
 ])
-@pytest.mark.parametrize("h_kv", [2, 120])         # one launch; more than 512 workgroups: a second launch for means and lengths
-def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch, h_kv):
-    n_b, s_max = 3, 576
+@pytest.mark.parametrize("h_kv", [2, 120])         # one launch; more than 192 workgroups: a second launch for means and lengths
+def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch, h_kv, s_max=576):
+    n_b = 3
     w = W.Workload("bulk", n_b, h_kv, h_kv, d_h, s_max, 16, 32, dtype, seed=900 + d_h + rows[0])
     print("[case]", d_h, dtype, start, rows, scratch, flush=True)
     old_k, old_v = W.draw_kv(w, "cuda", n_rows=max(max(start), 1), v_offset=True)
@@ -63,3 +65,10 @@ def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch, h
         else:
             assert torch.equal(c.v_mean[b].double().cpu(), mean0[b])
     assert c.workspace[256:16384].count_nonzero() == 0               # the counters are left as they were
+
+
+@pytest.mark.parametrize("d_h,dtype", [(64, "bf16"), (128, "f16"), (256, "bf16")])
+@pytest.mark.parametrize("start,rows", [((0, 7, 8), (64, 64, 64)), ((61, 0, 127), (33, 0, 49))])
+def test_short_append_for_many_heads(d_h, dtype, start, rows):
+    """768 KV heads and up to 64 rows: one workgroup per KV head, whatever d_h."""
+    test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, None, 256, s_max=192)
