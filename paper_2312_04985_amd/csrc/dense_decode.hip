@@ -19,14 +19,16 @@ constexpr int DW = DT / kWave;
 // when it rises.  The weights go through LDS to the lanes that hold the row's slice of V, as fp32, and V is
 // accumulated by plain fp32 FMAs.  Products of 16-bit inputs are exact in the matrix unit and summed in fp32.
 // Bound by HBM.  Measured (before: scores by FMAs and lane sums, two exponentials and a rescaling per row, head and lane,
-// and a second launch for the merge): 8 KV heads of 32 768 rows, 4 query heads each, bf16 47.4 -> 28.6 us (134 MB);
-// 60 KV heads of 8192 rows, 8 heads each 122 -> 54; 512 KV heads of 4096 rows, one head each 176 -> 159 (6.8 TB/s);
-// one row group of one head 10.6 -> 8.3.
+// and a second launch for the merge): 8 KV heads of 32 768 rows, 4 query heads each, bf16 44.2 -> 26.9 us (134 MB); 64 KV heads
+// of 8192 rows, 8 heads each 120 -> 53; 512 KV heads of 4096 rows, one head each 170 -> 157 (6.8 TB/s); one row group of one
+// head 9.5 -> 7.6.  Registers decide: with twice the rows per group and four copies of the group's code in every
+// instance, f16 with 4 and 8 heads went to scratch memory (64 KV heads of 5000 rows, 4 heads 47 us, now 31; 8 heads 68, now 39).
 template <class T, int DH, int G>
 struct DenseGeometry {
   static constexpr int LPR = DH / 8, RPW = kWave / LPR;      // lanes per row of V, rows per load of a wave
   static constexpr int KK = DH / 32;                         // matrix instructions (16-byte pieces per lane) per tile
-  static constexpr int TPG = DH == 256 ? 1 : (DH == 128 ? 2 : 4) / (G == 8 ? 2 : 1);   // two groups fit the registers
+  static constexpr int TPG = DH == 64 ? 2 : 1;               // two groups of 4 to 8 KB of K in flight fit the registers
+  static constexpr bool TIGHT = G == 8 || (G == 4 && DH == 256);   // ... with two copies of the group's code and no more
   static constexpr int R = 16 * TPG;                         // rows per group
   static constexpr int NV = R / RPW;                         // loads of V per group
   static constexpr int NH = G < 4 ? G : 4;                   // scores of a row that one lane holds
@@ -167,15 +169,28 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   if (r0 < s1) {
     uint4 ka[TPG][KK], va[NV], kb[TPG][KK], vb[NV];
     issue(ka, va, r0);
-    for (;;) {
-      const int r1 = r0 + DW * R, r2 = r1 + DW * R;
-      if (r1 >= s1) { consume(ka, va, r0); break; }
-      issue(kb, vb, r1);
-      consume(ka, va, r0);
-      if (r2 >= s1) { consume(kb, vb, r1); break; }
-      issue(ka, va, r2);
-      consume(kb, vb, r1);
-      r0 = r2;
+    if constexpr (Geo::TIGHT) {
+      for (;;) {                                 // (past the end of the run the loads repeat its first row, and nothing uses them)
+        const int r1 = r0 + DW * R;
+        issue(kb, vb, r1);
+        consume(ka, va, r0);
+        if (r1 >= s1) break;
+        r0 = r1 + DW * R;
+        issue(ka, va, r0);
+        consume(kb, vb, r1);
+        if (r0 >= s1) break;
+      }
+    } else {
+      for (;;) {
+        const int r1 = r0 + DW * R, r2 = r1 + DW * R;
+        if (r1 >= s1) { consume(ka, va, r0); break; }
+        issue(kb, vb, r1);
+        consume(ka, va, r0);
+        if (r2 >= s1) { consume(kb, vb, r1); break; }
+        issue(ka, va, r2);
+        consume(kb, vb, r1);
+        r0 = r2;
+      }
     }
   }
   // merge the row groups of a wave (they share the reference maximum), then the waves, per query head
