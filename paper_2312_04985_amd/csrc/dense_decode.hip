@@ -51,15 +51,18 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   __shared__ float4 red[DT];
   __shared__ int ticket;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = a.H / a.H_kv, gpk = g / G;       // query-head bundles per KV head
-  // Workgroups are dealt round-robin to the 8 XCDs: the unit varies fastest, so that every XCD gets its share of the
-  // splits at the ends of the sequences, which a ragged batch leaves empty.
-  const int units = a.B * a.H_kv * gpk, split = blockIdx.x / units;
-  int x = blockIdx.x - split * units;
-  const int unit = x;                            // (sequence, KV head, bundle)
-  const int bundle = x % gpk; x /= gpk;
-  const int hk = x % a.H_kv, b = x / a.H_kv;
-  const int h0 = hk * g + bundle * G;            // first query head served here
+  const int g = a.H / a.H_kv, gpk = dense_bundles(g, DH), per = (g + gpk - 1) / gpk;   // bundles per KV head, heads of a bundle
+  // Workgroups are dealt round-robin to the 8 XCDs: the KV head varies fastest and the split slowest, so that every XCD gets
+  // its share of the splits at the ends of the sequences, which a ragged batch leaves empty; the bundles of a KV head, which
+  // read the same rows, are 8 apart and share an XCD's L2.
+  const int heads = a.B * a.H_kv, pairs = heads * a.n_split;      // pairs: (KV head, split)
+  const int chunk = blockIdx.x / (8 * gpk), in_chunk = blockIdx.x - chunk * 8 * gpk;   // 8 pairs, or what is left of them
+  const int width = pairs - chunk * 8 < 8 ? pairs - chunk * 8 : 8, bundle = in_chunk / width;
+  const int pair = chunk * 8 + in_chunk - bundle * width, split = pair / heads, head = pair - split * heads;
+  const int unit = head * gpk + bundle;          // (sequence, KV head, bundle)
+  const int hk = head % a.H_kv, b = head / a.H_kv;
+  const int h0 = hk * g + bundle * per;          // first query head served here
+  const int n_heads = g - bundle * per < per ? g - bundle * per : per;   // <= G; the others repeat the last one
   int S = a.seq_lens[b];
   S = S < 0 ? 0 : (S > a.S_max ? a.S_max : S);
   const int s0 = split * a.rows_per_split;
@@ -67,7 +70,7 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   uint16_t* out = reinterpret_cast<uint16_t*>(a.out) + ((size_t)b * a.H + h0) * DH;
   if (s0 >= S) {                                 // nothing of this sequence here; an empty sequence: zeros
     if (S == 0 && split == 0)
-      for (int i = tid; i < G * DH; i += DT) out[i] = 0;
+      for (int i = tid; i < n_heads * DH; i += DT) out[i] = 0;
     return;
   }
   const int n_live = (S + a.rows_per_split - 1) / a.rows_per_split;   // workgroups of this unit that have rows
@@ -79,7 +82,8 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   // part of K, and dense_plan's smallest such product is 128.
   const char* K_run = reinterpret_cast<const char*>(a.K) + (kv_head * a.S_stride + s0) * (size_t)(DH * 2);
   const char* V_run = reinterpret_cast<const char*>(a.V) + (kv_head * a.S_stride + s0) * (size_t)(DH * 2);
-  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)b * a.H + h0 + row16 % G) * DH + quarter * 8;
+  const int q_row = row16 % G < n_heads ? row16 % G : n_heads - 1;
+  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)b * a.H + h0 + q_row) * DH + quarter * 8;
   uint4 qf[KK];                                  // row (lane % 16) % G of the query, channels 32 kk + 8 quarter ..
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const uint4*>(qp + kk * 32);
@@ -215,11 +219,13 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
   constexpr int SLOTS = G * DH / 4, GRPS = DT / SLOTS;
   static_assert(GRPS >= 1, "a slot of 4 channels per thread");
   const int slot = tid % SLOTS, grp = tid / SLOTS, t_s = slot / (DH / 4), c_s = slot % (DH / 4) * 4;
+  const int slots = n_heads * (DH / 4);          // the slots of real heads come first
   float4 y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   float m_all = -INFINITY, l_all = 0.0f;
-  const float* y_parts = a.partials + (size_t)unit * a.n_split * (G * DH);                  // [n_split][G][DH]
-  float* s_parts = a.partials + (size_t)units * a.n_split * (G * DH) + (size_t)unit * a.n_split * (G * 2);   // [n_split][G][2]
-  if (grp == 0) {
+  const size_t first = ((size_t)b * a.H + h0) * a.n_split;
+  const float* y_parts = a.partials + first * DH;                                           // [n_split][n_heads][DH]
+  float* s_parts = a.partials + (size_t)a.B * a.H * a.n_split * DH + first * 2;             // [n_split][n_heads][2]
+  if (grp == 0 && slot < slots) {
 #pragma unroll
     for (int w = 0; w < DW; ++w) m_all = fmaxf(m_all, part[w][t_s][DH]);
 #pragma unroll
@@ -233,8 +239,8 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
       if (!(l_all > 0.0f)) { y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f); l_all = 1.0f; }
       store_out4<T>(out + slot * 4, y4, 1.0f / l_all);
     } else {
-      store_agent4(y_parts, (uint32_t)(split * SLOTS + slot) * 16, y4);
-      if (c_s == 0) { store_agent(s_parts + (split * G + t_s) * 2, m_all); store_agent(s_parts + (split * G + t_s) * 2 + 1, l_all); }
+      store_agent4(y_parts, (uint32_t)(split * slots + slot) * 16, y4);
+      if (c_s == 0) { store_agent(s_parts + (split * n_heads + t_s) * 2, m_all); store_agent(s_parts + (split * n_heads + t_s) * 2 + 1, l_all); }
     }
   }
   if (n_live == 1) return;
@@ -246,26 +252,26 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
 #pragma unroll
     for (int j = 0; j < FLY; ++j) {
       const int s = s0 + j * GRPS;
-      v[j] = load_agent4(y_parts, (uint32_t)((s < n_live ? s : 0) * SLOTS + slot) * 16);
+      v[j] = load_agent4(y_parts, (uint32_t)((s < n_live ? s : 0) * slots + (slot < slots ? slot : 0)) * 16);
     }
   };
   fetch(grp);
-  for (int i = tid; i < n_live * G; i += DT) { stat[i * 2] = load_agent(s_parts + i * 2); stat[i * 2 + 1] = load_agent(s_parts + i * 2 + 1); }
+  for (int i = tid; i < n_live * n_heads; i += DT) { stat[i * 2] = load_agent(s_parts + i * 2); stat[i * 2 + 1] = load_agent(s_parts + i * 2 + 1); }
   __syncthreads();
-  for (int t = wave; t < G; t += DW) {           // two partials per lane: their weights, with the denominator in them
+  for (int t = wave; t < n_heads; t += DW) {           // two partials per lane: their weights, with the denominator in them
     float m[2], l[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int p = (lane + j * kWave) * G + t;
+      const int p = (lane + j * kWave) * n_heads + t;
       const bool on = lane + j * kWave < n_live;
       m[j] = on ? stat[p * 2] : -INFINITY; l[j] = on ? stat[p * 2 + 1] : 0.0f;
     }
     const float m_max = wave_max(fmaxf(m[0], m[1]));
     const float w0 = weight_exp2(m[0], m_max), w1 = weight_exp2(m[1], m_max);
     const float l_sum = wave_sum(l[0] * w0 + l[1] * w1);
-    if (lane < n_live) stat[(lane * G + t) * 2] = w0 / l_sum;
+    if (lane < n_live) stat[(lane * n_heads + t) * 2] = w0 / l_sum;
     if (lane == 0) stat[t * 2 + 1] = l_sum;
-    if (lane + kWave < n_live) stat[((lane + kWave) * G + t) * 2] = w1 / l_sum;
+    if (lane + kWave < n_live) stat[((lane + kWave) * n_heads + t) * 2] = w1 / l_sum;
   }
   __syncthreads();
   y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
 #pragma unroll
     for (int j = 0; j < FLY; ++j) {
       const int s = s0 + j * GRPS;
-      const float w = s < n_live ? stat[(s * G + t_s) * 2] : 0.0f;
+      const float w = s < n_live ? stat[(s * n_heads + t_s) * 2] : 0.0f;
       if (s < n_live) { y4.x += v[j].x * w; y4.y += v[j].y * w; y4.z += v[j].z * w; y4.w += v[j].w * w; }
     }
     s0 += FLY * GRPS;
@@ -292,19 +298,19 @@ __global__ __launch_bounds__(DT, 2) void dense_partial(const DenseArgs a) {
     }
   }
   if (!(stat[t_s * 2 + 1] > 0.0f)) y4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  if (grp == 0) store_out4<T>(out + slot * 4, y4, 1.0f);
+  if (grp == 0 && slot < slots) store_out4<T>(out + slot * 4, y4, 1.0f);
 }
 
 template <class T, int DH, int G>
 hipError_t launch_g(const DenseArgs& a, hipStream_t s) {
-  const int blocks = a.B * a.H_kv * (a.H / a.H_kv / G) * a.n_split;
+  const int blocks = a.B * a.H_kv * dense_bundles(a.H / a.H_kv, DH) * a.n_split;
   hipLaunchKernelGGL((dense_partial<T, DH, G>), dim3(blocks), dim3(DT), 0, s, a);
   return hipGetLastError();
 }
 
 template <class T, int DH>
 hipError_t launch_dh(const DenseArgs& a, hipStream_t s) {
-  switch (dense_bundle(a.H / a.H_kv, DH)) {
+  switch (dense_width(a.H / a.H_kv, DH)) {
     case 8:
       if constexpr (DH <= 128) return launch_g<T, DH, 8>(a, s);
       return hipErrorInvalidValue;

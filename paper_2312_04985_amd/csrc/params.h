@@ -55,8 +55,8 @@ struct AppendArgs {
 
 struct DenseArgs {
   const void* K; const void* V; const int32_t* seq_lens; const void* q; void* out;
-  float* partials;   // [unit][n_split][heads of the bundle][d_h] numerators, then [unit][n_split][heads][2] (max,
-                     // denominator); a unit is a (sequence, KV head, bundle of query heads)
+  float* partials;   // [unit][n_split][heads of the bundle][d_h] numerators, then [unit][n_split][heads of the bundle][2]
+                     // (max, denominator); a unit is a (sequence, KV head, bundle of query heads)
   int32_t* tickets;  // one counter per (sequence, KV head, bundle), 0 between launches; used where n_split > 1
   int32_t* err;
   int32_t B, H, H_kv, S_max, d_h, n_split, rows_per_split;
@@ -161,9 +161,14 @@ hipError_t launch_decode_shared(const DecodeArgs& a, float* z_ws, int dtype, hip
 size_t append_scratch_bytes(int64_t heads, int S_max, int d_h);
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t s);
 constexpr int kDenseSplits = 128;   // most workgroups one unit of dense_decode is split over (two per lane in the merge)
-// bundles of query heads that share a pass over their KV head's rows, for g query heads per KV head
-constexpr int dense_bundle(int g, int d_h) { return g % 8 == 0 && d_h <= 128 ? 8 : (g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1)); }
-constexpr int dense_bundles(int g, int d_h) { return g / dense_bundle(g, d_h); }
+// Query heads that share a pass over their KV head's rows, for g query heads per KV head: the kernel's width (up to 8; 4 at
+// d_h 256, by registers), and the bundles of at most that many.  A group that is no multiple of 4 is not cut into bundles of
+// 2 or 1, which would each read all rows again: the width's last heads repeat the bundle's last one (64 KV heads of 5000
+// rows, d_h 128: 3 heads 65 us as three bundles, 32 as one of width 4; 6 heads 66 and 34).
+constexpr int dense_width(int g, int d_h) {
+  return g <= 2 ? g : (g % 8 == 0 && d_h <= 128 ? 8 : (g % 4 == 0 || g == 3 || d_h > 128 ? 4 : 8));
+}
+constexpr int dense_bundles(int g, int d_h) { return (g + dense_width(g, d_h) - 1) / dense_width(g, d_h); }
 hipError_t launch_dense(const DenseArgs& a, int dtype, hipStream_t s);
 hipError_t launch_copy_probe(void* dst, const void* src, size_t n_bytes, hipStream_t s);
 hipError_t launch_read_probe(const void* src, size_t n_bytes, void* sink, hipStream_t s);

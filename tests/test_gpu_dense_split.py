@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d_h,g,dtype", [(64, 8, "f16"), (64, 1, "bf16"), (128, 8, "bf16"), (128, 4, "f16"), (128, 3, "bf16"),
-                                         (256, 8, "bf16"), (256, 4, "f16"), (256, 2, "bf16")])
+                                         (256, 8, "bf16"), (256, 4, "f16"), (256, 2, "bf16"),
+                                         # bundles that are not full: one of 6 or 7, 5 + 5, 6 + 5, two of 3, 3 + 2
+                                         (128, 6, "f16"), (64, 7, "bf16"), (128, 10, "bf16"), (64, 11, "f16"), (256, 6, "f16"), (256, 5, "bf16")])
 @pytest.mark.parametrize("b,h_kv,lens", [
     (4, 1, (1, 15, 16, 17)),                # below and above one tile of 16 rows
     (4, 2, (0, 255, 256, 321)),             # an empty sequence; one split, one row into the next
