@@ -52,15 +52,23 @@ void dense_split(const sparq_shape* s, int64_t units, int64_t target, int64_t mo
   *n_split = (s->S_max + rows - 1) / rows;
 }
 
-// Split-sequence plan of dense_decode.  Two workgroups fit on a CU, so 1024 are two rounds of the chip: lengths that
-// differ are evened out and the merges stay short.  Measured us at 256 / 512 / 1024 / 2048 workgroups: 512 units of 4096
-// rows 155 / 155 / 159 / 161; 60 units, 8 heads each, 8192 rows 64 / 54 / 54 / 60; 128 and 264 units with lengths over
-// 16x 252 / 256 / 199 / 190 and 143 / 140 / 110 / 100, hence 2048 where the caller says that lengths differ.  Few units
-// would be merged from very many partial results: 8 units of 32 768 rows 28.5 us from 31 each, 31.6 from 57; fewer
-// units need that many to fill the chip (one unit of 40 000 rows, 8 heads: 43 us from 64 each, 36 from 126).
+// Split-sequence plan of dense_decode.  Two workgroups fit on a CU.  Lengths that differ are evened out by 2048 of them, where
+// the caller says that they do (128 and 264 units of up to 8192 rows with lengths over 16x at 256 / 512 / 1024 / 2048 workgroups:
+// 252 / 256 / 199 / 190 and 143 / 140 / 110 / 100 us).  Otherwise 1024 are two rounds of the chip, but a workgroup has a start
+// and a merge to pay, so runs keep to 64 Ki elements of K at least, if need be with 512 or 256 workgroups (256 / 512 / 1024,
+// one query head: 64 units of 5000 rows of 64 16.9 / 16.9 / 19.8, 128 of 2500 16.5 / 16.8 / 19.0, 64 of 2500 of 128 16.9 /
+// 17.0 / 19.2, 128 of 2500 28.5 / 29.0 / 30.3; long runs the other way: 512 of 4096 of 128 155 / 155 / 159, lengths that
+// differ without the flag, 128 of up to 16 000, 142 / 133 / 121).  Few units would be merged from very many partial results:
+// 8 units of 32 768 rows 28.5 us from 31 each, 31.6 from 57; fewer units need that many to fill the chip (one unit of
+// 40 000 rows, 8 heads: 43 us from 64 each, 36 from 126).
 void dense_plan(const sparq_shape* s, int* n_split, int* rows_per_split) {
   const int64_t units = (int64_t)s->B * s->H_kv * dense_bundles(s->H / s->H_kv, s->d_h);
-  dense_split(s, units, (s->flags & SPARQ_FLAG_RAGGED_BATCH) ? 2048 : 1024, units >= 8 ? 32 : (units >= 3 ? 64 : kDenseSplits), n_split, rows_per_split);
+  const int64_t most = units >= 8 ? 32 : (units >= 3 ? 64 : kDenseSplits);
+  const bool ragged = (s->flags & SPARQ_FLAG_RAGGED_BATCH) != 0;
+  for (int target = ragged ? 2048 : 1024; target >= 256; target >>= 1) {
+    dense_split(s, units, target, most, n_split, rows_per_split);
+    if ((int64_t)*rows_per_split * s->d_h >= (ragged ? 32768 : 65536)) break;
+  }
 }
 
 // Partial results that the workspace has room for, per (sequence, KV head): what 2048 workgroups would leave.
