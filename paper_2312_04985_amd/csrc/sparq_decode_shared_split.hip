@@ -28,12 +28,14 @@ __device__ __forceinline__ void map_kv(int Ukv, int n, int& ukv, int& s) {
   }
 }
 
-// Thread groups that share the chunks of a gs_logits span (see there): 4 or 2 when the span has at most half as many
-// chunks more than a group has threads and there are that many batches of 8 channel rows, else 1.  (A few threads' second
-// chunk costs less than idle groups: with the four-position finish below 16.1 -> 12.5 us for 136 chunks of 32 rows.)  Host
-// and device agree through this.
+// Thread groups that share the chunks of a gs_logits span (see there): 4 when a group has a thread per chunk and there are
+// that many batches of 8 channel rows, 2 for spans of up to half as many chunks more with 8 batches, else 1: a second chunk
+// for some threads costs more than the batches in flight give.  Whole decode us by 1 / 2 / 4 groups, 32 heads on 8: 128
+// chunks 32 channels 34.4 / 34.2 / 33.6, 64 channels 38.9 / 37.9 / 36.3; 136 chunks 16 channels 33.2 / 34.3 / -, 32 channels
+// 35.7 / 35.8 / 38.5, 64 channels 39.1 / 38.3 / 39.8; 192 chunks 36.1 / 36.6 / 37.5 and 40.5 / 40.0 / 41.3; 256 chunks 38.2 /
+// 39.1 / - and 43.5 / 44.6 / -; 264 chunks 41.7 / 43.5 / -.  Host and device agree through this.
 __host__ __device__ constexpr int logit_row_groups(int span1, int n_batches) {
-  return (span1 <= NT / 4 * 8 * 3 / 2 && n_batches >= 4) ? 4 : ((span1 <= NT / 2 * 8 * 3 / 2 && n_batches >= 2) ? 2 : 1);
+  return span1 <= NT / 4 * 8 && n_batches >= 4 ? 4 : (span1 <= NT / 4 * 8 * 3 / 2 && n_batches >= 8 ? 2 : 1);
 }
 
 template <class T, int DH, int G>
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
   if (F > 1) {
     // Fewer chunks than threads: F groups of NT / F threads share every chunk, each taking 1 / F of the batches of 8
     // channel rows, so that a thread's loads are in flight together instead of going through the pipeline one
-    // batch after the other.  The groups' partial sums meet in LDS and the first group finishes the chunks.
+    // batch after the other.  The groups' partial sums meet in LDS and all threads finish the chunks.
     extern __shared__ __align__(16) float pacc[];                 // [F][G][span1]
     const int P = a.span1;
     if (F == 4) {
@@ -498,7 +500,7 @@ template <class T, int DH, int G>
 hipError_t launch_logits(const GsArgs& a, hipStream_t s) {
   const int F = logit_row_groups(a.span1, (a.d.r + 7) >> 3);
   const size_t lds = F > 1 ? (size_t)F * G * a.span1 * sizeof(float) : 0;
-  hipError_t e = allow_lds<gs_logits<T, DH, G>>(lds + 16 * 1024, 128 * 1024);   // at most 96 KiB dynamic on top of the static arrays
+  hipError_t e = allow_lds<gs_logits<T, DH, G>>(lds + 16 * 1024, 128 * 1024);   // at most 64 KiB dynamic on top of the static arrays
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gs_logits<T, DH, G>), dim3(a.d.B * a.d.H_kv * a.n1), dim3(NT), lds, s, a);
   return hipGetLastError();
