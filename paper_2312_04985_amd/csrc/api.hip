@@ -225,10 +225,10 @@ PlanInfo choose_plan(const sparq_shape* s) {
     if (one_wg) p.plan = kPlanShared;
     return p;
   }
-  // Few units with long caches: the digit-bucket plan, where it was measured faster than one workgroup per unit
-  // (H = 32, r = 32, k = S / 16, bucket / one-workgroup us per decode; S = 8192: 29/27, 32/29, 36/31, 41/32 at 32, 64,
-  // 96, 128 units; 12 288: 30/37, 36/39, 43/43, 49/43; 16 384: 33/46, 41/51, 49/55, 59/59; 24 576: 36/65, 48/70,
-  // 63/77, 95/79; 32 768: 41/82, 59/89, 94/98, 116/103), and whatever one workgroup's LDS cannot hold.
+  // Few units with long caches: the digit-bucket plan, where it was measured faster than one workgroup per unit, or as
+  // fast (H = 32, r = 32, k = S / 16, bucket / one-workgroup us per decode at 32, 64, 96, 128 units; S = 4096: 20/16, 21/17,
+  // 23/18, 25/18; 8192: 22/24, 25/25, 29/26, 34/28; 12 288: 24/32, 29/34, 36/35, 41/37; 16 384: 26/40, 33/42, 43/44, 52/46;
+  // 24 576: 30/56, 41/59, 57/62, 83/65; 32 768: 34/74, 51/77, 86/82, 102/88), and whatever one workgroup's LDS cannot hold.
   const int64_t units = (int64_t)s->B * s->H;
   const bool one_wg_fits = decode_lds_bytes(s->S_max, s->d_h) <= lds_max;
   const bool bucket_faster = (s->S_max >= 16384 && units <= 96) || (s->S_max >= 12288 && units <= 64);
