@@ -362,10 +362,11 @@ enum class Sums {
 // Ends with a barrier that also publishes the list.  Returns alpha; sums_out[0..1] receive the denominator and the
 // numerator.
 // kOwnWords: bit masks of each kind per lane, for up to 32 NT kOwnWords positions.
-template <Sums SUMS, int kOwnWords>
+// found() is called when the threshold is known (a time stamp of a profiling build).
+template <Sums SUMS, int kOwnWords, class Found>
 __device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
                                                 float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
-                                                int wave, uint32_t* key_out, int pos_base, float* sums_out) {
+                                                int wave, uint32_t* key_out, int pos_base, float* sums_out, Found&& found) {
   // first digit of the threshold
   uint32_t first = 0xffffffffu, last = 0xffffffffu;       // keys that share the decided bits lie in first .. last
   int need = k_old, in_bin = k_old;
@@ -444,6 +445,7 @@ __device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint
       if (d > digit) gt[w] |= bit;
     });
   }
+  found();
   float asum = 0.0f, esum = 0.0f;
   if (SUMS != Sums::kNone) {
     each(gt, [&](int, uint32_t, int at) { asum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
@@ -489,16 +491,21 @@ __device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint
   return alpha > 1.0f || (k_old == S_old && alpha == alpha) ? 1.0f : alpha;
 }
 
-template <Sums SUMS>
+struct NoStamp {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+template <Sums SUMS, class Found = NoStamp>
 __device__ __forceinline__ float select_compact(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
                                                 float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
-                                                int wave, uint32_t* key_out = nullptr, int pos_base = 0, float* sums_out = nullptr) {
+                                                int wave, uint32_t* key_out = nullptr, int pos_base = 0, float* sums_out = nullptr,
+                                                Found&& found = Found{}) {
   // (one mask per lane as a case of its own: straight code without the loops over masks, 0.4 us of a call of 11 us)
   if (S <= 32 * NT)
     return select_compact_words<SUMS, 1>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
-                                         pos_base, sums_out);
+                                         pos_base, sums_out, found);
   return select_compact_words<SUMS, 3>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
-                                       pos_base, sums_out);      // LDS ends at about 40 000 keys
+                                       pos_base, sums_out, found);      // LDS ends at about 40 000 keys
 }
 
 // A thread's share of the softmax denominator, summed while the logit numerators are produced: relative to the

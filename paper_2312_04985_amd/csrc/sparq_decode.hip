@@ -200,9 +200,9 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, L.sel.red[w]);
 
   // ---------------- stage 2 ----------------
-  SPARQ_STAMP(4);
   const float alpha = select_compact<Sums::kNumerator>(L.keys, L.keys, S, win.S_old, win.k_old, dmax, esc, zs.relative_to(dmax, esc),
-                                                       idx_out, a.idx_stride, L.sel, tid, lane, wave);
+                                                       idx_out, a.idx_stride, L.sel, tid, lane, wave, nullptr, 0, nullptr,
+                                                       [&]() { SPARQ_STAMP(4); });
   SPARQ_STAMP(5);
   if (tid == 0) {
     if (a.alpha_out) a.alpha_out[u] = alpha;
