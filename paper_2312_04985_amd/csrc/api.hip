@@ -262,7 +262,7 @@ GsLayout gs_layout(const sparq_shape* s, const PlanInfo& p) {
   return l;
 }
 
-struct BucketLayout { size_t tmax, zsum, anum, tau, coarse, fine, skey, spos, part, z, stat, esc, end; };
+struct BucketLayout { size_t tmax, zsum, anum, tau, zden, coarse, fine, skey, spos, part, z, stat, esc, end; };
 
 BucketLayout bucket_layout(const sparq_shape* s, const PlanInfo& p) {
   const size_t units = (size_t)s->B * s->H, slots = units * p.n_span;
@@ -272,6 +272,7 @@ BucketLayout bucket_layout(const sparq_shape* s, const PlanInfo& p) {
   l.zsum = off; off = align256(off + slots * sizeof(float));
   l.anum = off; off = align256(off + slots * sizeof(float));
   l.tau = off; off = align256(off + units * sizeof(float));
+  l.zden = off; off = align256(off + units * sizeof(float));
   l.coarse = off; off = align256(off + slots * 64 * sizeof(uint16_t));
   l.fine = off; off = align256(off + slots * bk_fine_len() * sizeof(uint16_t));
   l.skey = off; off = align256(off + slots * p.span_len * sizeof(uint32_t));
@@ -381,6 +382,11 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     ba.zsum_ws = reinterpret_cast<float*>(w + l.zsum);
     ba.anum_ws = reinterpret_cast<float*>(w + l.anum);
     ba.tau_ws = reinterpret_cast<float*>(w + l.tau);
+    ba.zden_ws = reinterpret_cast<float*>(w + l.zden);
+    // Up to 512 workgroups run at once (two per CU) and the unit's last one merges.  With more, each would hold its place for
+    // the two round trips of its arrival while others wait (100 units of 60 000 positions, 800 workgroups: 147.8 us per
+    // decode against 144.4 with a launch for the merges, 100 000 positions 209.2 / 203.3; 64 units of 60 000, 512: equal).
+    ba.merge = (int64_t)d.B * d.H * p.n_span <= 512;
     ba.tickets = reinterpret_cast<int32_t*>(w + kTicketOffset);
     ba.coarse_ws = reinterpret_cast<uint16_t*>(w + l.coarse);
     ba.fine_ws = reinterpret_cast<uint16_t*>(w + l.fine);

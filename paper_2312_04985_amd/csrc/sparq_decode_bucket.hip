@@ -18,6 +18,7 @@
 //               attention partial per span; the workgroup that finishes last of a unit's spans merges the partials, and
 //               blends and stores (a launch of its own for that took 4.8 us and its start: 32 heads on 8 KV heads at 32 768
 //               positions 34.8 -> 33.5 us per step, one head 27.2 -> 24.1)
+//   bk_combine  (one workgroup per unit) that last part, where there are more workgroups than run at once
 // Every workgroup attends over the selected rows of its own span: the gather is balanced when the selected
 // positions are spread over the sequence, and takes as long as the busiest span when they are not.
 // The local window is part of it: its positions count as bucket 2047, above every key's.
@@ -384,6 +385,77 @@ __host__ __device__ constexpr size_t bk_select_words(int span_len, int n_span, i
          5 * (kMaxSpans + 8) + NW * (DH + 2) + 32 + 16 + 16;
 }
 
+// What the end of a unit needs of the caller's inputs, for channel c.
+struct UnitInputs {
+  float mean = 0.0f;
+  uint16_t k = 0, v = 0;
+};
+__device__ __forceinline__ UnitInputs unit_inputs(const DecodeArgs& d, size_t kv_head, bool on, bool appended, int c, int d_h) {
+  UnitInputs in;
+  if (on) {
+    in.mean = d.v_mean[kv_head * d_h + c];
+    if (appended) {
+      in.v = reinterpret_cast<const uint16_t*>(d.v_new)[kv_head * d_h + c];
+      in.k = reinterpret_cast<const uint16_t*>(d.k_new)[kv_head * d_h + c];
+    }
+  }
+  return in;
+}
+
+// The end of a unit, by DH threads (thread c: channel c): merge the spans' partials, alpha from the spans' numerators, blend
+// with the mean value vector (Eq. 10), round and store, append.
+template <class T, int DH>
+__device__ __forceinline__ void finish_unit(const BucketArgs& a, int u, size_t kv_head, int S, bool appended, bool owner, int n_live,
+                                            float zden, int c, int lane, const UnitInputs& in) {
+  const DecodeArgs& d = a.d;
+  const float* parts = a.part_ws + (size_t)u * a.n_span * (DH + 2);
+  const float num_part = lane < n_live ? load_agent(a.anum_ws + (size_t)u * a.n_span + lane) : 0.0f;
+  float m_all = -INFINITY, l_all = 0.0f, y3 = 0.0f;
+  for (int w0 = 0; w0 < n_live; w0 += 16) {            // sixteen partials of this channel in flight at a time
+    float pm[16], pl[16], py[16];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const bool on = w0 + w < n_live;
+      const float* p = parts + (on ? w0 + w : 0) * (DH + 2);
+      pm[w] = load_agent(p + DH); pl[w] = load_agent(p + DH + 1); py[w] = load_agent(p + c);
+      if (!on) { pm[w] = -INFINITY; pl[w] = 0.0f; py[w] = 0.0f; }
+    }
+    float m_new = m_all;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) m_new = fmaxf(m_new, pm[w]);
+    const float sc = weight_exp2(m_all, m_new);
+    l_all *= sc; y3 *= sc;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const float sw = weight_exp2(pm[w], m_new);
+      l_all += pl[w] * sw;
+      y3 += py[w] * sw;
+    }
+    m_all = m_new;
+  }
+  y3 /= l_all;
+  const float alpha = wave_sum(num_part) / zden;       // fixed order
+  if (c == 0 && d.alpha_out) d.alpha_out[u] = alpha;
+  float vm = in.mean;
+  if (appended) {                          // the mean with the new row: what the blend uses and the owner stores
+    if (S == 1) vm = 0.0f;
+    vm += (T::widen(in.v) - vm) * (1.0f / (float)S);
+  }
+  float y = y3;
+  if (!(d.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * vm;
+  reinterpret_cast<uint16_t*>(d.out)[(size_t)u * DH + c] = T::narrow(y);
+  if (owner) {
+    d.v_mean_next[kv_head * DH + c] = vm;
+    if (appended) {
+      uint16_t* K_rows = reinterpret_cast<uint16_t*>(d.K) + kv_head * d.S_stride * (size_t)DH;
+      reinterpret_cast<uint16_t*>(d.V)[(kv_head * d.S_stride + (S - 1)) * DH + c] = in.v;
+      K_rows[(size_t)(S - 1) * DH + c] = in.k;
+      if ((S & 7) == 0)
+        flush_key_columns(reinterpret_cast<uint16_t*>(d.Kt) + kv_head * DH * (size_t)d.S_stride, K_rows, d.S_stride, DH, S, c, in.k);
+    }
+  }
+}
+
 // GROUP = true is the grouped-query rule: the tables and sorted arrays are the KV unit's (one selection for the
 // group's query heads, written by bk_group_scores), the statistics and alpha are the head's own, from the logits
 // gs_logits left in the workspace.
@@ -490,6 +562,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   __syncthreads();
   const int lc = ctl[0];
   const float gmax = red[30], zden = red[31];
+  if (!a.merge && s == 0 && tid == 0) a.zden_ws[u] = zden;
   for (int i = tid; i < a.n_span * 33; i += NT) {
     const int t = i / 33, j = i - t * 33;
     tabF[i] = a.fine_ws[(slot0 + t) * kFineLen + lc * 32 + j];
@@ -717,65 +790,25 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
     if (tid == 0) { store_agent(my_part + DH, m_all); store_agent(my_part + DH + 1, l_all); }
   }
 
-  // ---- the unit's last workgroup: merge the spans' partials, alpha from the spans' numerators, blend with the mean
-  // value vector (Eq. 10), round and store, append ----
-  float vm = 0.0f;
-  uint16_t vcode = 0, kc = 0;
-  if (tid < DH) {                          // requested while the partial is on its way
-    vm = d.v_mean[kv_head * DH + tid];
-    if (appended) {
-      vcode = reinterpret_cast<const uint16_t*>(d.v_new)[kv_head * DH + tid];
-      kc = reinterpret_cast<const uint16_t*>(d.k_new)[kv_head * DH + tid];
-    }
-  }
+  if (!a.merge) return;                    // bk_combine does the rest
+  // ---- the unit's last workgroup: merge the spans' partials, blend, store, append ----
+  const UnitInputs in = unit_inputs(d, kv_head, tid < DH, appended, tid, DH);   // requested while the partial is on its way
   if (!last_to_arrive(a.tickets + u, n_live, ctl + 15)) return;
-  if (tid >= DH) return;
-  const int c = tid;
-  const float* parts = a.part_ws + (size_t)u * a.n_span * (DH + 2);
-  const float num_part = lane < n_live ? load_agent(a.anum_ws + (size_t)u * a.n_span + lane) : 0.0f;
-  float m_all = -INFINITY, l_all = 0.0f, y3 = 0.0f;
-  for (int w0 = 0; w0 < n_live; w0 += 16) {            // sixteen partials of this channel in flight at a time
-    float pm[16], pl[16], py[16];
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      const bool on = w0 + w < n_live;
-      const float* p = parts + (on ? w0 + w : 0) * (DH + 2);
-      pm[w] = load_agent(p + DH); pl[w] = load_agent(p + DH + 1); py[w] = load_agent(p + c);
-      if (!on) { pm[w] = -INFINITY; pl[w] = 0.0f; py[w] = 0.0f; }
-    }
-    float m_new = m_all;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) m_new = fmaxf(m_new, pm[w]);
-    const float sc = weight_exp2(m_all, m_new);
-    l_all *= sc; y3 *= sc;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      const float sw = weight_exp2(pm[w], m_new);
-      l_all += pl[w] * sw;
-      y3 += py[w] * sw;
-    }
-    m_all = m_new;
-  }
-  y3 /= l_all;
-  const float alpha = wave_sum(num_part) / zden;       // fixed order
-  if (c == 0 && d.alpha_out) d.alpha_out[u] = alpha;
-  if (appended) {                          // the mean with the new row: what the blend uses and the owner stores
-    if (S == 1) vm = 0.0f;
-    vm += (T::widen(vcode) - vm) * (1.0f / (float)S);
-  }
-  float y = y3;
-  if (!(d.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * vm;
-  reinterpret_cast<uint16_t*>(d.out)[(size_t)u * DH + c] = T::narrow(y);
-  if (owner) {
-    d.v_mean_next[kv_head * DH + c] = vm;
-    if (appended) {
-      uint16_t* K_rows = reinterpret_cast<uint16_t*>(d.K) + kv_head * d.S_stride * (size_t)DH;
-      reinterpret_cast<uint16_t*>(d.V)[(kv_head * d.S_stride + (S - 1)) * DH + c] = vcode;
-      K_rows[(size_t)(S - 1) * DH + c] = kc;
-      if ((S & 7) == 0)
-        flush_key_columns(reinterpret_cast<uint16_t*>(d.Kt) + kv_head * DH * (size_t)d.S_stride, K_rows, d.S_stride, DH, S, c, kc);
-    }
-  }
+  if (tid < DH) finish_unit<T, DH>(a, u, kv_head, S, appended, owner, n_live, zden, tid, lane, in);
+}
+
+// One workgroup per unit, where bk_select_gather does not merge.
+template <class T, int DH>
+__global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
+  const DecodeArgs& d = a.d;
+  const int u = blockIdx.x, b = u / d.H, h = u - b * d.H, g = d.H / d.H_kv, hk = h / g;
+  const size_t kv_head = (size_t)b * d.H_kv + hk;
+  bool appended, bad, full;
+  const int S = visible_length(d, b, appended, bad, full);
+  if (S == 0) return;                      // outputs written by the first launch, state by bk_select_gather
+  const UnitInputs in = unit_inputs(d, kv_head, true, appended, threadIdx.x, DH);
+  finish_unit<T, DH>(a, u, kv_head, S, appended, d.k_new && h == hk * g, (S + a.span_len - 1) / a.span_len, a.zden_ws[u], threadIdx.x,
+                     threadIdx.x & (kWave - 1), in);
 }
 
 template <class T, int DH>
@@ -788,6 +821,8 @@ hipError_t launch_bucket(const BucketArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((bk_scores<T, DH>), dim3(units * a.n_span), dim3(NT), lds1, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((bk_select_gather<T, DH, false>), dim3(units * a.n_span), dim3(NT), lds2, s, a);
+  if ((e = hipGetLastError()) != hipSuccess || a.merge) return e;
+  hipLaunchKernelGGL((bk_combine<T, DH>), dim3(units), dim3(DH), 0, s, a);
   return hipGetLastError();
 }
 
@@ -811,6 +846,8 @@ hipError_t launch_bucket_group(const BucketArgs& a, hipStream_t s) {
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((bk_select_gather<T, DH, true>), dim3(units * a.n_span), dim3(NT), lds2, s, a);
+  if ((e = hipGetLastError()) != hipSuccess || a.merge) return e;
+  hipLaunchKernelGGL((bk_combine<T, DH>), dim3(units), dim3(DH), 0, s, a);
   return hipGetLastError();
 }
 

@@ -38,6 +38,12 @@ def test_last_workgroup_of_a_unit(h, h_kv, group, s_max, lens, r):
     assert b.cache.workspace[256:16384].count_nonzero() == 0
 
 
+@pytest.mark.parametrize("group", [False, True])
+def test_units_merged_by_a_launch_of_their_own(group):
+    """120 units of 5 spans: more workgroups than run at once."""
+    test_last_workgroup_of_a_unit(40, 20, group, 40960, (40959, 2047, 20000), 20)
+
+
 @pytest.mark.parametrize("h,h_kv,flags", [(4, 2, 0), (4, 1, B.SPARQ_FLAG_GQA_SHARED), (4, 2, B.SPARQ_FLAG_GQA_SHARED)])
 def test_a_unit_is_counted_from_zero(h, h_kv, flags):
     """What an earlier call left in the counters (sparq_decode_noalloc's buffer cannot be initialised again) changes nothing."""
