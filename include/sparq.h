@@ -132,10 +132,11 @@ typedef struct {
 } sparq_cache;
 
 /* Bytes of device workspace the calls below need for this shape (>= 64 KiB; depends on every field of
- * the shape, flags included).  The first 64 KiB are a control block (word 0 is the error word) that
- * sparq_workspace_init zeroes and the calls use for counters of finished workgroups, which they leave at zero (a
- * workspace that two calls ran on at the same time has to be initialised again); the rest is scratch: the split-sequence partials of dense_decode, the partial sums of a
- * bulk sparq_kv_append (which runs in a smaller workspace too, on fewer workgroups), and for sparq_decode the
+ * the shape, flags included).  The first 64 KiB are a control block that sparq_workspace_init zeroes: word 0 is the
+ * error word, bytes 256 .. 16383 are counters of finished workgroups, which every call leaves at zero (after two calls that
+ * ran on one workspace at the same time it has to be initialised again), the rest serves a bulk sparq_kv_append.
+ * Behind it lies scratch: the split-sequence partials of dense_decode, the partial sums of a bulk
+ * sparq_kv_append (which runs in a smaller workspace too, on fewer workgroups), and for sparq_decode the
  * keys / candidates / position lists of the multi-launch plans (few heads with long caches, S_max beyond one
  * workgroup's LDS) or the logits of the grouped-query rule.  One workspace serves one stream. */
 int sparq_workspace_bytes(const sparq_shape* shape, size_t* out_bytes);
@@ -215,9 +216,9 @@ int sparq_decode_noalloc(const sparq_shape* shape, const sparq_cache* cache, con
 /*
  * The whole decode step in one call: exactly sparq_kv_append with n_new = 1 followed by
  * sparq_decode (Section 4: the step writes k and v, updates the mean value vector and attends
- * over the cache including the new token).  One launch where one workgroup serves a head; the
- * launches of the few-heads-long-cache plan and of the two-level plan with the append in the last one; for the other
- * plans the append kernel followed by the decode launches.  The small state is not updated in place:
+ * over the cache including the new token).  One launch where one workgroup serves a head
+ * or, under SPARQ_FLAG_GQA_SHARED, a KV head; the launches of the few-heads-long-cache plan and of the two-level plan
+ * with the append in the last one; for the other plans the append kernel followed by the decode launches.  The small state is not updated in place:
  * the new lengths and means are written to seq_lens_next [B] and v_mean_next [B, H_kv, d_h]
  * (device, must not alias cache->seq_lens / cache->v_mean, which are only read) and the caller
  * swaps the two pairs of buffers between steps.  K and V receive row S_b in place, Kt as in

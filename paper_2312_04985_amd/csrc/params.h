@@ -10,8 +10,8 @@ constexpr int kDecodeThreads = 512;     // threads per workgroup of the fused de
 constexpr int kRadixBins = 2048;        // 11-bit digits: passes of 11, 11 and 10 bits
 constexpr int kWorkspaceHeader = 256;   // bytes; word 0 is the error word
 constexpr int kControlBytes = 65536;    // control block at the start of the workspace, zeroed by sparq_workspace_init
-// Counters of workgroups that have finished (last_to_arrive), inside the control block behind the header: all 0 between
-// launches.  The rest of the control block is scratch of the bulk append.
+// Counters of workgroups that have finished (last_to_arrive), inside the control block behind the header: left at 0 by
+// every launch (the digit-bucket plans clear theirs as well).  The rest of the control block is scratch of the bulk append.
 constexpr int kTicketOffset = kWorkspaceHeader;
 constexpr int kTickets = (16384 - kWorkspaceHeader) / 4;
 constexpr int kAppendScratchOffset = 16384;
