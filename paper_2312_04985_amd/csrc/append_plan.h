@@ -10,7 +10,7 @@ constexpr int kAppendThreads = 256;
 constexpr int append_tile(int d_h) { return 8 * kAppendThreads / (d_h / 8); }
 
 // Workgroups per KV head of a bulk append of `tiles` tiles per head: about kAppendGroups in all (8 per CU; three of them
-// fit by LDS), at most 128 per head, so that append_finish reads few partial sums.
+// run at once, by registers), at most 128 per head, so that append_finish reads few partial sums.
 constexpr int64_t kAppendGroups = 2048;
 constexpr int64_t append_groups(int64_t heads, int64_t tiles) {
   const int64_t per = (tiles * heads + kAppendGroups - 1) / kAppendGroups, n = (tiles + per - 1) / per;
