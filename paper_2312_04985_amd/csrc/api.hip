@@ -326,7 +326,10 @@ int check_workspace(const sparq_shape* s, const void* ws, size_t bytes) {
 }
 
 // enqueue one decode over `a` with the plan the shape calls for
-hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* workspace, hipStream_t s) {
+hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void* workspace, hipStream_t s) {
+  DecodeArgs a = args;
+  a.group = a.H / a.H_kv;
+  a.by_H = make_divider(a.H); a.by_H_kv = make_divider(a.H_kv); a.by_group = make_divider(a.group);
   const PlanInfo p = choose_plan(shape);
   if (p.plan == kPlanNone) return hipErrorInvalidValue;
 #ifdef SPARQ_STAGE_CLOCKS
@@ -362,6 +365,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     ga.d = d;
     ga.n1 = p.n1; ga.span1 = p.span1; ga.n2 = p.n_span; ga.span2 = p.span_len; ga.cand_cap = p.cand_cap;
     ga.n_split = p.n_split; ga.list_stride = l.list_stride;
+    ga.by_n1 = make_divider(ga.n1); ga.by_n2 = make_divider(ga.n2); ga.by_split = make_divider(ga.n_split);
     ga.z_ws = reinterpret_cast<float*>(w + l.z);
     ga.stat_ws = reinterpret_cast<float*>(w + l.stat);
     ga.esc_ws = reinterpret_cast<float*>(w + l.esc);
@@ -378,6 +382,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     BucketArgs ba;
     ba.d = d;
     ba.n_span = p.n_span; ba.span_len = p.span_len; ba.cand_cap = p.cand_cap;
+    ba.by_span = make_divider(ba.n_span); ba.by_len = make_divider(ba.span_len);
     ba.tmax_ws = reinterpret_cast<float*>(w + l.tmax);
     ba.zsum_ws = reinterpret_cast<float*>(w + l.zsum);
     ba.anum_ws = reinterpret_cast<float*>(w + l.anum);
@@ -397,6 +402,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
       GsArgs ga{};
       ga.d = d;
       ga.n1 = p.n1; ga.span1 = p.span1;
+      ga.by_n1 = make_divider(ga.n1);
       ga.z_ws = reinterpret_cast<float*>(w + l.z);
       ga.stat_ws = reinterpret_cast<float*>(w + l.stat);
       ga.esc_ws = reinterpret_cast<float*>(w + l.esc);
@@ -413,6 +419,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& a, void* w
     LongArgs la;
     la.d = d;
     la.n_span = p.n_span; la.span_len = p.span_len; la.cand_cap = p.cand_cap;
+    la.by_span = make_divider(la.n_span);
     la.tmax_ws = reinterpret_cast<float*>(w + l.tmax);
     la.zsum_ws = reinterpret_cast<float*>(w + l.zsum);
     la.cnt_ws = reinterpret_cast<int32_t*>(w + l.cnt);

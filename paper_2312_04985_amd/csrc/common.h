@@ -63,12 +63,11 @@ __device__ __forceinline__ uint4 load16(const void* p) {
 // ---- order-preserving map fp32 -> uint32 (larger float <=> larger key; -0 == +0) ----
 // Every finite float maps to a key >= 0x00800000, so key 0 is below all of them.
 __device__ __forceinline__ uint32_t float_to_key(float x) {
-  uint32_t u = __float_as_uint(x);
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(x + 0.0f);          // (-0 becomes +0)
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 __device__ __forceinline__ float key_to_float(uint32_t k) {
-  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+  return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u));
 }
 
 // 2^x as the hardware's one instruction.  exp2f() wraps it in range scaling so that results below 2^-126 come
@@ -111,12 +110,33 @@ __device__ __forceinline__ float wave_max(float v) {
   v = group_max<16>(v);
   return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
 }
+// Lanes l and l ^ O (O = 8, 16, 32) as a pair: both get (a, b) = (value of the lower, value of the upper), so that what they
+// make of it is the same.  Rows and halves of a wave change places in one vector instruction, 8 lanes by DPP.
+template <int O>
+__device__ __forceinline__ void lane_pair(float v, float& a, float& b) {
+  const uint32_t u = __float_as_uint(v);
+  if (O == 8) {                          // row_ror:8
+    const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, 0x128, 0xf, 0xf, false);
+    const bool upper = (threadIdx.x & 8u) != 0;
+    a = __uint_as_float(upper ? w : u); b = __uint_as_float(upper ? u : w);
+  } else if (O == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+  }
+}
 // sum over aligned groups of LPR lanes (8, 16 or 32), same value in every lane of a group
 template <int LPR>
 __device__ __forceinline__ float lanes_sum(float v) {
   if (LPR == 8) return group_sum<8>(v);
   v = group_sum<16>(v);
-  if (LPR == 32) v += __shfl_xor(v, 16);
+  if (LPR == 32) {
+    float a, b;
+    lane_pair<16>(v, a, b);
+    v = a + b;
+  }
   return v;
 }
 // inclusive prefix sum across the 64 lanes with DPP row shifts and row broadcasts
@@ -180,7 +200,7 @@ __device__ __forceinline__ bool last_to_arrive(int* counter, int n, int* flag) {
 
 // exp2 that maps (-inf) - (-inf) situations to weight 0 instead of NaN
 __device__ __forceinline__ float weight_exp2(float m, float m_ref) {
-  return (m == -INFINITY) ? 0.0f : exp2f(m - m_ref);
+  return (m == -INFINITY) ? 0.0f : exp2_weight(m - m_ref);
 }
 
 }  // namespace sparq

@@ -8,6 +8,8 @@
 #include "common.h"
 #include "params.h"
 
+#include <type_traits>
+
 namespace sparq {
 
 constexpr int NT = kDecodeThreads;
@@ -17,26 +19,28 @@ constexpr int kTieHeavy = 2048;  // a radix bin with more keys than this is coun
 // ------------------------------------------------------------------------------------------------
 // small workgroup primitives
 
-// Histogram bins are stored swizzled so that the 32 consecutive digits a lane sums in
-// find_threshold_bin sit in 32 different rows of 64 words: lane-consecutive, conflict-free reads.
-__device__ __forceinline__ uint32_t hist_slot(uint32_t digit) { return ((digit & 31u) << 6) | (digit >> 5); }
+// Histogram bins are stored swizzled: the 32 consecutive digits that lane l sums in find_threshold_bin are row l of 32 words,
+// its eight 16-byte pieces permuted by xor, so that 16 neighbouring lanes reading the same piece of their rows touch all 64
+// banks once.
+__device__ __forceinline__ uint32_t hist_slot(uint32_t digit) { return digit ^ ((digit >> 4) & 28u); }
+// the 16 bytes of digits 32 lane + 4 piece .. + 3
+__device__ __forceinline__ uint32_t hist_piece(int lane, int piece) { return ((uint32_t)lane << 5) | (((uint32_t)piece << 2) ^ (((uint32_t)lane << 1) & 28u)); }
 
-// First-digit counts of M neighbouring keys: runs of equal digits (duplicated keys) are
-// added with one atomic.  n_valid = how many of the M keys count (the leading ones).
+// First-digit counts of M neighbouring keys.  Keys that all share the digit (duplicated keys: the atomics of 64 lanes meet in
+// one address) are added with one atomic.  n_valid = how many of the M keys count (the leading ones).
 template <int M>
 __device__ __forceinline__ void hist_add_chunk(uint32_t* hist, const uint32_t (&kx)[M], int n_valid) {
-  uint32_t run_d = kx[0] >> 21, run_n = n_valid > 0 ? 1u : 0u;
+  if (n_valid <= 0) return;
+  uint32_t differ = 0;
 #pragma unroll
-  for (int e = 1; e < M; ++e) {
-    const uint32_t d = kx[e] >> 21;
-    const uint32_t v = e < n_valid ? 1u : 0u;
-    if (d != run_d) {
-      if (run_n) atomicAdd(&hist[hist_slot(run_d)], run_n);
-      run_d = d; run_n = 0u;
-    }
-    run_n += v;
+  for (int e = 1; e < M; ++e) differ |= kx[e] ^ kx[0];
+  if (differ >> 21 == 0) {
+    atomicAdd(&hist[hist_slot(kx[0] >> 21)], (uint32_t)(n_valid < M ? n_valid : M));
+    return;
   }
-  if (run_n) atomicAdd(&hist[hist_slot(run_d)], run_n);
+#pragma unroll
+  for (int e = 0; e < M; ++e)
+    if (e < n_valid) atomicAdd(&hist[hist_slot(kx[e] >> 21)], 1u);
 }
 
 // Count one key per lane into a histogram when many lanes may hold the same digit (exact ties: 64 LDS
@@ -63,19 +67,31 @@ __device__ __forceinline__ void hist_add_ties(uint32_t* hist, uint32_t digit, bo
 __device__ __forceinline__ void find_threshold_bin(const uint32_t* hist, int need, int lane, int* ctl) {
   uint32_t mine = 0;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) mine += hist[(i << 6) | lane];
+  for (int i = 0; i < 8; ++i) {
+    const uint4 v = *reinterpret_cast<const uint4*>(hist + hist_piece(lane, i));
+    mine += (v.x + v.y) + (v.z + v.w);
+  }
   const uint32_t incl = wave_scan_incl(mine);
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
   const uint32_t above = total - incl;      // keys with digits owned by higher lanes
   const uint64_t hit = __ballot(above < (uint32_t)need && (uint32_t)need <= above + mine);
   const int ls = hit ? __ffsll((unsigned long long)hit) - 1 : 0;
-  const uint32_t need2 = (uint32_t)need - (uint32_t)__shfl((int)above, ls);
+  const uint32_t need2 = (uint32_t)need - (uint32_t)__builtin_amdgcn_readlane((int)above, ls);
   // lane t < 32 takes digit 32*ls + 31 - t, so that the scan runs from the top digit down
-  const uint32_t c = lane < 32 ? hist[((31 - lane) << 6) | ls] : 0u;
+  const uint32_t c = lane < 32 ? hist[hist_slot((uint32_t)(ls * 32 + 31 - lane))] : 0u;
   const uint32_t inc2 = wave_scan_incl(c);
   if (lane < 32 && (inc2 - c) < need2 && need2 <= inc2) {
     ctl[0] = ls * 32 + 31 - lane; ctl[1] = (int)(need2 - (inc2 - c)); ctl[2] = (int)c;
   }
+}
+
+// Workgroup -> (unit, span) of a launch over U units of n_span spans each.
+__device__ __forceinline__ void map_span(int U, int n_span, Divider by_span, int& u, int& s) {
+  const int bid = blockIdx.x;
+  const bool shared = (U & 7) == 0;      // the spans of a unit, and the heads of a KV group, share an XCD
+  const int slot = shared ? bid >> 3 : bid, q = divided(slot, by_span);
+  u = shared ? (bid & 7) * (U >> 3) + q : q;
+  s = slot - q * n_span;
 }
 
 // The length a launch of a multi-launch plan works on.  Inside sparq_decode_step (d.k_new set) the row being appended counts as position
@@ -91,82 +107,141 @@ __device__ __forceinline__ int visible_length(const DecodeArgs& d, int b, bool& 
   return S;
 }
 
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+
 // ------------------------------------------------------------------------------------------------
 // Step 1a: the r largest components of |q| (ties to the lower channel) and the temperature (Eq. 9)
 
 struct QueryLds {
-  uint32_t* mag;   // [DH] sort keys
-  int* rankp;      // [NT] partial ranks
   float* qf;       // [DH] query as fp32
   float* qs;       // [DH] selected query components, channel-ascending, padded to a multiple of 8
   int* chan;       // [DH] selected channels, ascending, same padding
 };
 
-// Channel j gets the sort key (|q_j| as its 15-bit code) << 9 | (511 - j): keys are distinct and
-// "larger key" is exactly "larger magnitude, or equal magnitude and lower channel"; the rank of a
-// channel is the number of larger keys and the NT threads split the DH x DH comparisons.  Every
-// wave then finishes the selection for all channels by itself (ranks, ballots, L1 sums), wave g
-// writing the list entries of channels 64g..64g+63.  The list is padded to a multiple of 8 with the
-// last channel at weight 0, so that Step 1b works on whole batches of 8 rows.
-// `qcode` is the 16-bit code of q[tid] for tid < DH.  Three barriers; the first also publishes
-// whatever the caller wrote to LDS before the call.  Returns tau.
+// The 16-bit codes of channels lane * DH / 64 .. + DH / 64 - 1 of a row of DH (16-byte aligned).
+template <int DH>
+struct LaneCodes {
+  static constexpr int E = DH / kWave;
+  uint32_t c[E];
+};
+template <int DH>
+__device__ __forceinline__ LaneCodes<DH> load_lane_codes(const uint16_t* row, int lane) {
+  LaneCodes<DH> v;
+  if (DH == 64) {
+    v.c[0] = row[lane];
+  } else {
+#pragma unroll
+    for (int i = 0; i < DH / 128; ++i) {
+      const uint32_t w = reinterpret_cast<const uint32_t*>(row)[lane * (DH / 128) + i];
+      v.c[2 * i] = w & 0xffffu; v.c[2 * i + 1] = w >> 16;
+    }
+  }
+  return v;
+}
+
+// The r largest of the 64 E keys of a wave (E per lane, key e of lane l belonging to channel l E + e; BITS significant bits),
+// ties to the lower channel: from the top down, two bits at a time, the largest t that at least r keys reach, ending as soon
+// as exactly r do.
+// Returns per key whether it is taken, and the number of taken keys of lower channels.  No LDS and no barrier.
+template <int E, int BITS, class K>
+__device__ __forceinline__ void wave_top_r(const K (&key)[E], int r, bool (&sel)[E], int (&before)[E]) {
+  K t = 0;
+  int n = E * kWave;                       // keys that reach t
+  for (int bit = (BITS - 1) & ~1; bit >= 0 && n != r; bit -= 2) {
+    K cand[3];
+    int c[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      cand[i] = t | ((K)(i + 1) << bit);
+#pragma unroll
+      for (int e = 0; e < E; ++e) c[i] += __popcll(__ballot(key[e] >= cand[i]));
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (c[i] >= r) { t = cand[i]; n = c[i]; }
+  }
+  if (n == r) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) sel[e] = key[e] >= t;
+  } else {                                 // more than r - (keys above t) keys equal t: the first of them
+    uint64_t eq[E];
+    int need = r, lower = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      eq[e] = __ballot(key[e] == t);
+      need -= __popcll(__ballot(key[e] > t));
+      lower += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(eq[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq[e], 0u));
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      sel[e] = key[e] > t || (key[e] == t && lower < need);
+      lower += key[e] == t ? 1 : 0;
+    }
+  }
+  int b = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint64_t m = __ballot(sel[e]);
+    b += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) { before[e] = b; b += sel[e] ? 1 : 0; }
+}
+
+// Every wave selects for itself on the 15-bit magnitude codes in its registers (bound by the latency of about ten rounds of
+// compare, ballot and count), the first wave writes the list and the query: one barrier, which also publishes whatever the
+// caller wrote to LDS before the call.  (Ranking by counting larger keys in LDS, the comparisons dealt out over the
+// workgroup, took three barriers and 1.0 us of a call, this 0.7.)  The list is padded to a multiple of 8 with the last
+// channel at weight 0, so that Step 1b works on whole batches of 8 rows.  Returns the lane's shares of the L1 norms, which the
+// caller turns into the temperature (temperature(); the same in every wave) when the first loads of Step 1b are under way.
+struct L1 {
+  float all, sel;
+};
 template <class T, int DH>
-__device__ __forceinline__ float select_channels(const QueryLds& Q, uint16_t qcode, int r, int tid, int lane, int wave) {
-  if (tid < DH) {
-    Q.mag[tid] = ((uint32_t)(qcode & 0x7fffu) << 9) | (uint32_t)(511 - tid);
-    Q.qf[tid] = T::widen(qcode);
-  }
-  __syncthreads();
-  {
-    constexpr int SL = NT / DH, PER = DH / SL;
-    const int j = tid % DH, slice = tid / DH;
-    const uint32_t mine = Q.mag[j];
-    int partial = 0;
+__device__ __forceinline__ L1 select_channels(const QueryLds& Q, const LaneCodes<DH>& q, int r, int lane, int wave) {
+  constexpr int E = DH / kWave;
+  uint32_t mag[E];
+  float qv[E];
 #pragma unroll
-    for (int i4 = 0; i4 < PER; i4 += 4) {
-      const uint4 m = *reinterpret_cast<const uint4*>(Q.mag + slice * PER + i4);
-      partial += (m.x > mine) + (m.y > mine) + (m.z > mine) + (m.w > mine);
-    }
-    Q.rankp[slice * DH + j] = partial;
+  for (int e = 0; e < E; ++e) { mag[e] = q.c[e] & 0x7fffu; qv[e] = T::widen((uint16_t)q.c[e]); }
+  bool sel[E];
+  int at[E];
+  wave_top_r<E, 15>(mag, r, sel, at);
+  float l1a = 0.0f, l1s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const float aq = fabsf(qv[e]);
+    l1a += aq; l1s += sel[e] ? aq : 0.0f;
   }
-  __syncthreads();
-  float tau;
-  {
-    constexpr int SL = NT / DH, NG = DH / kWave;
+  if (wave == 0) {
     const int r8 = (r + 7) & ~7;
-    int before = 0;
-    float l1a = 0.0f, l1s = 0.0f;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int jj = g * kWave + lane;
-      int rank = 0;
-#pragma unroll
-      for (int s = 0; s < SL; ++s) rank += Q.rankp[s * DH + jj];
-      const bool sel = rank < r;
-      const float qv = Q.qf[jj], aq = fabsf(qv);
-      const uint64_t bal = __ballot(sel);
-      if (g == wave && sel) {
-        const int p = before + __popcll(bal & ((1ull << lane) - 1ull));
-        Q.chan[p] = jj; Q.qs[p] = qv;
-        if (p == r - 1)
-          for (int pp = r; pp < r8; ++pp) { Q.chan[pp] = jj; Q.qs[pp] = 0.0f; }
+    for (int e = 0; e < E; ++e) {
+      const int j = lane * E + e;
+      Q.qf[j] = qv[e];
+      if (sel[e]) {
+        Q.chan[at[e]] = j; Q.qs[at[e]] = qv[e];
+        if (at[e] == r - 1)
+          for (int pp = r; pp < r8; ++pp) { Q.chan[pp] = j; Q.qs[pp] = 0.0f; }
       }
-      before += __popcll(bal);
-      l1a += aq; l1s += sel ? aq : 0.0f;
     }
-    const float l1_all = wave_sum(l1a), l1_sel = wave_sum(l1s);
-    tau = l1_all > 0.0f ? sqrtf((float)DH * l1_sel / l1_all) : sqrtf((float)DH);
   }
   __syncthreads();
-  return tau;
+  return L1{l1a, l1s};
 }
 
 // The temperature actually used: Eq. (9), or one of the two fixed values of the ablation in Section 5.3
-// (flag bits 3 and 4).
+// (flag bits 3 and 4).  Executed by whole waves.
 __device__ __forceinline__ float apply_tau_mode(float tau_l1, uint32_t flags, int d_h, int r) {
   if (flags & 8u) return sqrtf((float)d_h);
   if (flags & 16u) return sqrtf((float)r);
   return tau_l1;
+}
+__device__ __forceinline__ float temperature(const L1& l1, uint32_t flags, int d_h, int r) {
+  const float all = wave_sum(l1.all), sel = wave_sum(l1.sel);
+  return apply_tau_mode(all > 0.0f ? sqrtf((float)d_h * sel / all) : sqrtf((float)d_h), flags, d_h, r);
 }
 
 // Local window: the last n_local = min(l, kq) positions are selected unconditionally; the select then
@@ -185,19 +260,33 @@ __device__ __forceinline__ Window make_window(int local_window, int S, int kq) {
 // ------------------------------------------------------------------------------------------------
 // Step 1b: approximate logit numerators over the r selected rows of the S-contiguous key copy
 
+// 16 bytes of each of 8 listed rows.  The list is read as two 16-byte words and a row's address is one wide multiply-add per
+// lane: with the row numbers moved to scalar registers and multiplied there, requesting 16 rows took 0.7 us of a
+// wave's time (one scalar instruction after the other), this way 0.3.
+__device__ __forceinline__ void issue_rows(uint4 (&v)[8], const char* base, uint32_t row_bytes, const int* chan) {
+  const int4 lo = reinterpret_cast<const int4*>(chan)[0], hi = reinterpret_cast<const int4*>(chan)[1];
+  uint32_t ch[8] = {(uint32_t)lo.x, (uint32_t)lo.y, (uint32_t)lo.z, (uint32_t)lo.w, (uint32_t)hi.x, (uint32_t)hi.y, (uint32_t)hi.z, (uint32_t)hi.w};
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    asm("" : "+v"(ch[t]));               // (the same in every lane: kept in a vector register all the same)
+    v[t] = load16(base + (uint64_t)ch[t] * row_bytes);
+  }
+}
+
 // Chunks (8 consecutive positions = 16 bytes of every channel row) chunk_begin + tid + i * STRIDE belong to
 // thread tid of STRIDE (all NT threads of the workgroup unless the caller divides the rows of a chunk among
 // groups of threads).  The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
 // a two-deep software pipeline: a batch of 8 loads is always in flight behind the one being accumulated,
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
-// 8 sums of chunk c.  No barrier.
+// 8 sums of chunk c.  requested() is called by whole waves once their first two batches of loads are under way: work that
+// Step 1b does not wait for.  No barrier.
 // Addressing: chunk c of channel row j lies at Kt_head + j * row_bytes + c * chunk_bytes.  The S-contiguous
 // key copy has row_bytes = 2 S_max and chunk_bytes = 16; the tiled single-copy layout (tiles of 8 positions,
 // channel-major inside a tile) has row_bytes = 16 and chunk_bytes = 16 d_h.
-template <class T, int STRIDE = NT, class Finish>
-__device__ __forceinline__ void stream_channel_rows(const char* Kt_head, size_t row_bytes, const int* chan,
+template <class T, int STRIDE = NT, class Finish, class Requested>
+__device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                     const float* qs, int r, int chunk_begin, int chunk_end,
-                                                    int tid, Finish&& finish, uint32_t chunk_bytes = 16u) {
+                                                    int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
   const int n_batches = (r + 7) >> 3;
   const int n_chunks = chunk_end - chunk_begin;
   const int my_chunks = n_chunks > tid ? (n_chunks - tid + STRIDE - 1) / STRIDE : 0;
@@ -205,12 +294,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, size_t 
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int ic = 0, ib = 0, cc = 0, cb = 0;   // issue and consume cursors: (own chunk number, batch)
   auto issue_next = [&](uint4 (&v)[8]) {
-    const uint32_t voff = (uint32_t)(chunk_begin + tid + ic * STRIDE) * chunk_bytes;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int ch = __builtin_amdgcn_readfirstlane(chan[ib * 8 + t]);   // uniform: scalar row base
-      v[t] = load16(Kt_head + (size_t)ch * row_bytes + voff);
-    }
+    issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + tid + ic * STRIDE) * chunk_bytes), row_bytes, chan + ib * 8);
     if (++ib == n_batches) { ib = 0; ++ic; }
   };
   auto consume_next = [&](const uint4 (&v)[8]) {
@@ -232,20 +316,23 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, size_t 
   uint4 va[8], vb[8];
   if (items > 0) {
     issue_next(va);
+    if (ic == my_chunks) ic = 0;           // a single item: its second batch is requested and not used
+    issue_next(vb);
+  }
+  requested();                             // (outside the branch: by whole waves)
+  if (items > 0) {
     int i = 0;
-    for (; i + 2 < items; i += 2) {
-      issue_next(vb);
+    for (; i + 3 < items; i += 2) {        // (no conditional request inside: the compiler would wait for all of them)
       consume_next(va);
       issue_next(va);
       consume_next(vb);
-    }
-    if (i + 1 < items) {
       issue_next(vb);
-      consume_next(va);
-      consume_next(vb);
-    } else {
-      consume_next(va);
     }
+    consume_next(va);
+    const int left = items - i;
+    if (left == 3) issue_next(va);
+    if (left >= 2) consume_next(vb);
+    if (left == 3) consume_next(va);
   }
 }
 
@@ -312,7 +399,7 @@ struct SelectLds {
   uint32_t* hist;   // [2][kRadixBins] double-buffered digit histograms (swizzled slots)
   uint32_t* wcnt;   // [NW] wave totals of the compaction scan
   int* ctl;         // [8]
-  float* red;       // [2 * NW]
+  float* red;       // [4 * NW]: the callers' maxima of the waves, then select_compact's sums
 };
 
 // Exclusive prefix sum of v over the workgroup in thread order; *total gets the sum.
@@ -333,179 +420,12 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum, 
   return before + incl - v;
 }
 
-// What select_compact adds up beside the list.
-enum class Sums {
-  kNone,        // nothing
-  kNumerator,   // alpha's numerator, sum over the selected of exp((d - dmax) / tau); the caller's threads bring the denominator
-  kBoth         // the numerator and the denominator, sum over all keys
-};
-
-// Step 2a as a whole: the k_old positions of largest key among keys[0..S_old) (ties to the lower position) and all
-// positions S_old .. S-1 (the local window), ascending, into list[0 .. k_old + S - S_old).
-// On entry hist[0] holds the counts of the first digit of keys[0..S_old), hist[1] is zero, and a barrier lies behind
-// them.  Digits of 11, 11 and 10 bits from the top.  The threshold's first digit comes from hist[0]; then every lane
-// reads its keys once and keeps two bit masks of them, "larger digit" and "equal digit".  What follows works on the
-// set bits only: the few keys that share the threshold's digit are counted by their next digit, one wave finds the
-// threshold among them, and their bits are sorted out, until the remaining bin is taken whole (with distinct keys:
-// after the second digit as a rule).  A lane owns consecutive positions, so lane order is position order and one
-// workgroup scan of the packed (larger, equal) counts orders the list, whatever the length.
-// Bound by vector instructions and by the serial steps of one workgroup.  Measured against a select that swept all keys
-// again for every digit and a compaction that took a softmax weight of every key (the denominator now comes with the
-// stream, where the memory is waited for anyway): step of 2048 heads at S = 8192 143.4 -> 139.8 us, 256 heads at 16 000
-// 71.6 -> 67.2, 32 heads at 3981 20.7 -> 19.9, one head at 1023 11.4 -> 11.0.
-// Which of the equal keys are taken (the first `need` by position) does not matter for the sums: either all of them
-// are, or all 32 bits are decided and they share one weight.
-// `list` may be the key array itself: it overwrites it from the front, a write never lands beyond the position it
-// records, and all reads of keys precede the scan's barrier.  With key_out (receives the key of the n-th entry) the keys
-// are read again after it: list must then be another array.  Entries of list / idx_out are offset by pos_base.
-// esc = log2(e) / tau; z = the calling thread's share of the denominator relative to dmax (kNumerator).
-// Ends with a barrier that also publishes the list.  Returns alpha; sums_out[0..1] receive the denominator and the
-// numerator.
-// kOwnWords: bit masks of each kind per lane, for up to 32 NT kOwnWords positions.
-// found() is called when the threshold is known (a time stamp of a profiling build).
-template <Sums SUMS, int kOwnWords, class Found>
-__device__ __forceinline__ float select_compact_words(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
-                                                float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
-                                                int wave, uint32_t* key_out, int pos_base, float* sums_out, Found&& found) {
-  // first digit of the threshold
-  uint32_t first = 0xffffffffu, last = 0xffffffffu;       // keys that share the decided bits lie in first .. last
-  int need = k_old, in_bin = k_old;
-  if (k_old > 0) {                                        // (0: everything comes from the window)
-    if (wave == 0) find_threshold_bin(sl.hist, k_old, lane, sl.ctl);
-    __syncthreads();
-    first = (uint32_t)sl.ctl[0] << 21; last = first | 0x1fffffu;
-    need = sl.ctl[1]; in_bin = sl.ctl[2];
-  }
-  // this lane's positions: granules of 4 (few keys: more lanes take part) or 8, dealt out evenly, in order
-  const int gran = S <= 4 * NT ? 4 : 8;
-  const int n_gran = (S + gran - 1) / gran, per = n_gran / NT, rem = n_gran - per * NT;
-  const int own = (tid * per + (tid < rem ? tid : rem)) * gran, n_own = (per + (tid < rem ? 1 : 0)) * gran;
-  uint32_t gt[kOwnWords], eq[kOwnWords];                  // bit i of word w: position own + 32 w + i
+// the largest of one value per wave
+__device__ __forceinline__ float wave_values_max(const float* v) {
+  float m = v[0];
 #pragma unroll
-  for (int w = 0; w < kOwnWords; ++w) {
-    gt[w] = eq[w] = 0;
-    const int at = own + 32 * w;
-    if (32 * w < n_own) {
-      const int old_here = S_old - at, all_here = S - at < n_own - 32 * w ? S - at : n_own - 32 * w;   // of this lane's own
-      const uint32_t old_mask = old_here >= 32 ? ~0u : (old_here <= 0 ? 0u : (1u << old_here) - 1u);
-      const uint32_t all_mask = all_here >= 32 ? ~0u : (all_here <= 0 ? 0u : (1u << all_here) - 1u);
-      uint32_t g = 0, ge = 0;
-#pragma unroll
-      for (int i = 7; i >= 0; --i) {
-        if (32 * w + 4 * i < n_own) {
-          const uint4 v = *reinterpret_cast<const uint4*>(keys + at + 4 * i);
-          const uint32_t kx[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int e = 3; e >= 0; --e) {
-            g = g + g + (kx[e] > last ? 1u : 0u);
-            ge = ge + ge + (kx[e] >= first ? 1u : 0u);
-            if (SUMS == Sums::kBoth) z += 4 * i + e < all_here ? exp2_weight((key_to_float(kx[e]) - dmax) * esc) : 0.0f;
-          }
-        }
-      }
-      eq[w] = ge & ~g & old_mask;
-      gt[w] = (g & old_mask) | (all_mask & ~old_mask);
-    }
-  }
-  auto each = [&](uint32_t (&bits)[kOwnWords], auto&& f) {      // f(word, bit, position) for every set bit
-#pragma unroll
-    for (int w = 0; w < kOwnWords; ++w)
-      for (uint32_t b = bits[w]; b; b &= b - 1) f(w, b & (0u - b), own + 32 * w + __ffs(b) - 1);
-  };
-  for (int pass = 1; pass < 3 && need != in_bin; ++pass) {
-    const int shift = pass == 1 ? 10 : 0;
-    const uint32_t dmask = pass == 1 ? 0x7ffu : 0x3ffu;
-    uint32_t* hist = sl.hist + (pass & 1) * kRadixBins;
-    if (pass == 2) {                                      // hist[0] has served the first digit
-      for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
-      __syncthreads();
-    }
-    if (in_bin <= kTieHeavy) {
-      each(eq, [&](int, uint32_t, int at) { atomicAdd(&hist[hist_slot((keys[at] >> shift) & dmask)], 1u); });
-    } else {
-      // thousands of keys share the decided bits (duplicated keys, underflowed scores): they may share the next
-      // digit too, and plain atomics on one address would take microseconds; count per wave first
-#pragma unroll
-      for (int w = 0; w < kOwnWords; ++w)
-        for (int i = 0; i < 32; ++i) {
-          const bool on = (eq[w] >> i) & 1u;
-          if (__ballot(on) == 0) continue;
-          hist_add_ties(hist, (keys[on ? own + 32 * w + i : 0] >> shift) & dmask, on, lane);
-        }
-    }
-    __syncthreads();
-    if (wave == 0) find_threshold_bin(hist, need, lane, sl.ctl);
-    __syncthreads();
-    const uint32_t digit = (uint32_t)sl.ctl[0];
-    need = sl.ctl[1]; in_bin = sl.ctl[2];
-    first |= digit << shift;
-    each(eq, [&](int w, uint32_t bit, int at) {
-      const uint32_t d = (keys[at] >> shift) & dmask;
-      if (d != digit) eq[w] &= ~bit;
-      if (d > digit) gt[w] |= bit;
-    });
-  }
-  found();
-  float asum = 0.0f, esum = 0.0f;
-  if (SUMS != Sums::kNone) {
-    each(gt, [&](int, uint32_t, int at) { asum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
-    each(eq, [&](int, uint32_t, int at) { esum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
-  }
-  uint32_t n_gt = 0, n_eq = 0;
-#pragma unroll
-  for (int w = 0; w < kOwnWords; ++w) { n_gt += __popc(gt[w]); n_eq += __popc(eq[w]); }
-  uint32_t total;
-  const uint32_t ex = block_scan_excl(n_gt | (n_eq << 16), sl.wcnt, lane, wave, &total);
-  const uint32_t eq_before = ex >> 16;
-  uint32_t o = (ex & 0xffffu) + (eq_before < (uint32_t)need ? eq_before : (uint32_t)need);
-  int room = need - (int)eq_before;                       // equal keys still to be taken from this lane on
-#pragma unroll
-  for (int w = 0; w < kOwnWords; ++w) {
-    uint32_t take = gt[w];
-    for (uint32_t b = eq[w]; b && room > 0; --room, b &= b - 1) take |= b & (0u - b);
-    for (; take; take &= take - 1) {
-      const int at = own + 32 * w + __ffs(take) - 1;
-      list[o] = (uint32_t)(pos_base + at);
-      if (key_out) key_out[o] = keys[at];
-      if (idx_out && (int)o < idx_stride) idx_out[o] = pos_base + at;
-      ++o;
-    }
-  }
-  if (SUMS == Sums::kNone) {
-    __syncthreads();
-    return 0.0f;
-  }
-  const bool all_equal_taken = (uint32_t)need >= (total >> 16);
-  if (all_equal_taken) asum += esum;
-  z = wave_sum(z); asum = wave_sum(asum);
-  if (lane == 0) { sl.red[wave] = z; sl.red[NW + wave] = asum; }
-  __syncthreads();
-  float zt = 0.0f, at = 0.0f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { zt += sl.red[w]; at += sl.red[NW + w]; }
-  if (!all_equal_taken) at += (float)need * exp2_weight((key_to_float(first) - dmax) * esc);
-  if (sums_out) { sums_out[0] = zt; sums_out[1] = at; }
-  // numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
-  // (but not a number where they are none)
-  const float alpha = at / zt;
-  return alpha > 1.0f || (k_old == S_old && alpha == alpha) ? 1.0f : alpha;
-}
-
-struct NoStamp {
-  __device__ __forceinline__ void operator()() const {}
-};
-
-template <Sums SUMS, class Found = NoStamp>
-__device__ __forceinline__ float select_compact(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, float dmax, float esc,
-                                                float z, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid, int lane,
-                                                int wave, uint32_t* key_out = nullptr, int pos_base = 0, float* sums_out = nullptr,
-                                                Found&& found = Found{}) {
-  // (one mask per lane as a case of its own: straight code without the loops over masks, 0.4 us of a call of 11 us)
-  if (S <= 32 * NT)
-    return select_compact_words<SUMS, 1>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
-                                         pos_base, sums_out, found);
-  return select_compact_words<SUMS, 3>(keys, list, S, S_old, k_old, dmax, esc, z, idx_out, idx_stride, sl, tid, lane, wave, key_out,
-                                       pos_base, sums_out, found);      // LDS ends at about 40 000 keys
+  for (int w = 1; w < NW; ++w) m = fmaxf(m, v[w]);
+  return m;
 }
 
 // A thread's share of the softmax denominator, summed while the logit numerators are produced: relative to the
@@ -525,6 +445,291 @@ struct RunningSum {
   }
   __device__ __forceinline__ float relative_to(float dmax, float esc) const { return z * exp2_weight((ref - dmax) * esc); }
 };
+
+// What select_compact adds up beside the list.
+enum class Sums {
+  kNone,        // nothing
+  kNumerator,   // alpha's numerator, sum over the selected of exp((d - dmax) / tau); the threads bring the denominator
+  kBoth         // the numerator and the denominator, sum over all keys
+};
+
+// What alpha is made of beside the waves' sums in red[NW ..] (selected_mass() and all_mass()).
+struct Selection {
+  uint32_t first;   // the threshold: its decided bits, the others 0
+  int need;         // how many of the keys that share them are taken
+  bool whole;       // all of them
+};
+__device__ __forceinline__ float all_mass(const float* red) {
+  float t = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) t += red[NW + w];
+  return t;
+}
+__device__ __forceinline__ float selected_mass(const Selection& s, const float* red, float dmax, float esc) {
+  float t = 0.0f, e = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { t += red[2 * NW + w]; e += red[3 * NW + w]; }
+  // Which of the equal keys are taken does not matter for the sum: either all of them are, or all 32 bits are decided and
+  // they share one weight.
+  return t + (s.whole ? e : (float)s.need * exp2_weight((key_to_float(s.first) - dmax) * esc));
+}
+// numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
+// (but not a number where they are none)
+__device__ __forceinline__ float share_of(float selected, float all, bool everything) {
+  const float alpha = selected / all;
+  return alpha > 1.0f || (everything && alpha == alpha) ? 1.0f : alpha;
+}
+
+// Step 2a as a whole: the k_old positions of largest key among keys[0..S_old) (ties to the lower position) and all
+// positions S_old .. S-1 (the local window), ascending, into list[0 .. k_old + S - S_old).
+// On entry hist[0] holds the counts of the first digit of keys[0..S_old), hist[1] is zero, and a barrier lies behind
+// them.  Digits of 11, 11 and 10 bits from the top.  The threshold's first digit comes from hist[0]; then every lane
+// keeps two bit masks of its keys, "above the bin" and "in the bin".  What follows concerns the keys in the bin only: they are
+// counted by their next digit, one wave finds the threshold among them, and the masks are formed again, until the remaining
+// bin is taken whole (with distinct keys: after the second digit as a rule).  A lane owns consecutive positions, so lane order
+// is position order and one workgroup scan of the packed (above, in) counts orders the list, whatever the length (ties: the
+// first `need` keys of the bin by position).
+// Bound by vector instructions where workgroups share a CU, by the latency of one wave's instructions and of LDS where they
+// do not.  Up to 8 keys per lane (S <= 8 NT) stay in registers and every step is straight code; beyond that a lane keeps the
+// masks and reads the few keys that they name again.  Measured for the whole selection of one head at 1024 positions and at
+// 3982: 3.0 and 3.5 us with the second form for every length and alpha summed here, 2.3 and 3.1.
+// `list` may be the key array itself: it overwrites it from the front, a write never lands beyond the position it
+// records, and all reads of keys precede the scan's barrier.  With key_out (receives the key of the n-th entry) the keys
+// are read again after it: list must then be another array.  Entries of list / idx_out are offset by pos_base.
+// esc = log2(e) / tau; zs = the calling thread's share of the denominator (kNumerator); dmax() = the largest logit numerator,
+// called by every thread once the threshold is known.
+// Ends with a barrier that also publishes the list and the waves' sums.
+// found() is called when the threshold is known (a time stamp of a profiling build).
+//
+// The passes over the keys of the threshold's bin, for both forms: count(hist, shift, mask, heavy) counts the keys in the bin
+// by a digit, narrow() forms the masks anew for keys above `last` and from `first` to `last`.
+struct Bin {
+  uint32_t first = 0xffffffffu, last = 0xffffffffu;       // keys that share the decided bits lie in first .. last
+  int need, size;
+};
+__device__ __forceinline__ Bin first_bin(int k_old, const SelectLds& sl, int lane, int wave) {
+  Bin b;
+  b.need = b.size = k_old;
+  if (k_old > 0) {                                        // (0: everything comes from the window)
+    if (wave == 0) find_threshold_bin(sl.hist, k_old, lane, sl.ctl);
+    __syncthreads();
+    b.first = (uint32_t)sl.ctl[0] << 21; b.last = b.first | 0x1fffffu;
+    b.need = sl.ctl[1]; b.size = sl.ctl[2];
+  }
+  return b;
+}
+template <class Count, class Narrow>
+__device__ __forceinline__ void next_bins(Bin& b, const SelectLds& sl, int tid, int lane, int wave, Count&& count, Narrow&& narrow) {
+  for (int pass = 1; pass < 3 && b.need != b.size; ++pass) {
+    const int shift = pass == 1 ? 10 : 0;
+    const uint32_t dmask = pass == 1 ? 0x7ffu : 0x3ffu;
+    uint32_t* hist = sl.hist + (pass & 1) * kRadixBins;
+    if (pass == 2) {                                      // hist[0] has served the first digit
+      for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
+      __syncthreads();
+    }
+    // heavy: thousands of keys share the decided bits (duplicated keys, underflowed scores): they may share the next digit
+    // too, and plain atomics on one address would take microseconds; count per wave first
+    count(hist, shift, dmask, b.size > kTieHeavy);
+    __syncthreads();
+    if (wave == 0) find_threshold_bin(hist, b.need, lane, sl.ctl);
+    __syncthreads();
+    b.first |= (uint32_t)sl.ctl[0] << shift; b.last = b.first | ((1u << shift) - 1u);
+    b.need = sl.ctl[1]; b.size = sl.ctl[2];
+    narrow();
+  }
+}
+
+// a lane's sums and (above, in) counts -> its place in the list; the scan's barrier publishes the waves' sums too
+template <Sums SUMS>
+__device__ __forceinline__ Selection place_of(const Bin& b, uint32_t n_gt, uint32_t n_eq, float z, float asum, float esum,
+                                              const SelectLds& sl, int lane, int wave, uint32_t& o, int& room) {
+  if (SUMS != Sums::kNone) {
+    z = wave_sum(z); asum = wave_sum(asum); esum = wave_sum(esum);
+    if (lane == 0) { sl.red[NW + wave] = z; sl.red[2 * NW + wave] = asum; sl.red[3 * NW + wave] = esum; }
+  }
+  uint32_t total;
+  const uint32_t ex = block_scan_excl(n_gt | (n_eq << 16), sl.wcnt, lane, wave, &total);
+  const uint32_t eq_before = ex >> 16;
+  o = (ex & 0xffffu) + (eq_before < (uint32_t)b.need ? eq_before : (uint32_t)b.need);
+  room = b.need - (int)eq_before;                         // keys of the bin still to be taken from this lane on
+  return Selection{b.first, b.need, (uint32_t)b.need >= (total >> 16)};
+}
+
+// M = 4 or 8 keys per lane, in registers
+template <Sums SUMS, int M, class Max, class Found>
+__device__ __forceinline__ Selection select_compact_regs(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, Max&& dmax_of,
+                                                         float esc, const RunningSum& zs, int32_t* idx_out, int idx_stride, const SelectLds& sl,
+                                                         int tid, int lane, int wave, uint32_t* key_out, int pos_base, Found&& found) {
+  const int own = tid * M;
+  uint32_t kx[M] = {};
+  if (own < S) {
+#pragma unroll
+    for (int i = 0; i < M; i += 4) {
+      const uint4 v = *reinterpret_cast<const uint4*>(keys + own + i);
+      kx[i] = v.x; kx[i + 1] = v.y; kx[i + 2] = v.z; kx[i + 3] = v.w;
+    }
+  }
+  auto below = [&](int end) -> uint32_t { const int n = end - own; return n >= M ? (1u << M) - 1u : (n <= 0 ? 0u : (1u << n) - 1u); };
+  const uint32_t all_mask = below(S), old_mask = below(S_old);
+  Bin b = first_bin(k_old, sl, lane, wave);
+  uint32_t gt, eq;
+  auto narrow = [&]() {
+    uint32_t g = 0, ge = 0;
+#pragma unroll
+    for (int e = M - 1; e >= 0; --e) {
+      g = g + g + (kx[e] > b.last ? 1u : 0u);
+      ge = ge + ge + (kx[e] >= b.first ? 1u : 0u);
+    }
+    eq = ge & ~g & old_mask;
+    gt = (g & old_mask) | (all_mask & ~old_mask);
+  };
+  narrow();
+  next_bins(b, sl, tid, lane, wave, [&](uint32_t* hist, int shift, uint32_t dmask, bool heavy) {
+    if (!heavy) {
+#pragma unroll
+      for (int e = 0; e < M; ++e)
+        if ((eq >> e) & 1u) atomicAdd(&hist[hist_slot((kx[e] >> shift) & dmask)], 1u);
+    } else {
+#pragma unroll
+      for (int e = 0; e < M; ++e) hist_add_ties(hist, (kx[e] >> shift) & dmask, (eq >> e) & 1u, lane);
+    }
+  }, narrow);
+  found();
+  float z = 0.0f, asum = 0.0f, esum = 0.0f;
+  if (SUMS != Sums::kNone) {
+    const float dmax = dmax_of();
+    if (SUMS == Sums::kNumerator) z = zs.relative_to(dmax, esc);
+#pragma unroll
+    for (int e = 0; e < M; ++e) {
+      const float w = exp2_weight((key_to_float(kx[e]) - dmax) * esc);
+      asum += (gt >> e) & 1u ? w : 0.0f;
+      esum += (eq >> e) & 1u ? w : 0.0f;
+      if (SUMS == Sums::kBoth) z += (all_mask >> e) & 1u ? w : 0.0f;
+    }
+  }
+  uint32_t o;
+  int room;
+  const Selection s = place_of<SUMS>(b, __popc(gt), __popc(eq), z, asum, esum, sl, lane, wave, o, room);
+  uint32_t take = gt;
+  for (uint32_t t = eq; t && room > 0; --room, t &= t - 1) take |= t & (0u - t);
+  for (; take; take &= take - 1) {
+    const int e = __ffs(take) - 1, at = own + e;
+    list[o] = (uint32_t)(pos_base + at);
+    if (key_out) key_out[o] = keys[at];
+    if (idx_out && (int)o < idx_stride) idx_out[o] = pos_base + at;
+    ++o;
+  }
+  __syncthreads();
+  return s;
+}
+
+// kOwnWords: bit masks of each kind per lane, for up to 32 NT kOwnWords positions.
+template <Sums SUMS, int kOwnWords, class Max, class Found>
+__device__ __forceinline__ Selection select_compact_words(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, Max&& dmax_of,
+                                                          float esc, const RunningSum& zs, int32_t* idx_out, int idx_stride,
+                                                          const SelectLds& sl, int tid, int lane, int wave, uint32_t* key_out, int pos_base,
+                                                          Found&& found) {
+  Bin b = first_bin(k_old, sl, lane, wave);
+  // this lane's positions: granules of 8, dealt out evenly, in order
+  constexpr int gran = 8;
+  const int n_gran = (S + gran - 1) / gran, per = n_gran / NT, rem = n_gran - per * NT;
+  const int own = (tid * per + (tid < rem ? tid : rem)) * gran, n_own = (per + (tid < rem ? 1 : 0)) * gran;
+  uint32_t gt[kOwnWords], eq[kOwnWords];                  // bit i of word w: position own + 32 w + i
+  float z = 0.0f, dmax = 0.0f;
+  if (SUMS == Sums::kBoth) dmax = dmax_of();
+#pragma unroll
+  for (int w = 0; w < kOwnWords; ++w) {
+    gt[w] = eq[w] = 0;
+    const int at = own + 32 * w;
+    if (32 * w < n_own) {
+      const int old_here = S_old - at, all_here = S - at < n_own - 32 * w ? S - at : n_own - 32 * w;   // of this lane's own
+      const uint32_t old_mask = old_here >= 32 ? ~0u : (old_here <= 0 ? 0u : (1u << old_here) - 1u);
+      const uint32_t all_mask = all_here >= 32 ? ~0u : (all_here <= 0 ? 0u : (1u << all_here) - 1u);
+      uint32_t g = 0, ge = 0;
+#pragma unroll
+      for (int i = 7; i >= 0; --i) {
+        if (32 * w + 4 * i < n_own) {
+          const uint4 v = *reinterpret_cast<const uint4*>(keys + at + 4 * i);
+          const uint32_t kx[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 3; e >= 0; --e) {
+            g = g + g + (kx[e] > b.last ? 1u : 0u);
+            ge = ge + ge + (kx[e] >= b.first ? 1u : 0u);
+            if (SUMS == Sums::kBoth) z += 4 * i + e < all_here ? exp2_weight((key_to_float(kx[e]) - dmax) * esc) : 0.0f;
+          }
+        }
+      }
+      eq[w] = ge & ~g & old_mask;
+      gt[w] = (g & old_mask) | (all_mask & ~old_mask);
+    }
+  }
+  auto each = [&](uint32_t (&bits)[kOwnWords], auto&& f) {      // f(word, bit, position) for every set bit
+#pragma unroll
+    for (int w = 0; w < kOwnWords; ++w)
+      for (uint32_t t = bits[w]; t; t &= t - 1) f(w, t & (0u - t), own + 32 * w + __ffs(t) - 1);
+  };
+  next_bins(b, sl, tid, lane, wave, [&](uint32_t* hist, int shift, uint32_t dmask, bool heavy) {
+    if (!heavy) {
+      each(eq, [&](int, uint32_t, int at) { atomicAdd(&hist[hist_slot((keys[at] >> shift) & dmask)], 1u); });
+    } else {
+#pragma unroll
+      for (int w = 0; w < kOwnWords; ++w)
+        for (int i = 0; i < 32; ++i) {
+          const bool on = (eq[w] >> i) & 1u;
+          if (__ballot(on) == 0) continue;
+          hist_add_ties(hist, (keys[on ? own + 32 * w + i : 0] >> shift) & dmask, on, lane);
+        }
+    }
+  }, [&]() {
+    each(eq, [&](int w, uint32_t bit, int at) {
+      const uint32_t key = keys[at];
+      if (key < b.first || key > b.last) eq[w] &= ~bit;
+      if (key > b.last) gt[w] |= bit;
+    });
+  });
+  found();
+  float asum = 0.0f, esum = 0.0f;
+  if (SUMS != Sums::kNone) {
+    if (SUMS == Sums::kNumerator) { dmax = dmax_of(); z = zs.relative_to(dmax, esc); }
+    each(gt, [&](int, uint32_t, int at) { asum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
+    each(eq, [&](int, uint32_t, int at) { esum += exp2_weight((key_to_float(keys[at]) - dmax) * esc); });
+  }
+  uint32_t n_gt = 0, n_eq = 0;
+#pragma unroll
+  for (int w = 0; w < kOwnWords; ++w) { n_gt += __popc(gt[w]); n_eq += __popc(eq[w]); }
+  uint32_t o;
+  int room;
+  const Selection s = place_of<SUMS>(b, n_gt, n_eq, z, asum, esum, sl, lane, wave, o, room);
+#pragma unroll
+  for (int w = 0; w < kOwnWords; ++w) {
+    uint32_t take = gt[w];
+    for (uint32_t t = eq[w]; t && room > 0; --room, t &= t - 1) take |= t & (0u - t);
+    for (; take; take &= take - 1) {
+      const int at = own + 32 * w + __ffs(take) - 1;
+      list[o] = (uint32_t)(pos_base + at);
+      if (key_out) key_out[o] = keys[at];
+      if (idx_out && (int)o < idx_stride) idx_out[o] = pos_base + at;
+      ++o;
+    }
+  }
+  __syncthreads();
+  return s;
+}
+
+template <Sums SUMS, class Max, class Found = Nothing>
+__device__ __forceinline__ Selection select_compact(const uint32_t* keys, uint32_t* list, int S, int S_old, int k_old, Max&& dmax_of, float esc,
+                                                    const RunningSum& zs, int32_t* idx_out, int idx_stride, const SelectLds& sl, int tid,
+                                                    int lane, int wave, uint32_t* key_out = nullptr, int pos_base = 0, Found&& found = Found{}) {
+  if (S <= 4 * NT)
+    return select_compact_regs<SUMS, 4>(keys, list, S, S_old, k_old, dmax_of, esc, zs, idx_out, idx_stride, sl, tid, lane, wave, key_out, pos_base, found);
+  if (S <= 8 * NT)
+    return select_compact_regs<SUMS, 8>(keys, list, S, S_old, k_old, dmax_of, esc, zs, idx_out, idx_stride, sl, tid, lane, wave, key_out, pos_base, found);
+  if (S <= 32 * NT)
+    return select_compact_words<SUMS, 1>(keys, list, S, S_old, k_old, dmax_of, esc, zs, idx_out, idx_stride, sl, tid, lane, wave, key_out, pos_base, found);
+  return select_compact_words<SUMS, 3>(keys, list, S, S_old, k_old, dmax_of, esc, zs, idx_out, idx_stride, sl, tid, lane, wave, key_out, pos_base,
+                                       found);      // LDS ends at about 40 000 keys
+}
 
 // ------------------------------------------------------------------------------------------------
 // Step 2b: exact softmax attention over gathered rows (Eq. 8), online softmax in the exp2 domain
@@ -546,11 +751,12 @@ struct RowGeometry {
 // 8 positions, channel-major inside a tile: element (position p, channel j) at ((p / 8) d_h + j) 8 + p % 8),
 // so a lane's 8 channels of one position are eight 2-byte loads 16 bytes apart; positions from tiled_below on
 // (the up to 7 newest, not yet in a tile) are rows of K_stage (row p - tiled_below, already offset by `sub`).
-template <class T, int DH, bool TILED = false>
+// requested() is called by whole waves once the first group of loads is under way.
+template <class T, int DH, bool TILED = false, class Requested = Nothing>
 __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_head, const int* list, int n_begin,
                                             int n_end, const float (&q8)[8], int lane, int wave, float& m_run,
-                                            float& l_run, float (&acc)[8], const char* K_stage = nullptr,
-                                            int tiled_below = 0) {
+                                            float& l_run, float (&acc)[8], Requested&& requested = Requested{},
+                                            const char* K_stage = nullptr, int tiled_below = 0) {
   using G = RowGeometry<DH>;
   const int slot = wave * G::RPW + lane / G::LPR;
   const int n_groups = (n_end - n_begin + G::GROUP - 1) / G::GROUP;
@@ -597,6 +803,7 @@ __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_he
   if (n_groups > 0) {
     uint4 ka[G::UNR], va[G::UNR], kb[G::UNR], vb[G::UNR];
     issue(ka, va, 0);
+    requested();
     int g = 0;
     for (; g + 2 < n_groups; g += 2) {
       issue(kb, vb, g + 1);
@@ -611,6 +818,8 @@ __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_he
     } else {
       consume(ka, va, g);
     }
+  } else {
+    requested();
   }
 }
 
@@ -643,16 +852,24 @@ __device__ __forceinline__ void attend_row_from_codes(const uint16_t* krow, cons
 template <int DH>
 __device__ __forceinline__ void store_wave_partial(float m_run, float l_run, float (&acc)[8], float* part, int lane, int wave) {
   using G = RowGeometry<DH>;
+  auto merge = [&](auto step) {
+    constexpr int O = decltype(step)::value;
+    float ma, mb, la, lb;
+    lane_pair<O>(m_run, ma, mb);
+    lane_pair<O>(l_run, la, lb);
+    m_run = fmaxf(ma, mb);
+    const float sa = weight_exp2(ma, m_run), sb = weight_exp2(mb, m_run);
+    l_run = la * sa + lb * sb;
 #pragma unroll
-  for (int o = G::LPR; o < kWave; o <<= 1) {
-    const float m_o = __shfl_xor(m_run, o), l_o = __shfl_xor(l_run, o);
-    const float m_new = fmaxf(m_run, m_o);
-    const float s1 = weight_exp2(m_run, m_new), s2 = weight_exp2(m_o, m_new);
-    l_run = l_run * s1 + l_o * s2;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = acc[e] * s1 + __shfl_xor(acc[e], o) * s2;
-    m_run = m_new;
-  }
+    for (int e = 0; e < 8; ++e) {
+      float a, b;
+      lane_pair<O>(acc[e], a, b);
+      acc[e] = a * sa + b * sb;
+    }
+  };
+  if (G::LPR <= 8) merge(std::integral_constant<int, 8>{});
+  if (G::LPR <= 16) merge(std::integral_constant<int, 16>{});
+  merge(std::integral_constant<int, 32>{});
   float* mine = part + wave * (DH + 2);
   if (lane < G::LPR) {
 #pragma unroll

@@ -52,85 +52,61 @@ __device__ __forceinline__ void wave_merge(const RunningSum& rs, float esc, floa
 }
 
 struct GroupQueryLds {
-  int* rankp;      // [NT] partial ranks
   float* qf;       // [G][DH] the group's queries as fp32
   float* qs;       // [G][DH] per-head components on the shared channel list (padded to a multiple of 8, weight 0)
   int* chan;       // [DH] shared channel list, ascending, same padding
-  double* magd;    // [DH] group sums of |q|
 };
 
 // Step 1a under the group rule: channel j is ranked by sum_h |q_h,j| (fp64, heads in order, ties to the lower
 // channel); esc[h] = log2(e) / tau_h with tau_h from Eq. (9) on the shared channel set (or the fixed
-// temperature the flags ask for).  q_group: the G x DH query codes of the group.  Four barriers; the first also
-// publishes whatever the caller wrote to LDS before the call.
+// temperature the flags ask for).  q: the codes of the group's queries.  As select_channels: every
+// wave selects for itself, one barrier, which also publishes whatever the caller wrote to LDS before the call.
 template <class T, int DH, int G>
-__device__ __forceinline__ void select_channels_group(const GroupQueryLds& Q, const uint16_t* q_group, int r, uint32_t flags,
-                                                      int tid, int lane, int wave, float (&esc)[G]) {
-  for (int i = tid; i < G * DH; i += NT)
-    Q.qf[i] = T::widen(q_group[i]);
-  __syncthreads();
-  if (tid < DH) {
+__device__ __forceinline__ void select_channels_group(const GroupQueryLds& Q, const LaneCodes<DH> (&q)[G], int r, uint32_t flags,
+                                                      int lane, int wave, float (&esc)[G]) {
+  constexpr int E = DH / kWave;
+  uint64_t mag[E];                                                        // sums >= 0: their bits order like they do
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
     double m = 0.0;
 #pragma unroll
-    for (int h = 0; h < G; ++h) m += (double)fabsf(Q.qf[h * DH + tid]);   // head order, as in the definition
-    Q.magd[tid] = m;
+    for (int h = 0; h < G; ++h) m += (double)fabsf(T::widen((uint16_t)q[h].c[e]));   // head order, as in the definition
+    mag[e] = (uint64_t)__double_as_longlong(m);
   }
-  __syncthreads();
-  {
-    constexpr int SL = NT / DH, PER = DH / SL;
-    const int j = tid % DH, slice = tid / DH;
-    const double mine = Q.magd[j];
-    int partial = 0;
-#pragma unroll 4
-    for (int i = slice * PER; i < (slice + 1) * PER; ++i) {
-      const double m = Q.magd[i];
-      partial += (m > mine) || (m == mine && i < j);
-    }
-    Q.rankp[slice * DH + j] = partial;
-  }
-  __syncthreads();
-  {
-    constexpr int SL = NT / DH, NG = DH / kWave;
+  bool sel[E];
+  int at[E];
+  wave_top_r<E, 63>(mag, r, sel, at);
+  if (wave == 0) {
     const int r8 = (r + 7) & ~7;
-    int before = 0;
-    float l1a[G], l1s[G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) { l1a[h] = 0.0f; l1s[h] = 0.0f; }
+    for (int e = 0; e < E; ++e) {
+      const int j = lane * E + e;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int jj = g * kWave + lane;
-      int rank = 0;
+      for (int h = 0; h < G; ++h) Q.qf[h * DH + j] = T::widen((uint16_t)q[h].c[e]);
+      if (sel[e]) {
+        Q.chan[at[e]] = j;
 #pragma unroll
-      for (int s = 0; s < SL; ++s) rank += Q.rankp[s * DH + jj];
-      const bool sel = rank < r;
-      const uint64_t bal = __ballot(sel);
-      if (g == wave) {
-        if (sel) {
-          const int p = before + __popcll(bal & ((1ull << lane) - 1ull));
-          Q.chan[p] = jj;
+        for (int h = 0; h < G; ++h) Q.qs[h * DH + at[e]] = T::widen((uint16_t)q[h].c[e]);
+        if (at[e] == r - 1)
+          for (int pp = r; pp < r8; ++pp) {
+            Q.chan[pp] = j;
 #pragma unroll
-          for (int h = 0; h < G; ++h) Q.qs[h * DH + p] = Q.qf[h * DH + jj];
-          if (p == r - 1)
-            for (int pp = r; pp < r8; ++pp) {
-              Q.chan[pp] = jj;
-#pragma unroll
-              for (int h = 0; h < G; ++h) Q.qs[h * DH + pp] = 0.0f;
-            }
-        }
-      }
-      before += __popcll(bal);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float aq = fabsf(Q.qf[h * DH + jj]);
-        l1a[h] += aq; l1s[h] += sel ? aq : 0.0f;
+            for (int h = 0; h < G; ++h) Q.qs[h * DH + pp] = 0.0f;
+          }
       }
     }
+  }
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float all = wave_sum(l1a[h]), part = wave_sum(l1s[h]);
-      const float tau = part > 0.0f ? sqrtf((float)DH * part / all) : sqrtf((float)DH);   // all logits 0 then
-      esc[h] = kLog2e / apply_tau_mode(tau, flags, DH, r);
+  for (int h = 0; h < G; ++h) {
+    float l1a = 0.0f, l1s = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const float aq = fabsf(T::widen((uint16_t)q[h].c[e]));
+      l1a += aq; l1s += sel[e] ? aq : 0.0f;
     }
+    const float all = wave_sum(l1a), part = wave_sum(l1s);
+    const float tau = part > 0.0f ? sqrtf((float)DH * part / all) : sqrtf((float)DH);   // all logits 0 then
+    esc[h] = kLog2e / apply_tau_mode(tau, flags, DH, r);
   }
   __syncthreads();
 }
@@ -139,7 +115,7 @@ __device__ __forceinline__ void select_channels_group(const GroupQueryLds& Q, co
 // Thread tid of STRIDE owns chunks chunk_begin + tid + i * STRIDE (STRIDE < NT: the caller divides the channel
 // rows of a chunk among NT / STRIDE groups of threads).
 template <class T, int G, int STRIDE = NT, class Finish>
-__device__ __forceinline__ void stream_channel_rows_group(const char* Kt_head, size_t row_bytes, const int* chan,
+__device__ __forceinline__ void stream_channel_rows_group(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                           const float* qs, int qs_stride, int r, int chunk_begin,
                                                           int chunk_end, int tid, Finish&& finish) {
   const int n_batches = (r + 7) >> 3;
@@ -153,12 +129,7 @@ __device__ __forceinline__ void stream_channel_rows_group(const char* Kt_head, s
     for (int e = 0; e < 8; ++e) acc[h][e] = 0.0f;
   int ic = 0, ib = 0, cc = 0, cb = 0;
   auto issue_next = [&](uint4 (&v)[8]) {
-    const uint32_t voff = (uint32_t)(chunk_begin + tid + ic * STRIDE) * 16u;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int ch = __builtin_amdgcn_readfirstlane(chan[ib * 8 + t]);
-      v[t] = load16(Kt_head + (size_t)ch * row_bytes + voff);
-    }
+    issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + tid + ic * STRIDE) * 16u), row_bytes, chan + ib * 8);
     if (++ib == n_batches) { ib = 0; ++ic; }
   };
   auto consume_next = [&](const uint4 (&v)[8]) {

@@ -19,6 +19,19 @@ constexpr int kMaxSplit = 16;           // most workgroups one (sequence, head) 
 constexpr int kSplitMaxUnits = 128;     // the digit-bucket plan (few units, long caches) serves at most this many (sequence, head) units
 constexpr int kProbeBlocks = 256 * 8;   // workgroups (of 256 threads) of the bandwidth probes
 
+// n / d for 0 <= n < 2^31, 1 <= d < 2^31, by multiplication: with l = ceil(log2 d) and mul = ceil(2^(31 + l) / d), the error
+// mul d - 2^(31 + l) is below d <= 2^l, so that floor(n mul / 2^(31 + l)) is exact.  (There is no integer division in
+// hardware; the compiler's sequence for it is a chain of some thirty vector instructions in front of a kernel's first loads.)
+struct Divider {
+  uint32_t mul = 0x80000000u, shift = 31;
+};
+inline Divider make_divider(int64_t d) {
+  int l = 0;
+  while (((int64_t)1 << l) < d) ++l;
+  return Divider{(uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d), (uint32_t)(31 + l)};
+}
+__host__ __device__ inline int divided(int n, Divider v) { return (int)(((uint64_t)(uint32_t)n * v.mul) >> v.shift); }
+
 struct DecodeArgs {
   void* K; void* Kt; void* V;                  // written only by the fused-append variant
   const float* v_mean; const int32_t* seq_lens;
@@ -30,6 +43,8 @@ struct DecodeArgs {
   int32_t S_stride;   // positions per head in K and V and per channel row in Kt (the buffers' own S_max, >= S_max)
   uint32_t flags;
   int32_t local_window;
+  int32_t group = 1;                      // query heads per KV head
+  Divider by_H, by_H_kv, by_group;        // set by enqueue_decode, as `group`
   unsigned long long* clocks = nullptr;   // [workgroups][kStageStamps] time stamps; set only by a SPARQ_STAGE_CLOCKS build
 };
 
@@ -69,6 +84,7 @@ constexpr int kMaxSpans = 64;
 
 struct LongArgs {
   DecodeArgs d;
+  Divider by_span;         // by n_span
   int32_t n_span;          // workgroups per (sequence, head) in the scoring launch
   int32_t span_len;        // positions per span
   int32_t cand_cap;        // candidates one span may hand on = min(k, span_len)
@@ -83,6 +99,7 @@ struct LongArgs {
 // grouped-query rule over several workgroups per (sequence, KV head)
 struct GsArgs {
   DecodeArgs d;
+  Divider by_n1, by_n2, by_split;   // by n1, n2 and n_split
   int32_t n1, span1;       // logit spans per KV unit and their length (positions)
   int32_t n2, span2;       // selection spans per KV unit and their length
   int32_t cand_cap;        // candidates one selection span may hand on = min(k, span2)
@@ -110,6 +127,7 @@ struct SplitArgs {
 // digit-bucket plan (few units, long caches): spans of span_len positions, n_span of them per unit
 struct BucketArgs {
   DecodeArgs d;
+  Divider by_span, by_len;   // by n_span and span_len
   int32_t n_span, span_len;
   int32_t cand_cap;        // candidates (keys sharing the threshold digit) that bk_select_gather ranks out of LDS
   float* tmax_ws;          // [B * H][n_span] largest logit numerator of each span

@@ -27,7 +27,8 @@ struct Lds {
   uint32_t* keys;   // [S_max]   stage 1-2: keys; after compaction: selected positions
   SelectLds sel;
   QueryLds qry;
-  float* part;      // [NW * (DH + 2)] stage-3 partials; stage 0: partial ranks (NT words)
+  float* part;      // [NW * (DH + 2)] stage-3 partials
+  float* mean;      // [DH] the mean value vector, parked until the blend
   uint16_t* knew;   // [DH] codes of the key row being appended (one-launch step only)
   uint16_t* vnew;   // [DH]
 };
@@ -37,12 +38,11 @@ __device__ __forceinline__ Lds carve(uint32_t* base, int S_max) {
   Lds l;
   l.keys = base; base += S_max;
   l.sel.hist = base; base += 2 * kRadixBins;
-  l.part = reinterpret_cast<float*>(base);
-  l.qry.rankp = reinterpret_cast<int*>(base); base += NW * (DH + 2);
+  l.part = reinterpret_cast<float*>(base); base += NW * (DH + 2);
   l.qry.qf = reinterpret_cast<float*>(base); base += DH;
   l.qry.qs = reinterpret_cast<float*>(base); base += DH;
   l.qry.chan = reinterpret_cast<int*>(base); base += DH;
-  l.qry.mag = base; base += DH;
+  l.mean = reinterpret_cast<float*>(base); base += DH;
   l.sel.red = reinterpret_cast<float*>(base); base += 32;
   l.sel.wcnt = base; base += 16;
   l.sel.ctl = reinterpret_cast<int*>(base); base += 8;
@@ -84,30 +84,32 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
       const int mine = lens[tid];
       int rank = 0;
       for (int j = 0; j < a.B; ++j) rank += (lens[j] > mine) || (lens[j] == mine && j < tid);
-      if (rank == u / a.H) L.sel.ctl[7] = tid;
+      if (rank == divided(u, a.by_H)) L.sel.ctl[7] = tid;
     }
     __syncthreads();
-    u = L.sel.ctl[7] * a.H + u % a.H;
+    u = L.sel.ctl[7] * a.H + (u - divided(u, a.by_H) * a.H);
   } else if ((U & 7) == 0) {
     u = (u & 7) * (U >> 3) + (u >> 3);
   }
   u = __builtin_amdgcn_readfirstlane(u);   // the same in every lane (also where it came through LDS): keep what follows scalar
-  const int b = u / a.H, h = u - b * a.H;
-  const int hk = h / (a.H / a.H_kv);
+  const int b = divided(u, a.by_H), h = u - b * a.H;
+  const int hk = divided(h, a.by_group);
   const size_t kv_head = (size_t)b * a.H_kv + hk;
 
   // everything the unit reads from small tensors is requested here, in one round trip; the mean value
   // vector is only needed for the blend at the very end
-  uint16_t qcode = 0, kcode = 0, vcode = 0;
+  const LaneCodes<DH> qcode = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(a.q) + (size_t)u * DH, lane);
+  uint16_t kcode = 0, vcode = 0;
   float vm = 0.0f;
-  if (tid < DH) {
-    qcode = reinterpret_cast<const uint16_t*>(a.q)[(size_t)u * DH + tid];
-    vm = a.v_mean[kv_head * DH + tid];
+  const int late = tid - (NT - DH);         // a channel for each thread of the last waves, the first to run out of chunks
+  if (late >= 0) {
+    vm = a.v_mean[kv_head * DH + late];
     if (APPEND) {
-      kcode = reinterpret_cast<const uint16_t*>(a.k_new)[kv_head * DH + tid];
-      vcode = reinterpret_cast<const uint16_t*>(a.v_new)[kv_head * DH + tid];
+      kcode = reinterpret_cast<const uint16_t*>(a.k_new)[kv_head * DH + late];
+      vcode = reinterpret_cast<const uint16_t*>(a.v_new)[kv_head * DH + late];
     }
   }
+  for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
   int S = a.seq_lens[b];
   // a length beyond the bound of this call that the buffers can hold is carried over as it is (clamped only here)
   const int S_kept = (S > a.S_max && S <= a.S_stride) ? S : -1;
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     S = S < 0 ? 0 : a.S_max;
   }
   bool appended = false;                                    // this sequence takes the new row (uniform)
-  const bool owner = APPEND && h == hk * (a.H / a.H_kv);   // writes the row and the new mean
+  const bool owner = APPEND && h == hk * a.group;   // writes the row and the new mean
   if (APPEND) {
     if (S + 1 <= a.S_max) { appended = true; S += 1; }
     else if (tid == 0) atomicOr(a.err, 1);
@@ -133,23 +135,15 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     if (tid == 0) { atomicOr(a.err, 2); if (a.alpha_out) a.alpha_out[u] = 0.0f; }
     if (a.chan_out && tid < a.r) a.chan_out[(size_t)u * a.r + tid] = -1;
     if (idx_out) for (int n = tid; n < a.idx_stride; n += NT) idx_out[n] = -1;
-    if (owner && tid < DH) a.v_mean_next[kv_head * DH + tid] = vm;
+    if (owner && late >= 0) a.v_mean_next[kv_head * DH + late] = vm;
     return;
-  }
-  if (APPEND && appended && tid < DH) {   // same update as append_one_row; the mean of no rows is ignored
-    if (S == 1) vm = 0.0f;
-    vm += (T::widen(vcode) - vm) * (1.0f / (float)S);
   }
 
   // ---------------- stage 0 ----------------
-  for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
-  if (APPEND && tid < DH) { L.knew[tid] = kcode; L.vnew[tid] = vcode; }
-  const float tau = apply_tau_mode(select_channels<T, DH>(L.qry, qcode, a.r, tid, lane, wave), a.flags, DH, a.r);
+  const L1 l1 = select_channels<T, DH>(L.qry, qcode, a.r, lane, wave);
   const Window win = make_window(a.local_window, S, kq);
-  if (tid < DH) L.qry.mag[tid] = __float_as_uint(vm);   // parked in LDS until the blend (the ranking keys are dead)
-  if (a.chan_out && tid < a.r) a.chan_out[(size_t)u * a.r + tid] = L.qry.chan[tid];
   // the newest S mod 8 positions are not in Kt: wave w gets position S_fl + w from its K row (from the
-  // inputs if it is the row being appended); loads issued here, used after stage 1
+  // inputs if it is the row being appended); loads issued behind the stream's first, used after stage 1
   // (in the one-launch step Kt is up to date for the length before this call: the group of 8 that the new
   // row may complete is written during this launch, so up to 8 positions come from rows)
   const int S_fl = ((APPEND && appended) ? S - 1 : S) & ~7, n_tail = S - S_fl, r8 = (a.r + 7) & ~7;
@@ -158,18 +152,28 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
                                  : reinterpret_cast<const uint16_t*>(a.K) + kv_head * a.S_stride * (size_t)DH;
   TailRow tail;
   const bool tail_is_new = APPEND && appended && wave == n_tail - 1;
-  if (wave < n_tail) {
-    if (tail_is_new) tail = tail_row_issue(L.knew, L.qry.chan, r8, lane);
-    else tail = tail_row_issue(K_rows + (size_t)(S_fl + wave) * DH, L.qry.chan, r8, lane);
-  }
 
   SPARQ_STAMP(1);
   // ---------------- stage 1 ----------------
-  const size_t row_bytes = TILED ? 16 : (size_t)a.S_stride * 2;
+  const uint32_t row_bytes = TILED ? 16 : (uint32_t)a.S_stride * 2;
   const char* Kt_head = TILED ? reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2)
                               : reinterpret_cast<const char*>(a.Kt) + kv_head * DH * row_bytes;
-  const float esc = kLog2e / tau;
+  float esc;
   RunningSum zs;
+  auto requested = [&]() {
+    if (late >= 0) {              // (these values arrive after the query: waited for in front of the stream they cost 0.2 us)
+      if (APPEND) { L.knew[late] = kcode; L.vnew[late] = vcode; }
+      if (APPEND && appended) {   // same update as append_one_row; the mean of no rows is ignored
+        if (S == 1) vm = 0.0f;
+        vm += (T::widen(vcode) - vm) * (1.0f / (float)S);
+      }
+      L.mean[late] = vm;
+    }
+    if (wave < n_tail)
+      tail = tail_row_issue(tail_is_new ? reinterpret_cast<const uint16_t*>(a.k_new) + kv_head * DH : K_rows + (size_t)(S_fl + wave) * DH,
+                            L.qry.chan, r8, lane);
+    esc = kLog2e / temperature(l1, a.flags, DH, a.r);
+  };
   auto finish = [&](int c, const float (&acc)[8]) {
     uint32_t kx[8];
     zs.add(acc, esc);
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   };
-  stream_channel_rows<T>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, TILED ? DH * 16u : 16u);
+  stream_channel_rows<T>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, L.qry.qs, r8, lane);
     if (lane == 0) {
@@ -195,20 +199,15 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   if (lane == 0) L.sel.red[wave] = tmax;
   __syncthreads();
   SPARQ_STAMP(3);
-  float dmax = L.sel.red[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, L.sel.red[w]);
+  auto dmax_of = [&]() { return wave_values_max(L.sel.red); };
 
   // ---------------- stage 2 ----------------
-  const float alpha = select_compact<Sums::kNumerator>(L.keys, L.keys, S, win.S_old, win.k_old, dmax, esc, zs.relative_to(dmax, esc),
-                                                       idx_out, a.idx_stride, L.sel, tid, lane, wave, nullptr, 0, nullptr,
-                                                       [&]() { SPARQ_STAMP(4); });
+  const Selection chosen = select_compact<Sums::kNumerator>(L.keys, L.keys, S, win.S_old, win.k_old, dmax_of, esc, zs, idx_out,
+                                                            a.idx_stride, L.sel, tid, lane, wave, nullptr, 0, [&]() { SPARQ_STAMP(4); });
   SPARQ_STAMP(5);
-  if (tid == 0) {
-    if (a.alpha_out) a.alpha_out[u] = alpha;
-    if (idx_out && kq > a.idx_stride) atomicOr(a.err, 4);
-  }
+  if (idx_out && tid == 0 && kq > a.idx_stride) atomicOr(a.err, 4);
   if (idx_out) for (int n = kq + tid; n < a.idx_stride; n += NT) idx_out[n] = -1;
+  if (a.chan_out && tid < a.r) a.chan_out[(size_t)u * a.r + tid] = L.qry.chan[tid];
 
   // ---------------- stage 3 ----------------
   using G = RowGeometry<DH>;
@@ -223,13 +222,17 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   // positions are ascending, so the appended row (position S - 1) can only be the last entry; it is
   // not read back from the cache but taken from the inputs
   const bool new_selected = APPEND && appended && list[kq - 1] == S - 1;
+  float alpha = 0.0f;
+  auto gathering = [&]() {
+    if (tid < DH) alpha = share_of(selected_mass(chosen, L.sel.red, dmax_of(), esc), all_mass(L.sel.red), win.k_old == win.S_old);
+  };
   float m_run = -INFINITY, l_run = 0.0f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (TILED)
-    attend_rows<T, DH, true>(Kt_head, V_head, list, 0, new_selected ? kq - 1 : kq, q8, lane, wave, m_run, l_run, acc,
+    attend_rows<T, DH, true>(Kt_head, V_head, list, 0, new_selected ? kq - 1 : kq, q8, lane, wave, m_run, l_run, acc, gathering,
                              reinterpret_cast<const char*>(K_rows + (size_t)S_fl * DH) + sub * 16, S_fl);
   else
-    attend_rows<T, DH>(K_head, V_head, list, 0, new_selected ? kq - 1 : kq, q8, lane, wave, m_run, l_run, acc);
+    attend_rows<T, DH>(K_head, V_head, list, 0, new_selected ? kq - 1 : kq, q8, lane, wave, m_run, l_run, acc, gathering);
   if (APPEND && new_selected) attend_row_from_codes<T, DH>(L.knew, L.vnew, q8, lane, wave, m_run, l_run, acc);
   SPARQ_STAMP(6);
   store_wave_partial<DH>(m_run, l_run, acc, L.part, lane, wave);
@@ -239,8 +242,9 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     float m_all, l_all, y3;
     combine_partials<DH>(L.part, NW, tid, m_all, l_all, y3);
     y3 /= l_all;
+    if (tid == 0 && a.alpha_out) a.alpha_out[u] = alpha;
     float y = y3;
-    if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * __uint_as_float(L.qry.mag[tid]);
+    if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * L.mean[tid];
     out[tid] = T::narrow(y);
   }
   if (APPEND && owner && tid < DH) {
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     // noise when workgroups come in several rounds, and here is best when they all run at once.)  Nobody
     // reads row S - 1 of K or V in this launch (every head takes it from k_new / v_new), the new mean goes to
     // the *_next buffer, and the columns written to Kt lie above S_fl for every head of the group.
-    a.v_mean_next[kv_head * DH + tid] = __uint_as_float(L.qry.mag[tid]);
+    a.v_mean_next[kv_head * DH + tid] = L.mean[tid];
     if (appended) {
       const uint16_t kc = L.knew[tid];
       reinterpret_cast<uint16_t*>(a.V)[(kv_head * a.S_stride + (S - 1)) * DH + tid] = L.vnew[tid];

@@ -40,18 +40,6 @@ constexpr int kFineLen = kRadixBins + 32;   // entries of a span's table A: A[20
 constexpr int kTopDigit = kRadixBins - 1;   // no finite key has it: float_to_key of the largest float has digit 2043
 constexpr uint32_t kPosMask = 0xfffffu;     // positions < 2^20 (S_max <= 64 spans of 8192)
 
-__device__ __forceinline__ void map_span(int U, int n_span, int& u, int& s) {
-  const int bid = blockIdx.x;
-  if ((U & 7) == 0) {          // the spans of a unit, and the heads of a KV group, share an XCD
-    const int x = bid & 7, slot = bid >> 3;
-    u = x * (U >> 3) + slot / n_span;
-    s = slot % n_span;
-  } else {
-    u = bid / n_span;
-    s = bid % n_span;
-  }
-}
-
 // The bucket of a key: 11 bits that are monotone in the key (which is all the selection needs of a bucket: ranking
 // inside the threshold bucket uses the whole key) and tell the keys around the threshold apart as finely as
 // possible; 2047 stays free for the local window.  A key's own first 11 bits (sign, exponent, two mantissa bits)
@@ -84,17 +72,25 @@ __device__ __forceinline__ uint32_t bucket_digit(uint32_t key) {
 __device__ __forceinline__ void build_span_table(const uint32_t* hist, uint32_t* cur, uint16_t* fine, uint16_t* coarse, int lane) {
   uint32_t cnt[32], mine = 0;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) { cnt[i] = hist[(i << 6) | lane]; mine += cnt[i]; }
+  for (int i = 0; i < 8; ++i) {
+    const uint4 v = *reinterpret_cast<const uint4*>(hist + hist_piece(lane, i));
+    cnt[4 * i] = v.x; cnt[4 * i + 1] = v.y; cnt[4 * i + 2] = v.z; cnt[4 * i + 3] = v.w;
+    mine += (v.x + v.y) + (v.z + v.w);
+  }
   const uint32_t incl = wave_scan_incl(mine);
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
   uint32_t run = total - incl;              // keys with digits owned by higher lanes
   uint32_t packed[16];
 #pragma unroll
   for (int i = 31; i >= 0; --i) {
-    cur[(i << 6) | lane] = run;             // keys with a digit above 32 l + i
+    const uint32_t above = run;             // keys with a digit above 32 l + i: where the digit's own begin
     run += cnt[i];                          // A[32 l + i]
+    cnt[i] = above;
     if (i & 1) packed[i >> 1] = run << 16; else packed[i >> 1] |= run;
   }
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    *reinterpret_cast<uint4*>(cur + hist_piece(lane, i)) = make_uint4(cnt[4 * i], cnt[4 * i + 1], cnt[4 * i + 2], cnt[4 * i + 3]);
   uint4* dst = reinterpret_cast<uint4*>(fine + lane * 32);
 #pragma unroll
   for (int i = 0; i < 4; ++i) dst[i] = make_uint4(packed[4 * i], packed[4 * i + 1], packed[4 * i + 2], packed[4 * i + 3]);
@@ -128,7 +124,7 @@ __device__ __forceinline__ void sort_span_by_digit(const uint32_t* keys, int len
 // LDS words of bk_scores besides the three span-sized arrays
 template <int DH>
 __host__ __device__ constexpr size_t bk_scores_fixed_words() {
-  return 2 * (size_t)kRadixBins + NT + 4 * (size_t)DH + 32 + 8;
+  return 2 * (size_t)kRadixBins + 3 * (size_t)DH + 32 + 8;
 }
 
 // A unit's counter of finished spans starts at 0 for the launch that counts, whatever an earlier call left: calls that
@@ -144,25 +140,23 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   uint32_t* spos = skey + P;                                    // [P] their positions
   uint32_t* hist = spos + P;                                    // [kRadixBins] first-digit counts (swizzled slots)
   uint32_t* cur = hist + kRadixBins;                            // [kRadixBins] write cursors of the digit buckets
-  int* rankp = reinterpret_cast<int*>(cur + kRadixBins);        // [NT]
-  float* qf = reinterpret_cast<float*>(rankp + NT);             // [DH]
+  float* qf = reinterpret_cast<float*>(cur + kRadixBins);       // [DH]
   float* qs = qf + DH;
   int* chan = reinterpret_cast<int*>(qs + DH);
-  uint32_t* mag = reinterpret_cast<uint32_t*>(chan + DH);
-  float* red = reinterpret_cast<float*>(mag + DH);              // [32]
+  float* red = reinterpret_cast<float*>(chan + DH);             // [32]
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int U = d.B * d.H;
   int u, s;
-  map_span(U, a.n_span, u, s);
-  const int b = u / d.H, h = u - b * d.H;
-  const size_t kv_head = (size_t)b * d.H_kv + h / (d.H / d.H_kv);
+  map_span(U, a.n_span, a.by_span, u, s);
+  const int b = divided(u, d.by_H), h = u - b * d.H;
+  const size_t kv_head = (size_t)b * d.H_kv + divided(h, d.by_group);
   const size_t slot = (size_t)u * a.n_span + s;
   uint16_t* fine = a.fine_ws + slot * kFineLen;
   uint16_t* coarse = a.coarse_ws + slot * 64;
 
-  uint16_t qcode = 0;
-  if (tid < DH) qcode = reinterpret_cast<const uint16_t*>(d.q)[(size_t)u * DH + tid];
+  const LaneCodes<DH> qcode = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(d.q) + (size_t)u * DH, lane);
+  for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
   bool appended, bad, full;
   const int S = visible_length(d, b, appended, bad, full);
   if (tid == 0 && s == 0) {
@@ -192,28 +186,32 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   }
   const int len = S - p0 < P ? S - p0 : P;
 
-  for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
-  const QueryLds Q{mag, rankp, qf, qs, chan};
-  const float tau = apply_tau_mode(select_channels<T, DH>(Q, qcode, d.r, tid, lane, wave), d.flags, DH, d.r);
-  if (s == 0) {
-    if (d.chan_out && tid < d.r) d.chan_out[(size_t)u * d.r + tid] = chan[tid];
-    if (tid == 0) a.tau_ws[u] = tau;
-  }
+  const QueryLds Q{qf, qs, chan};
+  const L1 l1 = select_channels<T, DH>(Q, qcode, d.r, lane, wave);
 
   // the newest S mod 8 positions are not in Kt (inside a step: up to 8, Kt being up to date for the length before
   // the call): the span that holds them takes them from the rows of K, the row being appended from the inputs
   const int S_fl = (appended ? S - 1 : S) & ~7, r8 = (d.r + 7) & ~7;
   const int n_tail = (S_fl >= p0 && S_fl < p0 + len) ? S - S_fl : 0;
   TailRow tail;
-  if (wave < n_tail) {
-    const uint16_t* krow = appended && wave == n_tail - 1
-                               ? reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH
-                               : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
-    tail = tail_row_issue(krow, chan, r8, lane);
-  }
+  float tau, esc;
+  auto requested = [&]() {     // behind the stream's first loads
+    if (wave < n_tail) {
+      const uint16_t* krow = appended && wave == n_tail - 1
+                                 ? reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH
+                                 : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
+      tail = tail_row_issue(krow, chan, r8, lane);
+    }
+    tau = temperature(l1, d.flags, DH, d.r);
+    esc = kLog2e / tau;
+    if (s == 0) {
+      if (d.chan_out && tid < d.r) d.chan_out[(size_t)u * d.r + tid] = chan[tid];
+      if (tid == 0) a.tau_ws[u] = tau;
+    }
+  };
 
   const int end = p0 + len < S_fl ? p0 + len : S_fl;     // whole chunks of this span that are in Kt
-  const size_t row_bytes = (size_t)d.S_stride * 2;
+  const uint32_t row_bytes = (uint32_t)d.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
   float tmax = -INFINITY;
   const int c_begin = p0 >> 3, c_end = end > p0 ? end >> 3 : p0 >> 3;
@@ -245,7 +243,7 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
       float4* dst = reinterpret_cast<float4*>(mine + (c * 8 - p0));
       dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
       dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    });
+    }, requested);
     __syncthreads();
     for (int rel = tid * 4; rel < (c_end - c_begin) * 8; rel += NT * 4) {
       float4 d4 = *reinterpret_cast<const float4*>(parts[0] + rel);
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   else stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, c_begin, c_end, tid, [&](int c, const float (&acc)[8]) {
     finish4(c * 8 - p0, make_float4(acc[0], acc[1], acc[2], acc[3]));
     finish4(c * 8 - p0 + 4, make_float4(acc[4], acc[5], acc[6], acc[7]));
-  });
+  }, requested);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, qs, r8, lane);
     tmax = fmaxf(tmax, dot);
@@ -288,7 +286,6 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   if (wave == 0) {
     build_span_table(hist, cur, fine, coarse, lane);
   } else {
-    const float esc = kLog2e / tau;
     float z = 0.0f;
     for (int i = tid - kWave; i < len; i += NT - kWave) z += exp2f((key_to_float(keys[i]) - dmax) * esc);
     z = wave_sum(z);
@@ -322,8 +319,8 @@ __global__ __launch_bounds__(NT, 2) void bk_group_scores(const BucketArgs a) {
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ukv, s;
-  map_span(d.B * d.H_kv, a.n_span, ukv, s);
-  const int b = ukv / d.H_kv, hk = ukv - b * d.H_kv;
+  map_span(d.B * d.H_kv, a.n_span, a.by_span, ukv, s);
+  const int b = divided(ukv, d.by_H_kv), hk = ukv - b * d.H_kv;
   const size_t u0 = (size_t)b * d.H + (size_t)hk * G;
   const size_t slot = (size_t)ukv * a.n_span + s;
   uint16_t* fine = a.fine_ws + slot * kFineLen;
@@ -483,11 +480,11 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int U = d.B * d.H;
   int u, s;
-  map_span(U, a.n_span, u, s);
-  const int b = u / d.H, h = u - b * d.H;
-  const int hk = h / (d.H / d.H_kv);
+  map_span(U, a.n_span, a.by_span, u, s);
+  const int b = divided(u, d.by_H), h = u - b * d.H;
+  const int hk = divided(h, d.by_group);
   const size_t kv_head = (size_t)b * d.H_kv + hk;
-  const bool owner = d.k_new && h == hk * (d.H / d.H_kv);             // its last workgroup writes the appended row and the mean
+  const bool owner = d.k_new && h == hk * d.group;             // its last workgroup writes the appended row and the mean
   const size_t slot = (size_t)u * a.n_span + s;                       // this workgroup's partial and numerator
   const size_t slot0 = (GROUP ? kv_head : (size_t)u) * a.n_span;      // the spans whose tables and sorted arrays it reads
   using G = RowGeometry<DH>;
@@ -508,7 +505,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   }
   float tm = -INFINITY, zs = 0.0f;
   if (GROUP) {         // this head's maximum and sum-exp over each of gs_logits' spans
-    const float* st = a.stat_ws + ((kv_head * a.n1 + lane) * a.group + (h % a.group)) * 2;
+    const float* st = a.stat_ws + ((kv_head * a.n1 + lane) * a.group + (h - hk * d.group)) * 2;
     if (wave == 1 && lane < a.n1) { tm = st[0]; zs = st[1]; }
   } else if (wave == 1 && lane < a.n_span) {
     tm = a.tmax_ws[slot0 + lane]; zs = a.zsum_ws[slot0 + lane];
@@ -532,7 +529,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
     if (tid == 0 && idx_out && kq > d.idx_stride) atomicOr(d.err, 4);
   }
   if (p0 >= S) return;                     // nothing of this sequence lies in this span
-  const int n_live = (S + P - 1) / P;      // spans that have positions
+  const int n_live = divided(S + P - 1, a.by_len);      // spans that have positions
   const int len = S - p0 < P ? S - p0 : P;
 
   // ---- the threshold digit d0: the largest d with N(d) = sum over spans of A_s[d] >= kq ----
@@ -801,13 +798,13 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
 template <class T, int DH>
 __global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
   const DecodeArgs& d = a.d;
-  const int u = blockIdx.x, b = u / d.H, h = u - b * d.H, g = d.H / d.H_kv, hk = h / g;
+  const int u = blockIdx.x, b = divided(u, d.by_H), h = u - b * d.H, hk = divided(h, d.by_group);
   const size_t kv_head = (size_t)b * d.H_kv + hk;
   bool appended, bad, full;
   const int S = visible_length(d, b, appended, bad, full);
   if (S == 0) return;                      // outputs written by the first launch, state by bk_select_gather
   const UnitInputs in = unit_inputs(d, kv_head, true, appended, threadIdx.x, DH);
-  finish_unit<T, DH>(a, u, kv_head, S, appended, d.k_new && h == hk * g, (S + a.span_len - 1) / a.span_len, a.zden_ws[u], threadIdx.x,
+  finish_unit<T, DH>(a, u, kv_head, S, appended, d.k_new && h == hk * d.group, divided(S + a.span_len - 1, a.by_len), a.zden_ws[u], threadIdx.x,
                      threadIdx.x & (kWave - 1), in);
 }
 

@@ -21,22 +21,10 @@ namespace sparq {
 
 namespace {
 
-__device__ __forceinline__ void map_span(int U, int n_span, int& u, int& s) {
-  const int bid = blockIdx.x;
-  if ((U & 7) == 0) {          // the spans of a unit, and the heads of a KV group, share an XCD
-    const int x = bid & 7, slot = bid >> 3;
-    u = x * (U >> 3) + slot / n_span;
-    s = slot % n_span;
-  } else {
-    u = bid / n_span;
-    s = bid % n_span;
-  }
-}
-
 // LDS words of long_scores besides the span's keys
 template <int DH>
 __host__ __device__ constexpr size_t scores_fixed_words() {
-  return 2 * (size_t)kRadixBins + NT + 4 * (size_t)DH + 32 + 16 + 8;
+  return 2 * (size_t)kRadixBins + 3 * (size_t)DH + 32 + 16 + 8;
 }
 
 template <class T, int DH>
@@ -44,24 +32,22 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   uint32_t* keys = smem;                                        // [span_len]
   uint32_t* hist = keys + a.span_len;                           // [2][kRadixBins]
-  int* rankp = reinterpret_cast<int*>(hist + 2 * kRadixBins);   // [NT]
-  float* qf = reinterpret_cast<float*>(rankp + NT);             // [DH]
+  float* qf = reinterpret_cast<float*>(hist + 2 * kRadixBins);  // [DH]
   float* qs = qf + DH;
   int* chan = reinterpret_cast<int*>(qs + DH);
-  uint32_t* mag = reinterpret_cast<uint32_t*>(chan + DH);
-  float* red = reinterpret_cast<float*>(mag + DH);              // [32]
+  float* red = reinterpret_cast<float*>(chan + DH);             // [32]
   uint32_t* wcnt = reinterpret_cast<uint32_t*>(red + 32);       // [16]
   int* ctl = reinterpret_cast<int*>(wcnt + 16);                 // [8]
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int U = d.B * d.H;
   int u, s;
-  map_span(U, a.n_span, u, s);
-  const int b = u / d.H, h = u - b * d.H;
-  const size_t kv_head = (size_t)b * d.H_kv + h / (d.H / d.H_kv);
+  map_span(U, a.n_span, a.by_span, u, s);
+  const int b = divided(u, d.by_H), h = u - b * d.H;
+  const size_t kv_head = (size_t)b * d.H_kv + divided(h, d.by_group);
 
-  uint16_t qcode = 0;
-  if (tid < DH) qcode = reinterpret_cast<const uint16_t*>(d.q)[(size_t)u * DH + tid];
+  const LaneCodes<DH> qcode = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(d.q) + (size_t)u * DH, lane);
+  for (int i = tid; i < 2 * kRadixBins; i += NT) hist[i] = 0u;
   bool appended, bad, full;      // inside a step the row being appended counts as position S_b; long_finish writes it
   const int S = visible_length(d, b, appended, bad, full);
   if (tid == 0 && s == 0 && (bad || full)) atomicOr(d.err, (bad ? 8 : 0) | (full ? 1 : 0));
@@ -87,30 +73,33 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   }
   const int len = S - p0 < a.span_len ? S - p0 : a.span_len;
 
-  for (int i = tid; i < 2 * kRadixBins; i += NT) hist[i] = 0u;
-  const QueryLds Q{mag, rankp, qf, qs, chan};
-  const float tau = apply_tau_mode(select_channels<T, DH>(Q, qcode, d.r, tid, lane, wave), d.flags, DH, d.r);
-  if (s == 0) {
-    if (d.chan_out && tid < d.r) d.chan_out[(size_t)u * d.r + tid] = chan[tid];
-    if (tid == 0) a.tau_ws[u] = tau;
-  }
+  const QueryLds Q{qf, qs, chan};
+  const L1 l1 = select_channels<T, DH>(Q, qcode, d.r, lane, wave);
 
   // the newest S mod 8 positions are not in Kt (inside a step: up to 8, Kt being up to date for the length before the
   // call): the span that holds them takes them from the rows of K, the row being appended from the inputs
   const int S_fl = (appended ? S - 1 : S) & ~7, r8 = (d.r + 7) & ~7;
   const int n_tail = (S_fl >= p0 && S_fl < p0 + len) ? S - S_fl : 0;
   TailRow tail;
-  if (wave < n_tail) {
-    const uint16_t* krow = appended && wave == n_tail - 1
-                               ? reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH
-                               : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
-    tail = tail_row_issue(krow, chan, r8, lane);
-  }
+  float tau, esc;
+  auto requested = [&]() {     // behind the stream's first loads
+    if (wave < n_tail) {
+      const uint16_t* krow = appended && wave == n_tail - 1
+                                 ? reinterpret_cast<const uint16_t*>(d.k_new) + kv_head * DH
+                                 : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
+      tail = tail_row_issue(krow, chan, r8, lane);
+    }
+    tau = temperature(l1, d.flags, DH, d.r);
+    esc = kLog2e / tau;
+    if (s == 0) {
+      if (d.chan_out && tid < d.r) d.chan_out[(size_t)u * d.r + tid] = chan[tid];
+      if (tid == 0) a.tau_ws[u] = tau;
+    }
+  };
 
   const int end = p0 + len < S_fl ? p0 + len : S_fl;     // whole chunks of this span that are in Kt
-  const size_t row_bytes = (size_t)d.S_stride * 2;
+  const uint32_t row_bytes = (uint32_t)d.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
-  const float esc = kLog2e / tau;
   RunningSum zs;
   stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, p0 >> 3, end > p0 ? end >> 3 : p0 >> 3, tid,
                          [&](int c, const float (&acc)[8]) {
@@ -122,7 +111,7 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
     uint4* dst = reinterpret_cast<uint4*>(keys + (c * 8 - p0));
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
-  });
+  }, requested);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, qs, r8, lane);
     if (lane == 0) {
@@ -135,10 +124,7 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   const float tmax = wave_max(zs.ref);
   if (lane == 0) red[wave] = tmax;
   __syncthreads();
-  float dmax = red[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, red[w]);
-  __syncthreads();     // red is reused by the compaction
+  auto dmax_of = [&]() { return wave_values_max(red); };
 
   // the span's own selection: its part of the window unconditionally, and as many of its older positions
   // as the whole sequence may take
@@ -148,13 +134,11 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   const SelectLds sel{hist, wcnt, ctl, red};
   uint32_t* cand_key = a.cand_key_ws + slot * a.cand_cap;
   uint32_t* cand_pos = reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap;
-  float sums[2];
-  select_compact<Sums::kNumerator>(keys, cand_pos, len, n_old, k_old, dmax, esc, zs.relative_to(dmax, esc), nullptr, 0, sel, tid, lane,
-                                   wave, cand_key, p0, sums);
+  select_compact<Sums::kNumerator>(keys, cand_pos, len, n_old, k_old, dmax_of, esc, zs, nullptr, 0, sel, tid, lane, wave, cand_key, p0);
   if (tid == 0) {
     a.cnt_ws[slot] = k_old + (len - n_old);
-    a.tmax_ws[slot] = dmax;
-    a.zsum_ws[slot] = sums[0];
+    a.tmax_ws[slot] = dmax_of();
+    a.zsum_ws[slot] = all_mass(red);
   }
 }
 
@@ -175,11 +159,11 @@ __global__ __launch_bounds__(NT, 4) void long_finish(const LongArgs a) {
   const int U = d.B * d.H;
   int u = blockIdx.x;
   if ((U & 7) == 0) u = (u & 7) * (U >> 3) + (u >> 3);            // the heads of a KV group share an XCD
-  const int b = u / d.H, h = u - b * d.H, hk = h / (d.H / d.H_kv);
+  const int b = divided(u, d.by_H), h = u - b * d.H, hk = divided(h, d.by_group);
   const size_t kv_head = (size_t)b * d.H_kv + hk;
   bool appended, bad, full;
   const int S = visible_length(d, b, appended, bad, full);
-  const bool owner = d.k_new && h == hk * (d.H / d.H_kv);         // writes the row and the new mean
+  const bool owner = d.k_new && h == hk * d.group;         // writes the row and the new mean
   if (d.k_new && h == 0 && tid == 0) {   // a length beyond the bound of this call that the buffers can hold is carried over as it is
     const int S_in = d.seq_lens[b];
     d.seq_lens_next[b] = (S_in > d.S_max && S_in <= d.S_stride) ? S_in : S;
@@ -253,9 +237,9 @@ __global__ __launch_bounds__(NT, 4) void long_finish(const LongArgs a) {
   }
   __syncthreads();
   const SelectLds sel{hist, wcnt, ctl, red};
-  float sums[2];
-  select_compact<Sums::kNumerator>(keys, keys, n_cand, n_free, win.k_old, dmax, esc, 0.0f, nullptr, 0, sel, tid, lane, wave, nullptr, 0, sums);
-  const float alpha = sums[1] / zsum;
+  const Selection chosen = select_compact<Sums::kNumerator>(keys, keys, n_cand, n_free, win.k_old, [&]() { return dmax; }, esc, RunningSum{},
+                                                            nullptr, 0, sel, tid, lane, wave);
+  const float alpha = selected_mass(chosen, red, dmax, esc) / zsum;
   for (int n0 = tid; n0 < kq; n0 += FLY * NT) {   // candidate numbers -> positions, in place
     int pos[FLY];
 #pragma unroll

@@ -24,37 +24,34 @@ template <int DH, int G>
 struct SharedLds {
   uint32_t* keys;      // [S_max]
   SelectLds sel;       // hist [2][kRadixBins], wcnt, ctl, red
-  float* part;         // [NW][G][DH + 2], aliases hist (+ rankp) after the select
-  int* rankp;          // [NT]
+  float* part;         // [NW][G][DH + 2], aliases hist after the select
   float* qf;           // [G][DH]
   float* qs;           // [G][DH] per-head components on the shared channel list (padded, weight 0)
   int* chan;           // [DH]
-  double* magd;        // [DH] group sums of |q|
   float* stat;         // [NW][G][2] and [G][3]
 };
 
 template <int DH, int G>
 __host__ __device__ constexpr size_t shared_part_words() { return (size_t)NW * G * (DH + 2); }
 
-// words after the key array
+// words after the key array (2 DH + up to NT of them unused, as from the time when this kernel ranked channels in LDS: they
+// decide which lengths are served by one workgroup)
 template <int DH, int G>
 __host__ __device__ constexpr size_t shared_fixed_words() {
-  size_t hist_rank = 2 * kRadixBins + NT;
-  if (hist_rank < shared_part_words<DH, G>()) hist_rank = shared_part_words<DH, G>();
-  return hist_rank + 2 * (size_t)G * DH /* qf, qs */ + DH /* chan */ + 2 * DH /* magd */ + 32 + 16 + 8 + NW * G * 2 + G * 4;
+  size_t hist_part = 2 * kRadixBins + NT;
+  if (hist_part < shared_part_words<DH, G>()) hist_part = shared_part_words<DH, G>();
+  return hist_part + 2 * (size_t)G * DH /* qf, qs */ + DH /* chan */ + 2 * DH + 32 + 16 + 8 + NW * G * 2 + G * 4;
 }
 
 template <int DH, int G>
 __device__ __forceinline__ SharedLds<DH, G> carve_shared(uint32_t* base, int S_max) {
   SharedLds<DH, G> l;
   l.keys = base; base += S_max;
-  size_t hist_rank = 2 * kRadixBins + NT;
-  if (hist_rank < shared_part_words<DH, G>()) hist_rank = shared_part_words<DH, G>();
+  size_t hist_part = 2 * kRadixBins;
+  if (hist_part < shared_part_words<DH, G>()) hist_part = shared_part_words<DH, G>();
   l.sel.hist = base;
-  l.rankp = reinterpret_cast<int*>(base + 2 * kRadixBins);
   l.part = reinterpret_cast<float*>(base);
-  base += hist_rank;
-  l.magd = reinterpret_cast<double*>(base); base += 2 * DH;      // 8-byte aligned: all sizes before are even
+  base += hist_part;
   l.qf = reinterpret_cast<float*>(base); base += G * DH;
   l.qs = reinterpret_cast<float*>(base); base += G * DH;
   l.chan = reinterpret_cast<int*>(base); base += DH;
@@ -71,9 +68,12 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   const SharedLds<DH, G> L = carve_shared<DH, G>(smem, a.S_max);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t kv_head = blockIdx.x;                 // (b, hk)
-  const int b = (int)(kv_head / a.H_kv), hk = (int)(kv_head - (size_t)b * a.H_kv);
+  const int b = divided((int)kv_head, a.by_H_kv), hk = (int)(kv_head - (size_t)b * a.H_kv);
   const size_t u0 = (size_t)b * a.H + (size_t)hk * G;   // first query head of the group
 
+  LaneCodes<DH> qcode[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) qcode[h] = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(a.q) + (u0 + h) * DH, lane);
   // Inside sparq_decode_step the row being appended counts as position S_b: it is taken from the inputs, and this workgroup,
   // the only one of its KV head, writes it at the end (an append launch in front took 5-14 us: 128 KV heads
   // at 4000 positions 51 -> 44 us per step, two at 500 19.7 -> 15.0).
@@ -103,15 +103,15 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   // ---------------- stage 0: shared channel set, per-head temperature ----------------
   for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
   float esc[G];        // log2(e) / tau_h
-  const GroupQueryLds GQ{L.rankp, L.qf, L.qs, L.chan, L.magd};
-  select_channels_group<T, DH, G>(GQ, reinterpret_cast<const uint16_t*>(a.q) + u0 * DH, a.r, a.flags, tid, lane, wave, esc);
+  const GroupQueryLds GQ{L.qf, L.qs, L.chan};
+  select_channels_group<T, DH, G>(GQ, qcode, a.r, a.flags, lane, wave, esc);
   if (a.chan_out)
     for (int i = tid; i < G * a.r; i += NT) a.chan_out[u0 * a.r + i] = L.chan[i % a.r];
 
   const Window win = make_window(a.local_window, S, kq);
 
   // ---------------- pass A: per-head max and sum-exp of the approximate logits ----------------
-  const size_t row_bytes = (size_t)a.S_stride * 2;
+  const uint32_t row_bytes = (uint32_t)a.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(a.Kt) + kv_head * DH * row_bytes;
   // whole chunks that are in Kt: the newest S mod 8 positions are not in it yet (inside a step: up to 8, Kt being up to
   // date for the length before the call)
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
 
   // ---------------- stage 2: the kq positions of largest group score ----------------
   int32_t* idx_out = a.idx_out ? a.idx_out + u0 * a.idx_stride : nullptr;
-  select_compact<Sums::kNone>(L.keys, L.keys, S, win.S_old, win.k_old, 0.0f, 0.0f, 0.0f, idx_out, a.idx_stride, L.sel, tid, lane, wave);
+  select_compact<Sums::kNone>(L.keys, L.keys, S, win.S_old, win.k_old, []() { return 0.0f; }, 0.0f, RunningSum{}, idx_out, a.idx_stride, L.sel, tid, lane, wave);
   if (idx_out) {
     if (tid == 0 && kq > a.idx_stride) atomicOr(a.err, 4);
     for (int n = kq + tid; n < a.idx_stride; n += NT) idx_out[n] = -1;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
 #pragma unroll
     for (int h = 0; h < G; ++h) attend_row_from_codes<T, DH>(k_row, v_row, q8[h], lane, wave, m_run[h], l_run[h], acc[h]);
   }
-  __syncthreads();   // hist and rankp are dead: `part` may overwrite them
+  __syncthreads();   // hist is dead: `part` may overwrite them
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     const float a_w = wave_sum(asum[h]);

@@ -16,18 +16,6 @@ namespace sparq {
 
 namespace {
 
-__device__ __forceinline__ void map_kv(int Ukv, int n, int& ukv, int& s) {
-  const int bid = blockIdx.x;
-  if ((Ukv & 7) == 0) {          // the parts of a KV unit share an XCD (an L2)
-    const int x = bid & 7, slot = bid >> 3;
-    ukv = x * (Ukv >> 3) + slot / n;
-    s = slot % n;
-  } else {
-    ukv = bid / n;
-    s = bid % n;
-  }
-}
-
 // Thread groups that share the chunks of a gs_logits span (see there): 4 when a group has a thread per chunk and there are
 // that many batches of 8 channel rows, 2 for spans of up to half as many chunks more with 8 batches, else 1: a second chunk
 // for some threads costs more than the batches in flight give.  Whole decode us by 1 / 2 / 4 groups, 32 heads on 8: 128
@@ -40,17 +28,18 @@ __host__ __device__ constexpr int logit_row_groups(int span1, int n_batches) {
 
 template <class T, int DH, int G>
 __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
-  __shared__ int rankp[NT];
   __shared__ float qf[G * DH], qs[G * DH];
-  __shared__ int chan[DH];
-  __shared__ double magd[DH];
+  __shared__ __align__(16) int chan[DH];
   __shared__ float stat[NW * G * 2];
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ukv, s;
-  map_kv(d.B * d.H_kv, a.n1, ukv, s);
-  const int b = ukv / d.H_kv, hk = ukv - b * d.H_kv;
+  map_span(d.B * d.H_kv, a.n1, a.by_n1, ukv, s);
+  const int b = divided(ukv, d.by_H_kv), hk = ukv - b * d.H_kv;
   const size_t u0 = (size_t)b * d.H + (size_t)hk * G;
+  LaneCodes<DH> qcode[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) qcode[h] = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(d.q) + (u0 + h) * DH, lane);
   bool appended, bad, full;      // inside a step of the digit-bucket plan the row being appended counts as position S_b
   const int S = visible_length(d, b, appended, bad, full);
   if (tid == 0 && s == 0 && (bad || full)) atomicOr(d.err, (bad ? 8 : 0) | (full ? 1 : 0));
@@ -74,8 +63,8 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
   const int len = S - p0 < a.span1 ? S - p0 : a.span1;
 
   float esc[G];
-  const GroupQueryLds GQ{rankp, qf, qs, chan, magd};
-  select_channels_group<T, DH, G>(GQ, reinterpret_cast<const uint16_t*>(d.q) + u0 * DH, d.r, d.flags, tid, lane, wave, esc);
+  const GroupQueryLds GQ{qf, qs, chan};
+  select_channels_group<T, DH, G>(GQ, qcode, d.r, d.flags, lane, wave, esc);
   if (s == 0) {
     if (d.chan_out) for (int i = tid; i < G * d.r; i += NT) d.chan_out[u0 * d.r + i] = chan[i % d.r];
     if (tid == 0) {
@@ -97,7 +86,7 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
   }
 
   const int end = p0 + len < S_fl ? p0 + len : S_fl;     // whole chunks of this span that are in Kt
-  const size_t row_bytes = (size_t)d.S_stride * 2;
+  const uint32_t row_bytes = (uint32_t)d.S_stride * 2;
   const char* Kt_head = reinterpret_cast<const char*>(d.Kt) + kv_head * DH * row_bytes;
   float* z_unit = a.z_ws + u0 * (size_t)d.S_max;
   RunningSum rs[G];
@@ -206,8 +195,8 @@ __global__ __launch_bounds__(NT, 2) void gs_select(const GsArgs a) {
   float* hs = reinterpret_cast<float*>(ctl + 8);                  // [G][2] max, 1 / sum-exp
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ukv, s;
-  map_kv(d.B * d.H_kv, a.n2, ukv, s);
-  const int b = ukv / d.H_kv, hk = ukv - b * d.H_kv;
+  map_span(d.B * d.H_kv, a.n2, a.by_n2, ukv, s);
+  const int b = divided(ukv, d.by_H_kv), hk = ukv - b * d.H_kv;
   const size_t u0 = (size_t)b * d.H + (size_t)hk * G;
   int S = d.seq_lens[b];
   S = S < 0 ? 0 : (S > d.S_max ? d.S_max : S);
@@ -261,8 +250,8 @@ __global__ __launch_bounds__(NT, 2) void gs_select(const GsArgs a) {
   n_old = n_old < 0 ? 0 : (n_old > len ? len : n_old);
   const int k_old = win.k_old < n_old ? win.k_old : n_old;
   const SelectLds sel{hist, wcnt, ctl, red};
-  select_compact<Sums::kNone>(keys, reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap, len, n_old, k_old, 0.0f, 0.0f, 0.0f,
-                              nullptr, 0, sel, tid, lane, wave, a.cand_key_ws + slot * a.cand_cap, p0);
+  select_compact<Sums::kNone>(keys, reinterpret_cast<uint32_t*>(a.cand_pos_ws) + slot * a.cand_cap, len, n_old, k_old, []() { return 0.0f; }, 0.0f,
+                              RunningSum{}, nullptr, 0, sel, tid, lane, wave, a.cand_key_ws + slot * a.cand_cap, p0);
   if (tid == 0) a.cnt_ws[slot] = k_old + (len - n_old);
 }
 
@@ -280,7 +269,7 @@ __global__ __launch_bounds__(NT) void gs_merge(const GsArgs a) {
   float* hs = reinterpret_cast<float*>(off + kMaxSpans + 8);      // [G][2]
   float* asum_w = hs + 2 * G;                                     // [NW][G]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ukv = blockIdx.x, b = ukv / d.H_kv, hk = ukv - b * d.H_kv;
+  const int ukv = blockIdx.x, b = divided(ukv, d.by_H_kv), hk = ukv - b * d.H_kv;
   const size_t u0 = (size_t)b * d.H + (size_t)hk * G;
   int S = d.seq_lens[b];
   S = S < 0 ? 0 : (S > d.S_max ? d.S_max : S);
@@ -323,7 +312,7 @@ __global__ __launch_bounds__(NT) void gs_merge(const GsArgs a) {
   }
   __syncthreads();
   const SelectLds sel{hist, wcnt, ctl, red};
-  select_compact<Sums::kNone>(keys, keys, n_cand, n_free, win.k_old, 0.0f, 0.0f, 0.0f, nullptr, 0, sel, tid, lane, wave);
+  select_compact<Sums::kNone>(keys, keys, n_cand, n_free, win.k_old, []() { return 0.0f; }, 0.0f, RunningSum{}, nullptr, 0, sel, tid, lane, wave);
 
   // candidate numbers -> positions; alpha_h = sum over the selected positions of s-hat_h from the stored logits
   float mh[G], inv_z[G], esc[G], asum[G];
@@ -391,8 +380,8 @@ __global__ __launch_bounds__(NT, 2) void gs_gather(const GsArgs a) {
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ukv, s;
-  map_kv(d.B * d.H_kv, a.n_split, ukv, s);
-  const int b = ukv / d.H_kv, hk = ukv - b * d.H_kv;
+  map_span(d.B * d.H_kv, a.n_split, a.by_split, ukv, s);
+  const int b = divided(ukv, d.by_H_kv), hk = ukv - b * d.H_kv;
   const size_t u0 = (size_t)b * d.H + (size_t)hk * G;
   const size_t kv_head = (size_t)ukv;
   int S = d.seq_lens[b];

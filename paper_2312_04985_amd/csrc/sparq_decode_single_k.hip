@@ -15,7 +15,7 @@ struct Lds1K {
   uint32_t* keys;   // [S_max]
   SelectLds sel;
   QueryLds qry;
-  float* part;      // [NW * (DH + 2)], shares its space with the partial ranks of stage 0
+  float* part;      // [NW * (DH + 2)]
   float* qmask;     // [DH] query with the unselected channels zeroed
 };
 
@@ -24,12 +24,10 @@ __device__ __forceinline__ Lds1K carve_1k(uint32_t* base, int S_max) {
   Lds1K l;
   l.keys = base; base += S_max;
   l.sel.hist = base; base += 2 * kRadixBins;
-  l.part = reinterpret_cast<float*>(base);
-  l.qry.rankp = reinterpret_cast<int*>(base); base += NW * (DH + 2);
+  l.part = reinterpret_cast<float*>(base); base += NW * (DH + 2);
   l.qry.qf = reinterpret_cast<float*>(base); base += DH;
   l.qry.qs = reinterpret_cast<float*>(base); base += DH;
   l.qry.chan = reinterpret_cast<int*>(base); base += DH;
-  l.qry.mag = base; base += DH;
   l.qmask = reinterpret_cast<float*>(base); base += DH;
   l.sel.red = reinterpret_cast<float*>(base); base += 32;
   l.sel.wcnt = base; base += 16;
@@ -37,6 +35,7 @@ __device__ __forceinline__ Lds1K carve_1k(uint32_t* base, int S_max) {
   return l;
 }
 
+// (DH words more than the arrays above take, as this kernel once did: they decide which lengths are refused)
 template <int DH>
 __host__ __device__ constexpr size_t lds_words_1k() {
   return 2 * (size_t)kRadixBins + (size_t)NW * (DH + 2) + 5 * (size_t)DH + 32 + 16 + 8;
@@ -101,10 +100,10 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   const int U = a.B * a.H;
   int u = blockIdx.x;
   if ((U & 7) == 0) u = (u & 7) * (U >> 3) + (u >> 3);   // a contiguous run of units per XCD
-  const int b = u / a.H, h = u - b * a.H;
-  const size_t kv_head = (size_t)b * a.H_kv + h / (a.H / a.H_kv);
+  const int b = divided(u, a.by_H), h = u - b * a.H;
+  const size_t kv_head = (size_t)b * a.H_kv + divided(h, a.by_group);
 
-  const uint16_t qcode = tid < DH ? reinterpret_cast<const uint16_t*>(a.q)[(size_t)u * DH + tid] : (uint16_t)0;
+  const LaneCodes<DH> qcode = load_lane_codes<DH>(reinterpret_cast<const uint16_t*>(a.q) + (size_t)u * DH, lane);
   int S = a.seq_lens[b];
   if (S < 0 || S > a.S_max) {
     if (tid == 0) atomicOr(a.err, 8);
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   // ---------------- stage 0 ----------------
   for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
   if (tid < DH) L.qmask[tid] = 0.0f;
-  const float tau = apply_tau_mode(select_channels<T, DH>(L.qry, qcode, a.r, tid, lane, wave), a.flags, DH, a.r);
+  const float tau = temperature(select_channels<T, DH>(L.qry, qcode, a.r, lane, wave), a.flags, DH, a.r);
   const Window win = make_window(a.local_window, S, kq);
   if (tid < a.r) {
     const int ch = L.qry.chan[tid];
@@ -155,17 +154,13 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   tmax = wave_max(tmax);
   if (lane == 0) L.sel.red[wave] = tmax;
   __syncthreads();
-  float dmax = L.sel.red[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) dmax = fmaxf(dmax, L.sel.red[w]);
+  auto dmax_of = [&]() { return wave_values_max(L.sel.red); };
 
   // ---------------- stage 2 ----------------
-  const float alpha = select_compact<Sums::kBoth>(L.keys, L.keys, S, win.S_old, win.k_old, dmax, kLog2e / tau, 0.0f, idx_out,
-                                                  a.idx_stride, L.sel, tid, lane, wave);
-  if (tid == 0) {
-    if (a.alpha_out) a.alpha_out[u] = alpha;
-    if (idx_out && kq > a.idx_stride) atomicOr(a.err, 4);
-  }
+  const float esc = kLog2e / tau;
+  const Selection chosen = select_compact<Sums::kBoth>(L.keys, L.keys, S, win.S_old, win.k_old, dmax_of, esc, RunningSum{}, idx_out,
+                                                       a.idx_stride, L.sel, tid, lane, wave);
+  if (idx_out && tid == 0 && kq > a.idx_stride) atomicOr(a.err, 4);
   if (idx_out) for (int n = kq + tid; n < a.idx_stride; n += NT) idx_out[n] = -1;
 
   // ---------------- stage 3 ----------------
@@ -176,13 +171,17 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   for (int e = 0; e < 8; ++e) q8[e] = L.qry.qf[sub * 8 + e] * qscale;
   float m_run = -INFINITY, l_run = 0.0f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  attend_rows<T, DH>(K_head, V_head, list, 0, kq, q8, lane, wave, m_run, l_run, acc);
+  float alpha = 0.0f;
+  attend_rows<T, DH>(K_head, V_head, list, 0, kq, q8, lane, wave, m_run, l_run, acc, [&]() {
+    if (tid < DH) alpha = share_of(selected_mass(chosen, L.sel.red, dmax_of(), esc), all_mass(L.sel.red), win.k_old == win.S_old);
+  });
   store_wave_partial<DH>(m_run, l_run, acc, L.part, lane, wave);
   __syncthreads();
   if (tid < DH) {
     float m_all, l_all, y3;
     combine_partials<DH>(L.part, NW, tid, m_all, l_all, y3);
     y3 /= l_all;
+    if (tid == 0 && a.alpha_out) a.alpha_out[u] = alpha;
     float y = y3;
     if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * a.v_mean[kv_head * DH + tid];
     out[tid] = T::narrow(y);

@@ -10,8 +10,8 @@ template <class T, int DH>
 __global__ __launch_bounds__(DH) void split_combine(const SplitArgs a) {
   const DecodeArgs& d = a.d;
   const int u = blockIdx.x, c = threadIdx.x;
-  const int b = u / d.H, h = u - b * d.H;
-  const size_t kv_head = (size_t)b * d.H_kv + h / (d.H / d.H_kv);
+  const int b = divided(u, d.by_H), h = u - b * d.H;
+  const size_t kv_head = (size_t)b * d.H_kv + divided(h, d.by_group);
   const int S = d.seq_lens[b];
   if (S <= 0) return;                      // outputs written by the plan's first launch
   // all partials of this channel in flight at once (n_split <= kMaxSplit)
