@@ -216,19 +216,28 @@ __global__ __launch_bounds__(BT) void append_rows(const AppendArgs a) {
   if (!a.tickets) return;
   if (a.n_split > 1) {
     if (!last_to_arrive(a.tickets + a.B + head, append_arrivals(plan), &last)) return;
-    const int used = run.used;
-    if (tid < DH) {
-      float* vm = a.v_mean + head * DH + tid;
+    // the partial sums dealt to BT / DH groups of threads, 16 in flight each (8 in flight for a channel's one thread: a whole
+    // call of 32 768 rows for one KV head 25.3 us, so 22.9)
+    constexpr int NG = BT / DH, FLY = 16;
+    const int used = run.used, c = tid % DH, g = tid / DH;
+    const double* part = a.part_ws + head * a.n_split * DH + c;
+    double tot = 0.0;
+    for (int s0 = g; s0 < used; s0 += NG * FLY) {
+      double v[FLY];
+#pragma unroll
+      for (int t = 0; t < FLY; ++t) v[t] = load_agent(part + (size_t)(s0 + t * NG < used ? s0 + t * NG : used - 1) * DH);
+#pragma unroll
+      for (int t = 0; t < FLY; ++t) tot += s0 + t * NG < used ? v[t] : 0.0;
+    }
+    if (NG > 1) {
+      colsum[g][c] = tot;
+      __syncthreads();
+    }
+    if (g == 0) {
+      float* vm = a.v_mean + head * DH + c;
       const double before = S > 0 ? (double)S * (double)*vm : 0.0;
-      const double* part = a.part_ws + head * a.n_split * DH + tid;
-      double tot = 0.0;
-      for (int s0 = 0; s0 < used; s0 += 8) {                           // eight partials in flight
-        double v[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = s0 + t < used ? load_agent(part + (size_t)(s0 + t) * DH) : 0.0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) tot += v[t];
-      }
+      for (int o = 1; o < NG; ++o) tot += colsum[o][c];
       *vm = (float)((before + tot) / (double)(S + n));
     }
   }
@@ -310,27 +319,38 @@ __global__ __launch_bounds__(BT) void append_rows_short(const AppendArgs a) {
 
 // The means and lengths after append_rows over several workgroups per KV head: one workgroup per (sequence, KV head).
 // The old length and the row count come from the workspace: seq_lens is written here.
-template <int DH>
-__global__ __launch_bounds__(BT) void append_finish(const AppendArgs a) {
-  constexpr int NG = BT / DH;
+// Bound by memory latency: the lengths, the old mean and the partial sums are requested together, the partial sums of
+// workgroups that had no rows among them (never written, and left out).  THREADS = 1024 where a KV head has more than 16
+// partial sums, so that all 128 at most are in flight at once (THREADS / DH groups of 16).  (With 8 per thread in flight behind the
+// lengths, a whole call: 31 777 rows for 8 KV heads 70.4 us, so 67.4.)
+template <int DH, int THREADS>
+__global__ __launch_bounds__(THREADS) void append_finish(const AppendArgs a) {
+  constexpr int NG = THREADS / DH, FLY = 16;
   __shared__ double sm[NG][DH];
   const int c = threadIdx.x % DH, grp = threadIdx.x / DH;
   const size_t head = blockIdx.x;
   const int b = (int)(head / a.H_kv);
   const int2 sn = a.span_ws[head];
+  float* vm = a.v_mean + head * DH + c;
+  const float old = *vm;
+  const double* part = a.part_ws + head * a.n_split * DH + c;
+  double v[FLY];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int t = 0; t < FLY; ++t) v[t] = s0 + t * NG < a.n_split ? part[(size_t)(s0 + t * NG) * DH] : 0.0;
+  };
+  fetch(grp);
   const int S = sn.x, n = sn.y;
   if (n == 0) return;
-  float* vm = a.v_mean + head * DH + c;
-  const double before = S > 0 ? (double)S * (double)*vm : 0.0;     // S = 0: whatever the buffer held is ignored
+  const double before = S > 0 ? (double)S * (double)old : 0.0;     // S = 0: whatever the buffer held is ignored
   const int used = append_run(S, n, 0, AppendSplit{a.n_split, a.tiles_per_split}, DH).used;   // workgroups that had rows
-  const double* part = a.part_ws + head * a.n_split * DH + c;
   double tot = 0.0;
-  for (int s0 = grp; s0 < used; s0 += NG * 8) {                    // eight partials in flight
-    double v[8];
+  for (int s0 = grp;;) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = s0 + t * NG < used ? part[(size_t)(s0 + t * NG) * DH] : 0.0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) tot += v[t];
+    for (int t = 0; t < FLY; ++t) tot += s0 + t * NG < used ? v[t] : 0.0;
+    s0 += NG * FLY;
+    if (s0 >= used) break;
+    fetch(s0);
   }
   sm[grp][c] = tot;
   __syncthreads();
@@ -581,7 +601,8 @@ hipError_t launch_rows_dh(const AppendArgs& args, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (!a.tiled && a.n_split > 1) hipLaunchKernelGGL(append_finish<DH>, dim3(heads), dim3(BT), 0, s, a);
+  if (!a.tiled && a.n_split > 16) hipLaunchKernelGGL((append_finish<DH, 1024>), dim3(heads), dim3(1024), 0, s, a);
+  else if (!a.tiled && a.n_split > 1) hipLaunchKernelGGL((append_finish<DH, BT>), dim3(heads), dim3(BT), 0, s, a);
   else hipLaunchKernelGGL(bump_seq_lens, dim3((a.B + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
 }

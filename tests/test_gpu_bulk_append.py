@@ -72,3 +72,26 @@ def test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, scratch, h
 def test_short_append_for_many_heads(d_h, dtype, start, rows):
     """768 KV heads and up to 64 rows: one workgroup per KV head, whatever d_h."""
     test_bulk_append_over_several_workgroups(d_h, dtype, start, rows, None, 256, s_max=192)
+
+
+@pytest.mark.parametrize("d_h,dtype", [(64, "f16"), (128, "bf16"), (256, "f16")])
+@pytest.mark.parametrize("h_kv,tiles", [(1, 16), (1, 17), (1, 65), (1, 96),         # one launch: up to 192 workgroups
+                                        (7, 16), (7, 17), (7, 64), (7, 65), (7, 128)])
+def test_many_partial_sums_per_head(d_h, dtype, h_kv, tiles):
+    """Around the numbers of partial sums that one round of loads takes; the second sequence leaves most workgroups without rows."""
+    rows = tiles * (16384 // d_h) - 63                    # append_split: that many tiles of 16384 / d_h positions
+    print("[case]", d_h, dtype, h_kv, tiles, rows, flush=True)
+    w = W.Workload("sums", 2, h_kv, h_kv, d_h, W.round_up(rows + 64, 64), 16, 32, dtype, seed=930 + d_h + tiles)
+    c = DecodeCache(2, h_kv, h_kv, w.S, d_h, 16, 32, w.torch_dtype)
+    k, v = W.draw_kv(w, "cuda", n_rows=rows, v_offset=True)
+    done = torch.zeros(2, dtype=torch.long)
+    for counts in ((5, 3), (rows, 70)):
+        c.append(k, v, torch.tensor(counts, dtype=torch.int32, device="cuda"))
+        for b, n in enumerate(counts):
+            s, e = int(done[b]), int(done[b]) + n
+            assert torch.equal(c.K[b, :, s:e], k[b, :, :n]) and torch.equal(c.V[b, :, s:e], v[b, :, :n])
+            mean = c.V[b, :, :e].double().mean(1)
+            assert (c.v_mean[b].double() - mean).abs().max().item() <= MEAN_TOL
+            done[b] = e
+    assert c.seq_lens.cpu().tolist() == done.tolist() and c.error_flags() == 0
+    assert c.workspace[256:16384].count_nonzero() == 0
