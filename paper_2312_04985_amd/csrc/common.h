@@ -74,6 +74,9 @@ __device__ __forceinline__ float key_to_float(uint32_t k) {
 // out as denormals; a softmax weight that small adds nothing to a sum whose largest term is 1.
 __device__ __forceinline__ float exp2_weight(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// log2 of a number that is no denormal, as the hardware's one instruction (log2f() scales denormals first).
+__device__ __forceinline__ float log2_normal(float x) { return __builtin_amdgcn_logf(x); }
+
 // ---- wave64 primitives (DPP: no LDS traffic, a few cycles each) ----
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {

@@ -223,9 +223,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   }
 
   // ---------------- stage 3: one gather for the G heads ----------------
-  using Geo = RowGeometry<DH>;
-  constexpr int UNR = 2, GROUP = Geo::RPI * UNR;
-  const int sub = lane % Geo::LPR, slot = wave * Geo::RPW + lane / Geo::LPR;
+  const int sub = lane % RowGeometry<DH>::LPR;
   const int* list = reinterpret_cast<const int*>(L.keys);
   const char* K_head = reinterpret_cast<const char*>(a.K) + kv_head * a.S_stride * (size_t)(DH * 2) + sub * 16;
   const char* V_head = reinterpret_cast<const char*>(a.V) + kv_head * a.S_stride * (size_t)(DH * 2) + sub * 16;
@@ -244,58 +242,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   }
   // positions are ascending: the appended row can only be the last entry
   const bool new_selected = appended && list[kq - 1] == S - 1;
-  const int n_rows = kq - (new_selected ? 1 : 0), n_groups = (n_rows + GROUP - 1) / GROUP;
-  auto issue = [&](uint4 (&kr)[UNR], uint4 (&vr)[UNR], int g) {
-#pragma unroll
-    for (int t = 0; t < UNR; ++t) {
-      const int n = g * GROUP + t * Geo::RPI + slot;
-      const uint32_t off = (uint32_t)list[n < n_rows ? n : n_rows - 1] * (uint32_t)(DH * 2);
-      kr[t] = load16(K_head + off);
-      vr[t] = load16(V_head + off);
-    }
-  };
-  auto consume = [&](const uint4 (&kr)[UNR], const uint4 (&vr)[UNR], int g) {
-#pragma unroll
-    for (int t = 0; t < UNR; ++t) {
-      const bool ok = g * GROUP + t * Geo::RPI + slot < n_rows;
-      float kf[8], vf[8];
-      unpack8<T>(kr[t], kf);
-      unpack8<T>(vr[t], vf);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float dot = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dot = fmaf(kf[e], q8[h][e], dot);
-        dot = lanes_sum<Geo::LPR>(dot);
-        if (ok) {
-          const float m_new = fmaxf(m_run[h], dot);
-          const float sc = exp2f(m_run[h] - m_new), pr = exp2f(dot - m_new);
-          l_run[h] = l_run[h] * sc + pr;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[h][e] = acc[h][e] * sc + pr * vf[e];
-          m_run[h] = m_new;
-        }
-      }
-    }
-  };
-  if (n_groups > 0) {
-    uint4 ka[UNR], va[UNR], kb2[UNR], vb2[UNR];
-    issue(ka, va, 0);
-    int g = 0;
-    for (; g + 2 < n_groups; g += 2) {
-      issue(kb2, vb2, g + 1);
-      consume(ka, va, g);
-      issue(ka, va, g + 2);
-      consume(kb2, vb2, g + 1);
-    }
-    if (g + 1 < n_groups) {
-      issue(kb2, vb2, g + 1);
-      consume(ka, va, g);
-      consume(kb2, vb2, g + 1);
-    } else {
-      consume(ka, va, g);
-    }
-  }
+  attend_rows_group<T, DH, G>(K_head, V_head, list, 0, kq - (new_selected ? 1 : 0), q8, lane, wave, m_run, l_run, acc);
   if (new_selected) {
 #pragma unroll
     for (int h = 0; h < G; ++h) attend_row_from_codes<T, DH>(k_row, v_row, q8[h], lane, wave, m_run[h], l_run[h], acc[h]);

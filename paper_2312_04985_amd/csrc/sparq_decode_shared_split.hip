@@ -394,9 +394,7 @@ __global__ __launch_bounds__(NT, 2) void gs_gather(const GsArgs a) {
   const int n0 = s * per < kq ? s * per : kq;
   const int n1 = n0 + per < kq ? n0 + per : kq;
 
-  using Geo = RowGeometry<DH>;
-  constexpr int UNR = 2, GROUP = Geo::RPI * UNR;
-  const int sub = lane % Geo::LPR, slot = wave * Geo::RPW + lane / Geo::LPR;
+  const int sub = lane % RowGeometry<DH>::LPR;
   const int* list = a.list_ws + (size_t)ukv * a.list_stride;
   const char* K_head = reinterpret_cast<const char*>(d.K) + kv_head * d.S_stride * (size_t)(DH * 2) + sub * 16;
   const char* V_head = reinterpret_cast<const char*>(d.V) + kv_head * d.S_stride * (size_t)(DH * 2) + sub * 16;
@@ -410,58 +408,7 @@ __global__ __launch_bounds__(NT, 2) void gs_gather(const GsArgs a) {
     for (int e = 0; e < 8; ++e) { q8[h][e] = f[e] * qscale; acc[h][e] = 0.0f; }
     m_run[h] = -INFINITY; l_run[h] = 0.0f;
   }
-  const int n_groups = (n1 - n0 + GROUP - 1) / GROUP;
-  auto issue = [&](uint4 (&kr)[UNR], uint4 (&vr)[UNR], int g) {
-#pragma unroll
-    for (int t = 0; t < UNR; ++t) {
-      const int n = n0 + g * GROUP + t * Geo::RPI + slot;
-      const uint32_t off = (uint32_t)list[n < n1 ? n : n1 - 1] * (uint32_t)(DH * 2);
-      kr[t] = load16(K_head + off);
-      vr[t] = load16(V_head + off);
-    }
-  };
-  auto consume = [&](const uint4 (&kr)[UNR], const uint4 (&vr)[UNR], int g) {
-#pragma unroll
-    for (int t = 0; t < UNR; ++t) {
-      const bool ok = n0 + g * GROUP + t * Geo::RPI + slot < n1;
-      float kf[8], vf[8];
-      unpack8<T>(kr[t], kf);
-      unpack8<T>(vr[t], vf);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float dot = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dot = fmaf(kf[e], q8[h][e], dot);
-        dot = lanes_sum<Geo::LPR>(dot);
-        if (ok) {
-          const float m_new = fmaxf(m_run[h], dot);
-          const float sc = exp2f(m_run[h] - m_new), pr = exp2f(dot - m_new);
-          l_run[h] = l_run[h] * sc + pr;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[h][e] = acc[h][e] * sc + pr * vf[e];
-          m_run[h] = m_new;
-        }
-      }
-    }
-  };
-  if (n_groups > 0) {
-    uint4 ka[UNR], va[UNR], kb2[UNR], vb2[UNR];
-    issue(ka, va, 0);
-    int g = 0;
-    for (; g + 2 < n_groups; g += 2) {
-      issue(kb2, vb2, g + 1);
-      consume(ka, va, g);
-      issue(ka, va, g + 2);
-      consume(kb2, vb2, g + 1);
-    }
-    if (g + 1 < n_groups) {
-      issue(kb2, vb2, g + 1);
-      consume(ka, va, g);
-      consume(kb2, vb2, g + 1);
-    } else {
-      consume(ka, va, g);
-    }
-  }
+  attend_rows_group<T, DH, G>(K_head, V_head, list, n0, n1, q8, lane, wave, m_run, l_run, acc);
 #pragma unroll
   for (int h = 0; h < G; ++h)
     store_wave_partial<DH>(m_run[h], l_run[h], acc[h], part + h * (DH + 2), lane, wave * G);   // part[wave][h]
