@@ -190,36 +190,33 @@ __device__ __forceinline__ void wave_top_r(const K (&key)[E], int r, bool (&sel)
   for (int e = 0; e < E; ++e) { before[e] = b; b += sel[e] ? 1 : 0; }
 }
 
-// Every wave selects for itself on the 15-bit magnitude codes in its registers (bound by the latency of about ten rounds of
-// compare, ballot and count), the first wave writes the list and the query: one barrier, which also publishes whatever the
-// caller wrote to LDS before the call.  (Ranking by counting larger keys in LDS, the comparisons dealt out over the
-// workgroup, took three barriers and 1.0 us of a call, this 0.7.)  The list is padded to a multiple of 8 with the last
-// channel at weight 0, so that Step 1b works on whole batches of 8 rows.  Returns the lane's shares of the L1 norms, which the
-// caller turns into the temperature (temperature(); the same in every wave) when the first loads of Step 1b are under way.
-struct L1 {
-  float all, sel;
-};
+// The first wave selects, on the 15-bit magnitude codes in its registers (about ten rounds of compare, ballot and count), and
+// writes the list, the query and the L1 norms of all and of the selected components (sums[0..1]): one barrier, which also
+// publishes whatever the caller wrote to LDS before the call.  The caller turns the norms into the temperature when the first
+// loads of Step 1b are under way.  The list is padded to a multiple of 8 with the last channel at weight 0, so that Step 1b
+// works on whole batches of 8 rows.
+// (Ranking by counting larger keys in LDS, the comparisons dealt out over the workgroup, took three barriers and 1.0 us of a
+// call, every wave selecting for itself 0.7: the two waves of a SIMD take turns, so that one wave is done sooner.  Per
+// step, every wave / the first: one head at 1024 positions 9.65 / 9.45 us, 32 heads at 3981 19.1 / 18.8, 32 heads on 8 KV heads
+// at 32 768 32.2 / 31.8, under the group rule 35.9 / 35.3; nothing where workgroups fill the chip.)
 template <class T, int DH>
-__device__ __forceinline__ L1 select_channels(const QueryLds& Q, const LaneCodes<DH>& q, int r, int lane, int wave) {
+__device__ __forceinline__ void select_channels(const QueryLds& Q, const LaneCodes<DH>& q, int r, float* sums, int lane, int wave) {
   constexpr int E = DH / kWave;
-  uint32_t mag[E];
-  float qv[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) { mag[e] = q.c[e] & 0x7fffu; qv[e] = T::widen((uint16_t)q.c[e]); }
-  bool sel[E];
-  int at[E];
-  wave_top_r<E, 15>(mag, r, sel, at);
-  float l1a = 0.0f, l1s = 0.0f;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const float aq = fabsf(qv[e]);
-    l1a += aq; l1s += sel[e] ? aq : 0.0f;
-  }
   if (wave == 0) {
+    uint32_t mag[E];
+    float qv[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) { mag[e] = q.c[e] & 0x7fffu; qv[e] = T::widen((uint16_t)q.c[e]); }
+    bool sel[E];
+    int at[E];
+    wave_top_r<E, 15>(mag, r, sel, at);
+    float l1a = 0.0f, l1s = 0.0f;
     const int r8 = (r + 7) & ~7;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int j = lane * E + e;
+      const float aq = fabsf(qv[e]);
+      l1a += aq; l1s += sel[e] ? aq : 0.0f;
       Q.qf[j] = qv[e];
       if (sel[e]) {
         Q.chan[at[e]] = j; Q.qs[at[e]] = qv[e];
@@ -227,20 +224,21 @@ __device__ __forceinline__ L1 select_channels(const QueryLds& Q, const LaneCodes
           for (int pp = r; pp < r8; ++pp) { Q.chan[pp] = j; Q.qs[pp] = 0.0f; }
       }
     }
+    l1a = wave_sum(l1a); l1s = wave_sum(l1s);
+    if (lane == 0) { sums[0] = l1a; sums[1] = l1s; }
   }
   __syncthreads();
-  return L1{l1a, l1s};
 }
 
 // The temperature actually used: Eq. (9), or one of the two fixed values of the ablation in Section 5.3
-// (flag bits 3 and 4).  Executed by whole waves.
+// (flag bits 3 and 4).
 __device__ __forceinline__ float apply_tau_mode(float tau_l1, uint32_t flags, int d_h, int r) {
   if (flags & 8u) return sqrtf((float)d_h);
   if (flags & 16u) return sqrtf((float)r);
   return tau_l1;
 }
-__device__ __forceinline__ float temperature(const L1& l1, uint32_t flags, int d_h, int r) {
-  const float all = wave_sum(l1.all), sel = wave_sum(l1.sel);
+__device__ __forceinline__ float temperature(const float* sums, uint32_t flags, int d_h, int r) {
+  const float all = sums[0], sel = sums[1];
   return apply_tau_mode(all > 0.0f ? sqrtf((float)d_h * sel / all) : sqrtf((float)d_h), flags, d_h, r);
 }
 
@@ -280,10 +278,12 @@ __device__ __forceinline__ void issue_rows(uint4 (&v)[8], const char* base, uint
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
 // 8 sums of chunk c.  requested() is called by whole waves once their first two batches of loads are under way: work that
 // Step 1b does not wait for.  No barrier.
+// ROW_BY_ROW keeps the compiler from widening the codes of several rows ahead, for callers whose registers do not hold that (it
+// costs 1-2 % of a call of few units where they do).
 // Addressing: chunk c of channel row j lies at Kt_head + j * row_bytes + c * chunk_bytes.  The S-contiguous
 // key copy has row_bytes = 2 S_max and chunk_bytes = 16; the tiled single-copy layout (tiles of 8 positions,
 // channel-major inside a tile) has row_bytes = 16 and chunk_bytes = 16 d_h.
-template <class T, int STRIDE = NT, class Finish, class Requested>
+template <class T, int STRIDE = NT, bool ROW_BY_ROW = false, class Finish, class Requested>
 __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                     const float* qs, int r, int chunk_begin, int chunk_end,
                                                     int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
@@ -305,6 +305,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
       unpack8<T>(v[t], f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = fmaf(f[e], qv, acc[e]);
+      if (ROW_BY_ROW) __builtin_amdgcn_sched_barrier(0);
     }
     if (++cb == n_batches) {
       finish(chunk_begin + tid + cc * STRIDE, acc);
@@ -399,7 +400,7 @@ struct SelectLds {
   uint32_t* hist;   // [2][kRadixBins] double-buffered digit histograms (swizzled slots)
   uint32_t* wcnt;   // [NW] wave totals of the compaction scan
   int* ctl;         // [8]
-  float* red;       // [4 * NW]: the callers' maxima of the waves, then select_compact's sums
+  float* red;       // [4 * NW]: the callers' maxima of the waves, then select_compact's sums ([30..31]: select_channels' until then)
 };
 
 // Exclusive prefix sum of v over the workgroup in thread order; *total gets the sum.

@@ -59,24 +59,24 @@ struct GroupQueryLds {
 
 // Step 1a under the group rule: channel j is ranked by sum_h |q_h,j| (fp64, heads in order, ties to the lower
 // channel); esc[h] = log2(e) / tau_h with tau_h from Eq. (9) on the shared channel set (or the fixed
-// temperature the flags ask for).  q: the codes of the group's queries.  As select_channels: every
-// wave selects for itself, one barrier, which also publishes whatever the caller wrote to LDS before the call.
+// temperature the flags ask for).  q: the codes of the group's queries.  As select_channels: by the
+// first wave, one barrier, which also publishes whatever the caller wrote to LDS before the call.  out: [G] floats of LDS.
 template <class T, int DH, int G>
 __device__ __forceinline__ void select_channels_group(const GroupQueryLds& Q, const LaneCodes<DH> (&q)[G], int r, uint32_t flags,
-                                                      int lane, int wave, float (&esc)[G]) {
+                                                      float* out, int lane, int wave, float (&esc)[G]) {
   constexpr int E = DH / kWave;
-  uint64_t mag[E];                                                        // sums >= 0: their bits order like they do
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    double m = 0.0;
-#pragma unroll
-    for (int h = 0; h < G; ++h) m += (double)fabsf(T::widen((uint16_t)q[h].c[e]));   // head order, as in the definition
-    mag[e] = (uint64_t)__double_as_longlong(m);
-  }
-  bool sel[E];
-  int at[E];
-  wave_top_r<E, 63>(mag, r, sel, at);
   if (wave == 0) {
+    uint64_t mag[E];                                                        // sums >= 0: their bits order like they do
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      double m = 0.0;
+#pragma unroll
+      for (int h = 0; h < G; ++h) m += (double)fabsf(T::widen((uint16_t)q[h].c[e]));   // head order, as in the definition
+      mag[e] = (uint64_t)__double_as_longlong(m);
+    }
+    bool sel[E];
+    int at[E];
+    wave_top_r<E, 63>(mag, r, sel, at);
     const int r8 = (r + 7) & ~7;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -95,20 +95,22 @@ __device__ __forceinline__ void select_channels_group(const GroupQueryLds& Q, co
           }
       }
     }
-  }
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float l1a = 0.0f, l1s = 0.0f;
+    for (int h = 0; h < G; ++h) {
+      float l1a = 0.0f, l1s = 0.0f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const float aq = fabsf(T::widen((uint16_t)q[h].c[e]));
-      l1a += aq; l1s += sel[e] ? aq : 0.0f;
+      for (int e = 0; e < E; ++e) {
+        const float aq = fabsf(T::widen((uint16_t)q[h].c[e]));
+        l1a += aq; l1s += sel[e] ? aq : 0.0f;
+      }
+      const float all = wave_sum(l1a), part = wave_sum(l1s);
+      const float tau = part > 0.0f ? sqrtf((float)DH * part / all) : sqrtf((float)DH);   // all logits 0 then
+      if (lane == 0) out[h] = kLog2e / apply_tau_mode(tau, flags, DH, r);
     }
-    const float all = wave_sum(l1a), part = wave_sum(l1s);
-    const float tau = part > 0.0f ? sqrtf((float)DH * part / all) : sqrtf((float)DH);   // all logits 0 then
-    esc[h] = kLog2e / apply_tau_mode(tau, flags, DH, r);
   }
   __syncthreads();
+#pragma unroll
+  for (int h = 0; h < G; ++h) esc[h] = out[h];
 }
 
 // Step 1b for G heads at once: like stream_channel_rows, every loaded 16-byte chunk feeds G accumulators.

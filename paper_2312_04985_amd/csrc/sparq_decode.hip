@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   }
 
   // ---------------- stage 0 ----------------
-  const L1 l1 = select_channels<T, DH>(L.qry, qcode, a.r, lane, wave);
+  select_channels<T, DH>(L.qry, qcode, a.r, L.sel.red + 30, lane, wave);
   const Window win = make_window(a.local_window, S, kq);
   // the newest S mod 8 positions are not in Kt: wave w gets position S_fl + w from its K row (from the
   // inputs if it is the row being appended); loads issued behind the stream's first, used after stage 1
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     if (wave < n_tail)
       tail = tail_row_issue(tail_is_new ? reinterpret_cast<const uint16_t*>(a.k_new) + kv_head * DH : K_rows + (size_t)(S_fl + wave) * DH,
                             L.qry.chan, r8, lane);
-    esc = kLog2e / temperature(l1, a.flags, DH, a.r);
+    esc = kLog2e / temperature(L.sel.red + 30, a.flags, DH, a.r);
   };
   auto finish = [&](int c, const float (&acc)[8]) {
     uint32_t kx[8];
@@ -184,7 +184,9 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   };
-  stream_channel_rows<T>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
+  // (row by row in bf16, which has no fused multiply-add on 16-bit codes: with codes widened ahead 28 bytes per lane went to
+  // scratch memory, 512 ragged heads of 256 channels 188 -> 198 us per step)
+  stream_channel_rows<T, NT, std::is_same<T, BF16>::value>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, L.qry.qs, r8, lane);
     if (lane == 0) {

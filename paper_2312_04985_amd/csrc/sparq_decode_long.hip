@@ -74,7 +74,7 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
   const int len = S - p0 < a.span_len ? S - p0 : a.span_len;
 
   const QueryLds Q{qf, qs, chan};
-  const L1 l1 = select_channels<T, DH>(Q, qcode, d.r, lane, wave);
+  select_channels<T, DH>(Q, qcode, d.r, red + 30, lane, wave);
 
   // the newest S mod 8 positions are not in Kt (inside a step: up to 8, Kt being up to date for the length before the
   // call): the span that holds them takes them from the rows of K, the row being appended from the inputs
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(NT, 4) void long_scores(const LongArgs a) {
                                  : reinterpret_cast<const uint16_t*>(d.K) + (kv_head * d.S_stride + S_fl + wave) * (size_t)DH;
       tail = tail_row_issue(krow, chan, r8, lane);
     }
-    tau = temperature(l1, d.flags, DH, d.r);
+    tau = temperature(red + 30, d.flags, DH, d.r);
     esc = kLog2e / tau;
     if (s == 0) {
       if (d.chan_out && tid < d.r) d.chan_out[(size_t)u * d.r + tid] = chan[tid];

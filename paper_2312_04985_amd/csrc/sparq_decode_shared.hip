@@ -104,7 +104,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
   for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
   float esc[G];        // log2(e) / tau_h
   const GroupQueryLds GQ{L.qf, L.qs, L.chan};
-  select_channels_group<T, DH, G>(GQ, qcode, a.r, a.flags, lane, wave, esc);
+  select_channels_group<T, DH, G>(GQ, qcode, a.r, a.flags, L.sel.red, lane, wave, esc);
   if (a.chan_out)
     for (int i = tid; i < G * a.r; i += NT) a.chan_out[u0 * a.r + i] = L.chan[i % a.r];
 

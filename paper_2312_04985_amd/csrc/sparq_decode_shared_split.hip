@@ -30,7 +30,7 @@ template <class T, int DH, int G>
 __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
   __shared__ float qf[G * DH], qs[G * DH];
   __shared__ __align__(16) int chan[DH];
-  __shared__ float stat[NW * G * 2];
+  __shared__ float stat[NW * G * 2], esc_all[G];
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ukv, s;
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(NT, 2) void gs_logits(const GsArgs a) {
 
   float esc[G];
   const GroupQueryLds GQ{qf, qs, chan};
-  select_channels_group<T, DH, G>(GQ, qcode, d.r, d.flags, lane, wave, esc);
+  select_channels_group<T, DH, G>(GQ, qcode, d.r, d.flags, esc_all, lane, wave, esc);
   if (s == 0) {
     if (d.chan_out) for (int i = tid; i < G * d.r; i += NT) d.chan_out[u0 * d.r + i] = chan[i % d.r];
     if (tid == 0) {

@@ -125,7 +125,8 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   // ---------------- stage 0 ----------------
   for (int i = tid; i < 2 * kRadixBins; i += NT) L.sel.hist[i] = 0u;
   if (tid < DH) L.qmask[tid] = 0.0f;
-  const float tau = temperature(select_channels<T, DH>(L.qry, qcode, a.r, lane, wave), a.flags, DH, a.r);
+  select_channels<T, DH>(L.qry, qcode, a.r, L.sel.red + 30, lane, wave);
+  const float tau = temperature(L.sel.red + 30, a.flags, DH, a.r);
   const Window win = make_window(a.local_window, S, kq);
   if (tid < a.r) {
     const int ch = L.qry.chan[tid];
