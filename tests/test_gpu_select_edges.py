@@ -32,3 +32,23 @@ def test_thousands_of_equal_keys_around_the_threshold(same):
     for stream in range(3):
         q = W.draw_queries(w, b.K_src, b.seq_lens, stream=stream)[0].contiguous()
         print(Hn.compare_decode(b, q, local_window=11), flush=True)
+
+
+@pytest.mark.parametrize("S", [2048, 4095, 4096, 4097])
+def test_selection_where_the_keys_of_a_lane_double(S):
+    test_selection_edges(S, 13, 0)
+
+
+@pytest.mark.parametrize("d_h,dtype", [(64, "bf16"), (128, "f16"), (256, "bf16")])
+@pytest.mark.parametrize("h,h_kv,flags", [(2, 2, 0), (4, 2, B.SPARQ_FLAG_GQA_SHARED), (4, 1, B.SPARQ_FLAG_GQA_SHARED)])
+@pytest.mark.parametrize("r", [1, 9, -1, 0])
+def test_channels_of_equal_magnitude(d_h, dtype, h, h_kv, flags, r):
+    """Queries of a few magnitudes: the first of the equal channels are taken."""
+    r = r if r > 0 else d_h + r
+    w = W.Workload("ties", 2, h, h_kv, d_h, 300, r, 40, dtype, seed=970 + r)
+    print("[case]", d_h, dtype, h, h_kv, flags, r, flush=True)
+    b = Hn.build_cache(w, v_offset=True, flags=flags)
+    q = W.draw_queries(w, b.K_src, b.seq_lens, q_scale=0.05)[0]
+    q = (torch.round(q.float() * 8).clamp(-2, 2) / 8).to(q.dtype).contiguous()
+    q[0, 0] = 0.125 * (1 - 2 * (torch.arange(d_h, device=q.device) % 2))          # one magnitude
+    print(Hn.compare_decode(b, q, flags=flags), flush=True)
