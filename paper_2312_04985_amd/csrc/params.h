@@ -151,6 +151,50 @@ struct BucketArgs {
   const float* esc_ws = nullptr;    // [B * H] log2(e) / tau
 };
 
+// Where bk_select_gather's arrays lie in its LDS, in 4-byte words.  The bitmap has a word per 32 positions, and a span is a
+// multiple of 64: it is rounded up to whole 16-byte pieces, since the histogram behind it is read in such pieces.
+struct BkSelectLds {
+  int keyval;   // [span_len] keys of this span's selected positions, by position
+  int list;     // [span_len] this span's selected positions, ascending
+  int bitmap;   // [span_len / 32] selected positions of this span
+  int ckey;     // [cand_cap] candidates: keys with the threshold digit (more than cand_cap are read again by every pass)
+  int cpos;     // [cand_cap] their positions
+  int hist;     // [kRadixBins]
+  int tab;      // [n_span][33] A_s[32 lc + t] (at least kDecodeThreads words)
+  int above;    // [n_span] entries of span s above the threshold digit
+  int with;     // [n_span] entries of span s with the threshold digit
+  int before;   // [n_span + 1] candidates before span s
+  int taken;    // [n_span] selected candidates of span s
+  int offs;     // [n_span + 1] list entries before span s
+  int part;     // [waves][d_h + 2] attention partials of the waves
+  int red;      // [32]
+  int wcnt;     // [16]
+  int ctl;      // [16]
+  int words;
+};
+__host__ __device__ constexpr BkSelectLds bk_select_lds(int d_h, int span_len, int n_span, int cand_cap) {
+  BkSelectLds l{};
+  int w = 0;
+  l.keyval = w; w += span_len;
+  l.list = w; w += span_len;
+  l.bitmap = w; w += (span_len / 32 + 3) & ~3;
+  l.ckey = w; w += cand_cap;
+  l.cpos = w; w += cand_cap;
+  l.hist = w; w += kRadixBins;
+  l.tab = w; w += n_span * 33 > kDecodeThreads ? n_span * 33 : kDecodeThreads;
+  l.above = w; w += kMaxSpans + 8;
+  l.with = w; w += kMaxSpans + 8;
+  l.before = w; w += kMaxSpans + 8;
+  l.taken = w; w += kMaxSpans + 8;
+  l.offs = w; w += kMaxSpans + 8;
+  l.part = w; w += kDecodeThreads / 64 * (d_h + 2);
+  l.red = w; w += 32;
+  l.wcnt = w; w += 16;
+  l.ctl = w; w += 16;
+  l.words = w;
+  return l;
+}
+
 // LDS bytes the fused decode kernel needs for a cache of S_max rows and head dimension d_h
 size_t decode_lds_bytes(int S_max, int d_h);
 size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // 0: no grouped-query kernel for this shape

@@ -372,16 +372,6 @@ __global__ __launch_bounds__(NT, 2) void bk_group_scores(const BucketArgs a) {
   sort_span_by_digit<true>(keys, len, w0, p0, cur, skey, spos, a.skey_ws + slot * P, a.spos_ws + slot * P, tid);
 }
 
-// LDS words of bk_select_gather: two span-sized arrays and the bitmap, the candidates (keys sharing the
-// threshold digit: up to cand_cap of them are ranked out of LDS, more are read again by every pass), a
-// histogram, the table window of every span, per-span counters, the attention partials of the waves
-__host__ __device__ constexpr size_t bk_tab_words(int n_span) { return n_span * 33 > NT ? (size_t)n_span * 33 : (size_t)NT; }
-template <int DH>
-__host__ __device__ constexpr size_t bk_select_words(int span_len, int n_span, int cand_cap) {
-  return 2 * (size_t)span_len + span_len / 32 + 2 * (size_t)cand_cap + kRadixBins + bk_tab_words(n_span) +
-         5 * (kMaxSpans + 8) + NW * (DH + 2) + 32 + 16 + 16;
-}
-
 // What the end of a unit needs of the caller's inputs, for channel c.
 struct UnitInputs {
   float mean = 0.0f;
@@ -460,22 +450,23 @@ template <class T, int DH, bool GROUP>
 __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   const int P = a.span_len;
-  uint32_t* keyval = smem;                                  // [P] keys of this span's selected positions, by position
-  int* list = reinterpret_cast<int*>(keyval + P);           // [P] this span's selected positions, ascending
-  uint32_t* bitmap = reinterpret_cast<uint32_t*>(list + P); // [P / 32] selected positions of this span
-  uint32_t* ckey = bitmap + P / 32;                         // [cand_cap] candidates: keys with the threshold digit
-  uint32_t* cpos = ckey + a.cand_cap;                       // [cand_cap]
-  uint32_t* hist = cpos + a.cand_cap;                       // [kRadixBins]
-  uint32_t* tabF = hist + kRadixBins;                       // [n_span][33] A_s[32 lc + t] (at least NT words)
-  int* a_s = reinterpret_cast<int*>(tabF + bk_tab_words(a.n_span)); // [n_span] entries of span s above the threshold digit
-  int* c_s = a_s + kMaxSpans + 8;                           // [n_span] entries of span s with the threshold digit
-  int* cpre = c_s + kMaxSpans + 8;                          // [n_span + 1] candidates before span s
-  int* csel = cpre + kMaxSpans + 8;                         // [n_span] selected candidates of span s
-  int* offs = csel + kMaxSpans + 8;                         // [n_span + 1] list entries before span s
-  float* part = reinterpret_cast<float*>(offs + kMaxSpans + 8);   // [NW][DH + 2] attention partials of the waves
-  float* red = part + NW * (DH + 2);                        // [32]
-  uint32_t* wcnt = reinterpret_cast<uint32_t*>(red + 32);   // [16]
-  int* ctl = reinterpret_cast<int*>(wcnt + 16);             // [16]
+  const BkSelectLds at = bk_select_lds(DH, P, a.n_span, a.cand_cap);
+  uint32_t* keyval = smem + at.keyval;
+  int* list = reinterpret_cast<int*>(smem + at.list);
+  uint32_t* bitmap = smem + at.bitmap;
+  uint32_t* ckey = smem + at.ckey;
+  uint32_t* cpos = smem + at.cpos;
+  uint32_t* hist = smem + at.hist;
+  uint32_t* tabF = smem + at.tab;
+  int* a_s = reinterpret_cast<int*>(smem + at.above);
+  int* c_s = reinterpret_cast<int*>(smem + at.with);
+  int* cpre = reinterpret_cast<int*>(smem + at.before);
+  int* csel = reinterpret_cast<int*>(smem + at.taken);
+  int* offs = reinterpret_cast<int*>(smem + at.offs);
+  float* part = reinterpret_cast<float*>(smem + at.part);
+  float* red = reinterpret_cast<float*>(smem + at.red);
+  uint32_t* wcnt = smem + at.wcnt;
+  int* ctl = reinterpret_cast<int*>(smem + at.ctl);
   const DecodeArgs& d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int U = d.B * d.H;
@@ -862,12 +853,7 @@ size_t bk_scores_lds_bytes(int span_len, int d_h) {
 }
 
 size_t bk_select_lds_bytes(int span_len, int d_h, int n_span, int cand_cap) {
-  switch (d_h) {
-    case 64: return 4 * bk_select_words<64>(span_len, n_span, cand_cap);
-    case 128: return 4 * bk_select_words<128>(span_len, n_span, cand_cap);
-    case 256: return 4 * bk_select_words<256>(span_len, n_span, cand_cap);
-    default: return 0;
-  }
+  return 4 * (size_t)bk_select_lds(d_h, span_len, n_span, cand_cap).words;
 }
 
 int bk_fine_len() { return kFineLen; }
