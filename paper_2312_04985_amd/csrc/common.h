@@ -9,6 +9,7 @@ constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ---- 16-bit storage formats: exact widening to fp32, round-to-nearest-even narrowing ----
 struct F16 {
@@ -54,11 +55,11 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
 // this read.  Measured against plain loads: the decode step 6-10 % faster on every many-head workload (config 2
 // 52.8 -> 47.6 us, config 4 157.3 -> 147.4, config 5 243.6 -> 222.1), 1-3 % slower only where the query heads of
 // a KV group select for themselves in the one-launch kernel and find each other's rows in L2.
-__device__ __forceinline__ uint4 load16(const void* p) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return make_uint4(v.x, v.y, v.z, v.w);
+template <class V>
+__device__ __forceinline__ V load16_as(const void* p) {
+  return __builtin_bit_cast(V, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
+__device__ __forceinline__ uint4 load16(const void* p) { return load16_as<uint4>(p); }
 
 // ---- order-preserving map fp32 -> uint32 (larger float <=> larger key; -0 == +0) ----
 // Every finite float maps to a key >= 0x00800000, so key 0 is below all of them.
@@ -174,12 +175,10 @@ __device__ __forceinline__ void store_agent(double* p, double v) { __hip_atomic_
 __device__ __forceinline__ double load_agent(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // 16 bytes at byte offset `off` of `base` (wave-uniform), the same way (bit 4 of the cache policy is the agent scope's sc1)
 __device__ __forceinline__ void store_agent4(const float* base, uint32_t off, const float4& v) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
   __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffffffu, 0x00027000), off, 0, 16);
 }
 __device__ __forceinline__ float4 load_agent4(const float* base, uint32_t off) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffffffu, 0x00027000), off, 0, 16);
   return make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
 }

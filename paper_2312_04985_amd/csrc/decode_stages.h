@@ -261,13 +261,15 @@ __device__ __forceinline__ Window make_window(int local_window, int S, int kq) {
 // 16 bytes of each of 8 listed rows.  The list is read as two 16-byte words and a row's address is one wide multiply-add per
 // lane: with the row numbers moved to scalar registers and multiplied there, requesting 16 rows took 0.7 us of a
 // wave's time (one scalar instruction after the other), this way 0.3.
-__device__ __forceinline__ void issue_rows(uint4 (&v)[8], const char* base, uint32_t row_bytes, const int* chan) {
+// V: u32x4 keeps the 16 bytes of a request in one register tuple, uint4 are four words that the compiler may part.
+template <class V>
+__device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t row_bytes, const int* chan) {
   const int4 lo = reinterpret_cast<const int4*>(chan)[0], hi = reinterpret_cast<const int4*>(chan)[1];
   uint32_t ch[8] = {(uint32_t)lo.x, (uint32_t)lo.y, (uint32_t)lo.z, (uint32_t)lo.w, (uint32_t)hi.x, (uint32_t)hi.y, (uint32_t)hi.z, (uint32_t)hi.w};
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     asm("" : "+v"(ch[t]));               // (the same in every lane: kept in a vector register all the same)
-    v[t] = load16(base + (uint64_t)ch[t] * row_bytes);
+    v[t] = load16_as<V>(base + (uint64_t)ch[t] * row_bytes);
   }
 }
 
@@ -278,12 +280,16 @@ __device__ __forceinline__ void issue_rows(uint4 (&v)[8], const char* base, uint
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
 // 8 sums of chunk c.  requested() is called by whole waves once their first two batches of loads are under way: work that
 // Step 1b does not wait for.  No barrier.
-// ROW_BY_ROW keeps the compiler from widening the codes of several rows ahead, for callers whose registers do not hold that (it
-// costs 1-2 % of a call of few units where they do).
+// The buffers are tuples of four registers each (u32x4).  As uint4 the compiler carried them through the loop word by word:
+// copies of words still in flight, each with its wait, and bf16 codes widened several rows ahead, which went to scratch memory
+// with the append and was held back there, and in every other bf16 call of the one-workgroup kernel, by a scheduling barrier
+// behind each row.  Per decode / step in bf16, barrier / tuples: 32 heads at 3981 positions 17.9 / 16.8 and 18.6 / 17.5 us, 64
+// heads of 64 channels at 6000 15.0 / 14.2 and 16.4 / 15.1, 512 at 4096 44.3 / 45.0 and 51.1 / 49.5, 2048 at 8192 132.5 / 130.2
+// and 138.5 / 137.9; 2048 in f16 130.6 / 129.0 and 137.5 / 136.8.
 // Addressing: chunk c of channel row j lies at Kt_head + j * row_bytes + c * chunk_bytes.  The S-contiguous
 // key copy has row_bytes = 2 S_max and chunk_bytes = 16; the tiled single-copy layout (tiles of 8 positions,
 // channel-major inside a tile) has row_bytes = 16 and chunk_bytes = 16 d_h.
-template <class T, int STRIDE = NT, bool ROW_BY_ROW = false, class Finish, class Requested>
+template <class T, int STRIDE = NT, class Finish, class Requested>
 __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                     const float* qs, int r, int chunk_begin, int chunk_end,
                                                     int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
@@ -293,19 +299,18 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
   const int items = my_chunks * n_batches;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int ic = 0, ib = 0, cc = 0, cb = 0;   // issue and consume cursors: (own chunk number, batch)
-  auto issue_next = [&](uint4 (&v)[8]) {
+  auto issue_next = [&](u32x4 (&v)[8]) {
     issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + tid + ic * STRIDE) * chunk_bytes), row_bytes, chan + ib * 8);
     if (++ib == n_batches) { ib = 0; ++ic; }
   };
-  auto consume_next = [&](const uint4 (&v)[8]) {
+  auto consume_next = [&](const u32x4 (&v)[8]) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const float qv = qs[cb * 8 + t];
       float f[8];
-      unpack8<T>(v[t], f);
+      unpack8<T>(make_uint4(v[t].x, v[t].y, v[t].z, v[t].w), f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = fmaf(f[e], qv, acc[e]);
-      if (ROW_BY_ROW) __builtin_amdgcn_sched_barrier(0);
     }
     if (++cb == n_batches) {
       finish(chunk_begin + tid + cc * STRIDE, acc);
@@ -314,7 +319,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
       cb = 0; ++cc;
     }
   };
-  uint4 va[8], vb[8];
+  u32x4 va[8], vb[8];
   if (items > 0) {
     issue_next(va);
     if (ic == my_chunks) ic = 0;           // a single item: its second batch is requested and not used
@@ -386,7 +391,6 @@ __device__ __forceinline__ void flush_key_columns(uint16_t* Kt_head, const uint1
                                                   int S, int j, uint16_t newest) {
   // (a non-temporal store: each of these 16 bytes is a line of its own that nothing reads for the next 8 steps; with
   // 2048 KV heads the step is 1-2 % faster, with 512 it is 0.5 % slower)
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const uint4 c = gather_key_columns(K_head, d_h, S, j, newest);
   u32x4 v;
   v.x = c.x; v.y = c.y; v.z = c.z; v.w = c.w;

@@ -83,7 +83,6 @@ __global__ __launch_bounds__(512) void append_one_row(const AppendArgs a) {
 constexpr int BT = kAppendThreads;
 // (rows of K and V leave as non-temporal stores: 84 -> 78 us for that prompt; the columns of Kt do not: 78 -> 82)
 __device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   u32x4 v; v.x = c.x; v.y = c.y; v.z = c.z; v.w = c.w;
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }

@@ -184,9 +184,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   };
-  // (row by row in bf16, which has no fused multiply-add on 16-bit codes: with codes widened ahead 28 bytes per lane went to
-  // scratch memory, 512 ragged heads of 256 channels 188 -> 198 us per step)
-  stream_channel_rows<T, NT, std::is_same<T, BF16>::value>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
+  stream_channel_rows<T>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
   if (wave < n_tail) {
     const float dot = tail_row_dot<T>(tail, L.qry.qs, r8, lane);
     if (lane == 0) {

@@ -114,7 +114,6 @@ __device__ __forceinline__ void sort_span_by_digit(const uint32_t* keys, int len
   }
   __syncthreads();
   // (non-temporal stores: the next launch reads only the head of each array; config 3's step 37.3 -> 36.7 us)
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   for (int i = tid * 4; i < len; i += NT * 4) {     // span_len is a multiple of 64: whole 16-byte pieces
     __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(skey + i), reinterpret_cast<u32x4*>(gkey + i));
     __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(spos + i), reinterpret_cast<u32x4*>(gpos + i));
