@@ -7,6 +7,7 @@
 #pragma once
 #include "common.h"
 #include "params.h"
+#include "two_ahead.h"
 
 #include <type_traits>
 
@@ -278,7 +279,7 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
 // groups of threads).  The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
 // a two-deep software pipeline: a batch of 8 loads is always in flight behind the one being accumulated,
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
-// 8 sums of chunk c.  requested() is called by whole waves once their first two batches of loads are under way: work that
+// 8 sums of chunk c.  requested() is called by whole waves once their first batches of loads are under way: work that
 // Step 1b does not wait for.  No barrier.
 // The buffers are tuples of four registers each (u32x4).  As uint4 the compiler carried them through the loop word by word:
 // copies of words still in flight, each with its wait, and bf16 codes widened several rows ahead, which went to scratch memory
@@ -319,27 +320,9 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
       cb = 0; ++cc;
     }
   };
-  u32x4 va[8], vb[8];
-  if (items > 0) {
-    issue_next(va);
-    if (ic == my_chunks) ic = 0;           // a single item: its second batch is requested and not used
-    issue_next(vb);
-  }
-  requested();                             // (outside the branch: by whole waves)
-  if (items > 0) {
-    int i = 0;
-    for (; i + 3 < items; i += 2) {        // (no conditional request inside: the compiler would wait for all of them)
-      consume_next(va);
-      issue_next(va);
-      consume_next(vb);
-      issue_next(vb);
-    }
-    consume_next(va);
-    const int left = items - i;
-    if (left == 3) issue_next(va);
-    if (left >= 2) consume_next(vb);
-    if (left == 3) consume_next(va);
-  }
+  u32x4 v[2][8];
+  two_ahead(items, __any(items > 1), [&](auto buffer) { issue_next(v[buffer.value]); }, [&](auto buffer) { consume_next(v[buffer.value]); },
+            requested, [&]() { ic = 0; });
 }
 
 // ------------------------------------------------------------------------------------------------
