@@ -52,3 +52,21 @@ def test_channels_of_equal_magnitude(d_h, dtype, h, h_kv, flags, r):
     q = (torch.round(q.float() * 8).clamp(-2, 2) / 8).to(q.dtype).contiguous()
     q[0, 0] = 0.125 * (1 - 2 * (torch.arange(d_h, device=q.device) % 2))          # one magnitude
     print(Hn.compare_decode(b, q, flags=flags), flush=True)
+
+
+@pytest.mark.parametrize("share", [0.5, 0.8, 1.0])
+@pytest.mark.parametrize("h,h_kv,d_h,S,window,flags", [(2, 2, 64, 203, 0, 0), (2, 2, 128, 1203, 5, 0), (2, 2, 64, 5001, 13, 0),        # one workgroup per head
+                                                       (4, 4, 64, 16501, 11, 0), (4, 2, 64, 16501, 11, B.SPARQ_FLAG_GQA_SHARED),     # spans
+                                                       (130, 130, 64, 35501, 11, 0)])                                               # two levels
+def test_most_keys_share_a_first_digit(h, h_kv, d_h, S, window, flags, share):
+    """One key row in most places: the digit that most lanes of a wave hold is counted over the wave, the others by themselves."""
+    w = W.Workload("hot", 1, h, h_kv, d_h, S, 8, max(1, S // 9), "f16" if S % 4 == 1 else "bf16", seed=1400 + S)
+    print("[case]", h, h_kv, d_h, S, window, flags, share, flush=True)
+    b = Hn.build_cache(w)
+    gen = torch.Generator().manual_seed(w.seed)
+    at = torch.where(torch.rand(S, generator=gen) < share, torch.full((S,), S // 3), torch.arange(S)).to(b.K_src.device)
+    K = b.K_src[:, :, at].contiguous()
+    b = Hn.Built(w, type(b.cache)(w.B, w.H, w.H_kv, W.round_up(w.S, 64), w.d_h, w.r, w.k, w.torch_dtype), K, b.V_src, b.seq_lens, None)
+    b.cache.append(b.K_src, b.V_src)
+    q = W.draw_queries(w, b.K_src, b.seq_lens, q_scale=0.05)[0].contiguous()
+    print(Hn.compare_decode(b, q, local_window=window, flags=flags), flush=True)
