@@ -475,10 +475,9 @@ __device__ __forceinline__ float selected_mass(const Selection& s, const float* 
   // they share one weight.
   return t + (s.whole ? e : (float)s.need * exp2_weight((key_to_float(s.first) - dmax) * esc));
 }
-// numerator and denominator are summed in different orders: a share is at most 1, and 1 where everything is selected
-// (but not a number where they are none)
-__device__ __forceinline__ float share_of(float selected, float all, bool everything) {
-  const float alpha = selected / all;
+// alpha's numerator and denominator are summed in different orders (and launches): a share is at most 1, and 1 where everything
+// is selected (but not a number where they are none)
+__device__ __forceinline__ float as_share(float alpha, bool everything) {
   return alpha > 1.0f || (everything && alpha == alpha) ? 1.0f : alpha;
 }
 

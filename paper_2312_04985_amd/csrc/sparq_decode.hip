@@ -224,7 +224,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   const bool new_selected = APPEND && appended && list[kq - 1] == S - 1;
   float alpha = 0.0f;
   auto gathering = [&]() {
-    if (tid < DH) alpha = share_of(selected_mass(chosen, L.sel.red, dmax_of(), esc), all_mass(L.sel.red), win.k_old == win.S_old);
+    if (tid < DH) alpha = as_share(selected_mass(chosen, L.sel.red, dmax_of(), esc) / all_mass(L.sel.red), kq == S);
   };
   float m_run = -INFINITY, l_run = 0.0f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};

@@ -391,7 +391,7 @@ __device__ __forceinline__ UnitInputs unit_inputs(const DecodeArgs& d, size_t kv
 // The end of a unit, by DH threads (thread c: channel c): merge the spans' partials, alpha from the spans' numerators, blend
 // with the mean value vector (Eq. 10), round and store, append.
 template <class T, int DH>
-__device__ __forceinline__ void finish_unit(const BucketArgs& a, int u, size_t kv_head, int S, bool appended, bool owner, int n_live,
+__device__ __forceinline__ void finish_unit(const BucketArgs& a, int u, size_t kv_head, int S, int kq, bool appended, bool owner, int n_live,
                                             float zden, int c, int lane, const UnitInputs& in) {
   const DecodeArgs& d = a.d;
   const float* parts = a.part_ws + (size_t)u * a.n_span * (DH + 2);
@@ -420,7 +420,7 @@ __device__ __forceinline__ void finish_unit(const BucketArgs& a, int u, size_t k
     m_all = m_new;
   }
   y3 /= l_all;
-  const float alpha = wave_sum(num_part) / zden;       // fixed order
+  const float alpha = as_share(wave_sum(num_part) / zden, kq == S);       // fixed order
   if (c == 0 && d.alpha_out) d.alpha_out[u] = alpha;
   float vm = in.mean;
   if (appended) {                          // the mean with the new row: what the blend uses and the owner stores
@@ -781,7 +781,7 @@ __global__ __launch_bounds__(NT) void bk_select_gather(const BucketArgs a) {
   // ---- the unit's last workgroup: merge the spans' partials, blend, store, append ----
   const UnitInputs in = unit_inputs(d, kv_head, tid < DH, appended, tid, DH);   // requested while the partial is on its way
   if (!last_to_arrive(a.tickets + u, n_live, ctl + 15)) return;
-  if (tid < DH) finish_unit<T, DH>(a, u, kv_head, S, appended, owner, n_live, zden, tid, lane, in);
+  if (tid < DH) finish_unit<T, DH>(a, u, kv_head, S, kq, appended, owner, n_live, zden, tid, lane, in);
 }
 
 // One workgroup per unit, where bk_select_gather does not merge.
@@ -794,8 +794,10 @@ __global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
   const int S = visible_length(d, b, appended, bad, full);
   if (S == 0) return;                      // outputs written by the first launch, state by bk_select_gather
   const UnitInputs in = unit_inputs(d, kv_head, true, appended, threadIdx.x, DH);
-  finish_unit<T, DH>(a, u, kv_head, S, appended, d.k_new && h == hk * d.group, divided(S + a.span_len - 1, a.by_len), a.zden_ws[u], threadIdx.x,
-                     threadIdx.x & (kWave - 1), in);
+  int kb = d.k_per_seq ? d.k_per_seq[b] : d.k;
+  kb = kb < 1 ? 1 : (kb > d.k ? d.k : kb);
+  finish_unit<T, DH>(a, u, kv_head, S, kb < S ? kb : S, appended, d.k_new && h == hk * d.group, divided(S + a.span_len - 1, a.by_len),
+                     a.zden_ws[u], threadIdx.x, threadIdx.x & (kWave - 1), in);
 }
 
 template <class T, int DH>

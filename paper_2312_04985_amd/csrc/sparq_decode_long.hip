@@ -239,7 +239,7 @@ __global__ __launch_bounds__(NT, 4) void long_finish(const LongArgs a) {
   const SelectLds sel{hist, wcnt, ctl, red};
   const Selection chosen = select_compact<Sums::kNumerator>(keys, keys, n_cand, n_free, win.k_old, [&]() { return dmax; }, esc, RunningSum{},
                                                             nullptr, 0, sel, tid, lane, wave);
-  const float alpha = selected_mass(chosen, red, dmax, esc) / zsum;
+  const float alpha = as_share(selected_mass(chosen, red, dmax, esc) / zsum, kq == S);
   for (int n0 = tid; n0 < kq; n0 += FLY * NT) {   // candidate numbers -> positions, in place
     int pos[FLY];
 #pragma unroll

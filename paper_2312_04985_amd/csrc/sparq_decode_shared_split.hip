@@ -361,7 +361,7 @@ __global__ __launch_bounds__(NT) void gs_merge(const GsArgs a) {
   if (tid < G) {
     float t = 0.0f;
     for (int w = 0; w < NW; ++w) t += asum_w[w * G + tid];
-    const float alpha = t * hs[tid * 2 + 1];
+    const float alpha = as_share(t * hs[tid * 2 + 1], kq == S);
     a.alpha_ws[u0 + tid] = alpha;
     if (d.alpha_out) d.alpha_out[u0 + tid] = alpha;
   }

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_single_k(const DecodeArgs 
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float alpha = 0.0f;
   attend_rows<T, DH>(K_head, V_head, list, 0, kq, q8, lane, wave, m_run, l_run, acc, [&]() {
-    if (tid < DH) alpha = share_of(selected_mass(chosen, L.sel.red, dmax_of(), esc), all_mass(L.sel.red), win.k_old == win.S_old);
+    if (tid < DH) alpha = as_share(selected_mass(chosen, L.sel.red, dmax_of(), esc) / all_mass(L.sel.red), kq == S);
   });
   store_wave_partial<DH>(m_run, l_run, acc, L.part, lane, wave);
   __syncthreads();
