@@ -197,10 +197,10 @@ __host__ __device__ constexpr BkSelectLds bk_select_lds(int d_h, int span_len, i
 
 // LDS bytes the fused decode kernel needs for a cache of S_max rows and head dimension d_h
 size_t decode_lds_bytes(int S_max, int d_h);
-size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // 0: no grouped-query kernel for this shape
+size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // LDS that admits S_max; 0: no grouped-query kernel for this shape
 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t s);
-size_t decode_single_k_lds_bytes(int S_max, int d_h);
+size_t decode_single_k_lds_bytes(int S_max, int d_h);   // LDS that admits S_max
 hipError_t launch_decode_single_k(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t long_scores_lds_bytes(int span_len, int d_h);
 size_t long_merge_lds_bytes(int n_span, int cand_cap);

@@ -28,19 +28,28 @@ struct SharedLds {
   float* qf;           // [G][DH]
   float* qs;           // [G][DH] per-head components on the shared channel list (padded, weight 0)
   int* chan;           // [DH]
-  float* stat;         // [NW][G][2] and [G][3]
+  float* stat;         // [NW][G][2]
 };
 
 template <int DH, int G>
 __host__ __device__ constexpr size_t shared_part_words() { return (size_t)NW * G * (DH + 2); }
 
-// words after the key array (2 DH + up to NT of them unused, as from the time when this kernel ranked channels in LDS: they
-// decide which lengths are served by one workgroup)
+// words after the key array
 template <int DH, int G>
 __host__ __device__ constexpr size_t shared_fixed_words() {
+  size_t hist_part = 2 * kRadixBins;
+  if (hist_part < shared_part_words<DH, G>()) hist_part = shared_part_words<DH, G>();
+  return hist_part + 2 * (size_t)G * DH /* qf, qs */ + DH /* chan */ + 32 + 16 + 8 + NW * G * 2;
+}
+
+// One workgroup serves lengths up to which the keys and this many words fit the LDS.  More than the arrays take: the line between
+// the plans, and with it the workspace of a shape, stays where the plans were compared.
+template <int DH, int G>
+__host__ __device__ constexpr size_t shared_limit_words() {
   size_t hist_part = 2 * kRadixBins + NT;
   if (hist_part < shared_part_words<DH, G>()) hist_part = shared_part_words<DH, G>();
-  return hist_part + 2 * (size_t)G * DH /* qf, qs */ + DH /* chan */ + 2 * DH + 32 + 16 + 8 + NW * G * 2 + G * 4;
+  constexpr size_t others = 2 * (size_t)G * DH + 3 * DH + 56 + NW * G * 2 + G * 4;
+  return hist_part + others;
 }
 
 template <int DH, int G>
@@ -296,6 +305,7 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
 
 template <class T, int DH, int G>
 hipError_t launch_shared_g(const DecodeArgs& a, float* z_ws, hipStream_t s) {
+  static_assert(shared_limit_words<DH, G>() >= shared_fixed_words<DH, G>(), "what the plan admits fits");
   const size_t lds = 4 * ((size_t)a.S_max + shared_fixed_words<DH, G>());
   auto kern = sparq_decode_shared<T, DH, G>;
   hipError_t e = allow_lds<sparq_decode_shared<T, DH, G>>(lds);
@@ -314,19 +324,19 @@ hipError_t launch_shared_dh(const DecodeArgs& a, float* z_ws, hipStream_t s) {
 }
 
 template <int DH>
-size_t shared_lds(int S_max, int g) {
-  return 4 * ((size_t)S_max + (g == 2 ? shared_fixed_words<DH, 2>() : shared_fixed_words<DH, 4>()));
+size_t shared_limit(int S_max, int g) {
+  return 4 * ((size_t)S_max + (g == 2 ? shared_limit_words<DH, 2>() : shared_limit_words<DH, 4>()));
 }
 
 }  // namespace
 
-// LDS bytes of the grouped-query kernel, 0 if the group size or head dimension has no kernel
+// LDS bytes that admit a length to the grouped-query kernel, 0 if the group size or head dimension has no kernel
 size_t decode_shared_lds_bytes(int S_max, int d_h, int g) {
   if (g != 2 && g != 4) return 0;
   switch (d_h) {
-    case 64: return shared_lds<64>(S_max, g);
-    case 128: return shared_lds<128>(S_max, g);
-    case 256: return shared_lds<256>(S_max, g);
+    case 64: return shared_limit<64>(S_max, g);
+    case 128: return shared_limit<128>(S_max, g);
+    case 256: return shared_limit<256>(S_max, g);
     default: return 0;
   }
 }

@@ -35,11 +35,13 @@ __device__ __forceinline__ Lds1K carve_1k(uint32_t* base, int S_max) {
   return l;
 }
 
-// (DH words more than the arrays above take, as this kernel once did: they decide which lengths are refused)
 template <int DH>
 __host__ __device__ constexpr size_t lds_words_1k() {
-  return 2 * (size_t)kRadixBins + (size_t)NW * (DH + 2) + 5 * (size_t)DH + 32 + 16 + 8;
+  return 2 * (size_t)kRadixBins + (size_t)NW * (DH + 2) + 4 * (size_t)DH + 32 + 16 + 8;
 }
+// Lengths are served up to which the keys, the arrays above and DH words more fit the LDS: what is refused stays refused.
+template <int DH>
+__host__ __device__ constexpr size_t limit_words_1k() { return lds_words_1k<DH>() + DH; }
 
 // Step 1b from the row-major keys: rows 0..S-1 of one KV head, LPR lanes per row as in the gather of
 // Step 2, groups of UNR loads through a two-deep software pipeline.  finish(position, dot) is called by
@@ -203,9 +205,9 @@ hipError_t launch_1k(const DecodeArgs& a, hipStream_t s) {
 
 size_t decode_single_k_lds_bytes(int S_max, int d_h) {
   switch (d_h) {
-    case 64: return 4 * ((size_t)S_max + lds_words_1k<64>());
-    case 128: return 4 * ((size_t)S_max + lds_words_1k<128>());
-    case 256: return 4 * ((size_t)S_max + lds_words_1k<256>());
+    case 64: return 4 * ((size_t)S_max + limit_words_1k<64>());
+    case 128: return 4 * ((size_t)S_max + limit_words_1k<128>());
+    case 256: return 4 * ((size_t)S_max + limit_words_1k<256>());
     default: return 0;
   }
 }
