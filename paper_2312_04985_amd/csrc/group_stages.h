@@ -179,10 +179,10 @@ __device__ __forceinline__ void stream_channel_rows_group(const char* Kt_head, u
 // lane and load (registers), one rescaling of a head's sums for both.  Bound by vector instructions: with a rescaling per row,
 // exponentials that scale denormals first, and group_score's the same, one workgroup per KV head with 4 heads took 73.5 us
 // per step for 512 KV heads of 4096 positions, so 70.2; 128 of 8192 77.5 / 69.7; 4 of 3000 34.9 / 30.9.
-template <class T, int DH, int G, class Requested = Nothing>
+template <class T, int DH, int G>
 __device__ __forceinline__ void attend_rows_group(const char* K_head, const char* V_head, const int* list, int n_begin, int n_end,
                                                   const float (&q8)[G][8], int lane, int wave, float (&m_run)[G], float (&l_run)[G],
-                                                  float (&acc)[G][8], Requested&& requested = Requested{}) {
+                                                  float (&acc)[G][8]) {
   using Geo = RowGeometry<DH>;
   constexpr int UNR = 2, GROUP = Geo::RPI * UNR;
   const int slot = wave * Geo::RPW + lane / Geo::LPR;
@@ -233,7 +233,6 @@ __device__ __forceinline__ void attend_rows_group(const char* K_head, const char
   if (n_groups > 0) {
     uint4 ka[UNR], va[UNR], kb[UNR], vb[UNR];
     issue(ka, va, 0);
-    requested();
     int g = 0;
     for (; g + 2 < n_groups; g += 2) {
       issue(kb, vb, g + 1);
@@ -248,8 +247,6 @@ __device__ __forceinline__ void attend_rows_group(const char* K_head, const char
     } else {
       consume(ka, va, g);
     }
-  } else {
-    requested();
   }
 }
 

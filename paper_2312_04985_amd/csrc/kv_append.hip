@@ -320,8 +320,9 @@ __global__ __launch_bounds__(BT) void append_rows_short(const AppendArgs a) {
 // The old length and the row count come from the workspace: seq_lens is written here.
 // Bound by memory latency: the lengths, the old mean and the partial sums are requested together, the partial sums of
 // workgroups that had no rows among them (never written, and left out).  THREADS = 1024 where a KV head has more than 16
-// partial sums, so that all 128 at most are in flight at once (THREADS / DH groups of 16).  (With 8 per thread in flight behind the
-// lengths, a whole call: 31 777 rows for 8 KV heads 70.4 us, so 67.4.)
+// partial sums: THREADS / DH groups of 16 are in flight at once, which is all of them (128 at most) for d_h 64 and 128; at d_h 256
+// it is 64, and heads with more take a second round.  (With 8 per thread in flight behind the lengths, a whole call: 31 777 rows
+// for 8 KV heads 70.4 us, so 67.4.)
 template <int DH, int THREADS>
 __global__ __launch_bounds__(THREADS) void append_finish(const AppendArgs a) {
   constexpr int NG = THREADS / DH, FLY = 16;
