@@ -281,7 +281,8 @@ __global__ __launch_bounds__(NT, 2) void sparq_decode_shared(const DecodeArgs a,
     // inv_z of head h: recompute from the broadcast statistics is not needed, every thread holds all G
     float alpha = 0.0f;
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) if (hh == h) alpha = as_share(a_all * inv_z[hh], kq == S);
+    for (int hh = 0; hh < G; ++hh) if (hh == h) alpha = a_all * inv_z[hh];
+    alpha = as_share(alpha, kq == S);
     float vm = a.v_mean[kv_head * DH + c];
     if (appended) {                        // the mean with the new row; the mean of no rows is ignored
       if (S == 1) vm = 0.0f;
