@@ -398,8 +398,8 @@ def measure(name, K, Wm, args, full):
 def main():
     args = parse()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
-        print("bench.py: this build runs on ONE GPU; --gpus N with N > 1 is not supported "
-              "(units shard over batch and KV heads with no exchange; see DESIGN.md)", file=sys.stderr)
+        print("bench.py runs on ONE GPU; --gpus N with N > 1 is not supported "
+              "(units shard over batch and KV heads with no exchange)", file=sys.stderr)
         sys.exit(2)
 
     import torch
@@ -444,7 +444,7 @@ def main():
                              "dense_us": round(r.get("dense_ms_per_step", float("nan")) * 1e3, 2),
                              "speedup_vs_dense": r.get("speedup_vs_dense"), "plan": r["plan"],
                              "algorithmic_bytes_per_launch": r["roofline"]["algorithmic_bytes_per_launch"]}
-        # config 3 once more under the paper's grouped-query rule (a quarter of the bytes: one selection per KV head)
+        # the long grouped-query workload once more under the paper's grouped-query rule (a quarter of the bytes: one selection per KV head)
         import copy
         ga = copy.copy(args); ga.gqa_shared = True
         r = measure("c3_llama3_8b_gqa", min(K, 100), min(Wm, 10), ga, full=False)

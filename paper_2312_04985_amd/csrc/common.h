@@ -52,8 +52,8 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
 
 // 16 bytes of cache data: every such load in this library reads what the launch uses once (rows of Kt, K and V,
 // sorted keys), so it is marked non-temporal: the line is not kept in L2 or in the memory-side cache on account of
-// this read.  Measured against plain loads: the decode step 6-10 % faster on every many-head workload (config 2
-// 52.8 -> 47.6 us, config 4 157.3 -> 147.4, config 5 243.6 -> 222.1), 1-3 % slower only where the query heads of
+// this read.  Measured against plain loads: the decode step 6-10 % faster on every many-head workload (512 heads
+// of 4096 positions 52.8 -> 47.6 us, 2048 of 8192 157.3 -> 147.4, 512 ragged ones of 256 channels 243.6 -> 222.1), 1-3 % slower only where the query heads of
 // a KV group select for themselves in the one-launch kernel and find each other's rows in L2.
 template <class V>
 __device__ __forceinline__ V load16_as(const void* p) {

@@ -113,7 +113,8 @@ __device__ __forceinline__ void sort_span_by_digit(const uint32_t* keys, int len
     spos[e] = (uint32_t)(p0 + i);
   }
   __syncthreads();
-  // (non-temporal stores: the next launch reads only the head of each array; config 3's step 37.3 -> 36.7 us)
+  // (non-temporal stores: the next launch reads only the head of each array; 32 heads on 8 KV heads at 32 768
+  // positions: step 37.3 -> 36.7 us)
   for (int i = tid * 4; i < len; i += NT * 4) {     // span_len is a multiple of 64: whole 16-byte pieces
     __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(skey + i), reinterpret_cast<u32x4*>(gkey + i));
     __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(spos + i), reinterpret_cast<u32x4*>(gpos + i));
