@@ -16,7 +16,9 @@ SH, K1, TK = B.SPARQ_FLAG_GQA_SHARED, B.SPARQ_FLAG_SINGLE_K, B.SPARQ_FLAG_TILED_
     (4, 4, 2, 128, 2048, "sparq_decode_fused", 0), (4, 4, 2, 64, 2048, "sparq_decode_fused", TK), (4, 4, 2, 64, 2048, "stored once", K1),
     (4, 4, 2, 128, 16384, "digit-bucket", 0), (4, 4, 2, 128, 36032, "digit-bucket", 0), (5, 32, 32, 64, 36032, "two-level", 0),
     (4, 4, 2, 128, 2048, "one workgroup per KV head", SH), (4, 4, 1, 64, 2048, "one workgroup per KV head", SH),
-    (4, 4, 2, 128, 16384, "grouped-query rule on the digit-bucket", SH), (5, 32, 8, 64, 20480, "several workgroups per KV head", SH)])
+    (4, 4, 2, 128, 16384, "grouped-query rule on the digit-bucket", SH), (5, 32, 8, 64, 20480, "several workgroups per KV head", SH),
+    # 120 units of 5 spans: the digit-bucket plan's merges in a launch of their own
+    (5, 24, 12, 64, 40960, "digit-bucket", 0), (5, 24, 12, 64, 40960, "grouped-query rule on the digit-bucket", SH)])
 def test_alpha_is_a_share(Bn, h, h_kv, d_h, S_max, plan, flags):
     k = 1201
     w = W.Workload("share", Bn, h, h_kv, d_h, k + 2, 24, k, "f16", seed=1500 + d_h)
