@@ -412,6 +412,97 @@ __device__ __forceinline__ void flush_key_columns(uint16_t* Kt_head, const uint1
 }
 
 // ------------------------------------------------------------------------------------------------
+// transpose 8 rows x 8 channels of 16-bit codes: w[c] = the 8 rows' codes of channel c
+__device__ __forceinline__ void transpose_piece(const uint4 (&rows)[8], uint4 (&w)[8]) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const uint32_t a = c < 2 ? rows[e].x : (c < 4 ? rows[e].y : (c < 6 ? rows[e].z : rows[e].w));
+      const uint32_t b = c < 2 ? rows[e + 1].x : (c < 4 ? rows[e + 1].y : (c < 6 ? rows[e + 1].z : rows[e + 1].w));
+      o[e >> 1] = (c & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+    }
+    w[c] = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+}
+
+// The append of sparq_decode_step inside the decode's launch, for channel c of a KV head: the new row (codes kc, vc) into K and
+// V at position S - 1, the mean that includes it into the *_next buffer, and with a row that completes a group of 8 the
+// channel's 8 columns of Kt (TILED: its 16 bytes of the tile).  No workgroup of the launch reads what this writes: every head
+// takes the row from k_new / v_new, the columns lie above its S_fl, the state it reads is the old one.
+template <int DH, bool TILED>
+__device__ __forceinline__ void append_channel(const DecodeArgs& a, size_t kv_head, int c, int S, bool appended, uint16_t kc, uint16_t vc, float mean) {
+  a.v_mean_next[kv_head * DH + c] = mean;
+  if (!appended) return;
+  uint16_t* K_head = reinterpret_cast<uint16_t*>(a.K) + kv_head * a.S_stride * (size_t)DH;
+  // rows by position: the rows of K, or the rows of the newest positions (tiled layout)
+  uint16_t* rows = TILED ? reinterpret_cast<uint16_t*>(a.Kt) + kv_head * (size_t)(8 * DH) - (size_t)((S - 1) & ~7) * DH : K_head;
+  reinterpret_cast<uint16_t*>(a.V)[(kv_head * a.S_stride + (S - 1)) * DH + c] = vc;
+  if (!TILED || (S & 7) != 0) rows[(size_t)(S - 1) * DH + c] = kc;
+  if ((S & 7) != 0) return;
+  if (!TILED)
+    flush_key_columns(reinterpret_cast<uint16_t*>(a.Kt) + kv_head * DH * (size_t)a.S_stride, rows, a.S_stride, DH, S, c, kc);
+  else
+    *reinterpret_cast<uint4*>(K_head + (size_t)(S - 8) * DH + (size_t)c * 8) = gather_key_columns(rows, DH, S, c, kc);
+}
+
+// ... by workgroups of their own, the last of the grid, which take the places that decoding workgroups have left: workgroup i of
+// append_workgroups() has NT / (DH / 8) KV heads, a thread 8 channels of one.  Bound by the scattered stores of a completed group;
+// few workgroups spread them over the launch's end.  (A channel per thread, eight times as many workgroups: 2048 heads at 4096
+// positions 182 us per such step, so 179.)
+template <int DH>
+inline int append_workgroups(int64_t heads) { return (int)((heads * (DH / 8) + NT - 1) / NT); }
+
+template <class T, int DH, bool TILED>
+__device__ __forceinline__ void append_heads(const DecodeArgs& a, int i) {
+  constexpr int LPR = DH / 8;
+  const int head = i * (NT / LPR) + (int)threadIdx.x / LPR, j0 = ((int)threadIdx.x % LPR) * 8;
+  if (head >= a.B * a.H_kv) return;
+  const int b = divided(head, a.by_H_kv);
+  const size_t at = (size_t)head * DH + j0;
+  const uint4 kc = load16(reinterpret_cast<const uint16_t*>(a.k_new) + at), vc = load16(reinterpret_cast<const uint16_t*>(a.v_new) + at);
+  float m[8];
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) {
+    const float4 v = *reinterpret_cast<const float4*>(a.v_mean + at + e);
+    m[e] = v.x; m[e + 1] = v.y; m[e + 2] = v.z; m[e + 3] = v.w;
+  }
+  bool appended, bad, full;               // (reported by the decoding workgroups)
+  const int S = visible_length(a, b, appended, bad, full);
+  if (appended) {
+    uint16_t* K_head = reinterpret_cast<uint16_t*>(a.K) + (size_t)head * a.S_stride * DH;
+    // rows by position: the rows of K, or the rows of the newest positions (tiled layout)
+    uint16_t* rows = TILED ? reinterpret_cast<uint16_t*>(a.Kt) + (size_t)head * (8 * DH) - (size_t)((S - 1) & ~7) * DH : K_head;
+    *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.V) + ((size_t)head * a.S_stride + (S - 1)) * DH + j0) = vc;
+    if (!TILED || (S & 7) != 0) *reinterpret_cast<uint4*>(rows + (size_t)(S - 1) * DH + j0) = kc;
+    if ((S & 7) == 0) {
+      uint4 r[8], w[8];
+#pragma unroll
+      for (int e = 0; e < 7; ++e) r[e] = *reinterpret_cast<const uint4*>(rows + (size_t)(S - 8 + e) * DH + j0);
+      r[7] = kc;
+      transpose_piece(r, w);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        uint16_t* dst = TILED ? K_head + (size_t)(S - 8) * DH + (size_t)(j0 + e) * 8
+                              : reinterpret_cast<uint16_t*>(a.Kt) + ((size_t)head * DH + j0 + e) * a.S_stride + (S - 8);
+        const u32x4 c = {w[e].x, w[e].y, w[e].z, w[e].w};
+        __builtin_nontemporal_store(c, reinterpret_cast<u32x4*>(dst));
+      }
+    }
+    float f[8];
+    unpack8<T>(vc, f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {         // the mean of no rows is ignored
+      if (S == 1) m[e] = 0.0f;
+      m[e] += (f[e] - m[e]) * (1.0f / (float)S);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) *reinterpret_cast<float4*>(a.v_mean_next + at + e) = make_float4(m[e], m[e + 1], m[e + 2], m[e + 3]);
+}
+
+// ------------------------------------------------------------------------------------------------
 // Step 2a: the kq positions with the largest keys (ties to the lower position)
 
 struct SelectLds {

@@ -89,21 +89,6 @@ __device__ __forceinline__ void store16_nt(void* p, const uint4& c) {
 template <int DH>
 constexpr int ATP = append_tile(DH);       // positions per tile
 
-// transpose 8 rows x 8 channels of 16-bit codes: w[c] = the 8 rows' codes of channel c
-__device__ __forceinline__ void transpose_piece(const uint4 (&rows)[8], uint4 (&w)[8]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    uint32_t o[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      const uint32_t a = c < 2 ? rows[e].x : (c < 4 ? rows[e].y : (c < 6 ? rows[e].z : rows[e].w));
-      const uint32_t b = c < 2 ? rows[e + 1].x : (c < 4 ? rows[e + 1].y : (c < 6 ? rows[e + 1].z : rows[e + 1].w));
-      o[e >> 1] = (c & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
-    }
-    w[c] = make_uint4(o[0], o[1], o[2], o[3]);
-  }
-}
-
 // the codes of positions 0 .. left - 1 of a group of 8, 16 bytes where it is whole
 __device__ __forceinline__ void store_columns(uint16_t* dst, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, int left) {
   if (left >= 8) {

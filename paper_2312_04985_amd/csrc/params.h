@@ -44,6 +44,7 @@ struct DecodeArgs {
   uint32_t flags;
   int32_t local_window;
   int32_t group = 1;                      // query heads per KV head
+  int32_t append_apart = 0;               // the step's append has workgroups of its own, behind the decoding ones
   Divider by_H, by_H_kv, by_group;        // set by enqueue_decode, as `group`
   unsigned long long* clocks = nullptr;   // [workgroups][kStageStamps] time stamps; set only by a SPARQ_STAGE_CLOCKS build
 };

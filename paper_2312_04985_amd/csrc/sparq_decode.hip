@@ -53,9 +53,9 @@ __device__ __forceinline__ Lds carve(uint32_t* base, int S_max) {
 
 // APPEND = true is the one-launch decode step: the new key/value row of every KV head (k_new, v_new)
 // counts as position S_b of its sequence without being read back from the cache.  Every workgroup
-// takes that row from the inputs; the workgroup of the first query head of a KV group also writes
-// it into K, V and Kt and stores the updated mean; lengths and means go to the *_next buffers, so no
-// workgroup can observe another one's update of the state it reads.
+// takes that row from the inputs; the workgroup of the first query head of a KV group, or workgroups of the append's own
+// behind the decoding ones (append_apart), also write it into K, V and Kt and store the updated mean; lengths and means go to
+// the *_next buffers, so no workgroup can observe another one's update of the state it reads.
 // TILED = true reads the single-copy tiled key layout (flag bit 6): a.K holds tiles of 8 positions, channel-major
 // inside a tile, a.Kt the up to 7 newest rows of every KV head (8 rows of d_h each) that do not fill a tile yet.
 // Step 1b then strides through the tiles (16 bytes per position chunk and channel), Step 2b collects a row's
@@ -65,6 +65,12 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   extern __shared__ __align__(16) uint32_t smem[];
   const Lds L = carve<DH>(smem, a.S_max);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int U = a.B * a.H;
+  int u = blockIdx.x;
+  if (APPEND && u >= U) {                  // (append_apart)
+    append_heads<T, DH, TILED>(a, u - U);
+    return;
+  }
 
 #ifdef SPARQ_STAGE_CLOCKS
   unsigned long long stamp[kStageStamps];
@@ -74,8 +80,6 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   // Default: every XCD gets a contiguous run of units, so the query heads of a KV group share an L2.
   // With the ragged-batch hint (and no grouped heads): workgroup i serves the sequence with the
   // (i / H)-th largest length, so the longest sequences start first and the short ones fill in behind.
-  const int U = a.B * a.H;
-  int u = blockIdx.x;
   if ((a.flags & 4u) && a.H == a.H_kv && a.B > 1 && a.B <= NT) {
     int* lens = reinterpret_cast<int*>(L.keys);   // free until stage 1
     if (tid < a.B) lens[tid] = a.seq_lens[tid];
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     S = S < 0 ? 0 : a.S_max;
   }
   bool appended = false;                                    // this sequence takes the new row (uniform)
-  const bool owner = APPEND && h == hk * a.group;   // writes the row and the new mean
+  const bool owner = APPEND && !a.append_apart && h == hk * a.group;   // writes the row and the new mean
   if (APPEND) {
     if (S + 1 <= a.S_max) { appended = true; S += 1; }
     else if (tid == 0) atomicOr(a.err, 1);
@@ -247,31 +251,11 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     if (!(a.flags & 1u)) y = alpha * y3 + (1.0f - alpha) * L.mean[tid];
     out[tid] = T::narrow(y);
   }
-  if (APPEND && owner && tid < DH) {
-    // The append's stores come last.  (Measured at five places of the kernel: in front of stage 0 they sit
-    // on the critical path of every wait that follows, because a wait for a load also waits for the stores
-    // issued before it; after Step 1b, after the select, after the compaction and here cost the same within
-    // noise when workgroups come in several rounds, and here is best when they all run at once.)  Nobody
-    // reads row S - 1 of K or V in this launch (every head takes it from k_new / v_new), the new mean goes to
-    // the *_next buffer, and the columns written to Kt lie above S_fl for every head of the group.
-    a.v_mean_next[kv_head * DH + tid] = L.mean[tid];
-    if (appended) {
-      const uint16_t kc = L.knew[tid];
-      reinterpret_cast<uint16_t*>(a.V)[(kv_head * a.S_stride + (S - 1)) * DH + tid] = L.vnew[tid];
-      if (!TILED) {
-        reinterpret_cast<uint16_t*>(a.K)[(kv_head * a.S_stride + (S - 1)) * DH + tid] = kc;
-        // a step that completes a group of 8 positions copies it to Kt (one 16-byte store per channel row)
-        if ((S & 7) == 0)
-          flush_key_columns(reinterpret_cast<uint16_t*>(a.Kt) + kv_head * DH * (size_t)a.S_stride, K_rows, a.S_stride, DH, S, tid, kc);
-      } else if ((S & 7) != 0) {
-        const_cast<uint16_t*>(K_rows)[(size_t)(S - 1) * DH + tid] = kc;        // row (S - 1) mod 8 of the small buffer
-      } else {
-        // the eighth row completes a tile: channel tid's 8 positions are 16 contiguous bytes of it
-        const uint4 cols = gather_key_columns(K_rows, DH, S, tid, kc);
-        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.K) + (kv_head * a.S_stride + (size_t)(S - 8)) * DH + (size_t)tid * 8) = cols;
-      }
-    }
-  }
+  // The append's stores come last.  (Measured at five places of the kernel: in front of stage 0 they sit
+  // on the critical path of every wait that follows, because a wait for a load also waits for the stores
+  // issued before it; after Step 1b, after the select, after the compaction and here cost the same within
+  // noise when workgroups come in several rounds, and here is best when they all run at once.)
+  if (APPEND && owner && tid < DH) append_channel<DH, TILED>(a, kv_head, tid, S, appended, L.knew[tid], L.vnew[tid], L.mean[tid]);
 #ifdef SPARQ_STAGE_CLOCKS
   SPARQ_STAMP(8);
   if (a.clocks && tid == 0)
@@ -279,13 +263,25 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
 #endif
 }
 
+// Whether a step's append has workgroups of its own.  At the end of a decoding workgroup its stores hold the place on the CU
+// until the memory has taken them; where more workgroups wait for it, that adds up over the rounds, most of all in the steps
+// that complete a group of 8 (d_h 16-byte stores to as many lines per KV head).  Where all run at once, or in two rounds,
+// nobody waits for the last stores of a workgroup, and the others would only begin then.  us per step, in the decoding
+// workgroups / apart, at 4096 positions of 128 channels, k = 512, a step that completes a group and one that does not: 512 units
+// 47.5 / 52.1 and 44.3 / 45.5; 1024 94.1 / 95.0 and 86.4 / 86.4; 1536 143.2 / 141.2; 2048 189.4 / 182.8 and 169.4 / 168.4;
+// 2048 at 8192 positions, k = 256, 162.6 / 146.5 and 137.8 / 131.0.
+// (The append's workgroups in front of the decoding ones, or a quarter, half or three quarters into the grid: 2-11 % more.)
+constexpr bool append_apart(int64_t units) { return units > 1024; }
+
 template <class T, int DH, bool APPEND, bool TILED>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t s) {
   const size_t lds = decode_lds_bytes(a.S_max, DH);
   auto kern = sparq_decode_fused<T, DH, APPEND, TILED>;
   hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, TILED>>(lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(a.B * a.H), dim3(NT), lds, s, a);
+  DecodeArgs d = a;
+  d.append_apart = APPEND && append_apart((int64_t)a.B * a.H);
+  hipLaunchKernelGGL(kern, dim3(a.B * a.H + (d.append_apart ? append_workgroups<DH>((int64_t)a.B * a.H_kv) : 0)), dim3(NT), lds, s, d);
   return hipGetLastError();
 }
 
