@@ -40,7 +40,7 @@ __device__ __forceinline__ void hist_add_chunk(uint32_t* hist, const uint32_t (&
   const uint32_t d1 = kx[1] >> 21, d2 = kx[6] >> 21;
   const uint32_t h1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d1), h2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d2);
   const int n1 = __popcll(__ballot(d1 == h1)), n2 = __popcll(__ballot(d2 == h2));
-  if ((n1 > n2 ? n1 : n2) > kHot) {
+  if (__builtin_expect((n1 > n2 ? n1 : n2) > kHot, 0)) {
     const uint32_t hot = n1 > n2 ? h1 : h2;
     uint32_t n = 0;
 #pragma unroll
@@ -194,7 +194,7 @@ __device__ __forceinline__ void wave_top_r(const K (&key)[E], int r, bool (&sel)
     for (int i = 0; i < 3; ++i)
       if (c[i] >= r) { t = cand[i]; n = c[i]; }
   }
-  if (n == r) {
+  if (__builtin_expect(n == r, 1)) {
 #pragma unroll
     for (int e = 0; e < E; ++e) sel[e] = key[e] >= t;
   } else {                                 // more than r - (keys above t) keys equal t: the first of them
@@ -633,7 +633,7 @@ __device__ __forceinline__ void next_bins(Bin& b, const SelectLds& sl, int tid, 
     const int shift = pass == 1 ? 10 : 0;
     const uint32_t dmask = pass == 1 ? 0x7ffu : 0x3ffu;
     uint32_t* hist = sl.hist + (pass & 1) * kRadixBins;
-    if (pass == 2) {                                      // hist[0] has served the first digit
+    if (__builtin_expect(pass == 2, 0)) {                                      // hist[0] has served the first digit
       for (int i = tid; i < kRadixBins; i += NT) hist[i] = 0u;
       __syncthreads();
     }
@@ -695,7 +695,7 @@ __device__ __forceinline__ Selection select_compact_regs(const uint32_t* keys, u
   };
   narrow();
   next_bins(b, sl, tid, lane, wave, [&](uint32_t* hist, int shift, uint32_t dmask, bool heavy) {
-    if (!heavy) {
+    if (__builtin_expect(!heavy, 1)) {
 #pragma unroll
       for (int e = 0; e < M; ++e)
         if ((eq >> e) & 1u) atomicAdd(&hist[hist_slot((kx[e] >> shift) & dmask)], 1u);
@@ -779,7 +779,7 @@ __device__ __forceinline__ Selection select_compact_words(const uint32_t* keys, 
       for (uint32_t t = bits[w]; t; t &= t - 1) f(w, t & (0u - t), own + 32 * w + __ffs(t) - 1);
   };
   next_bins(b, sl, tid, lane, wave, [&](uint32_t* hist, int shift, uint32_t dmask, bool heavy) {
-    if (!heavy) {
+    if (__builtin_expect(!heavy, 1)) {
       each(eq, [&](int, uint32_t, int at) { atomicAdd(&hist[hist_slot((keys[at] >> shift) & dmask)], 1u); });
     } else {
 #pragma unroll

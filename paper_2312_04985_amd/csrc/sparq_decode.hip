@@ -60,6 +60,9 @@ __device__ __forceinline__ Lds carve(uint32_t* base, int S_max) {
 // inside a tile, a.Kt the up to 7 newest rows of every KV head (8 rows of d_h each) that do not fill a tile yet.
 // Step 1b then strides through the tiles (16 bytes per position chunk and channel), Step 2b collects a row's
 // components from its tile, and the append writes a row of the small buffer, or a whole tile with the eighth row.
+// Blocks that ordinary calls skip are marked (__builtin_expect, here and in the stages), so that the compiler moves them behind the
+// code that runs: where few workgroups wait for instructions, jumping over them costs: the step of one head at 1023 positions 9.83 us, so
+// 9.42; of 32 heads at 1500 12.3 / 11.9; 512 heads and more equal.
 template <class T, int DH, bool APPEND, bool TILED>
 __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
@@ -67,7 +70,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int U = a.B * a.H;
   int u = blockIdx.x;
-  if (APPEND && u >= U) {                  // (append_apart)
+  if (APPEND && __builtin_expect(u >= U, 0)) {            // (append_apart)
     append_heads<T, DH, TILED>(a, u - U);
     return;
   }
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   // Default: every XCD gets a contiguous run of units, so the query heads of a KV group share an L2.
   // With the ragged-batch hint (and no grouped heads): workgroup i serves the sequence with the
   // (i / H)-th largest length, so the longest sequences start first and the short ones fill in behind.
-  if ((a.flags & 4u) && a.H == a.H_kv && a.B > 1 && a.B <= NT) {
+  if (__builtin_expect((a.flags & 4u) && a.H == a.H_kv && a.B > 1 && a.B <= NT, 0)) {
     int* lens = reinterpret_cast<int*>(L.keys);   // free until stage 1
     if (tid < a.B) lens[tid] = a.seq_lens[tid];
     __syncthreads();
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   int S = a.seq_lens[b];
   // a length beyond the bound of this call that the buffers can hold is carried over as it is (clamped only here)
   const int S_kept = (S > a.S_max && S <= a.S_stride) ? S : -1;
-  if (S < 0 || S > a.S_max) {
+  if (__builtin_expect(S < 0 || S > a.S_max, 0)) {
     if (tid == 0) atomicOr(a.err, 8);
     S = S < 0 ? 0 : a.S_max;
   }
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   const bool owner = APPEND && !a.append_apart && h == hk * a.group;   // writes the row and the new mean
   if (APPEND) {
     if (S + 1 <= a.S_max) { appended = true; S += 1; }
-    else if (tid == 0) atomicOr(a.err, 1);
+    else if (__builtin_expect(tid == 0, 0)) atomicOr(a.err, 1);
     if (h == 0 && tid == 0) a.seq_lens_next[b] = S_kept >= 0 ? S_kept : S;
   }
   int kb = a.k_per_seq ? a.k_per_seq[b] : a.k;
@@ -134,7 +137,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
 
   uint16_t* out = reinterpret_cast<uint16_t*>(a.out) + (size_t)u * DH;
   int32_t* idx_out = a.idx_out ? a.idx_out + (size_t)u * a.idx_stride : nullptr;
-  if (S == 0) {   // nothing cached: defined output, raise the flag
+  if (__builtin_expect(S == 0, 0)) {   // nothing cached: defined output, raise the flag
     if (tid < DH) out[tid] = 0;
     if (tid == 0) { atomicOr(a.err, 2); if (a.alpha_out) a.alpha_out[u] = 0.0f; }
     if (a.chan_out && tid < a.r) a.chan_out[(size_t)u * a.r + tid] = -1;
