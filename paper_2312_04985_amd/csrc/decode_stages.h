@@ -305,9 +305,14 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
   }
 }
 
-// Chunks (8 consecutive positions = 16 bytes of every channel row) chunk_begin + tid + i * STRIDE belong to
-// thread tid of STRIDE (all NT threads of the workgroup unless the caller divides the rows of a chunk among
-// groups of threads).  The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
+// Chunks (8 consecutive positions = 16 bytes of every channel row) belong to the STRIDE threads (all NT of the workgroup unless
+// the caller divides the rows of a chunk among groups of threads): up to two per thread, chunk_begin + tid + i * STRIDE; beyond,
+// they are cut into runs of 64, one chunk per lane, and every wave takes consecutive runs (the first waves one more where they
+// do not come out even), so that the waves read at places an eighth of the row apart.  (Side by side, the workgroup
+// advancing 8 KB of every row at a time, all requests of a moment lay at one offset of rows whose stride is a power of two or
+// nearly: 512 heads of 128 channels at 16 384 positions 142.7 us per decode, so 132.9; of 256 channels 371 / 340, at 16 440
+// 373 / 341; lengths far from a power of two equal.)
+// The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
 // a two-deep software pipeline: a batch of 8 loads is always in flight behind the one being accumulated,
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
 // 8 sums of chunk c.  requested() is called by whole waves once their first batches of loads are under way: work that
@@ -327,12 +332,20 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
                                                     int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
   const int n_batches = (r + 7) >> 3;
   const int n_chunks = chunk_end - chunk_begin;
-  const int my_chunks = n_chunks > tid ? (n_chunks - tid + STRIDE - 1) / STRIDE : 0;
+  constexpr int W = STRIDE / kWave;
+  int own = tid, my_chunks = n_chunks > tid ? (n_chunks - tid + STRIDE - 1) / STRIDE : 0, step = STRIDE;
+  if (n_chunks > 2 * STRIDE) {
+    const int w = tid / kWave, runs = (n_chunks + kWave - 1) / kWave, per = runs / W, more = runs % W;
+    own += (w * (per - 1) + (w < more ? w : more)) * kWave;
+    my_chunks = (n_chunks - own + kWave - 1) / kWave;
+    if (my_chunks > per + (w < more)) my_chunks = per + (w < more);
+    step = kWave;
+  }
   const int items = my_chunks * n_batches;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int ic = 0, ib = 0, cc = 0, cb = 0;   // issue and consume cursors: (own chunk number, batch)
   auto issue_next = [&](u32x4 (&v)[8]) {
-    issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + tid + ic * STRIDE) * chunk_bytes), row_bytes, chan + ib * 8);
+    issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + own + ic * step) * chunk_bytes), row_bytes, chan + ib * 8);
     if (++ib == n_batches) { ib = 0; ++ic; }
   };
   auto consume_next = [&](const u32x4 (&v)[8]) {
@@ -345,7 +358,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
       for (int e = 0; e < 8; ++e) acc[e] = fmaf(f[e], qv, acc[e]);
     }
     if (++cb == n_batches) {
-      finish(chunk_begin + tid + cc * STRIDE, acc);
+      finish(chunk_begin + own + cc * step, acc);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
       cb = 0; ++cc;
