@@ -195,7 +195,18 @@ bool shared_bucket_plan(const sparq_shape* s, size_t lds_max, PlanInfo* p) {
   return true;
 }
 
-PlanInfo choose_plan(const sparq_shape* s) {
+// Few units whose idle CUs fetch for them (decode_helped): what one workgroup per unit takes grows with what it reads of a unit, so
+// that from 12 288 positions on the digit-bucket plan is faster where that is much.  us per decode, helped / bucket, caches in HBM,
+// r and k: 32 units of 12 300 positions 32, 256 22.4 / 24.6; 32, 512 24.3 / 25.2; 32, 1024 28.0 / 26.1; 16, 512 19.6 / 23.5; 64, 512
+// 33.9 / 29.3; 48 units 32, 512 25.5 / 27.5; 64 units 32, 256 25.3 / 29.2; 32, 1500 36.9 / 34.9; 24 units 32, 1000 27.3 / 25.4; 16
+// units 32, 256 21.5 / 21.3.
+bool helped_faster(const sparq_shape* s) {
+  const int64_t units = (int64_t)s->B * s->H;
+  return units > 16 && units <= 64 && (int64_t)s->S_max * s->r * 2 + (int64_t)s->k * s->d_h * 4 <= 1000000;
+}
+
+// by_size: as if helped_faster were not; workspaces are sized by that, so that a call with another r or k is not refused.
+PlanInfo choose_plan(const sparq_shape* s, bool by_size = false) {
   PlanInfo p{kPlanNone, 0, 0, 0, 0, 0, 0};
   const size_t lds_max = (size_t)max_lds_bytes();
   if (single_k(s)) {
@@ -231,7 +242,7 @@ PlanInfo choose_plan(const sparq_shape* s) {
   // 24 576: 30/56, 41/59, 57/62, 83/65; 32 768: 34/74, 51/77, 86/82, 102/88), and whatever one workgroup's LDS cannot hold.
   const int64_t units = (int64_t)s->B * s->H;
   const bool one_wg_fits = decode_lds_bytes(s->S_max, s->d_h) <= lds_max;
-  const bool bucket_faster = (s->S_max >= 16384 && units <= 96) || (s->S_max >= 12288 && units <= 64);
+  const bool bucket_faster = ((s->S_max >= 16384 && units <= 96) || (s->S_max >= 12288 && units <= 64)) && (by_size || !helped_faster(s));
   if (units <= kSplitMaxUnits && s->S_max >= 8192 && (bucket_faster || !one_wg_fits) && bucket_plan(s, lds_max, &p)) {
     p.plan = kPlanBucket;
     return p;
@@ -308,7 +319,7 @@ LongLayout long_layout(const sparq_shape* s, const PlanInfo& p) {
 
 size_t workspace_need(const sparq_shape* s) {
   size_t need = (size_t)kControlBytes + (size_t)s->B * s->H * dense_room(s) * (s->d_h + 2) * sizeof(float);
-  const PlanInfo p = choose_plan(s);
+  const PlanInfo p = choose_plan(s, true);
   size_t e = 0;
   if (p.plan == kPlanLong) e = long_layout(s, p).end;
   if (p.plan == kPlanBucket || p.plan == kPlanSharedBucket) e = bucket_layout(s, p).end;

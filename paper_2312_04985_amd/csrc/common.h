@@ -55,8 +55,10 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
 // this read.  Measured against plain loads: the decode step 6-10 % faster on every many-head workload (512 heads
 // of 4096 positions 52.8 -> 47.6 us, 2048 of 8192 157.3 -> 147.4, 512 ragged ones of 256 channels 243.6 -> 222.1), 1-3 % slower only where the query heads of
 // a KV group select for themselves in the one-launch kernel and find each other's rows in L2.
-template <class V>
+// KEEP: an ordinary load, for lines that other workgroups of the launch use too.
+template <class V, bool KEEP = false>
 __device__ __forceinline__ V load16_as(const void* p) {
+  if (KEEP) return __builtin_bit_cast(V, *reinterpret_cast<const u32x4*>(p));
   return __builtin_bit_cast(V, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
 __device__ __forceinline__ uint4 load16(const void* p) { return load16_as<uint4>(p); }

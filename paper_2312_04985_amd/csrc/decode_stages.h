@@ -294,14 +294,14 @@ __device__ __forceinline__ Window make_window(int local_window, int S, int kq) {
 // lane: with the row numbers moved to scalar registers and multiplied there, requesting 16 rows took 0.7 us of a
 // wave's time (one scalar instruction after the other), this way 0.3.
 // V: u32x4 keeps the 16 bytes of a request in one register tuple, uint4 are four words that the compiler may part.
-template <class V>
+template <bool KEEP = false, class V>
 __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t row_bytes, const int* chan) {
   const int4 lo = reinterpret_cast<const int4*>(chan)[0], hi = reinterpret_cast<const int4*>(chan)[1];
   uint32_t ch[8] = {(uint32_t)lo.x, (uint32_t)lo.y, (uint32_t)lo.z, (uint32_t)lo.w, (uint32_t)hi.x, (uint32_t)hi.y, (uint32_t)hi.z, (uint32_t)hi.w};
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     asm("" : "+v"(ch[t]));               // (the same in every lane: kept in a vector register all the same)
-    v[t] = load16_as<V>(base + (uint64_t)ch[t] * row_bytes);
+    v[t] = load16_as<V, KEEP>(base + (uint64_t)ch[t] * row_bytes);
   }
 }
 
@@ -326,7 +326,7 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
 // Addressing: chunk c of channel row j lies at Kt_head + j * row_bytes + c * chunk_bytes.  The S-contiguous
 // key copy has row_bytes = 2 S_max and chunk_bytes = 16; the tiled single-copy layout (tiles of 8 positions,
 // channel-major inside a tile) has row_bytes = 16 and chunk_bytes = 16 d_h.
-template <class T, int STRIDE = NT, class Finish, class Requested>
+template <class T, int STRIDE = NT, bool KEEP = false, class Finish, class Requested>
 __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                     const float* qs, int r, int chunk_begin, int chunk_end,
                                                     int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
@@ -334,7 +334,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
   const int n_chunks = chunk_end - chunk_begin;
   constexpr int W = STRIDE / kWave;
   int own = tid, my_chunks = n_chunks > tid ? (n_chunks - tid + STRIDE - 1) / STRIDE : 0, step = STRIDE;
-  if (n_chunks > 2 * STRIDE) {
+  if (!KEEP && n_chunks > 2 * STRIDE) {
     const int w = tid / kWave, runs = (n_chunks + kWave - 1) / kWave, per = runs / W, more = runs % W;
     own += (w * (per - 1) + (w < more ? w : more)) * kWave;
     my_chunks = (n_chunks - own + kWave - 1) / kWave;
@@ -345,7 +345,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int ic = 0, ib = 0, cc = 0, cb = 0;   // issue and consume cursors: (own chunk number, batch)
   auto issue_next = [&](u32x4 (&v)[8]) {
-    issue_rows(v, Kt_head + (size_t)((uint32_t)(chunk_begin + own + ic * step) * chunk_bytes), row_bytes, chan + ib * 8);
+    issue_rows<KEEP>(v, Kt_head + (size_t)((uint32_t)(chunk_begin + own + ic * step) * chunk_bytes), row_bytes, chan + ib * 8);
     if (++ib == n_batches) { ib = 0; ++ic; }
   };
   auto consume_next = [&](const u32x4 (&v)[8]) {
@@ -874,7 +874,7 @@ struct RowGeometry {
 // so a lane's 8 channels of one position are eight 2-byte loads 16 bytes apart; positions from tiled_below on
 // (the up to 7 newest, not yet in a tile) are rows of K_stage (row p - tiled_below, already offset by `sub`).
 // requested() is called by whole waves once the first group of loads is under way.
-template <class T, int DH, bool TILED = false, class Requested = Nothing>
+template <class T, int DH, bool TILED = false, bool KEEP = false, class Requested = Nothing>
 __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_head, const int* list, int n_begin,
                                             int n_end, const float (&q8)[8], int lane, int wave, float& m_run,
                                             float& l_run, float (&acc)[8], Requested&& requested = Requested{},
@@ -889,7 +889,7 @@ __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_he
       const int p = list[n < n_end ? n : n_end - 1];
       const uint32_t off = (uint32_t)p * (uint32_t)(DH * 2);   // < S_max * 512 bytes
       if (!TILED) {
-        kr[t] = load16(K_head + off);
+        kr[t] = load16_as<uint4, KEEP>(K_head + off);
       } else if (p >= tiled_below) {
         kr[t] = load16(K_stage + (uint32_t)(p - tiled_below) * (uint32_t)(DH * 2));
       } else {
@@ -898,7 +898,7 @@ __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_he
         const uint32_t c0 = tp[0], c1 = tp[8], c2 = tp[16], c3 = tp[24], c4 = tp[32], c5 = tp[40], c6 = tp[48], c7 = tp[56];
         kr[t] = make_uint4(c0 | (c1 << 16), c2 | (c3 << 16), c4 | (c5 << 16), c6 | (c7 << 16));
       }
-      vr[t] = load16(V_head + off);
+      vr[t] = load16_as<uint4, KEEP>(V_head + off);
     }
   };
   // The rows of a group are weighted against one maximum: one rescaling of the sums for UNR rows.  (One per row: 512 heads of

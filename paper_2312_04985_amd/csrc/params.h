@@ -44,6 +44,8 @@ struct DecodeArgs {
   uint32_t flags;
   int32_t local_window;
   int32_t group = 1;                      // query heads per KV head
+  int32_t helpers = 0, per_xcd = 0;       // few units: workgroups that fetch for each unit's own, units per XCD
+  Divider by_xcd;                         // by per_xcd
   int32_t append_apart = 0;               // the step's append has workgroups of its own, behind the decoding ones
   Divider by_H, by_H_kv, by_group;        // set by enqueue_decode, as `group`
   unsigned long long* clocks = nullptr;   // [workgroups][kStageStamps] time stamps; set only by a SPARQ_STAGE_CLOCKS build
@@ -201,6 +203,8 @@ size_t decode_lds_bytes(int S_max, int d_h);
 size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // LDS that admits S_max; 0: no grouped-query kernel for this shape
 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t s);
+bool decode_helped(const DecodeArgs& a);                // few units: launch_decode goes on with launch_decode_helped
+hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t decode_single_k_lds_bytes(int S_max, int d_h);   // LDS that admits S_max
 hipError_t launch_decode_single_k(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t long_scores_lds_bytes(int span_len, int d_h);
