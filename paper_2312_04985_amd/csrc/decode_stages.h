@@ -11,10 +11,25 @@
 
 #include <type_traits>
 
-namespace sparq {
+// Waves per workgroup of what a source builds from the stages: 8, or what it defines before it includes this (4).  The two
+// are namespaces of their own, so that no linker takes one's code for the other's.
+#ifndef SPARQ_WAVES
+#define SPARQ_WAVES 8
+#endif
+#if SPARQ_WAVES == 8
+#define SPARQ_STAGES waves8
+#elif SPARQ_WAVES == 4
+#define SPARQ_STAGES waves4
+#else
+#error "4 or 8 waves"
+#endif
 
-constexpr int NT = kDecodeThreads;
-constexpr int NW = NT / kWave;   // waves per workgroup
+namespace sparq {
+inline namespace SPARQ_STAGES {
+
+constexpr int NW = SPARQ_WAVES;   // waves per workgroup
+constexpr int NT = NW * kWave;
+static_assert(SPARQ_WAVES != 8 || NT == kDecodeThreads, "what the host sizes LDS for");
 constexpr int kTieHeavy = 2048;  // a radix bin with more keys than this is counted tie-robustly in the next pass
 
 // ------------------------------------------------------------------------------------------------
@@ -375,7 +390,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
 // channel on every append: those cost a 32-byte memory transaction each).  Positions 8 floor(S/8) .. S-1
 // therefore are not in Kt yet; there are at most 7 of them and their approximate logit numerators come
 // from the rows of K: wave w takes position 8 floor(S/8) + w, lane l the channels l, l + 64, ... of the
-// padded list.  The loads are issued before Step 1b streams Kt and used after it.
+// padded list; with fewer than 8 waves a wave takes several.  The loads are issued before Step 1b streams Kt and used after it.
 struct TailRow {
   uint16_t raw[4];   // up to 256 list entries over 64 lanes
 };
@@ -1030,4 +1045,5 @@ __device__ __forceinline__ void combine_partials(const float* parts, int n_parts
   }
 }
 
+}  // inline namespace
 }  // namespace sparq

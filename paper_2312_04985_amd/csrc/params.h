@@ -205,6 +205,8 @@ size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // LDS that admits 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_helped(const DecodeArgs& a);                // few units: launch_decode goes on with launch_decode_helped
 hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s);
+bool decode_short(const DecodeArgs& a);                 // many units with short caches: ... with launch_decode_short
+hipError_t launch_decode_short(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t decode_single_k_lds_bytes(int S_max, int d_h);   // LDS that admits S_max
 hipError_t launch_decode_single_k(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t long_scores_lds_bytes(int span_len, int d_h);

@@ -12,6 +12,7 @@
 #include "decode_stages.h"
 
 namespace sparq {
+inline namespace SPARQ_STAGES {
 
 // A SPARQ_STAGE_CLOCKS build (a second library for profiling, never the default one) keeps nine time stamps per
 // workgroup in scalar registers and stores them when the workgroup ends; otherwise the macro is empty.
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     __syncthreads();
   }
   const Window win = make_window(a.local_window, S, kq);
-  // the newest S mod 8 positions are not in Kt: wave w gets position S_fl + w from its K row (from the
+  // the newest S mod 8 positions are not in Kt: wave w gets position S_fl + w (and S_fl + w + NW) from its K row (from the
   // inputs if it is the row being appended); loads issued behind the stream's first, used after stage 1
   // (in the one-launch step Kt is up to date for the length before this call: the group of 8 that the new
   // row may complete is written during this launch, so up to 8 positions come from rows)
@@ -181,8 +182,9 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   // rows of K by position (two-copy layout), or the rows of the newest positions S_fl .. (tiled layout)
   const uint16_t* K_rows = TILED ? reinterpret_cast<const uint16_t*>(a.Kt) + kv_head * (size_t)(8 * DH) - (size_t)S_fl * DH
                                  : reinterpret_cast<const uint16_t*>(a.K) + kv_head * a.S_stride * (size_t)DH;
-  TailRow tail;
-  const bool tail_is_new = APPEND && appended && wave == n_tail - 1;
+  constexpr int TAILS = (8 + NW - 1) / NW;                  // per wave: positions S_fl + wave, S_fl + wave + NW, ...
+  static_assert(TAILS * NW >= 8, "every one of up to 8 positions has a wave");
+  TailRow tail[TAILS];
 
   SPARQ_STAMP(1);
   // ---------------- stage 1 ----------------
@@ -200,9 +202,13 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
       }
       L.mean[late] = vm;
     }
-    if (wave < n_tail)
-      tail = tail_row_issue(tail_is_new ? reinterpret_cast<const uint16_t*>(a.k_new) + kv_head * DH : K_rows + (size_t)(S_fl + wave) * DH,
-                            L.qry.chan, r8, lane);
+#pragma unroll
+    for (int t = 0; t < TAILS; ++t) {
+      const int n = wave + t * NW;
+      if (n < n_tail)
+        tail[t] = tail_row_issue(APPEND && appended && n == n_tail - 1 ? reinterpret_cast<const uint16_t*>(a.k_new) + kv_head * DH
+                                                                       : K_rows + (size_t)(S_fl + n) * DH, L.qry.chan, r8, lane);
+    }
     esc = kLog2e / temperature(L.sel.red + 30, a.flags, DH, a.r);
   };
   auto finish = [&](int c, const float (&acc)[8]) {
@@ -216,13 +222,17 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   };
   stream_channel_rows<T, NT, HELP>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
-  if (wave < n_tail) {
-    const float dot = tail_row_dot<T>(tail, L.qry.qs, r8, lane);
-    if (lane == 0) {
-      zs.add({dot}, esc);
-      const uint32_t key = float_to_key(dot);
-      L.keys[S_fl + wave] = key;
-      if (S_fl + wave < win.S_old) atomicAdd(&L.sel.hist[hist_slot(key >> 21)], 1u);
+#pragma unroll
+  for (int t = 0; t < TAILS; ++t) {
+    const int n = wave + t * NW;
+    if (n < n_tail) {
+      const float dot = tail_row_dot<T>(tail[t], L.qry.qs, r8, lane);
+      if (lane == 0) {
+        zs.add({dot}, esc);
+        const uint32_t key = float_to_key(dot);
+        L.keys[S_fl + n] = key;
+        if (S_fl + n < win.S_old) atomicAdd(&L.sel.hist[hist_slot(key >> 21)], 1u);
+      }
     }
   }
   SPARQ_STAMP(2);
@@ -311,4 +321,20 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
 #endif
 }
 
+// Whether a step's append has workgroups of its own.  At the end of a decoding workgroup its stores hold the place on the CU
+// until the memory has taken them; where more workgroups wait for it, that adds up over the rounds, most of all in the steps
+// that complete a group of 8 (d_h 16-byte stores to as many lines per KV head).  Where all run at once, or in two rounds,
+// nobody waits for the last stores of a workgroup, and the others would only begin then.  us per step, in the decoding
+// workgroups / apart, at 4096 positions of 128 channels, k = 512, a step that completes a group and one that does not: 512 units
+// 47.5 / 52.1 and 44.3 / 45.5; 1024 94.1 / 95.0 and 86.4 / 86.4; 1536 143.2 / 141.2; 2048 189.4 / 182.8 and 169.4 / 168.4;
+// 2048 at 8192 positions, k = 256, 162.6 / 146.5 and 137.8 / 131.0.
+// (The append's workgroups in front of the decoding ones, or a quarter, half or three quarters into the grid: 2-11 % more.)
+constexpr bool append_apart(int64_t units) { return units > 1024; }
+
+// LDS bytes for a cache of S_max rows and head dimension d_h
+inline size_t fused_lds_bytes(int S_max, int d_h) {
+  return 4 * ((size_t)S_max + 2 * kRadixBins + (size_t)NW * (d_h + 2) + 5 * (size_t)d_h + 32 + 16 + 8);
+}
+
+}  // inline namespace
 }  // namespace sparq
