@@ -113,7 +113,7 @@ bool tiled_k(const sparq_shape* shape) { return (shape->flags & SPARQ_FLAG_TILED
 
 // Which kernels serve a shape.  Every plan keeps one 4-byte key per position (or per candidate) of its
 // unit of work in LDS; that decides what fits.
-enum Plan { kPlanNone, kPlanFused, kPlanLong, kPlanShared, kPlanSharedSplit, kPlanSingleK, kPlanBucket, kPlanSharedBucket };
+enum Plan { kPlanNone, kPlanFused, kPlanLong, kPlanShared, kPlanSharedSplit, kPlanSingleK, kPlanSingleBucket, kPlanBucket, kPlanSharedBucket };
 struct PlanInfo { Plan plan; int n_split, n_span, span_len, cand_cap, n1, span1; };
 
 // The two-level plan: spans of `span` positions select their own top-k, one workgroup per unit merges at
@@ -205,13 +205,22 @@ bool helped_faster(const sparq_shape* s) {
   return units > 16 && units <= 64 && (int64_t)s->S_max * s->r * 2 + (int64_t)s->k * s->d_h * 4 <= 1000000;
 }
 
+// A key cache stored once, few units: Step 1 reads whole rows, which one workgroup gets at 60 GB/s.  us per decode, one workgroup per
+// unit / digit buckets, 128 channels, k 256 unless said: 1 unit at 2000 positions 16.8 / 22.3, 4096 28.8 / 22.9; 20 on 5 KV heads at 15 202,
+// k 1901, 102.7 / 39.4; 32 at 3000 26.0 / 25.9, 4096 30.8 / 26.0, 16 384 with k 1024 96.7 / 45.5; of 64 channels at 4096 20.7 / 22.4; of 256 at
+// 2000 33.1 / 34.6, 4096 52.8 / 33.9; 64 units at 4918 37.8 / 35.9, 12 000 72.3 / 52.7; 96 at 4096 34.1 / 37.5, 12 000 76.1 / 72.1; 128 at
+// 4096 36.5 / 43.7, 20 000 130.6 / 130.6.
+bool single_bucket_faster(const sparq_shape* s) {
+  return (int64_t)s->B * s->H <= 64 && s->S_max >= 2048 + 2048 * 128 / s->d_h;
+}
+
 // by_size: as if helped_faster were not; workspaces are sized by that, so that a call with another r or k is not refused.
 PlanInfo choose_plan(const sparq_shape* s, bool by_size = false) {
   PlanInfo p{kPlanNone, 0, 0, 0, 0, 0, 0};
   const size_t lds_max = (size_t)max_lds_bytes();
   if (single_k(s)) {
     const size_t need = wants_shared(s) ? 0 : decode_single_k_lds_bytes(s->S_max, s->d_h);
-    if (need != 0 && need <= lds_max) p.plan = kPlanSingleK;
+    if (need != 0 && need <= lds_max) p.plan = single_bucket_faster(s) && bucket_plan(s, lds_max, &p) ? kPlanSingleBucket : kPlanSingleK;
     return p;
   }
   if (tiled_k(s)) {            // one kernel reads the tiled layout: one workgroup per head
@@ -337,12 +346,14 @@ int check_workspace(const sparq_shape* s, const void* ws, size_t bytes) {
 }
 
 // enqueue one decode over `a` with the plan the shape calls for
-hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void* workspace, hipStream_t s) {
+hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void* workspace, size_t workspace_bytes, hipStream_t s) {
   DecodeArgs a = args;
   a.group = a.H / a.H_kv;
   a.by_H = make_divider(a.H); a.by_H_kv = make_divider(a.H_kv); a.by_group = make_divider(a.group);
-  const PlanInfo p = choose_plan(shape);
+  PlanInfo p = choose_plan(shape);
   if (p.plan == kPlanNone) return hipErrorInvalidValue;
+  // (a workspace that the call accepts may have been sized for another plan: then one workgroup per unit, which needs none)
+  if (p.plan == kPlanSingleBucket && workspace_bytes < bucket_layout(shape, p).end) p.plan = kPlanSingleK;
 #ifdef SPARQ_STAGE_CLOCKS
   if (p.plan == kPlanFused) {
     DecodeArgs c = a;
@@ -351,10 +362,10 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void
   }
 #endif
   if (p.plan == kPlanFused) return launch_decode(a, shape->dtype, s);
-  const bool one_k = p.plan == kPlanSingleK;
+  const bool one_k = p.plan == kPlanSingleK || p.plan == kPlanSingleBucket;
   DecodeArgs d = a;
-  if (a.k_new && (p.plan == kPlanSharedSplit || p.plan == kPlanSingleK)) {
-    // the grouped-query rule over several workgroups and the single-copy kernel have no append built in: the append
+  if (a.k_new && (p.plan == kPlanSharedSplit || one_k)) {
+    // the grouped-query rule over several workgroups and the single-copy kernels have no append built in: the append
     // kernel writes the *_next state, and they decode from that
     AppendArgs ap;
     ap.K = a.K; ap.Kt = one_k ? nullptr : a.Kt; ap.V = a.V; ap.v_mean = const_cast<float*>(a.v_mean); ap.seq_lens = const_cast<int32_t*>(a.seq_lens);
@@ -366,7 +377,7 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void
     d.v_mean = a.v_mean_next; d.seq_lens = a.seq_lens_next;
     d.k_new = nullptr; d.v_new = nullptr; d.v_mean_next = nullptr; d.seq_lens_next = nullptr;
   }
-  if (one_k) return launch_decode_single_k(d, shape->dtype, s);
+  if (p.plan == kPlanSingleK) return launch_decode_single_k(d, shape->dtype, s);
   if (p.plan == kPlanShared)
     return launch_decode_shared(d, reinterpret_cast<float*>(static_cast<char*>(workspace) + kControlBytes), shape->dtype, s);
   char* w = static_cast<char*>(workspace);
@@ -388,10 +399,11 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void
     ga.part_ws = reinterpret_cast<float*>(w + l.part);
     return launch_decode_shared_split(ga, shape->dtype, s);
   }
-  if (p.plan == kPlanBucket || p.plan == kPlanSharedBucket) {
+  if (p.plan == kPlanBucket || p.plan == kPlanSharedBucket || p.plan == kPlanSingleBucket) {
     const BucketLayout l = bucket_layout(shape, p);
     BucketArgs ba;
     ba.d = d;
+    ba.rows = p.plan == kPlanSingleBucket;
     ba.n_span = p.n_span; ba.span_len = p.span_len; ba.cand_cap = p.cand_cap;
     ba.by_span = make_divider(ba.n_span); ba.by_len = make_divider(ba.span_len);
     ba.tmax_ws = reinterpret_cast<float*>(w + l.tmax);
@@ -481,6 +493,9 @@ int sparq_workspace_bytes(const sparq_shape* caller_shape, size_t* out_bytes) {
   const size_t need = workspace_need(shape);
   const size_t append = tiled_k(shape) ? 0 : kAppendScratchOffset + append_scratch_bytes((int64_t)shape->B * shape->H_kv, shape->S_max, shape->d_h);
   *out_bytes = append > need ? append : need;
+  // the digit-bucket plan for a key cache stored once is used where a caller brings the room for it
+  const PlanInfo p = choose_plan(shape);
+  if (p.plan == kPlanSingleBucket && bucket_layout(shape, p).end > *out_bytes) *out_bytes = bucket_layout(shape, p).end;
   return SPARQ_OK;
 }
 
@@ -533,7 +548,7 @@ int sparq_decode(const sparq_shape* caller_shape, const sparq_cache* cache, cons
   a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
   a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
   a.local_window = shape->local_window;
-  return enqueue_decode(shape, a, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
+  return enqueue_decode(shape, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
 int sparq_decode_noalloc(const sparq_shape* caller_shape, const sparq_cache* cache, const void* q,
@@ -559,7 +574,7 @@ int sparq_decode_noalloc(const sparq_shape* caller_shape, const sparq_cache* cac
   a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
   a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
   a.local_window = shape->local_window;
-  return enqueue_decode(shape, a, ws, s) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
+  return enqueue_decode(shape, a, ws, kStaticScratchBytes, s) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
 int sparq_decode_step(const sparq_shape* caller_shape, const sparq_cache* cache, const void* k_new,
@@ -588,7 +603,7 @@ int sparq_decode_step(const sparq_shape* caller_shape, const sparq_cache* cache,
   a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
   a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
   a.local_window = shape->local_window;
-  return enqueue_decode(shape, a, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
+  return enqueue_decode(shape, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
 int dense_decode(const sparq_shape* caller_shape, const sparq_cache* cache, const void* q, void* out,
@@ -642,6 +657,7 @@ const char* sparq_decode_plan(const sparq_shape* caller_shape) {
     case kPlanShared: return "sparq_decode_shared (grouped-query rule, one workgroup per KV head)";
     case kPlanSharedBucket: return "gs_logits + bk_group_scores + bk_select_gather (grouped-query rule on the digit-bucket plan)";
     case kPlanSharedSplit: return "gs_logits + gs_select + gs_merge + gs_gather + split_combine (grouped-query rule, several workgroups per KV head)";
+    case kPlanSingleBucket: return "bk_scores + bk_select_gather (digit-bucket plan, key cache stored once)";
     case kPlanSingleK: return "sparq_decode_single_k (key cache stored once)";
     default: return "unsupported";
   }

@@ -976,6 +976,57 @@ __device__ __forceinline__ void attend_rows(const char* K_head, const char* V_he
   }
 }
 
+// Step 1b from the row-major keys: rows 0..S-1 of one KV head (or of a span), LPR lanes per row as in the gather of
+// Step 2, groups of UNR loads through a two-deep software pipeline.  finish(position, dot) is called by
+// the first lane of each row's lane group.  qm8 = the lane's 8 masked query components.
+template <class T, int DH, class Finish>
+__device__ __forceinline__ void stream_key_rows(const char* K_head_sub, int S, const float (&qm8)[8], int lane, int wave,
+                                                Finish&& finish) {
+  using G = RowGeometry<DH>;
+  constexpr int UNR = 8, GROUP = G::RPI * UNR;
+  const int slot = wave * G::RPW + lane / G::LPR;
+  const bool first = lane % G::LPR == 0;
+  const int n_groups = (S + GROUP - 1) / GROUP;
+  auto issue = [&](uint4 (&kr)[UNR], int g) {
+#pragma unroll
+    for (int t = 0; t < UNR; ++t) {
+      const int n = g * GROUP + t * G::RPI + slot;
+      kr[t] = load16(K_head_sub + (size_t)(n < S ? n : S - 1) * (DH * 2));
+    }
+  };
+  auto consume = [&](const uint4 (&kr)[UNR], int g) {
+#pragma unroll
+    for (int t = 0; t < UNR; ++t) {
+      const int n = g * GROUP + t * G::RPI + slot;
+      float f[8];
+      unpack8<T>(kr[t], f);
+      float dot = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dot = fmaf(f[e], qm8[e], dot);
+      dot = lanes_sum<G::LPR>(dot);
+      if (first && n < S) finish(n, dot);
+    }
+  };
+  if (n_groups > 0) {
+    uint4 ka[UNR], kb[UNR];
+    issue(ka, 0);
+    int g = 0;
+    for (; g + 2 < n_groups; g += 2) {
+      issue(kb, g + 1);
+      consume(ka, g);
+      issue(ka, g + 2);
+      consume(kb, g + 1);
+    }
+    if (g + 1 < n_groups) {
+      issue(kb, g + 1);
+      consume(ka, g);
+      consume(kb, g + 1);
+    } else {
+      consume(ka, g);
+    }
+  }
+}
+
 // One more row, given as 16-bit codes in LDS (the row a decode step appends), folded into the state of
 // the lane group with slot 0.  Executed by all lanes; no barrier.
 template <class T, int DH>

@@ -138,6 +138,7 @@ struct BucketArgs {
   float* anum_ws;          // [B * H][n_span] the span's share of alpha's numerator (relative to the sequence maximum)
   float* tau_ws;           // [B * H]
   float* zden_ws;          // [B * H] softmax denominator of the approximate scores, for bk_combine
+  int32_t rows = 0;        // the key cache is stored once, as rows
   int32_t merge;           // the unit's last workgroup of the gather merges (else bk_combine, in a launch of its own)
   int32_t* tickets;        // [B * H] counters of finished spans, cleared by the plan's own first launches
   uint16_t* coarse_ws;     // [B * H][n_span][64] A[32 l]

@@ -25,6 +25,7 @@
 // The grouped-query rule runs on the same plan: gs_logits leaves every head's logit numerators and statistics in
 // the workspace, bk_group_scores turns the group score into keys and publishes the spans per KV unit, and
 // bk_select_gather<GROUP> runs per query head on the KV unit's tables (alpha from the head's own logits).
+// A key cache stored once runs on it too: bk_scores<ROWS> reads the rows of K instead of Kt.
 // Inside sparq_decode_step the launches count the row being appended as position S_b (taken from the inputs wherever it
 // is needed); the last workgroup of the first query head of a KV group writes it to the cache: no launch reads that row
 // from the cache, and the columns of Kt that it may complete are only read by the first launch.
@@ -131,7 +132,9 @@ __host__ __device__ constexpr size_t bk_scores_fixed_words() {
 // were wrongly allowed to overlap spoil their own results and no later ones.
 __device__ __forceinline__ void clear_ticket(int32_t* p) { __hip_atomic_store(p, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <class T, int DH>
+// ROWS: the key cache is stored once, as rows (no Kt): the span's rows are read whole and multiplied by the query with the
+// unselected channels zeroed, as sparq_decode_single_k does.  No row is being appended then.
+template <class T, int DH, bool ROWS>
 __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   const int P = a.span_len;
@@ -187,12 +190,18 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
   const int len = S - p0 < P ? S - p0 : P;
 
   const QueryLds Q{qf, qs, chan};
+  float* qmask = reinterpret_cast<float*>(cur);               // (ROWS; `cur` is free until the table)
+  if (ROWS && tid < DH) qmask[tid] = 0.0f;
   select_channels<T, DH>(Q, qcode, d.r, red + 30, lane, wave);
+  if (ROWS) {
+    if (tid < d.r) qmask[chan[tid]] = qs[tid];
+    __syncthreads();
+  }
 
   // the newest S mod 8 positions are not in Kt (inside a step: up to 8, Kt being up to date for the length before
   // the call): the span that holds them takes them from the rows of K, the row being appended from the inputs
   const int S_fl = (appended ? S - 1 : S) & ~7, r8 = (d.r + 7) & ~7;
-  const int n_tail = (S_fl >= p0 && S_fl < p0 + len) ? S - S_fl : 0;
+  const int n_tail = !ROWS && S_fl >= p0 && S_fl < p0 + len ? S - S_fl : 0;
   TailRow tail;
   float tau, esc;
   auto requested = [&]() {     // behind the stream's first loads
@@ -256,7 +265,21 @@ __global__ __launch_bounds__(NT, 4) void bk_scores(const BucketArgs a) {
     }
   };
   const int n_chunks = c_end - c_begin;
-  if (n_chunks <= NT / 4 && nb >= 4) shared_chunks(std::integral_constant<int, 4>{});
+  if (ROWS) {
+    using G = RowGeometry<DH>;
+    const int sub = lane % G::LPR;
+    float qm8[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qm8[e] = qmask[sub * 8 + e];
+    requested();
+    stream_key_rows<T, DH>(reinterpret_cast<const char*>(d.K) + (kv_head * d.S_stride + p0) * (size_t)(DH * 2) + sub * 16, len, qm8, lane, wave,
+                           [&](int n, float dot) {
+      tmax = fmaxf(tmax, dot);
+      const uint32_t key = float_to_key(dot);
+      keys[n] = key;
+      if (p0 + n < win.S_old) atomicAdd(&hist[hist_slot(bucket_digit<false>(key))], 1u);
+    });
+  } else if (n_chunks <= NT / 4 && nb >= 4) shared_chunks(std::integral_constant<int, 4>{});
   else if (n_chunks <= NT / 2 && nb >= 2) shared_chunks(std::integral_constant<int, 2>{});
   else stream_channel_rows<T>(Kt_head, row_bytes, chan, qs, d.r, c_begin, c_end, tid, [&](int c, const float (&acc)[8]) {
     finish4(c * 8 - p0, make_float4(acc[0], acc[1], acc[2], acc[3]));
@@ -803,14 +826,14 @@ __global__ __launch_bounds__(DH) void bk_combine(const BucketArgs a) {
                      a.zden_ws[u], threadIdx.x, threadIdx.x & (kWave - 1), in);
 }
 
-template <class T, int DH>
+template <class T, int DH, bool ROWS>
 hipError_t launch_bucket(const BucketArgs& a, hipStream_t s) {
   const int units = a.d.B * a.d.H;
   const size_t lds1 = bk_scores_lds_bytes(a.span_len, DH), lds2 = bk_select_lds_bytes(a.span_len, DH, a.n_span, a.cand_cap);
   hipError_t e;
-  if ((e = allow_lds<bk_scores<T, DH>>(lds1)) != hipSuccess) return e;
+  if ((e = allow_lds<bk_scores<T, DH, ROWS>>(lds1)) != hipSuccess) return e;
   if ((e = allow_lds<bk_select_gather<T, DH, false>>(lds2)) != hipSuccess) return e;
-  hipLaunchKernelGGL((bk_scores<T, DH>), dim3(units * a.n_span), dim3(NT), lds1, s, a);
+  hipLaunchKernelGGL((bk_scores<T, DH, ROWS>), dim3(units * a.n_span), dim3(NT), lds1, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((bk_select_gather<T, DH, false>), dim3(units * a.n_span), dim3(NT), lds2, s, a);
   if ((e = hipGetLastError()) != hipSuccess || a.merge) return e;
@@ -843,6 +866,17 @@ hipError_t launch_bucket_group(const BucketArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <bool ROWS>
+hipError_t launch_bucket_any(const BucketArgs& a, int dtype, hipStream_t s) {
+  const bool bf = dtype == 1;
+  switch (a.d.d_h) {
+    case 64:  return bf ? launch_bucket<BF16, 64, ROWS>(a, s) : launch_bucket<F16, 64, ROWS>(a, s);
+    case 128: return bf ? launch_bucket<BF16, 128, ROWS>(a, s) : launch_bucket<F16, 128, ROWS>(a, s);
+    case 256: return bf ? launch_bucket<BF16, 256, ROWS>(a, s) : launch_bucket<F16, 256, ROWS>(a, s);
+    default:  return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 size_t bk_group_scores_lds_bytes(int span_len) { return 4 * (3 * (size_t)span_len + 2 * kRadixBins + 16); }
@@ -863,13 +897,7 @@ size_t bk_select_lds_bytes(int span_len, int d_h, int n_span, int cand_cap) {
 int bk_fine_len() { return kFineLen; }
 
 hipError_t launch_decode_bucket(const BucketArgs& a, int dtype, hipStream_t s) {
-  const bool bf = dtype == 1;
-  switch (a.d.d_h) {
-    case 64:  return bf ? launch_bucket<BF16, 64>(a, s) : launch_bucket<F16, 64>(a, s);
-    case 128: return bf ? launch_bucket<BF16, 128>(a, s) : launch_bucket<F16, 128>(a, s);
-    case 256: return bf ? launch_bucket<BF16, 256>(a, s) : launch_bucket<F16, 256>(a, s);
-    default:  return hipErrorInvalidValue;
-  }
+  return a.rows ? launch_bucket_any<true>(a, dtype, s) : launch_bucket_any<false>(a, dtype, s);
 }
 
 hipError_t launch_decode_bucket_group(const BucketArgs& a, int dtype, hipStream_t s) {
