@@ -210,6 +210,8 @@ bool decode_short(const DecodeArgs& a);                 // many units with short
 hipError_t launch_decode_short(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t decode_single_k_lds_bytes(int S_max, int d_h);   // LDS that admits S_max
 hipError_t launch_decode_single_k(const DecodeArgs& a, int dtype, hipStream_t s);
+bool decode_single_k_short(const DecodeArgs& a);        // many units with short caches: ... with launch_decode_single_k_short
+hipError_t launch_decode_single_k_short(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t long_scores_lds_bytes(int span_len, int d_h);
 size_t long_merge_lds_bytes(int n_span, int cand_cap);
 hipError_t launch_decode_long(const LongArgs& a, int dtype, hipStream_t s);

@@ -40,3 +40,16 @@ def test_decode_and_step(Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window, more
     grow = lambda src, new: torch.where(at, new, torch.nn.functional.pad(src, (0, 0, 0, S + 1 - src.shape[2])))
     grown = Hn.Built(w, c, grow(b.K_src, kn), grow(b.V_src, vn), lens + 1, None)
     Hn.compare_decode(grown, q, flags=K1 | more, local_window=window, step_rows=(kn[:, :, 0].contiguous(), vn[:, :, 0].contiguous()))
+
+
+@pytest.mark.parametrize("Bn,h,h_kv,d_h,S_max,r,k,dtype,dup,window", [
+    (129, 4, 4, 128, 64, 16, 64, "f16", 0, 0), (65, 8, 2, 64, 192, 9, 33, "bf16", 0, 0), (43, 12, 12, 256, 128, 40, 20, "bf16", 0, 9),
+    (27, 20, 4, 128, 576, 32, 100, "bf16", 400, 0)])
+def test_many_units_with_short_caches(Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window):
+    """Workgroups of four waves."""
+    w = W.Workload("single short", Bn, h, h_kv, d_h, S_max, r, k, dtype, seed=2400 + S_max)
+    lens = S_max - torch.arange(Bn, dtype=torch.int32) * 5 % S_max
+    print("[case]", Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window, flush=True)
+    b = Hn.build_cache(w, seq_lens=lens, S_max=S_max, v_offset=True, dup_rows=dup, flags=K1)
+    q = W.draw_queries(w, b.K_src, lens, q_scale=0.05)[0].contiguous()
+    Hn.compare_decode(b, q, flags=K1, local_window=window)
