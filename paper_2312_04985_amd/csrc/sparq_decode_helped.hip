@@ -43,12 +43,14 @@ hipError_t launch_any(const DecodeArgs& a, int dtype, hipStream_t s) {
 // 1500 positions 12.7 / 11.6 and 12.0 / 11.1, 4096 18.3 / 15.9 and 17.5 / 14.8, 8192 23.2 / 19.3 and 22.7 / 17.6; 8 heads at 11 000 26.9 /
 // 22.2 and 23.3 / 20.4; 16 of 256 channels at 4096 27.7 / 22.3 and 26.4 / 20.9; 72 at 12 000 31.4 / 27.5 and 29.2 / 22.9; 96 at 6500
 // 25.8 / 24.9 and 23.5 / 19.2, at 10 000 30.7 / 31.9 and 27.6 / 27.0; 128 at 4096 20.5 / 19.7 and 19.9 / 17.7, at 8192 26.6 / 29.6 and
-// 26.2 / 25.9.  One head at 1023 10.6 / 10.1 and 9.4 / 9.6.
+// 26.2 / 25.9.  The smallest calls gain in the first column and lose in the second: a step of one head at 1023 10.6 / 10.1 and 9.4 / 9.6, 56
+// heads of 256 channels at 217 12.0 / 11.7 and 10.9 / 11.2, 64 at 300 10.5 / 10.0 and 9.6 / 9.8; 32 at 700 10.7 / 10.2 and 10.1 / 9.9, 64 at 500 11.6 /
+// 10.9 and 10.7 / 10.5, 128 at 134 11.8 / 11.3 and 11.3 / 10.9.
 bool decode_helped(const DecodeArgs& a) {
   const int64_t units = (int64_t)a.B * a.H;
   if ((a.flags & 64u) || units > 128) return false;      // (not for the tiled layout)
-  if (workgroups_per_unit(units_per_xcd(a)) < 3) return units * a.S_max <= 640 * 1024;
-  return units >= 16 || a.S_max > 1024;
+  if (a.S_max <= 1024 && units * a.S_max < 22000) return false;
+  return workgroups_per_unit(units_per_xcd(a)) >= 3 || units * a.S_max <= 640 * 1024;
 }
 
 hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s) {
