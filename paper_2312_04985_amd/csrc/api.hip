@@ -345,6 +345,14 @@ int check_workspace(const sparq_shape* s, const void* ws, size_t bytes) {
   return SPARQ_OK;
 }
 
+// the sizes of a call; the pointers are the caller's to set
+DecodeArgs sized_args(const sparq_shape* shape, int S_stride) {
+  DecodeArgs a{};
+  a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = S_stride; a.d_h = shape->d_h;
+  a.r = shape->r; a.k = shape->k; a.flags = shape->flags; a.local_window = shape->local_window;
+  return a;
+}
+
 // enqueue one decode over `a` with the plan the shape calls for
 hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void* workspace, size_t workspace_bytes, hipStream_t s) {
   DecodeArgs a = args;
@@ -454,6 +462,13 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void
   return hipErrorInvalidValue;
 }
 
+// the build of the one-workgroup-per-head kernel that a call gets
+const char* fused_name(const DecodeArgs& a) {
+  if (decode_helped(a)) return "sparq_decode_fused (one workgroup per head, one launch), idle CUs fetch";
+  if (decode_short(a)) return "sparq_decode_fused (one workgroup per head, one launch), workgroups of four waves";
+  return "sparq_decode_fused (one workgroup per head, one launch)";
+}
+
 bool decode_supported(const sparq_shape* shape) { return choose_plan(shape).plan != kPlanNone; }
 
 // ---- library-owned scratch for sparq_decode_noalloc ----
@@ -540,14 +555,12 @@ int sparq_decode(const sparq_shape* caller_shape, const sparq_cache* cache, cons
   rc = check_workspace(shape, workspace, workspace_bytes);
   if (rc != SPARQ_OK) return rc;
   if (!decode_supported(shape)) return SPARQ_EUNSUPPORTED;
-  DecodeArgs a;
+  DecodeArgs a = sized_args(shape, caller_shape->S_max);
   a.K = cache->K; a.Kt = cache->Kt; a.V = cache->V; a.v_mean = cache->v_mean; a.seq_lens = cache->seq_lens;
   a.q = q; a.k_per_seq = k_per_seq; a.out = out; a.alpha_out = alpha_out; a.idx_out = idx_out;
   a.k_new = nullptr; a.v_new = nullptr; a.v_mean_next = nullptr; a.seq_lens_next = nullptr;
   a.chan_out = chan_out; a.err = static_cast<int32_t*>(workspace);
-  a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
-  a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
-  a.local_window = shape->local_window;
+  a.idx_stride = idx_out ? idx_stride : 0;
   return enqueue_decode(shape, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
@@ -566,14 +579,12 @@ int sparq_decode_noalloc(const sparq_shape* caller_shape, const sparq_cache* cac
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   void* ws = static_scratch(s);
   if (!ws) return SPARQ_ELAUNCH;
-  DecodeArgs a;
+  DecodeArgs a = sized_args(shape, caller_shape->S_max);
   a.K = cache->K; a.Kt = cache->Kt; a.V = cache->V; a.v_mean = cache->v_mean; a.seq_lens = cache->seq_lens;
   a.q = q; a.k_per_seq = k_per_seq; a.out = out; a.alpha_out = alpha_out; a.idx_out = idx_out;
   a.k_new = nullptr; a.v_new = nullptr; a.v_mean_next = nullptr; a.seq_lens_next = nullptr;
   a.chan_out = chan_out; a.err = error_word ? error_word : static_cast<int32_t*>(ws);
-  a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
-  a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
-  a.local_window = shape->local_window;
+  a.idx_stride = idx_out ? idx_stride : 0;
   return enqueue_decode(shape, a, ws, kStaticScratchBytes, s) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
@@ -595,14 +606,12 @@ int sparq_decode_step(const sparq_shape* caller_shape, const sparq_cache* cache,
   rc = check_workspace(shape, workspace, workspace_bytes);
   if (rc != SPARQ_OK) return rc;
   if (!decode_supported(shape)) return SPARQ_EUNSUPPORTED;
-  DecodeArgs a;
+  DecodeArgs a = sized_args(shape, caller_shape->S_max);
   a.K = cache->K; a.Kt = cache->Kt; a.V = cache->V; a.v_mean = cache->v_mean; a.seq_lens = cache->seq_lens;
   a.q = q; a.k_per_seq = k_per_seq; a.out = out; a.alpha_out = alpha_out; a.idx_out = idx_out;
   a.k_new = k_new; a.v_new = v_new; a.v_mean_next = v_mean_next; a.seq_lens_next = seq_lens_next;
   a.chan_out = chan_out; a.err = static_cast<int32_t*>(workspace);
-  a.B = shape->B; a.H = shape->H; a.H_kv = shape->H_kv; a.S_max = shape->S_max; a.S_stride = caller_shape->S_max; a.d_h = shape->d_h;
-  a.r = shape->r; a.k = shape->k; a.idx_stride = idx_out ? idx_stride : 0; a.flags = shape->flags;
-  a.local_window = shape->local_window;
+  a.idx_stride = idx_out ? idx_stride : 0;
   return enqueue_decode(shape, a, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPARQ_OK : SPARQ_ELAUNCH;
 }
 
@@ -651,14 +660,16 @@ const char* sparq_decode_plan(const sparq_shape* caller_shape) {
   const sparq_shape sized = bounded(caller_shape);
   const sparq_shape* shape = &sized;
   switch (choose_plan(shape).plan) {
-    case kPlanFused: return "sparq_decode_fused (one workgroup per head, one launch)";
+    case kPlanFused: return fused_name(sized_args(shape, caller_shape->S_max));
     case kPlanLong: return "long_scores + long_finish (two-level selection plan)";
     case kPlanBucket: return "bk_scores + bk_select_gather (digit-bucket plan)";
     case kPlanShared: return "sparq_decode_shared (grouped-query rule, one workgroup per KV head)";
     case kPlanSharedBucket: return "gs_logits + bk_group_scores + bk_select_gather (grouped-query rule on the digit-bucket plan)";
     case kPlanSharedSplit: return "gs_logits + gs_select + gs_merge + gs_gather + split_combine (grouped-query rule, several workgroups per KV head)";
     case kPlanSingleBucket: return "bk_scores + bk_select_gather (digit-bucket plan, key cache stored once)";
-    case kPlanSingleK: return "sparq_decode_single_k (key cache stored once)";
+    case kPlanSingleK:
+      return decode_single_k_short(sized_args(shape, caller_shape->S_max)) ? "sparq_decode_single_k (key cache stored once), workgroups of four waves"
+                                                                           : "sparq_decode_single_k (key cache stored once)";
     default: return "unsupported";
   }
 }
