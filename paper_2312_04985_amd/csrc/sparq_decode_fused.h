@@ -51,6 +51,18 @@ __device__ __forceinline__ Lds carve(uint32_t* base, int S_max) {
   return l;
 }
 
+// The arguments in front of the first loads, requested at once.  A helped workgroup's place in the grid may be no unit's, and the
+// compiler moves every request that it can behind that branch: four round trips for arguments, one after the other, where the other
+// builds have one or two.  us per step with the caches in L2, as it was / so / without helpers: one head at 1500 positions 9.65 / 9.43 / 9.34, at
+// 2000 11.0 / 10.7 / 10.7; 32 heads at 1500 10.3 / 10.0 / 9.9.  (The append's inputs among them: 256 channels 1.5 % faster, 64 and 128 1 %
+// slower, which is how the code comes to lie.)
+template <int DH>
+__device__ __forceinline__ void request_arguments(const DecodeArgs& a) {
+  asm volatile("" :: "s"(a.seq_lens), "s"(a.q), "s"(a.B), "s"(a.H), "s"(a.H_kv), "s"(a.S_max), "s"(a.flags), "s"(a.per_xcd), "s"(a.by_xcd.mul),
+               "s"(a.by_xcd.shift), "s"(a.by_H.mul), "s"(a.by_H.shift), "s"(a.by_group.mul), "s"(a.by_group.shift));
+  if (DH == 256) asm volatile("" :: "s"(a.v_mean), "s"(a.k_new), "s"(a.v_new));
+}
+
 // APPEND = true is the one-launch decode step: the new key/value row of every KV head (k_new, v_new)
 // counts as position S_b of its sequence without being read back from the cache.  Every workgroup
 // takes that row from the inputs; the workgroup of the first query head of a KV group, or workgroups of the append's own
@@ -77,6 +89,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   int u = blockIdx.x;
   int share = 0;                           // 0: the unit's own workgroup, 1 .. helpers: one that fetches for it
   if (HELP) {
+    request_arguments<DH>(a);
     const int slot = u >> 3;
     share = divided(slot, a.by_xcd);
     u = (u & 7) * a.per_xcd + (slot - share * a.per_xcd);
@@ -160,7 +173,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
 
   // ---------------- stage 0 ----------------
   select_channels<T, DH>(L.qry, qcode, a.r, L.sel.red + 30, lane, wave);
-  if (HELP && share) {                     // begin with another batch of rows
+  if (HELP && __builtin_expect(share != 0, 0)) {                     // begin with another batch of rows
     const int rows = (a.r + 7) & ~7;
     int ch = 0;
     float qv = 0.0f;
@@ -241,7 +254,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
   __syncthreads();
   SPARQ_STAMP(3);
   auto dmax_of = [&]() { return wave_values_max(L.sel.red); };
-  if (HELP && share) {
+  if (HELP && __builtin_expect(share != 0, 0)) {
     // positions share - 1, share - 1 + helpers, ...: the keys of the threshold's first digit may be taken, those above are
     const Bin bin = first_bin(win.k_old, L.sel, lane, wave);
     const bool whole = bin.size <= 2 * bin.need + NT;        // (many equal keys: only those that are certain)
