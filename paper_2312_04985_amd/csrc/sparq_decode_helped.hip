@@ -37,19 +37,17 @@ hipError_t launch_any(const DecodeArgs& a, int dtype, hipStream_t s) {
 
 }  // namespace
 
-// Where CUs are idle.  With three or more workgroups per unit (80 units) it is always faster but for the smallest calls, whose
-// loads are all on their way at once; with two (128 units) as long as what the units read stays in the L2 of their
-// XCD.  us per decode without / with helpers, caches in HBM (40 caches in turn) and in the memory-side cache (3 in turn): 32 heads at
-// 1500 positions 12.7 / 11.6 and 12.0 / 11.1, 4096 18.3 / 15.9 and 17.5 / 14.8, 8192 23.2 / 19.3 and 22.7 / 17.6; 8 heads at 11 000 26.9 /
-// 22.2 and 23.3 / 20.4; 16 of 256 channels at 4096 27.7 / 22.3 and 26.4 / 20.9; 72 at 12 000 31.4 / 27.5 and 29.2 / 22.9; 96 at 6500
-// 25.8 / 24.9 and 23.5 / 19.2, at 10 000 30.7 / 31.9 and 27.6 / 27.0; 128 at 4096 20.5 / 19.7 and 19.9 / 17.7, at 8192 26.6 / 29.6 and
-// 26.2 / 25.9.  The smallest calls gain in the first column and lose in the second: a step of one head at 1023 10.6 / 10.1 and 9.4 / 9.6, 56
-// heads of 256 channels at 217 12.0 / 11.7 and 10.9 / 11.2, 64 at 300 10.5 / 10.0 and 9.6 / 9.8; 32 at 700 10.7 / 10.2 and 10.1 / 9.9, 64 at 500 11.6 /
-// 10.9 and 10.7 / 10.5, 128 at 134 11.8 / 11.3 and 11.3 / 10.9.
+// Where CUs are idle: with three or more workgroups per unit (80 units) always, with two (128 units) as long as what the units
+// read stays in the L2 of their XCD.  us per step without / with helpers, 128 channels, r 16 unless said, every line from HBM (a gigabyte
+// read between the calls) and with the caches in L2 or in the memory-side cache (3 in turn):
+// 1 head at 100 positions, k 16, 12.2 / 11.8 and 9.1 / 9.1; 300, k 64, 12.5 / 11.9 and 9.2 / 9.2; 1023, k 128, 13.4 / 12.3 and 9.5 / 9.5; 4000, k 128, 14.7 /
+// 13.1 and 10.4 / 10.4; 32 heads at 300, k 64, 13.1 / 12.6 and 9.7 / 9.7; 1500, k 128, 14.3 / 13.1 and 10.1 / 10.1; 6000, r 32, k 512, 24.0 / 19.5 and 20.0 /
+// 16.0; 128 at 100, k 16, 12.9 / 12.5 and 9.7 / 9.6; 500, k 64, 13.7 / 13.0 and 10.2 / 10.1; 2000, r 32, k 256, 17.9 / 16.1 and 14.4 / 12.9; at 8192, not
+// helped, k 512, 40 caches in turn 26.6 / 29.6 and 3 in turn 26.2 / 25.9.
+// (There was a line below which small calls had none, drawn when the helped build itself cost them 0.2 us.)
 bool decode_helped(const DecodeArgs& a) {
   const int64_t units = (int64_t)a.B * a.H;
   if ((a.flags & 64u) || units > 128) return false;      // (not for the tiled layout)
-  if (a.S_max <= 1024 && units * a.S_max < 22000) return false;
   return workgroups_per_unit(units_per_xcd(a)) >= 3 || units * a.S_max <= 640 * 1024;
 }
 

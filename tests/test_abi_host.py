@@ -85,6 +85,8 @@ def test_plan_choice_between_the_bucket_plan_and_one_workgroup_per_unit():
 def test_the_plan_names_the_build_of_the_one_workgroup_kernel():
     plan = lambda **kw: B.sparq_decode_plan(shape(r=16, k=64, **kw)).split("launch)")[-1].split("once)")[-1]
     assert plan(B=1, H=32, H_kv=32, S_max=4096) == ", idle CUs fetch"
+    assert plan(B=1, H=1, H_kv=1, S_max=1024) == plan(B=1, H=1, H_kv=1, S_max=1088) == plan(B=4, H=32, H_kv=32, S_max=64) == ", idle CUs fetch"
+    assert plan(B=129, H=1, H_kv=1, S_max=64) == plan(B=4, H=32, H_kv=32, S_max=5184) == ""
     assert plan(B=64, H=32, H_kv=32, S_max=512) == ", workgroups of four waves"
     assert plan(B=16, H=32, H_kv=32, S_max=4096) == plan(B=64, H=32, H_kv=32, S_max=8192) == ""
     assert plan(B=1, H=4, H_kv=4, S_max=2048, flags=B.SPARQ_FLAG_TILED_K) == ""
