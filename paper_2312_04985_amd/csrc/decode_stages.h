@@ -479,8 +479,7 @@ __device__ __forceinline__ void append_channel(const DecodeArgs& a, size_t kv_he
 // append_workgroups() has NT / (DH / 8) KV heads, a thread 8 channels of one.  Bound by the scattered stores of a completed group;
 // few workgroups spread them over the launch's end.  (A channel per thread, eight times as many workgroups: 2048 heads at 4096
 // positions 182 us per such step, so 179.)
-template <int DH>
-inline int append_workgroups(int64_t heads) { return (int)((heads * (DH / 8) + NT - 1) / NT); }
+inline int append_workgroups(int64_t heads, int d_h) { return (int)((heads * (d_h / 8) + NT - 1) / NT); }
 
 template <class T, int DH, bool TILED>
 __device__ __forceinline__ void append_heads(const DecodeArgs& a, int i) {

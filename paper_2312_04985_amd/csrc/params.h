@@ -46,7 +46,6 @@ struct DecodeArgs {
   int32_t group = 1;                      // query heads per KV head
   int32_t helpers = 0, per_xcd = 0;       // few units: workgroups that fetch for each unit's own, units per XCD
   Divider by_xcd;                         // by per_xcd
-  int32_t append_apart = 0;               // the step's append has workgroups of its own, behind the decoding ones
   Divider by_H, by_H_kv, by_group;        // set by enqueue_decode, as `group`
   unsigned long long* clocks = nullptr;   // [workgroups][kStageStamps] time stamps; set only by a SPARQ_STAGE_CLOCKS build
 };
@@ -206,6 +205,8 @@ size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // LDS that admits 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_helped(const DecodeArgs& a);                // few units: launch_decode goes on with launch_decode_helped
 hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s);
+bool decode_apart(const DecodeArgs& a);                 // a step of many units: ... with launch_step_apart
+hipError_t launch_step_apart(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_short(const DecodeArgs& a);                 // many units with short caches: ... with launch_decode_short
 hipError_t launch_decode_short(const DecodeArgs& a, int dtype, hipStream_t s);
 size_t decode_single_k_lds_bytes(int S_max, int d_h);   // LDS that admits S_max

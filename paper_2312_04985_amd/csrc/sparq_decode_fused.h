@@ -65,8 +65,8 @@ __device__ __forceinline__ void request_arguments(const DecodeArgs& a) {
 
 // APPEND = true is the one-launch decode step: the new key/value row of every KV head (k_new, v_new)
 // counts as position S_b of its sequence without being read back from the cache.  Every workgroup
-// takes that row from the inputs; the workgroup of the first query head of a KV group, or workgroups of the append's own
-// behind the decoding ones (append_apart), also write it into K, V and Kt and store the updated mean; lengths and means go to
+// takes that row from the inputs; the workgroup of the first query head of a KV group, or (APART) workgroups of the append's own
+// behind the decoding ones, also write it into K, V and Kt and store the updated mean; lengths and means go to
 // the *_next buffers, so no workgroup can observe another one's update of the state it reads.
 // TILED = true reads the single-copy tiled key layout (flag bit 6): a.K holds tiles of 8 positions, channel-major
 // inside a tile, a.Kt the up to 7 newest rows of every KV head (8 rows of d_h each) that do not fill a tile yet.
@@ -80,7 +80,7 @@ __device__ __forceinline__ void request_arguments(const DecodeArgs& a) {
 // Blocks that ordinary calls skip are marked (__builtin_expect, here and in the stages), so that the compiler moves them behind the
 // code that runs: where few workgroups wait for instructions, jumping over them costs: the step of one head at 1023 positions 9.83 us, so
 // 9.42; of 32 heads at 1500 12.3 / 11.9; 512 heads and more equal.
-template <class T, int DH, bool APPEND, bool TILED, bool HELP>
+template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART>
 __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   const Lds L = carve<DH>(smem, a.S_max);
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     share = divided(slot, a.by_xcd);
     u = (u & 7) * a.per_xcd + (slot - share * a.per_xcd);
     if (u >= U) return;
-  } else if (APPEND && __builtin_expect(u >= U, 0)) {     // (append_apart)
+  } else if (APART && __builtin_expect(u >= U, 0)) {
     append_heads<T, DH, TILED>(a, u - U);
     return;
   }
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     S = S < 0 ? 0 : a.S_max;
   }
   bool appended = false;                                    // this sequence takes the new row (uniform)
-  const bool owner = APPEND && !a.append_apart && share == 0 && h == hk * a.group;   // writes the row and the new mean
+  const bool owner = APPEND && !APART && share == 0 && h == hk * a.group;   // writes the row and the new mean
   if (APPEND) {
     if (S + 1 <= a.S_max) { appended = true; S += 1; }
     else if (__builtin_expect(tid == 0 && share == 0, 0)) atomicOr(a.err, 1);
@@ -334,19 +334,32 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
 #endif
 }
 
-// Whether a step's append has workgroups of its own.  At the end of a decoding workgroup its stores hold the place on the CU
-// until the memory has taken them; where more workgroups wait for it, that adds up over the rounds, most of all in the steps
-// that complete a group of 8 (d_h 16-byte stores to as many lines per KV head).  Where all run at once, or in two rounds,
-// nobody waits for the last stores of a workgroup, and the others would only begin then.  us per step, in the decoding
-// workgroups / apart, at 4096 positions of 128 channels, k = 512, a step that completes a group and one that does not: 512 units
-// 47.5 / 52.1 and 44.3 / 45.5; 1024 94.1 / 95.0 and 86.4 / 86.4; 1536 143.2 / 141.2; 2048 189.4 / 182.8 and 169.4 / 168.4;
-// 2048 at 8192 positions, k = 256, 162.6 / 146.5 and 137.8 / 131.0.
-// (The append's workgroups in front of the decoding ones, or a quarter, half or three quarters into the grid: 2-11 % more.)
-constexpr bool append_apart(int64_t units) { return units > 1024; }
-
 // LDS bytes for a cache of S_max rows and head dimension d_h
 inline size_t fused_lds_bytes(int S_max, int d_h) {
   return 4 * ((size_t)S_max + 2 * kRadixBins + (size_t)NW * (d_h + 2) + 5 * (size_t)d_h + 32 + 16 + 8);
+}
+
+// One launch of `grid` workgroups.
+template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART>
+hipError_t launch_fused(const DecodeArgs& a, int grid, hipStream_t s) {
+  const size_t lds = fused_lds_bytes(a.S_max, DH);
+  auto kern = sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART>;
+  hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART>>(lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, s, a);
+  return hipGetLastError();
+}
+
+// ... for the cache's type and head dimension
+template <bool APPEND, bool TILED, bool HELP, bool APART>
+hipError_t launch_fused(const DecodeArgs& a, int dtype, int grid, hipStream_t s) {
+  const bool bf = dtype == 1;
+  switch (a.d_h) {
+    case 64:  return bf ? launch_fused<BF16, 64, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 64, APPEND, TILED, HELP, APART>(a, grid, s);
+    case 128: return bf ? launch_fused<BF16, 128, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 128, APPEND, TILED, HELP, APART>(a, grid, s);
+    case 256: return bf ? launch_fused<BF16, 256, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 256, APPEND, TILED, HELP, APART>(a, grid, s);
+    default:  return hipErrorInvalidValue;
+  }
 }
 
 }  // inline namespace

@@ -10,31 +10,6 @@ namespace {
 int units_per_xcd(const DecodeArgs& a) { return (a.B * a.H + 7) / 8; }
 int workgroups_per_unit(int per_xcd) { return 32 / per_xcd < 8 ? 32 / per_xcd : 8; }
 
-template <class T, int DH, bool APPEND>
-hipError_t launch_one(const DecodeArgs& a, hipStream_t s) {
-  const size_t lds = decode_lds_bytes(a.S_max, DH);
-  hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, false, true>>(lds);
-  if (e != hipSuccess) return e;
-  DecodeArgs d = a;
-  d.per_xcd = units_per_xcd(a);
-  d.by_xcd = make_divider(d.per_xcd);
-  const int n = workgroups_per_unit(d.per_xcd);
-  d.helpers = n - 1;
-  hipLaunchKernelGGL((sparq_decode_fused<T, DH, APPEND, false, true>), dim3(8 * d.per_xcd * n), dim3(NT), lds, s, d);
-  return hipGetLastError();
-}
-
-template <bool APPEND>
-hipError_t launch_any(const DecodeArgs& a, int dtype, hipStream_t s) {
-  const bool bf = dtype == 1;
-  switch (a.d_h) {
-    case 64:  return bf ? launch_one<BF16, 64, APPEND>(a, s) : launch_one<F16, 64, APPEND>(a, s);
-    case 128: return bf ? launch_one<BF16, 128, APPEND>(a, s) : launch_one<F16, 128, APPEND>(a, s);
-    case 256: return bf ? launch_one<BF16, 256, APPEND>(a, s) : launch_one<F16, 256, APPEND>(a, s);
-    default:  return hipErrorInvalidValue;
-  }
-}
-
 }  // namespace
 
 // Where CUs are idle: with three or more workgroups per unit (80 units) always, with two (128 units) as long as what the units
@@ -52,7 +27,12 @@ bool decode_helped(const DecodeArgs& a) {
 }
 
 hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s) {
-  return a.k_new ? launch_any<true>(a, dtype, s) : launch_any<false>(a, dtype, s);
+  DecodeArgs d = a;
+  d.per_xcd = units_per_xcd(a);
+  d.by_xcd = make_divider(d.per_xcd);
+  const int n = workgroups_per_unit(d.per_xcd), grid = 8 * d.per_xcd * n;
+  d.helpers = n - 1;
+  return a.k_new ? launch_fused<true, false, true, false>(d, dtype, grid, s) : launch_fused<false, false, true, false>(d, dtype, grid, s);
 }
 
 }  // namespace sparq

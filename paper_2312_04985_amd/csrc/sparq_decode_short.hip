@@ -4,32 +4,6 @@
 
 namespace sparq {
 
-namespace {
-
-template <class T, int DH, bool APPEND>
-hipError_t launch_one(const DecodeArgs& a, hipStream_t s) {
-  const size_t lds = fused_lds_bytes(a.S_max, DH);
-  hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, false, false>>(lds);
-  if (e != hipSuccess) return e;
-  DecodeArgs d = a;
-  d.append_apart = APPEND && append_apart((int64_t)a.B * a.H);
-  hipLaunchKernelGGL((sparq_decode_fused<T, DH, APPEND, false, false>), dim3(a.B * a.H + (d.append_apart ? append_workgroups<DH>((int64_t)a.B * a.H_kv) : 0)), dim3(NT), lds, s, d);
-  return hipGetLastError();
-}
-
-template <bool APPEND>
-hipError_t launch_any(const DecodeArgs& a, int dtype, hipStream_t s) {
-  const bool bf = dtype == 1;
-  switch (a.d_h) {
-    case 64:  return bf ? launch_one<BF16, 64, APPEND>(a, s) : launch_one<F16, 64, APPEND>(a, s);
-    case 128: return bf ? launch_one<BF16, 128, APPEND>(a, s) : launch_one<F16, 128, APPEND>(a, s);
-    case 256: return bf ? launch_one<BF16, 256, APPEND>(a, s) : launch_one<F16, 256, APPEND>(a, s);
-    default:  return hipErrorInvalidValue;
-  }
-}
-
-}  // namespace
-
 // More units than run at once in workgroups of eight waves (two per CU), as long as four of these fit the LDS of a CU and a unit's
 // reads do not bind the call: a unit is a chain of serial stages, so that twice as many units under way hide twice as much of it;
 // with much to read both wait for the memory.  us per step, eight waves / four, 128 channels, r 32 unless said: 2048 heads at 200
@@ -43,7 +17,10 @@ bool decode_short(const DecodeArgs& a) {
 }
 
 hipError_t launch_decode_short(const DecodeArgs& a, int dtype, hipStream_t s) {
-  return a.k_new ? launch_any<true>(a, dtype, s) : launch_any<false>(a, dtype, s);
+  const int units = a.B * a.H;
+  if (!a.k_new) return launch_fused<false, false, false, false>(a, dtype, units, s);
+  if (!decode_apart(a)) return launch_fused<true, false, false, false>(a, dtype, units, s);
+  return launch_fused<true, false, false, true>(a, dtype, units + append_workgroups((int64_t)a.B * a.H_kv, a.d_h), s);
 }
 
 }  // namespace sparq
