@@ -88,7 +88,11 @@ def test_the_plan_names_the_build_of_the_one_workgroup_kernel():
     assert plan(B=1, H=1, H_kv=1, S_max=1024) == plan(B=1, H=1, H_kv=1, S_max=1088) == plan(B=4, H=32, H_kv=32, S_max=64) == ", idle CUs fetch"
     assert plan(B=129, H=1, H_kv=1, S_max=64) == plan(B=4, H=32, H_kv=32, S_max=5184) == ""
     assert plan(B=64, H=32, H_kv=32, S_max=512) == ", workgroups of four waves"
-    assert plan(B=16, H=32, H_kv=32, S_max=4096) == plan(B=64, H=32, H_kv=32, S_max=8192) == ""
+    assert plan(B=16, H=32, H_kv=32, S_max=4096) == plan(B=32, H=32, H_kv=32, S_max=8192) == ""
+    apart = ", append of a step apart"
+    assert plan(B=64, H=32, H_kv=32, S_max=8192) == plan(B=64, H=32, H_kv=16, S_max=8192) == apart
+    assert plan(B=64, H=32, H_kv=8, S_max=8192) == plan(B=128, H=32, H_kv=4, S_max=8192) == ""
+    assert plan(B=64, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_TILED_K) == apart
     assert plan(B=1, H=4, H_kv=4, S_max=2048, flags=B.SPARQ_FLAG_TILED_K) == ""
     assert plan(B=64, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_SINGLE_K) == ", workgroups of four waves"
     assert plan(B=16, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_SINGLE_K) == ""

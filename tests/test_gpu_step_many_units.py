@@ -1,4 +1,4 @@
-"""The one-launch step where its append has workgroups of its own (more than 1024 units): against append + decode, bit for bit."""
+"""The one-launch step of many units, its append in the decoding workgroups and in workgroups of its own: against append + decode, bit for bit."""
 import pytest
 import torch
 
@@ -12,15 +12,24 @@ pytestmark = pytest.mark.gpu
 TK = B.SPARQ_FLAG_TILED_K
 
 
-@pytest.mark.parametrize("Bn,h,h_kv,d_h,dtype,flags", [
-    (103, 10, 10, 128, "f16", 0), (103, 10, 5, 64, "bf16", 0), (205, 5, 1, 256, "f16", 0), (41, 25, 25, 256, "bf16", 0),
-    (1025, 1, 1, 64, "f16", TK), (103, 10, 5, 128, "bf16", TK), (103, 10, 5, 128, "f16", B.SPARQ_FLAG_RAGGED_BATCH)])
-def test_step_equals_append_then_decode(Bn, h, h_kv, d_h, dtype, flags):
-    S_max = 128
-    w = W.Workload("many units", Bn, h, h_kv, d_h, S_max, 12, 20, dtype, seed=1700 + d_h)
+SHORT, APART, ONE = "workgroups of four waves", "append of a step apart", "one launch)"
+
+
+@pytest.mark.parametrize("Bn,h,h_kv,d_h,S_max,r,k,dtype,flags,build", [
+    (103, 10, 10, 128, 128, 12, 20, "f16", 0, SHORT), (103, 10, 5, 64, 128, 12, 20, "bf16", 0, SHORT), (205, 5, 1, 256, 128, 12, 20, "f16", 0, SHORT),
+    (41, 25, 25, 256, 128, 12, 20, "bf16", 0, SHORT), (1025, 1, 1, 64, 128, 12, 20, "f16", TK, APART), (103, 10, 5, 128, 128, 12, 20, "bf16", TK, APART),
+    (103, 10, 10, 128, 128, 12, 20, "f16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT), (261, 4, 4, 64, 128, 12, 20, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT),
+    (400, 3, 3, 128, 64, 12, 20, "f16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT),
+    # what a unit reads binds the call: workgroups of eight waves, the append in its own beyond 512 KV heads
+    (103, 10, 10, 128, 704, 12, 704, "f16", 0, APART), (41, 26, 26, 256, 448, 64, 448, "bf16", 0, APART), (1025, 1, 1, 64, 1408, 12, 1408, "bf16", 0, APART),
+    (103, 10, 5, 128, 704, 12, 704, "bf16", 0, APART), (103, 10, 10, 64, 1408, 9, 1408, "f16", B.SPARQ_FLAG_RAGGED_BATCH, APART),
+    (260, 4, 4, 64, 1408, 9, 1400, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, APART), (103, 20, 4, 128, 704, 12, 704, "f16", 0, ONE)])
+def test_step_equals_append_then_decode(Bn, h, h_kv, d_h, S_max, r, k, dtype, flags, build):
+    w = W.Workload("many units", Bn, h, h_kv, d_h, S_max, r, k, dtype, seed=1700 + d_h)
     lens = (torch.arange(Bn, dtype=torch.int32) * 7) % (S_max + 1)      # every length mod 8, empty and full sequences
     lens[:3] = torch.tensor([0, S_max, S_max - 1])
-    assert B.sparq_decode_plan(B.make_shape(Bn, h, h_kv, S_max, d_h, 12, 20, w.torch_dtype, flags)).startswith("sparq_decode_fused")
+    print("[case]", Bn, h, h_kv, d_h, S_max, r, k, dtype, flags, build, flush=True)
+    assert B.sparq_decode_plan(B.make_shape(Bn, h, h_kv, S_max, d_h, r, k, w.torch_dtype, flags)).endswith(build)
     one, two = (Hn.build_cache(w, seq_lens=lens, S_max=S_max, v_offset=True, flags=flags) for _ in range(2))
     q = W.draw_queries(w, one.K_src, lens.clamp(min=1), q_scale=0.05)[0].contiguous()
     for step in range(3):
