@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsparq.so")
 LIB_CLOCKS = os.path.join(HERE, "libsparq_clocks.so")
-SOURCES = ["api.hip", "sparq_decode.hip", "sparq_decode_apart.hip", "sparq_decode_helped.hip", "sparq_decode_short.hip", "sparq_decode_split.hip", "sparq_decode_shared.hip", "sparq_decode_shared_split.hip", "sparq_decode_single_k.hip", "sparq_decode_single_k_short.hip", "sparq_decode_long.hip", "sparq_decode_bucket.hip", "dense_decode.hip", "kv_append.hip"]
+SOURCES = ["api.hip", "sparq_decode.hip", "sparq_decode_apart.hip", "sparq_decode_runs.hip", "sparq_decode_helped.hip", "sparq_decode_short.hip", "sparq_decode_split.hip", "sparq_decode_shared.hip", "sparq_decode_shared_split.hip", "sparq_decode_single_k.hip", "sparq_decode_single_k_short.hip", "sparq_decode_long.hip", "sparq_decode_bucket.hip", "dense_decode.hip", "kv_append.hip"]
 HEADERS = ["common.h", "params.h", "decode_stages.h", "group_stages.h", "two_ahead.h", "append_plan.h", "sparq_decode_fused.h", "sparq_decode_single_k.h", os.path.join("..", "..", "include", "sparq.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -466,6 +466,9 @@ hipError_t enqueue_decode(const sparq_shape* shape, const DecodeArgs& args, void
 const char* fused_name(const DecodeArgs& a) {
   if (decode_helped(a)) return "sparq_decode_fused (one workgroup per head, one launch), idle CUs fetch";
   if (decode_short(a)) return "sparq_decode_fused (one workgroup per head, one launch), workgroups of four waves";
+  if (decode_runs(a))
+    return decode_apart(a) ? "sparq_decode_fused (one workgroup per head, one launch), waves read apart, append of a step apart"
+                           : "sparq_decode_fused (one workgroup per head, one launch), waves read apart";
   if (decode_apart(a)) return "sparq_decode_fused (one workgroup per head, one launch), append of a step apart";
   return "sparq_decode_fused (one workgroup per head, one launch)";
 }

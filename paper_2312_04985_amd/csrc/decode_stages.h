@@ -320,13 +320,11 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
   }
 }
 
-// Chunks (8 consecutive positions = 16 bytes of every channel row) belong to the STRIDE threads (all NT of the workgroup unless
-// the caller divides the rows of a chunk among groups of threads): up to two per thread, chunk_begin + tid + i * STRIDE; beyond,
-// they are cut into runs of 64, one chunk per lane, and every wave takes consecutive runs (the first waves one more where they
-// do not come out even), so that the waves read at places an eighth of the row apart.  (Side by side, the workgroup
-// advancing 8 KB of every row at a time, all requests of a moment lay at one offset of rows whose stride is a power of two or
-// nearly: 512 heads of 128 channels at 16 384 positions 142.7 us per decode, so 132.9; of 256 channels 371 / 340, at 16 440
-// 373 / 341; lengths far from a power of two equal.)
+// Chunks (8 consecutive positions = 16 bytes of every channel row) chunk_begin + tid + i * STRIDE belong to
+// thread tid of STRIDE (all NT threads of the workgroup unless the caller divides the rows of a chunk among
+// groups of threads).  RUNS: where that is more than two per thread, they are cut into runs of 64, one chunk per lane, and every wave
+// takes consecutive runs (the first waves one more where they do not come out even), so that the waves read at places an eighth of the row apart
+// and not side by side (for row strides at which that is faster: decode_runs).
 // The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
 // a two-deep software pipeline: a batch of 8 loads is always in flight behind the one being accumulated,
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the
@@ -341,7 +339,7 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
 // Addressing: chunk c of channel row j lies at Kt_head + j * row_bytes + c * chunk_bytes.  The S-contiguous
 // key copy has row_bytes = 2 S_max and chunk_bytes = 16; the tiled single-copy layout (tiles of 8 positions,
 // channel-major inside a tile) has row_bytes = 16 and chunk_bytes = 16 d_h.
-template <class T, int STRIDE = NT, bool KEEP = false, class Finish, class Requested>
+template <class T, int STRIDE = NT, bool KEEP = false, bool RUNS = false, class Finish, class Requested>
 __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_t row_bytes, const int* chan,
                                                     const float* qs, int r, int chunk_begin, int chunk_end,
                                                     int tid, Finish&& finish, Requested&& requested, uint32_t chunk_bytes = 16u) {
@@ -349,7 +347,7 @@ __device__ __forceinline__ void stream_channel_rows(const char* Kt_head, uint32_
   const int n_chunks = chunk_end - chunk_begin;
   constexpr int W = STRIDE / kWave;
   int own = tid, my_chunks = n_chunks > tid ? (n_chunks - tid + STRIDE - 1) / STRIDE : 0, step = STRIDE;
-  if (!KEEP && n_chunks > 2 * STRIDE) {
+  if (RUNS && n_chunks > 2 * STRIDE) {
     const int w = tid / kWave, runs = (n_chunks + kWave - 1) / kWave, per = runs / W, more = runs % W;
     own += (w * (per - 1) + (w < more ? w : more)) * kWave;
     my_chunks = (n_chunks - own + kWave - 1) / kWave;

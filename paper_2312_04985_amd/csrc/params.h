@@ -205,6 +205,8 @@ size_t decode_shared_lds_bytes(int S_max, int d_h, int g);   // LDS that admits 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_helped(const DecodeArgs& a);                // few units: launch_decode goes on with launch_decode_helped
 hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s);
+bool decode_runs(const DecodeArgs& a);                  // row strides near 32 KiB: ... with launch_decode_runs
+hipError_t launch_decode_runs(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_apart(const DecodeArgs& a);                 // a step of many units: ... with launch_step_apart
 hipError_t launch_step_apart(const DecodeArgs& a, int dtype, hipStream_t s);
 bool decode_short(const DecodeArgs& a);                 // many units with short caches: ... with launch_decode_short

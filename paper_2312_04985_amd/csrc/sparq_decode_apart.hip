@@ -21,7 +21,7 @@ bool decode_apart(const DecodeArgs& a) { return (int64_t)a.B * a.H > 1024 && (in
 
 hipError_t launch_step_apart(const DecodeArgs& a, int dtype, hipStream_t s) {
   const int grid = a.B * a.H + append_workgroups((int64_t)a.B * a.H_kv, a.d_h);
-  return (a.flags & 64u) ? launch_fused<true, true, false, true>(a, dtype, grid, s) : launch_fused<true, false, false, true>(a, dtype, grid, s);
+  return (a.flags & 64u) ? launch_fused<true, true, false, true, false>(a, dtype, grid, s) : launch_fused<true, false, false, true, false>(a, dtype, grid, s);
 }
 
 }  // namespace sparq

@@ -72,6 +72,7 @@ __device__ __forceinline__ void request_arguments(const DecodeArgs& a) {
 // inside a tile, a.Kt the up to 7 newest rows of every KV head (8 rows of d_h each) that do not fill a tile yet.
 // Step 1b then strides through the tiles (16 bytes per position chunk and channel), Step 2b collects a row's
 // components from its tile, and the append writes a row of the small buffer, or a whole tile with the eighth row.
+// RUNS = true reads the channel rows in runs (stream_channel_rows).
 // HELP = true is for few units: every unit has a.helpers more workgroups on its XCD, on CUs that would be idle, which write
 // nothing.  Bound is what a CU can have on its way from beyond its L2 (60 GB/s; from L2 160): a helper goes through Step 1 as
 // well, in another order of the channel rows, so that each brings a part of them into the L2 that all share, and once
@@ -80,7 +81,7 @@ __device__ __forceinline__ void request_arguments(const DecodeArgs& a) {
 // Blocks that ordinary calls skip are marked (__builtin_expect, here and in the stages), so that the compiler moves them behind the
 // code that runs: where few workgroups wait for instructions, jumping over them costs: the step of one head at 1023 positions 9.83 us, so
 // 9.42; of 32 heads at 1500 12.3 / 11.9; 512 heads and more equal.
-template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART>
+template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART, bool RUNS>
 __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   const Lds L = carve<DH>(smem, a.S_max);
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(NT, 4) void sparq_decode_fused(const DecodeArgs a) 
     dst[0] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
     dst[1] = make_uint4(kx[4], kx[5], kx[6], kx[7]);
   };
-  stream_channel_rows<T, NT, HELP>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
+  stream_channel_rows<T, NT, HELP, RUNS>(Kt_head, row_bytes, L.qry.chan, L.qry.qs, a.r, 0, S_fl >> 3, tid, finish, requested, TILED ? DH * 16u : 16u);
 #pragma unroll
   for (int t = 0; t < TAILS; ++t) {
     const int n = wave + t * NW;
@@ -340,24 +341,24 @@ inline size_t fused_lds_bytes(int S_max, int d_h) {
 }
 
 // One launch of `grid` workgroups.
-template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART>
+template <class T, int DH, bool APPEND, bool TILED, bool HELP, bool APART, bool RUNS>
 hipError_t launch_fused(const DecodeArgs& a, int grid, hipStream_t s) {
   const size_t lds = fused_lds_bytes(a.S_max, DH);
-  auto kern = sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART>;
-  hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART>>(lds);
+  auto kern = sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART, RUNS>;
+  hipError_t e = allow_lds<sparq_decode_fused<T, DH, APPEND, TILED, HELP, APART, RUNS>>(lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, s, a);
   return hipGetLastError();
 }
 
 // ... for the cache's type and head dimension
-template <bool APPEND, bool TILED, bool HELP, bool APART>
+template <bool APPEND, bool TILED, bool HELP, bool APART, bool RUNS>
 hipError_t launch_fused(const DecodeArgs& a, int dtype, int grid, hipStream_t s) {
   const bool bf = dtype == 1;
   switch (a.d_h) {
-    case 64:  return bf ? launch_fused<BF16, 64, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 64, APPEND, TILED, HELP, APART>(a, grid, s);
-    case 128: return bf ? launch_fused<BF16, 128, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 128, APPEND, TILED, HELP, APART>(a, grid, s);
-    case 256: return bf ? launch_fused<BF16, 256, APPEND, TILED, HELP, APART>(a, grid, s) : launch_fused<F16, 256, APPEND, TILED, HELP, APART>(a, grid, s);
+    case 64:  return bf ? launch_fused<BF16, 64, APPEND, TILED, HELP, APART, RUNS>(a, grid, s) : launch_fused<F16, 64, APPEND, TILED, HELP, APART, RUNS>(a, grid, s);
+    case 128: return bf ? launch_fused<BF16, 128, APPEND, TILED, HELP, APART, RUNS>(a, grid, s) : launch_fused<F16, 128, APPEND, TILED, HELP, APART, RUNS>(a, grid, s);
+    case 256: return bf ? launch_fused<BF16, 256, APPEND, TILED, HELP, APART, RUNS>(a, grid, s) : launch_fused<F16, 256, APPEND, TILED, HELP, APART, RUNS>(a, grid, s);
     default:  return hipErrorInvalidValue;
   }
 }

@@ -32,7 +32,7 @@ hipError_t launch_decode_helped(const DecodeArgs& a, int dtype, hipStream_t s) {
   d.by_xcd = make_divider(d.per_xcd);
   const int n = workgroups_per_unit(d.per_xcd), grid = 8 * d.per_xcd * n;
   d.helpers = n - 1;
-  return a.k_new ? launch_fused<true, false, true, false>(d, dtype, grid, s) : launch_fused<false, false, true, false>(d, dtype, grid, s);
+  return a.k_new ? launch_fused<true, false, true, false, false>(d, dtype, grid, s) : launch_fused<false, false, true, false, false>(d, dtype, grid, s);
 }
 
 }  // namespace sparq

@@ -4,14 +4,14 @@
 namespace sparq {
 
 // Side by side, the workgroup advancing 8 KB of every row at a time, all requests of a moment lie at one offset of rows whose
-// stride is 32 KiB or nearly.  us per decode, side by side / apart, r 32, k 512 unless said.
-// Strides of 16 320, 16 448, 32 640, 32 704, 32 832, 32 896 positions, whatever the units, groups, types, r and d_h: 256 heads of 128 channels at 16 320
-// 63.5 / 56.9, 16 448 62.6 / 58.0, 32 640 105.2 / 99.8, 32 896 107.8 / 102.2; 512 on 128 KV heads at 16 320 93.6 / 81.1, 16 448 96.0 / 83.6; r 64 on 128 KV heads
-// 99.1 / 79.3; 160 heads of 64 channels, r 16, 28.5 / 25.6; 512 of 256, r 64, 264.1 / 247.8; between 2 % slower and 6 % faster: 64 channels with r 8 at 32 640 and beyond.
-// Exact multiples: 512 KV heads and more at 16 384 121.3 / 111.2, r 16 65.2 / 64.6, r 64 218.6 / 184.6, 64 channels r 16 61.7 / 59.3, r 64 218.7 / 186.0; 256 channels,
-// r 64, equal.  With fewer it goes either way, and by more the other one: 160 heads 46.6 / 52.1, 192 with r 48 69.9 / 72.5 and with r 64 90.9 / 73.2, 256 of
-// 64 channels with r 16 31.8 / 34.6, on 128 KV heads 30.2 / 37.0; r 8 equal.
-// Everywhere else: as fast or slower (14 336 52.3 / 56.1, 18 432 on 128 KV heads 88.2 / 93.6, 33 024 109.2 / 113.3, 8256 67.2 / 68.0).
+// stride is 32 KiB or nearly.  us per decode, side by side / apart, 128 channels, r 32, k 512 unless said:
+// Strides of 16 320, 16 448, 32 640, 32 704, 32 832, 32 896 positions are up to 28 % faster, whatever the units, groups, r and d_h: 256 heads at 16 320 63.5 / 56.9,
+// 16 448 62.6 / 58.0, 32 640 105.2 / 99.8, 32 896 107.8 / 102.2; 512 on 128 KV heads at 16 320 93.6 / 81.1, 16 448 96.0 / 83.6; 256 on 128, r 64, at 16 320 102.7 / 80.3;
+// 160 of 64 channels, r 16, at 16 320 28.5 / 25.6; 512 of 256, r 64, 264.1 / 247.8; the least with r 8 at 32 704: equal.
+// Exact multiples, 512 KV heads and more: 16 384 120.2 / 108.7, r 16 64.6 / 63.0, r 64 220.8 / 185.1; 64 channels, r 16, 60.9 / 58.2, r 48 159.4 / 139.9; 256, r 64, equal; with r 8
+// equal.  With fewer KV heads it goes either way: 160 heads 46.6 / 52.5, 192 with r 48 69.9 / 72.5 and with r 64 90.9 / 73.2, 256 of 64 channels, r 16, 31.7 / 34.7, on
+// 128 KV heads 30.2 / 37.0.
+// Everywhere else as fast or slower (14 336 52.3 / 56.1, 18 432 on 128 KV heads 88.2 / 93.6, 33 024 109.2 / 113.3, 8256 67.2 / 68.0).
 // In a build of its own, as the append's workgroups.
 bool decode_runs(const DecodeArgs& a) {
   if ((a.flags & 64u) || a.S_max <= 2 * 8 * kDecodeThreads) return false;       // (not for the tiled layout; up to two chunks per thread)

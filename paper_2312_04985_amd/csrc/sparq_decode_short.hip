@@ -22,7 +22,7 @@ bool decode_short(const DecodeArgs& a) {
 
 hipError_t launch_decode_short(const DecodeArgs& a, int dtype, hipStream_t s) {
   const int units = a.B * a.H;
-  return a.k_new ? launch_fused<true, false, false, false>(a, dtype, units, s) : launch_fused<false, false, false, false>(a, dtype, units, s);
+  return a.k_new ? launch_fused<true, false, false, false, false>(a, dtype, units, s) : launch_fused<false, false, false, false, false>(a, dtype, units, s);
 }
 
 }  // namespace sparq

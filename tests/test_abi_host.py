@@ -93,6 +93,17 @@ def test_the_plan_names_the_build_of_the_one_workgroup_kernel():
     assert plan(B=64, H=32, H_kv=32, S_max=8192) == plan(B=64, H=32, H_kv=16, S_max=8192) == apart
     assert plan(B=64, H=32, H_kv=8, S_max=8192) == plan(B=128, H=32, H_kv=4, S_max=8192) == ""
     assert plan(B=64, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_TILED_K) == apart
+    runs = ", waves read apart"
+    for S in (16320, 16448, 32640, 32704, 32832, 32896):
+        assert plan(B=5, H=32, H_kv=4, S_max=S) == runs and plan(B=64, H=32, H_kv=32, S_max=S) == runs + apart
+    for S in (8192, 8256, 14336, 16256, 16512, 18432, 24576, 32576, 32960):
+        assert plan(B=5, H=32, H_kv=4, S_max=S) == plan(B=16, H=32, H_kv=32, S_max=S) == ""
+    for S in (16384, 32768):                       # exact multiples: from 512 KV heads on
+        assert plan(B=16, H=32, H_kv=32, S_max=S) == runs and plan(B=16, H=32, H_kv=16, S_max=S) == plan(B=5, H=32, H_kv=32, S_max=S) == ""
+    # the stride is the buffers', the bound does not change it
+    assert plan(B=16, H=32, H_kv=32, S_max=16384, S_bound=8256) == runs and plan(B=16, H=32, H_kv=32, S_max=16384, S_bound=8192) == ""
+    assert plan(B=16, H=32, H_kv=32, S_max=32768, S_bound=16384) == runs and plan(B=16, H=32, H_kv=32, S_max=65536, S_bound=16384) == ""
+    assert plan(B=5, H=32, H_kv=32, S_max=16320, flags=B.SPARQ_FLAG_TILED_K) == ""
     assert plan(B=1, H=4, H_kv=4, S_max=2048, flags=B.SPARQ_FLAG_TILED_K) == ""
     assert plan(B=64, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_SINGLE_K) == ", workgroups of four waves"
     assert plan(B=16, H=32, H_kv=32, S_max=512, flags=B.SPARQ_FLAG_SINGLE_K) == ""
