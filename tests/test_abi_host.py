@@ -82,6 +82,20 @@ def test_plan_choice_between_the_bucket_plan_and_one_workgroup_per_unit():
     assert "two-level" in plan(B=5, S_max=65536)
 
 
+def test_plan_choice_between_the_bucket_plan_and_helped_units():
+    """From 12 288 positions on: one workgroup per unit with helpers where positions, channels and selected rows are few."""
+    plan = lambda units, S, r, k, d_h=128: B.sparq_decode_plan(shape(B=1, H=units, H_kv=units, S_max=S, r=r, k=k, d_h=d_h))
+    for S, r, k, d_h in ((12352, 32, 256, 128), (12352, 32, 450, 128), (16320, 16, 700, 128), (24000, 8, 256, 128), (28032, 8, 256, 128), (12352, 32, 512, 64),
+                         (16320, 16, 400, 256), (28032, 8, 350, 256)):
+        for units in (17, 32, 64):
+            assert plan(units, S, r, k, d_h).endswith("idle CUs fetch"), (units, S, r, k, d_h)
+        assert "digit-bucket" in plan(16, S, r, k, d_h) and "digit-bucket" not in plan(129, S, r, k, d_h)
+    for S, r, k, d_h in ((12288, 32, 512, 128), (12352, 32, 1024, 128), (12352, 64, 512, 128), (24000, 8, 900, 128), (28032, 8, 900, 128), (28736, 8, 16, 128), (32000, 8, 900, 128),
+                         (32000, 12, 300, 128), (24000, 16, 800, 64), (28032, 8, 1500, 64), (32000, 8, 1500, 64), (32000, 8, 300, 256)):
+        for units in (17, 32, 64):
+            assert "digit-bucket" in plan(units, S, r, k, d_h), (units, S, r, k, d_h)
+
+
 def test_the_plan_names_the_build_of_the_one_workgroup_kernel():
     plan = lambda **kw: B.sparq_decode_plan(shape(r=16, k=64, **kw)).split("launch)")[-1].split("once)")[-1]
     assert plan(B=1, H=32, H_kv=32, S_max=4096) == ", idle CUs fetch"
