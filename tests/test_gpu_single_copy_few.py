@@ -44,9 +44,12 @@ def test_decode_and_step(Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window, more
 
 @pytest.mark.parametrize("Bn,h,h_kv,d_h,S_max,r,k,dtype,dup,window", [
     (129, 4, 4, 128, 64, 16, 64, "f16", 0, 0), (65, 8, 2, 64, 192, 9, 33, "bf16", 0, 0), (43, 12, 12, 256, 128, 40, 20, "bf16", 0, 9),
-    (27, 20, 4, 128, 576, 32, 100, "bf16", 400, 0)])
+    (27, 20, 4, 128, 576, 32, 100, "bf16", 400, 0), (9, 58, 2, 64, 1088, 8, 200, "f16", 0, 0), (9, 58, 1, 64, 2048, 16, 228, "bf16", 1500, 13),
+    (9, 58, 1, 64, 2112, 9, 230, "f16", 0, 0), (9, 58, 1, 64, 2496, 8, 39, "bf16", 2000, 0), (9, 58, 1, 128, 1216, 16, 30, "f16", 0, 5)])
 def test_many_units_with_short_caches(Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window):
     """Workgroups of four waves."""
+    sh = B.make_shape(Bn, h, h_kv, S_max, d_h, r, k, {"f16": torch.float16, "bf16": torch.bfloat16}[dtype], K1, window)
+    assert B.sparq_decode_plan(sh).endswith("workgroups of four waves")
     w = W.Workload("single short", Bn, h, h_kv, d_h, S_max, r, k, dtype, seed=2400 + S_max)
     lens = S_max - torch.arange(Bn, dtype=torch.int32) * 5 % S_max
     print("[case]", Bn, h, h_kv, d_h, S_max, r, k, dtype, dup, window, flush=True)

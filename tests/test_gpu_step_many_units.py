@@ -18,7 +18,7 @@ SHORT, APART, ONE = "workgroups of four waves", "append of a step apart", "one l
 @pytest.mark.parametrize("Bn,h,h_kv,d_h,S_max,r,k,dtype,flags,build", [
     (103, 10, 10, 128, 128, 12, 20, "f16", 0, SHORT), (103, 10, 5, 64, 128, 12, 20, "bf16", 0, SHORT), (205, 5, 1, 256, 128, 12, 20, "f16", 0, SHORT),
     (41, 25, 25, 256, 128, 12, 20, "bf16", 0, SHORT), (1025, 1, 1, 64, 128, 12, 20, "f16", TK, APART), (103, 10, 5, 128, 128, 12, 20, "bf16", TK, APART),
-    (103, 10, 10, 128, 128, 12, 20, "f16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT), (261, 4, 4, 64, 128, 12, 20, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT),
+    (103, 10, 10, 128, 128, 12, 20, "f16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT), (205, 6, 6, 64, 128, 12, 20, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT),
     (400, 3, 3, 128, 64, 12, 20, "f16", B.SPARQ_FLAG_RAGGED_BATCH, SHORT),
     # what a unit reads binds the call: workgroups of eight waves, the append in its own beyond 512 KV heads
     (103, 10, 10, 128, 704, 12, 704, "f16", 0, APART), (41, 26, 26, 256, 448, 64, 448, "bf16", 0, APART), (1025, 1, 1, 64, 1408, 12, 1408, "bf16", 0, APART),

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("r", [1, 8, 9])
 @pytest.mark.parametrize("chunks", [0, 1, 63, 65, 511, 512, 513, 575, 577, 1025])
 def test_one_item_per_thread(d_h, dtype, r, chunks, flags):
-    """One workgroup of 512 threads per head; the second sequence is shorter and ends inside a wave's chunks."""
+    """A workgroup of 512 threads per head, row-major keys with helpers beside it (four units; without: test_gpu_eight_waves.py); the second
+    sequence is shorter and ends inside a wave's chunks."""
     w = W.Workload("items", 2, 2, 2, d_h, chunks * 8 + 5, r, 20, dtype, seed=1200 + chunks)
     print("[case]", d_h, dtype, r, chunks, flags, flush=True)
     lens = torch.tensor([w.S, max(1, w.S - 8 * 37)], dtype=torch.int32)
