@@ -197,16 +197,22 @@ bool shared_bucket_plan(const sparq_shape* s, size_t lds_max, PlanInfo* p) {
 
 // Few units whose idle CUs fetch for them (decode_helped): what one workgroup per unit takes grows with the positions, the channel rows
 // and the selected rows (0.2 us per 1000 positions, 0.025 for each of their channels, 4.3-13 for 1000 selected rows of 64-256 channels);
-// the digit-bucket plan takes 22 to 31 us wherever between 12 288 and 35 000 positions.  us per decode, helped / bucket, caches in HBM, 32 units of 128
-// channels, positions, r, k: 12 300 32, 256 22.4 / 24.6; 32, 512 24.3 / 25.2; 32, 1024 28.0 / 26.1; 64, 512 33.9 / 29.3; 16 300 8, 256 16.5 / 22.6; 16, 700
-// 22.6 / 25.1; 20 000 16, 500 22.8 / 24.6; 24 000 8, 256 19.7 / 23.1; 16, 300 23.3 / 24.8; 8, 900 24.7 / 24.2; 28 000 8, 256 20.4 / 23.8; 8, 900 25.2 / 24.8; 32 000
-// 8, 256 23.4 / 23.9; 12, 300 27.3 / 25.3; 8, 900 28.5 / 25.1 (a lane's 64 keys lie a whole round of LDS banks apart); of 64 channels 12 350 32, 512 22.8 / 24.7; 24 000
-// 16, 800 26.5 / 25.6; 28 000 8, 1500 26.1 / 25.2; of 256 12 350 32, 128 21.0 / 24.1; 28 000 8, 400 24.2 / 24.7; 32 000 8, 300 26.3 / 24.5.  17, 48 and 64 units gain more
-// by it (24 000 16, 200 21.4 / 26.2, 22.2 / 26.6, 22.6 / 28.8).  Next to the line, 17 / 32 / 64 units: 12 280 32, 480 21.2 / 22.1, 22.7 / 25.0, 24.8 / 28.7; 28 600 14, 30 21.1 /
-// 25.7, 21.2 / 24.5, 22.0 / 29.2.  16 units 12 300 32, 256 21.5 / 21.3.
+// the digit-bucket plan takes 22 to 31 us wherever between 12 288 and 35 000 positions, least with 32 units, most with 64.  us per decode,
+// helped / bucket, caches in HBM, 32 units of 128 channels, positions, r, k: 12 300 32, 256 22.4 / 24.6; 32, 1024 28.0 / 26.1; 64, 512 33.9 / 29.3; 16 300 8, 256
+// 16.5 / 22.6; 16, 700 22.6 / 25.1; 20 000 16, 500 22.8 / 24.6; 24 000 8, 256 19.7 / 23.1; 16, 300 23.3 / 24.8; 8, 900 24.7 / 24.2; 28 000 8, 256 20.4 / 23.8; 16, 150
+// 23.4 / 25.3; 8, 900 25.2 / 24.8; 32 000 8, 256 23.4 / 23.9; 12, 300 27.3 / 25.3; 8, 900 28.5 / 25.1 (a lane's 64 keys lie a whole round of LDS banks apart); of 64
+// channels 12 350 32, 512 22.8 / 24.7; 24 000 16, 800 26.5 / 25.6; 28 000 8, 1500 26.1 / 25.2; of 256 12 350 32, 128 21.0 / 24.1; 28 000 8, 400 24.2 / 24.7; 32 000 8, 300
+// 26.3 / 24.5.  48 and 64 units: 24 000 16, 300 23.3 / 26.8 and 24.2 / 29.4; 32 000 8, 900 28.9 / 27.2 and 28.9 / 28.8; 12, 300 27.5 / 28.2 and 27.8 / 30.6; 34 000 8, 800
+// 27.6 / 27.3 and 27.8 / 29.8; 12, 128 26.2 / 28.3 and 26.1 / 30.3; of 64 channels 32 000 8, 1500 30.0 / 27.1 and 29.8 / 28.5.  Next to the lines, 17 / 32 / 64
+// units: 12 280 32, 480 21.2 / 22.1, 22.7 / 25.0, 24.8 / 28.7; 28 600 14, 30 21.1 / 25.7, 21.2 / 24.5, 22.0 / 29.2; 33, 48 and 64 units 28 000 8, 900 25.2 / 26.2,
+// 25.1 / 26.4, 26.0 / 28.9.  (17 to 30 units stand between: 24 000 8, 900 24.1 / 25.5 with 24; the line is that of 32.)  16 units 12 300 32, 256 21.5 / 21.3.
 bool helped_faster(const sparq_shape* s) {
-  const int64_t units = (int64_t)s->B * s->H, k = s->k < s->S_max ? s->k : s->S_max;
-  return units > 16 && units <= 64 && s->S_max <= 28672 && (int64_t)s->S_max * (2 * s->r + 16) + k * (3 * s->d_h + 200) <= 1280000;
+  const int64_t units = (int64_t)s->B * s->H, S = s->S_max, k = s->k < s->S_max ? s->k : s->S_max;
+  if (units <= 16 || units > 64) return false;
+  const int64_t rows = k * (s->d_h + 64);
+  const bool few_reads = S * s->r * 2 + k * s->d_h * 4 <= 1000000;
+  if (S > 28672) return units > 32 && few_reads && rows <= 153600;
+  return S * (2 * s->r + 16) + k * (3 * s->d_h + 200) <= 1280000 || (few_reads && rows <= (units > 32 ? 172800 : 96000));
 }
 
 // A key cache stored once, few units: Step 1 reads whole rows, which one workgroup gets at 60 GB/s.  us per decode, one workgroup per

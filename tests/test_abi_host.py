@@ -90,10 +90,12 @@ def test_plan_choice_between_the_bucket_plan_and_helped_units():
         for units in (17, 32, 64):
             assert plan(units, S, r, k, d_h).endswith("idle CUs fetch"), (units, S, r, k, d_h)
         assert "digit-bucket" in plan(16, S, r, k, d_h) and "digit-bucket" not in plan(129, S, r, k, d_h)
-    for S, r, k, d_h in ((12288, 32, 512, 128), (12352, 32, 1024, 128), (12352, 64, 512, 128), (24000, 8, 900, 128), (28032, 8, 900, 128), (28736, 8, 16, 128), (32000, 8, 900, 128),
-                         (32000, 12, 300, 128), (24000, 16, 800, 64), (28032, 8, 1500, 64), (32000, 8, 1500, 64), (32000, 8, 300, 256)):
+    for S, r, k, d_h in ((12288, 32, 512, 128), (12352, 32, 1024, 128), (12352, 64, 512, 128), (32000, 8, 900, 128), (28032, 8, 1500, 64), (32000, 8, 1500, 64)):
         for units in (17, 32, 64):
             assert "digit-bucket" in plan(units, S, r, k, d_h), (units, S, r, k, d_h)
+    for S, r, k, d_h in ((24000, 8, 900, 128), (28032, 8, 900, 128), (28736, 8, 16, 128), (32000, 12, 300, 128), (34048, 8, 800, 128), (34944, 13, 88, 128),
+                         (24000, 16, 800, 64)):
+        assert "digit-bucket" in plan(32, S, r, k, d_h) and plan(33, S, r, k, d_h).endswith("idle CUs fetch"), (S, r, k, d_h)
 
 
 def test_the_plan_names_the_build_of_the_one_workgroup_kernel():

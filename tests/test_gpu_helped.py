@@ -31,7 +31,7 @@ def decode_and_step(w, lens, dup, window):
     (1, 1, 1, 128, 17, 1, 3, "f16", 0, 0), (3, 1, 1, 64, 63, 9, 40, "bf16", 50, 2), (16, 8, 4, 256, 130, 40, 25, "f16", 0, 0), (5, 5, 5, 128, 420, 8, 100, "bf16", 300, 0),
     # long ones of few rows, which the digit-bucket plan serves with more
     (1, 20, 5, 64, 12301, 8, 100, "f16", 0, 0), (2, 16, 4, 128, 16385, 16, 300, "bf16", 9000, 0), (1, 64, 2, 64, 28600, 8, 400, "f16", 0, 7),
-    (3, 6, 2, 256, 14001, 8, 200, "bf16", 0, 0)])
+    (3, 6, 2, 256, 14001, 8, 200, "bf16", 0, 0), (1, 36, 4, 64, 33001, 8, 300, "f16", 20000, 0)])
 def test_decode_and_step(Bn, h, h_kv, d_h, S, r, k, dtype, dup, window):
     w = W.Workload("helped", Bn, h, h_kv, d_h, S, r, k, dtype, seed=1900 + Bn)
     lens = (S - torch.arange(Bn, dtype=torch.int32) * 13 % max(S // 2, 1))          # the last rows of every kind: mod 8, tails
