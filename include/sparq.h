@@ -51,7 +51,7 @@ typedef enum {
   SPARQ_OK = 0,
   SPARQ_EINVAL = -1,       /* null / misaligned pointer, inconsistent shape */
   SPARQ_EUNSUPPORTED = -2, /* valid request this build has no kernel for */
-  SPARQ_EWORKSPACE = -3,   /* workspace missing or smaller than sparq_workspace_bytes */
+  SPARQ_EWORKSPACE = -3,   /* workspace missing or smaller than the call needs (at most sparq_workspace_bytes) */
   SPARQ_ELAUNCH = -4,      /* the HIP runtime refused the launch */
   SPARQ_ETOOLARGE = -5     /* sparq_decode_noalloc: the shape needs more scratch than the built-in buffer */
 } sparq_status;
@@ -70,7 +70,9 @@ enum {
   SPARQ_FLAG_GQA_SHARED = 1u << 1,
   /* scheduling hint, no effect on results: the sequence lengths of the batch differ widely;
    * sparq_decode / sparq_decode_step then start the longest sequences first.  Honoured by the
-   * one-workgroup-per-head plan for 2 <= B <= 512 and H = H_kv; ignored otherwise */
+   * one-workgroup-per-head plan for H = H_kv and 2 <= B <= 512 (256 in workgroups of four waves); ignored
+   * otherwise, also where idle CUs fetch (at most 128 heads, all of which start at once).  sparq_decode_plan
+   * says which of these a shape gets. */
   SPARQ_FLAG_RAGGED_BATCH = 1u << 2,
   /* the fixed temperatures of the paper's ablation (Section 5.3, "Approximate softmax
    * temperature") in place of Eq. (9): tau = sqrt(d_h), or tau = sqrt(r).  At most one of the two. */
@@ -78,7 +80,10 @@ enum {
   SPARQ_FLAG_TAU_SQRT_R = 1u << 4,
   /* the key cache is stored once, d_h-contiguous only (the "1 x K" variant of Section 6.1): cache.Kt
    * is ignored and may be null, sparq_kv_append writes no second copy, and Step 1 reads the rows of K
-   * whole (S d_h elements instead of S r).  Not combined with SPARQ_FLAG_GQA_SHARED. */
+   * whole (S d_h elements instead of S r).  Not combined with SPARQ_FLAG_GQA_SHARED.  One workgroup per head
+   * in one launch, or, for at most 64 (sequence, head) units from S_max = 2048 + 262 144 / d_h, spans of each unit in two
+   * launches with scratch in the workspace; a workspace that is smaller than sparq_workspace_bytes by that scratch is
+   * accepted too and gets one workgroup per head (the same selection, sums in another order). */
   SPARQ_FLAG_SINGLE_K = 1u << 5,
   /* the key cache is stored once in a layout that serves both steps (Section 6.1 closes by asking for
    * alternatives to storing K twice): tiles of 8 positions, channel-major inside a tile.  cache.K is then
@@ -175,7 +180,8 @@ int sparq_kv_append(const sparq_shape* shape, const sparq_cache* cache, const vo
  * Sizes: every plan keeps 4 bytes per position (or per candidate) of its unit of work in LDS.  One
  * workgroup per head serves S_max up to about 35 000.  Few (sequence, head) units with long caches (at most 96
  * from S_max = 16 384, at most 64 from 12 288, at most 128 beyond what one workgroup holds) are spread over spans of
- * up to 8192 positions (at most 64 spans: S_max <= 524 288, any k).
+ * up to 8192 positions (at most 64 spans: S_max <= 524 288, any k); of these, 17 to 64 units whose r and k are small for S_max
+ * stay with one workgroup per head.  Workspaces are sized for either, whatever r and k.
  * Larger batches with longer caches are selected in two levels (spans of 8192 positions, at most 64 of
  * them, ceil(S_max / 8192) * min(k, 8192) candidates <= about 36 000: e.g. S_max = 524 288 at k = 512), also
  * under SPARQ_FLAG_GQA_SHARED.  SPARQ_FLAG_SINGLE_K and SPARQ_FLAG_TILED_K stop at about 35 000.
@@ -188,6 +194,8 @@ int sparq_kv_append(const sparq_shape* shape, const sparq_cache* cache, const vo
  *   idx_out    device [B, H, idx_stride] int32 or NULL: i2 ascending, padded with -1
  *   chan_out   device [B, H, r] int32 or NULL: i1 ascending
  * Reads the cache, writes only the outputs and the error word.
+ * A call of at most 128 heads that one workgroup each serves uses the CUs that it leaves idle as well, for workgroups that
+ * fetch what the heads' own will read and write nothing; work on another stream shares the CUs with them.
  */
 int sparq_decode(const sparq_shape* shape, const sparq_cache* cache, const void* q,
                  const int32_t* k_per_seq, void* out, float* alpha_out, int32_t* idx_out,
@@ -254,14 +262,15 @@ int sparq_copy_probe(void* dst, const void* src, size_t n_bytes, void* hip_strea
  * folded word to `sink` (device, at least 2 MiB = 2048 workgroups x 256 threads x 4 bytes). */
 int sparq_read_probe(const void* src, size_t n_bytes, void* sink, size_t sink_bytes, void* hip_stream);
 
-/* Which kernels sparq_decode / sparq_decode_step launch for this shape (a static string naming the plan
- * and its launches; "unsupported" where sparq_decode would return SPARQ_EUNSUPPORTED).  Host only. */
+/* Which kernels sparq_decode / sparq_decode_step launch for this shape in a workspace of sparq_workspace_bytes (a static string
+ * naming the plan, its launches and, of the one-workgroup-per-head kernels, the build; "unsupported" where sparq_decode would
+ * return SPARQ_EUNSUPPORTED).  Host only. */
 const char* sparq_decode_plan(const sparq_shape* shape);
 
 /* Profiling builds only (the library compiled with -DSPARQ_STAGE_CLOCKS; the default build returns
  * SPARQ_EUNSUPPORTED): for shapes served by one workgroup per head, every sparq_decode / sparq_decode_step
  * launch also leaves *stamps_per_workgroup 64-bit time stamps per workgroup (10 ns ticks of the device's
- * constant 100 MHz counter; workgroups in launch order) at workspace + *offset_bytes: start, Step 1 channels
+ * constant 100 MHz counter; workgroups in launch order, or by (sequence, head) where idle CUs fetch) at workspace + *offset_bytes: start, Step 1 channels
  * selected, the first wave's share of the Step 1 stream done, all approximate scores in LDS, Step 2 threshold
  * found, position list compacted, the first wave's rows attended, all partial results in LDS, end.
  * sparq_workspace_bytes of such a build includes the room.  Host only. */

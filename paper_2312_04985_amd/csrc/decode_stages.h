@@ -1,9 +1,9 @@
 // The stages of the SparQ decode step (Section 4, Steps 1-3) as workgroup-level device functions.
 // Every decode plan is a different distribution of these stages over workgroups: one workgroup per
-// (sequence, head) (sparq_decode.hip), digit buckets over spans (sparq_decode_bucket.hip), two-level selection
+// (sequence, head) (sparq_decode_fused.h), digit buckets over spans (sparq_decode_bucket.hip), two-level selection
 // (sparq_decode_long.hip), the grouped-query rule (sparq_decode_shared.hip), the single-copy key cache
 // (sparq_decode_single_k.hip); the append kernels use the column flush.
-// Unless noted, functions are called by all kDecodeThreads threads of a workgroup (they contain barriers).
+// Unless noted, functions are called by all NT threads of a workgroup (they contain barriers).
 #pragma once
 #include "common.h"
 #include "params.h"
@@ -323,8 +323,8 @@ __device__ __forceinline__ void issue_rows(V (&v)[8], const char* base, uint32_t
 // Chunks (8 consecutive positions = 16 bytes of every channel row) chunk_begin + tid + i * STRIDE belong to
 // thread tid of STRIDE (all NT threads of the workgroup unless the caller divides the rows of a chunk among
 // groups of threads).  RUNS: where that is more than two per thread, they are cut into runs of 64, one chunk per lane, and every wave
-// takes consecutive runs (the first waves one more where they do not come out even), so that the waves read at places an eighth of the row apart
-// and not side by side (for row strides at which that is faster: decode_runs).
+// takes consecutive runs (the first waves one more where they do not come out even), so that the NW waves read at places 1 / NW of the row
+// apart and not side by side (for row strides at which that is faster: decode_runs).
 // The (chunk, batch-of-8-rows) pairs a thread owns form one flat sequence that runs through
 // a two-deep software pipeline: a batch of 8 loads is always in flight behind the one being accumulated,
 // also across chunk boundaries.  fp32 FMA in ascending channel order.  finish(c, acc) is called with the

@@ -6,7 +6,7 @@
 
 namespace sparq {
 
-constexpr int kDecodeThreads = 512;     // threads per workgroup of the fused decode kernel
+constexpr int kDecodeThreads = 512;     // threads per workgroup of the decode kernels (256 in the builds of four waves)
 constexpr int kRadixBins = 2048;        // 11-bit digits: passes of 11, 11 and 10 bits
 constexpr int kWorkspaceHeader = 256;   // bytes; word 0 is the error word
 constexpr int kControlBytes = 65536;    // control block at the start of the workspace, zeroed by sparq_workspace_init
