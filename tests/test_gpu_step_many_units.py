@@ -23,7 +23,7 @@ SHORT, APART, ONE = "workgroups of four waves", "append of a step apart", "one l
     # what a unit reads binds the call: workgroups of eight waves, the append in its own beyond 512 KV heads
     (103, 10, 10, 128, 704, 12, 704, "f16", 0, APART), (41, 26, 26, 256, 448, 64, 448, "bf16", 0, APART), (1025, 1, 1, 64, 1408, 12, 1408, "bf16", 0, APART),
     (103, 10, 5, 128, 704, 12, 704, "bf16", 0, APART), (103, 10, 10, 64, 1408, 9, 1408, "f16", B.SPARQ_FLAG_RAGGED_BATCH, APART),
-    (260, 4, 4, 64, 1408, 9, 1400, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, APART), (103, 20, 4, 128, 704, 12, 704, "f16", 0, ONE)])
+    (260, 4, 4, 64, 1408, 9, 1400, "bf16", B.SPARQ_FLAG_RAGGED_BATCH, APART), (103, 20, 4, 128, 704, 12, 704, "f16", 0, ONE), (103, 10, 10, 64, 16320, 9, 300, "f16", 0, "waves read apart, " + APART)])
 def test_step_equals_append_then_decode(Bn, h, h_kv, d_h, S_max, r, k, dtype, flags, build):
     w = W.Workload("many units", Bn, h, h_kv, d_h, S_max, r, k, dtype, seed=1700 + d_h)
     lens = (torch.arange(Bn, dtype=torch.int32) * 7) % (S_max + 1)      # every length mod 8, empty and full sequences
